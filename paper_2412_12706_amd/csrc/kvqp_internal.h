@@ -69,7 +69,9 @@ struct CompressPlan {
     int n_chunks;                 // key chunks of the scoring passes
     int n_wg, chunks_per_wg;      // scoring workgroups per kv head and their share
     int n_row_slabs;              // 64-row slabs of query rows (1, 2 or 4)
-    size_t off_stats_part, off_stats, off_vote, off_pooled, off_sel, off_idx, total;
+    int n_seg, seg_tiles;         // pooling workgroups per kv head and their share in pooling tiles
+    int p_stride;                 // score codes of a head, padded to whole 16-byte pieces
+    size_t off_stats_part, off_stats, off_vote, off_pooled, off_idx, total;
 };
 CompressPlan plan_compress(const kvqp_cfg& cfg);
 

@@ -14,9 +14,10 @@
 //   score_pass<STATS>  a reference and the exp-sum of every window row (pass 1)
 //   stats_combine      merges the per-wave row statistics
 //   score_pass<VOTES>  recomputes the tiles, normalises, sums columns (pass 2)
-//   select_topk        pool, radix-select the cut, ordered compaction; scores
-//                      within a relative 2e-5 of the cut are first re-scored in
-//                      binary64 so that binary32 rounding cannot move the cut
+//   pool_scores        max-pool the votes, count the pooled scores in bins
+//   select_topk        find the cut, ordered compaction; scores within a relative
+//                      2e-5 of the cut are first re-scored in binary64 so that
+//                      binary32 rounding cannot move the cut
 // Keys stream through LDS once per pass in 64- or 128-key chunks shared by the
 // four waves of a workgroup; query rows stay in registers as MFMA operands.
 #include "kvqp_internal.h"
@@ -272,24 +273,49 @@ __global__ __launch_bounds__(256) void stats_combine(const float2* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// Selection: pool, find the cut with a radix select on the binary32 patterns,
-// refine the candidates next to the cut in binary64, compact in position order.
-// One workgroup per (batch, kv head); the data (<= a few hundred KB of scores)
-// stays in L2.
+// Selection: pool, find the cut, refine the candidates next to it in binary64,
+// compact in position order.
+//
+// What bounds it is a chain of dependent waits (memory, LDS, barriers) on few
+// workgroups, never bandwidth: a head's scores are at most half a megabyte.  The
+// work is therefore cut so that the part that grows with the prefix is spread
+// over many workgroups and the rest touches each score once:
+//   pool_scores  several workgroups per head: max-pool the votes, store the upper 16
+//                bits of each pooled score, and count the scores in 4096 bins of equal
+//                bit-pattern width (64 per factor of two: at most 1.6 % wide)
+//   select_topk  one workgroup per head: the counts give the bin of the cut; ONE
+//                sweep over the 16-bit codes leaves a mask bit per sure survivor and
+//                collects the few candidates of that bin, whose scores are pooled
+//                again and give the exact cut; survivors leave through the mask.
+// Prefixes of one pooling tile (4096) do both in the second kernel.  A single
+// workgroup per head that did everything, with a four-pass radix select over all
+// scores, took 45 / 87 / 310 us for 8 heads of 4064 / 32736 / 131008 candidates
+// and 120 us for 256 heads of 32736; these take 12 / 5 + 20 / 6.5 + 36 and 17 + 28 us.
 // ---------------------------------------------------------------------------
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kMaxRows = 128;         // rows of 1024 candidates: prefixes up to 131072 tokens
-constexpr int kRegRows = 32;          // rows whose pooled scores stay in registers (prefixes up to 32768)
+constexpr int kMaxPrefix = 131072;
+constexpr int kOctets = kMaxPrefix / (8 * kSelThreads);   // groups of eight candidates per thread
+constexpr int kPoolTile = 4 * kSelThreads;   // candidates of one pooling step, four consecutive ones per thread
+constexpr int kMaxPoolRadius = 31;    // pool_kernel <= 63
+constexpr int kStage = kPoolTile + 2 * kMaxPoolRadius + 2;   // votes of a step with the halo on either side (whole 16-byte pieces)
+constexpr int kBins = 4096;           // score bins: the bit pattern >> kBinShift, 2^-55 .. 2^9, clamped at both ends
+constexpr int kBinShift = 17;
+constexpr int kCodeShift = 15;        // the stored code of a score: its pattern's upper 16 bits below the sign
+constexpr int kBinBase = ((136 << 23) >> kBinShift) - kBins;   // 2^9 is the first pattern past the last bin (votes stay below 256 rows)
+constexpr int kMaxSegs = 16;          // pooling workgroups per head
+constexpr int kMaxSegTiles = 15;      // (a workgroup's bin counts are stored in 16 bits)
+constexpr int kListCap = 3840;        // candidates around the cut held in LDS; more are swept from memory
+constexpr int kDigit = 11;            // bits per pass of the radix select among them
 constexpr int kMaxBand = 512;         // candidates re-scored per head; beyond that binary32 decides (and the caller is told)
-constexpr int kVoteSlots = 2048;       // binary64 votes (distinct positions) held in LDS during the re-scoring
-constexpr int kStageRows = 4;          // rows of votes staged in LDS per pooling step
-constexpr int kMaxPoolRadius = 31;     // pool_kernel <= 63
+constexpr int kVoteSlots = 2048;      // binary64 votes (distinct positions) held in LDS during the re-scoring
+constexpr int kPartSlots = 1792;      // ... and partial votes of a batch of positions
 constexpr float kBandRel = 2.0e-5f;   // >> the binary32 error of a vote (a few 1e-7 relative)
 
 struct SelectArgs {
     const float* vote;      // [heads, P]
-    float* pooled;          // [heads, P]
+    uint16_t* code;         // [heads, p_stride] codes of the pooled scores; candidate j at code_at(j)
+    uint16_t* bins;         // [heads, n_seg, kBins] counts of every pooling workgroup
     int32_t* idx;           // [heads, n_kept]
     int32_t* unrefined;     // [heads] or NULL: candidates near the cut that binary32 decided (0: all re-scored)
     const int32_t* head_n;  // a head's own cut (<= n_kept), or NULL for n_kept everywhere
@@ -297,39 +323,66 @@ struct SelectArgs {
     const uint16_t* k;
     const float2* stats;    // (m, 1/Z) binary32
     const double* zsum;     // Z binary64
-    int P, L, W, n_kept, pool, gq, n_q_heads, n_kv_heads, rows, rows_pad;
+    int P, p_stride, L, W, n_kept, pool, gq, n_q_heads, n_kv_heads, rows, rows_pad;
+    int n_seg, seg_tiles;   // pooling workgroups per head and their pooling tiles
     float scale_log2;
     float sm_scale;
 };
 
 __device__ __forceinline__ uint32_t score_key(float v) { return __float_as_uint(v); }  // scores are >= 0: bits order like values
+__device__ __forceinline__ int score_bin(uint32_t key) { return min(max((int)(key >> kBinShift) - kBinBase, 0), kBins - 1); }
 
-// Exclusive scan, in place, of a table of n <= 2 * kSelThreads ints in LDS; returns the total.
-__device__ int scan_table(int* tab, int n, int* swave) {
+// Eight consecutive candidates share 16 bytes, candidates q and q + 4 the 32-bit word q (so that a
+// comparison of both halves of the four words yields their mask byte in order).
+__device__ __forceinline__ int code_at(int j) { return (j & ~7) | ((j & 3) << 1) | ((j >> 2) & 1); }
+typedef unsigned short us2v __attribute__((ext_vector_type(2)));
+// mask byte: bit i set where the code of candidate i exceeds t
+__device__ __forceinline__ uint32_t codes_above(const uint4& w4, uint32_t t) {
+    const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+    const us2v tt = {(unsigned short)t, (unsigned short)t}, one = {1, 1};
+    uint32_t m = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        union { uint32_t u; us2v v; } x; x.u = w[q];
+        x.v = __builtin_elementwise_min(__builtin_elementwise_sub_sat(x.v, tt), one);
+        m |= x.u << q;
+    }
+    return (m | (m >> 12)) & 0xffu;
+}
+
+// Sum of c over the threads before this one (the caller puts a barrier between two uses of swave).
+__device__ __forceinline__ int sum_before(int c, int* swave) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int e0 = 2 * threadIdx.x, e1 = e0 + 1;
-    const int v0 = e0 < n ? tab[e0] : 0, v1 = e1 < n ? tab[e1] : 0;
-    int inc = v0 + v1;
+    int inc = c;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const int o = __shfl_up(inc, off);
         if (lane >= off) inc += o;
     }
-    __syncthreads();
     if (lane == 63) swave[w] = inc;
     __syncthreads();
-    int base = 0, total = 0;
+    int before = inc - c;
 #pragma unroll
-    for (int i = 0; i < kSelWaves; ++i) {
-        const int t = swave[i];
-        if (i < w) base += t;
-        total += t;
+    for (int i = 0; i < kSelWaves; ++i)
+        if (i < w) before += swave[i];
+    return before;
+}
+// Sum of c over the threads after this one (the caller puts a barrier between two uses of swave).
+__device__ __forceinline__ int sum_after(int c, int* swave) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int suf = c;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_down(suf, off);
+        if (lane + off < 64) suf += o;
     }
-    const int excl = base + inc - (v0 + v1);
-    if (e0 < n) tab[e0] = excl;
-    if (e1 < n) tab[e1] = excl + v0;
+    if (lane == 0) swave[w] = suf;
     __syncthreads();
-    return total;
+    int after = suf - c;
+#pragma unroll
+    for (int i = 0; i < kSelWaves; ++i)
+        if (i > w) after += swave[i];
+    return after;
 }
 
 __device__ __forceinline__ float half_lo(uint32_t w) { return __half2float(__ushort_as_half((uint16_t)(w & 0xffffu))); }
@@ -374,49 +427,111 @@ __device__ double vote_f64_part(const SelectArgs& a, int head, int key, int row_
     return acc;
 }
 
-// Visit every candidate of this thread: j = row * 1024 + thread, v = its pooled score (-1 past the
-// end).  The first kRegRows rows come from registers, the rest from the pooled array.
-#define KVQP_FOR_ROWS(...)                                                            \
-    _Pragma("unroll") for (int row = 0; row < kRegRows; ++row) {                      \
-        if (row < n_rows) {                                                           \
-            const int j = row * kSelThreads + (int)threadIdx.x;                       \
-            const float v = pv[row];                                                  \
-            __VA_ARGS__                                                               \
-        }                                                                             \
-    }                                                                                 \
-    for (int row = kRegRows; row < n_rows; ++row) {                                   \
-        const int j = row * kSelThreads + (int)threadIdx.x;                           \
-        const float v = j < P ? pooled[j] : -1.0f;                                    \
-        __VA_ARGS__                                                                   \
+// Max-pooling of one tile: the votes of candidates j0 - r .. j0 + kPoolTile + r go through LDS (-1,
+// below any vote, outside the prefix) and every thread pools four consecutive candidates, reading
+// the votes its windows share once (10 votes for a pool of 7, in three 16-byte reads).
+struct VoteTile { float v[5]; };
+__device__ __forceinline__ VoteTile fetch_votes(const float* vote, int P, int r, int j0) {
+    VoteTile t;
+#pragma unroll
+    for (int u = 0; u < 5; ++u) {
+        const int i = (int)threadIdx.x + u * kSelThreads, j = j0 - r + i;
+        t.v[u] = (i < kPoolTile + 2 * r && j >= 0 && j < P) ? vote[j] : -1.0f;
     }
+    return t;
+}
+__device__ __forceinline__ void stage_votes(const VoteTile& t, float* stage) {
+#pragma unroll
+    for (int u = 0; u < 5; ++u) {
+        const int i = (int)threadIdx.x + u * kSelThreads;
+        if (i < kStage) stage[i] = t.v[u];
+    }
+}
+__device__ __forceinline__ float4 pool_four(const float* stage, int r) {
+    const float4* s = reinterpret_cast<const float4*>(stage) + threadIdx.x;
+    float o[4] = {-1.0f, -1.0f, -1.0f, -1.0f};
+    for (int q = 0; 4 * q <= 2 * r + 3; ++q) {
+        const float4 x4 = s[q];
+        const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+        if (q > 0 && 4 * q + 3 <= 2 * r) {           // inside all four windows
+            const float m = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = fmaxf(o[i], m);
+        } else {
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (4 * q + w >= i && 4 * q + w <= 2 * r + i) o[i] = fmaxf(o[i], x[w]);   // (uniform)
+        }
+    }
+    return make_float4(o[0], o[1], o[2], o[3]);
+}
 
-// One workgroup per (batch, kv head).  Candidate j lives at (row j / 1024, thread j % 1024), so
-// every sweep is coalesced and "position order" is (row, wave, lane): ordered compaction needs only
-// per-(row, wave) counts (one ballot each), one table scan, and a popcount below the lane.  The
-// pooled scores of prefixes up to 32768 tokens never leave the registers.
+// Pooled scores and their bin counts; workgroup x of a head takes seg_tiles consecutive tiles.
+__global__ __launch_bounds__(kSelThreads) void pool_scores(const SelectArgs a) {
+    __shared__ __align__(16) float stage[kStage];
+    __shared__ __align__(16) int hist[kBins];
+    const int head = blockIdx.y;
+    const int P = a.P, k = a.head_n ? a.head_n[head] : a.n_kept;
+    if (k <= 0 || k >= P) return;               // (nothing of this head is cut)
+    const float* vote = a.vote + (size_t)head * P;
+    uint32_t* code = reinterpret_cast<uint32_t*>(a.code + (size_t)head * a.p_stride);
+    const int r = (a.pool - 1) / 2;
+    const int t_begin = blockIdx.x * a.seg_tiles, t_end = min((P + kPoolTile - 1) / kPoolTile, t_begin + a.seg_tiles);
+    VoteTile next = fetch_votes(vote, P, r, t_begin * kPoolTile);
+    *reinterpret_cast<int4*>(hist + 4 * threadIdx.x) = make_int4(0, 0, 0, 0);
+    for (int t = t_begin; t < t_end; ++t) {
+        stage_votes(next, stage);
+        __syncthreads();
+        if (t + 1 < t_end) next = fetch_votes(vote, P, r, (t + 1) * kPoolTile);   // in flight while this tile is pooled
+        const float4 o = pool_four(stage, r);
+        const int j = t * kPoolTile + 4 * (int)threadIdx.x;
+        const uint32_t key[4] = {score_key(o.x), score_key(o.y), score_key(o.z), score_key(o.w)};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (j + i < P) atomicAdd(&hist[score_bin(key[i])], 1);
+        // codes of the thread's four candidates (0 past the end), then the octet's words: the even
+        // thread stores words 0 and 1, the odd one words 2 and 3
+        uint32_t cd[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) cd[i] = j + i < P ? key[i] >> kCodeShift : 0u;
+        const bool odd = threadIdx.x & 1;
+        const uint32_t give0 = odd ? cd[0] : cd[2], give1 = odd ? cd[1] : cd[3];
+        const uint32_t got0 = __builtin_amdgcn_mov_dpp(give0, 0xB1 /*quad_perm [1,0,3,2]*/, 0xf, 0xf, true);
+        const uint32_t got1 = __builtin_amdgcn_mov_dpp(give1, 0xB1, 0xf, 0xf, true);
+        if ((j & ~7) < P)
+            *reinterpret_cast<uint2*>(code + (j >> 1)) = odd ? make_uint2(got0 | (cd[2] << 16), got1 | (cd[3] << 16))
+                                                             : make_uint2(cd[0] | (got0 << 16), cd[1] | (got1 << 16));
+        __syncthreads();
+    }
+    const int4 c = *reinterpret_cast<const int4*>(hist + 4 * threadIdx.x);
+    uint2* out = reinterpret_cast<uint2*>(a.bins + ((size_t)head * a.n_seg + blockIdx.x) * kBins) + threadIdx.x;
+    *out = make_uint2((uint32_t)c.x | ((uint32_t)c.y << 16), (uint32_t)c.z | ((uint32_t)c.w << 16));
+}
+
+// One workgroup per (batch, kv head).  keep: the survivor mask, bit j % 8 of byte j / 8.
+// ONE: the whole prefix is one pooling tile, pooled and counted here; thread t keeps the scores of
+// candidates 4 t .. 4 t + 3.
+template <bool ONE>
 __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
-    __shared__ __align__(16) int hist[kSelWaves][256];   // later reused for the binary64 partial votes (2048 doubles)
-    __shared__ int tab_a[kMaxRows * kSelWaves];   // per (row, wave): survivors that need no second look
-    __shared__ int tab_b[kMaxRows * kSelWaves];   // per (row, wave): band members (or ties at the cut)
+    __shared__ __align__(16) uint32_t keep[(ONE ? kPoolTile : kMaxPrefix) / 32];
+    __shared__ __align__(16) int tab[2 * kSelThreads];            // the band
+    __shared__ int hist[1 << kDigit];                             // radix digits; later the positions to re-score
+    __shared__ __align__(16) unsigned char big[kListCap * 8];     // candidates around the cut; before that the pooling stage and the bins (ONE); later the binary64 votes, or the mask of the ties
     __shared__ int swave[kSelWaves];
-    __shared__ uint32_t s_red[2 * kSelWaves];
+    __shared__ int s_bin, s_list, s_sure, s_need, s_band, s_hot;
     __shared__ uint32_t s_prefix;
-    __shared__ int s_need;
-    __shared__ int band_idx[kMaxBand];
-    __shared__ int band_start[kMaxBand];          // first position whose vote this member owns
-    __shared__ int band_off[kMaxBand + 1];        // offset of its owned votes in the vote list
-    __shared__ double band_score[kMaxBand];
-    __shared__ int band_take[kMaxBand + 1];       // after the scan: taken band members before position c
-    __shared__ __align__(16) float stage[kStageRows * kSelThreads + 2 * kMaxPoolRadius];   // votes of a few rows plus halo; later the binary64 votes
+    static_assert(kListCap * 8 >= kStage * 4 && kListCap * 8 >= kBins * 4 && kListCap * 8 >= (kPartSlots + kVoteSlots) * 8 &&
+                  kListCap * 8 >= kMaxPrefix / 8 && kVoteSlots <= (1 << kDigit), "aliases fit");
 
     const int head = blockIdx.x;
     const int P = a.P, k = a.head_n ? a.head_n[head] : a.n_kept;
     const float* vote = a.vote + (size_t)head * P;
-    float* pooled = a.pooled + (size_t)head * P;
+    const uint16_t* code = a.code + (size_t)head * a.p_stride;
     int32_t* idx = a.idx + (size_t)head * a.n_kept;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n_rows = (P + kSelThreads - 1) / kSelThreads;
-    const unsigned long long lt_mask = (1ull << lane) - 1ull;
+    const int r = (a.pool - 1) / 2;
 
     if (a.unrefined && threadIdx.x == 0) a.unrefined[head] = 0;   // (overwritten below by the same thread if binary32 decides)
     if (k <= 0) return;   // (a head-level count may be zero)
@@ -424,254 +539,319 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
         for (int j = threadIdx.x; j < k; j += kSelThreads) idx[j] = j;
         return;
     }
+    if (threadIdx.x == 0) { s_list = 0; s_sure = 0; s_band = 0; s_hot = 0; }
 
-    // ---- max-pool (clipped at both ends) and the range of the pooled scores ----
-    const int r = (a.pool - 1) / 2;
-    uint32_t kmin = 0xffffffffu, kmax = 0u;
-    float pv[kRegRows];
+    // ---- the bin of the k-th largest score ----
+    const int n_oct = (P + 7) / 8;
+    uint4 oct[ONE ? 1 : kOctets];                  // the thread's octets of codes: thread + 1024 i
+    uint32_t own[4];                               // ONE: the thread's scores (all ones past the end: neither above nor around the cut)
+    int c[4] = {0, 0, 0, 0};                       // counts of bins 4 thread .. 4 thread + 3
+    if constexpr (ONE) {
+        float* stage = reinterpret_cast<float*>(big);
+        stage_votes(fetch_votes(vote, P, r, 0), stage);
+        if (threadIdx.x < kPoolTile / 32) keep[threadIdx.x] = 0u;
+        __syncthreads();
+        const float4 o = pool_four(stage, r);
+        __syncthreads();
+        const float ov[4] = {o.x, o.y, o.z, o.w};
+        int* bins = reinterpret_cast<int*>(big);
+        *reinterpret_cast<int4*>(bins + 4 * threadIdx.x) = make_int4(0, 0, 0, 0);
+        __syncthreads();
 #pragma unroll
-    for (int row = 0; row < kRegRows; ++row) pv[row] = -1.0f;
-    // A step stages kStageRows * 1024 consecutive votes plus r on either side in LDS (-1, below any
-    // vote, outside the prefix); every thread then takes the maximum over its window per row.  The
-    // votes of the next step are requested before this step's are pooled, so only the first step
-    // waits for memory.
-    float nx[kStageRows + 1];
-    auto fetch = [&](int row0) {
-        const int base = row0 * kSelThreads - r;
+        for (int i = 0; i < 4; ++i) {
+            own[i] = 4 * (int)threadIdx.x + i < P ? score_key(ov[i]) : 0xffffffffu;
+            if (4 * (int)threadIdx.x + i < P) atomicAdd(&bins[score_bin(own[i])], 1);
+        }
+        __syncthreads();
+        const int4 b = *reinterpret_cast<const int4*>(bins + 4 * threadIdx.x);
+        c[0] = b.x; c[1] = b.y; c[2] = b.z; c[3] = b.w;
+    } else {
+        const uint2* bins = reinterpret_cast<const uint2*>(a.bins + (size_t)head * a.n_seg * kBins) + threadIdx.x;
+        uint2 b[kMaxSegs];
 #pragma unroll
-        for (int u = 0; u <= kStageRows; ++u) {
-            const int i = (int)threadIdx.x + u * kSelThreads, j = base + i;
-            nx[u] = (i < kStageRows * kSelThreads + 2 * r && j >= 0 && j < P) ? vote[j] : -1.0f;
+        for (int s = 0; s < kMaxSegs; ++s) b[s] = s < a.n_seg ? bins[(size_t)s * (kBins / 4)] : make_uint2(0u, 0u);
+        // all codes are requested before the counts are looked at
+#pragma unroll
+        for (int i = 0; i < kOctets; ++i) {
+            const int o = (int)threadIdx.x + i * kSelThreads;
+            oct[i] = o < n_oct ? reinterpret_cast<const uint4*>(code)[o] : make_uint4(0u, 0u, 0u, 0u);
+        }
+#pragma unroll
+        for (int s = 0; s < kMaxSegs; ++s) {
+            c[0] += (int)(b[s].x & 0xffffu); c[1] += (int)(b[s].x >> 16);
+            c[2] += (int)(b[s].y & 0xffffu); c[3] += (int)(b[s].y >> 16);
+        }
+    }
+    {
+        int above = sum_after(c[0] + c[1] + c[2] + c[3], swave);
+#pragma unroll
+        for (int i = 3; i >= 0; --i) {
+            if (above < k && above + c[i] >= k) s_bin = 4 * (int)threadIdx.x + i;    // exactly one bin
+            above += c[i];
+        }
+    }
+    __syncthreads();
+    // Candidates of that bin and one code on either side (32768 patterns; the band around the cut
+    // reaches at most 2e-5 * 2^24 = 336): codes clo .. chi, patterns klo .. khi.  Everything above survives.
+    const int cb = __builtin_amdgcn_readfirstlane(s_bin);
+    constexpr uint32_t kCodesPerBin = 1u << (kBinShift - kCodeShift);
+    const uint32_t clo = cb == 0 ? 0u : (uint32_t)(cb + kBinBase) * kCodesPerBin - 1u;
+    const uint32_t chi = cb == kBins - 1 ? 0xffffu : (uint32_t)(cb + 1 + kBinBase) * kCodesPerBin;
+    const uint32_t klo = clo << kCodeShift, khi = (chi << kCodeShift) | ((1u << kCodeShift) - 1u);
+
+    // ---- one sweep: the mask of what lies above, the list of what lies around the cut ----
+    uint32_t* list_key = reinterpret_cast<uint32_t*>(big);
+    int* list_pos = reinterpret_cast<int*>(big + kListCap * 4);
+    int sure = 0;
+    if constexpr (ONE) {
+        uint32_t bits = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bits |= (int)own[i] > (int)khi ? 1u << i : 0u;
+        sure = __popc(bits);
+        if (bits) atomicOr(&keep[threadIdx.x >> 3], bits << (4 * (threadIdx.x & 7)));
+    } else {
+#pragma unroll
+        for (int i = 0; i < kOctets; ++i) {
+            const int o = (int)threadIdx.x + i * kSelThreads;
+            if (o < n_oct) {
+                const uint32_t above = codes_above(oct[i], chi);
+                uint32_t around = clo ? codes_above(oct[i], clo - 1u) & ~above : 0xffu & ~above;
+                if (8 * o + 8 > P) around &= (1u << (P - 8 * o)) - 1u;      // (past the end the codes are 0)
+                reinterpret_cast<unsigned char*>(keep)[o] = (unsigned char)above;
+                sure += __popc(above);
+                if (around) {
+                    int e = atomicAdd(&s_list, __popc(around));
+                    for (; around; around &= around - 1u, ++e)
+                        if (e < kListCap) list_pos[e] = 8 * o + __builtin_ctz(around);
+                }
+            }
+        }
+        for (int o = n_oct + (int)threadIdx.x; o < (n_oct + 3) / 4 * 4; o += kSelThreads) reinterpret_cast<unsigned char*>(keep)[o] = 0;
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) sure += __shfl_xor(sure, off);
+    if (lane == 0 && sure) atomicAdd(&s_sure, sure);
+    __syncthreads();
+    const int n_list = __builtin_amdgcn_readfirstlane(s_list);
+    const int need_around = k - __builtin_amdgcn_readfirstlane(s_sure);   // how many of the candidates around the cut survive
+    // the pooled score of a candidate, from the votes
+    auto pooled_key = [&](int j) -> uint32_t {
+        const int t1 = min(j + r, P - 1);
+        float best = -1.0f;
+        for (int t = max(j - r, 0); t <= t1; t += 8) {      // (eight votes in flight; past the window its last one again)
+            float x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = vote[min(t + u, t1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) best = fmaxf(best, x[u]);
+        }
+        return score_key(best);
+    };
+    if constexpr (!ONE) {
+        if (n_list <= kListCap)
+            for (int e = threadIdx.x; e < n_list; e += kSelThreads) list_key[e] = pooled_key(list_pos[e]);   // (read back by the same thread only)
+    }
+    // every candidate around the cut: from the thread's own scores (ONE), from the list (in no
+    // particular order), or, where the list is too short (thousands of scores within two percent of
+    // the cut), from the codes
+    auto each_around = [&](auto visit) {
+        if constexpr (ONE) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (own[i] >= klo && own[i] <= khi) visit(own[i], 4 * (int)threadIdx.x + i);
+        } else if (n_list <= kListCap) {
+            for (int e = threadIdx.x; e < n_list; e += kSelThreads) visit(list_key[e], list_pos[e]);
+        } else {
+            for (int j = threadIdx.x; j < P; j += kSelThreads) {
+                const uint32_t cd = code[code_at(j)];
+                if (cd >= clo && cd <= chi) visit(pooled_key(j), j);
+            }
         }
     };
-#define KVQP_POOL_STEP(ROW0, STORE)                                                                \
-    {                                                                                              \
-        _Pragma("unroll") for (int u = 0; u <= kStageRows; ++u) {                                  \
-            const int i = (int)threadIdx.x + u * kSelThreads;                                      \
-            if (i < kStageRows * kSelThreads + 2 * r) stage[i] = nx[u];                            \
-        }                                                                                          \
-        __syncthreads();                                                                           \
-        if ((ROW0) + kStageRows < n_rows) fetch((ROW0) + kStageRows);                              \
-        _Pragma("unroll") for (int q = 0; q < kStageRows; ++q) {                                   \
-            const int row = (ROW0) + q;                                                            \
-            const int j = row * kSelThreads + (int)threadIdx.x;                                    \
-            if (j < P) {                                                                           \
-                const float* w = stage + q * kSelThreads + threadIdx.x;                            \
-                float best = w[0];                                                                 \
-                for (int t = 1; t <= 2 * r; ++t) best = fmaxf(best, w[t]);                         \
-                STORE;                                                                             \
-                kmin = min(kmin, score_key(best)); kmax = max(kmax, score_key(best));              \
-            }                                                                                      \
-        }                                                                                          \
-        __syncthreads();                                                                           \
-    }
-    fetch(0);
-#pragma unroll
-    for (int row0 = 0; row0 < kRegRows; row0 += kStageRows)
-        if (row0 < n_rows) KVQP_POOL_STEP(row0, pv[row] = best)
-    for (int row0 = kRegRows; row0 < n_rows; row0 += kStageRows) KVQP_POOL_STEP(row0, pooled[j] = best)
-#undef KVQP_POOL_STEP
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, off));
-        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off));
-    }
-    if (lane == 0) { s_red[wave] = kmin; s_red[kSelWaves + wave] = kmax; }
-    __syncthreads();   // also orders the pooled[] writes before the sweeps below (same workgroup)
-    kmin = s_red[0]; kmax = s_red[kSelWaves];
-#pragma unroll
-    for (int i = 1; i < kSelWaves; ++i) { kmin = min(kmin, s_red[i]); kmax = max(kmax, s_red[kSelWaves + i]); }
+    auto set_keep = [&](int j) { atomicOr(&keep[j >> 5], 1u << (j & 31)); };
 
-    // ---- radix select of the k-th largest score, on keys relative to the minimum so that the
-    // digits that all candidates share (sign, exponent) do not pile into one histogram bin ----
-    const uint32_t span = kmax - kmin;
-    int top_shift = 24;
-    while (top_shift > 0 && (span >> top_shift) == 0) top_shift -= 8;
-    if (threadIdx.x == 0) { s_prefix = 0u; s_need = k; }
-    for (int shift = top_shift; shift >= 0; shift -= 8) {
-        for (int i = threadIdx.x; i < kSelWaves * 256; i += kSelThreads) (&hist[0][0])[i] = 0;
-        __syncthreads();
-        // (scalar copies: nothing in the sweep below then waits on LDS, so its atomics overlap)
-        const uint32_t prefix = __builtin_amdgcn_readfirstlane(s_prefix);
-        const int need = __builtin_amdgcn_readfirstlane(s_need);
-        const uint32_t himask = (shift == 24) ? 0u : (0xffffffffu << (shift + 8));
-        KVQP_FOR_ROWS(
-            const uint32_t key = score_key(v) - kmin;
-            const bool act = j < P && (key & himask) == prefix;
-            const int bin = (key >> shift) & 255;
-            // (an LDS atomic costs the CU a fixed time even with no lane active: skip those)
-            if (__builtin_amdgcn_ballot_w64(act) != 0ull)
-                if (act) atomicAdd(&hist[wave][bin], 1);
-        )
-        __syncthreads();
-        // bins summed over the waves, then "how many candidates in bins above mine" per bin
-        if (wave < 4) {
-            const int bin = threadIdx.x;                  // 256 threads, one bin each
-            int c = 0;
-#pragma unroll
-            for (int w = 0; w < kSelWaves; ++w) c += hist[w][bin];
-            // suffix sum within the wave (bins descend with rank), then across the four waves
-            int suf = c;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int o = __shfl_down(suf, off);
-                if (lane + off < 64) suf += o;
-            }
-            if (lane == 0) swave[wave] = suf;             // total of this wave's 64 bins
-            hist[0][bin] = c;                             // (own column only: no other thread reads hist[0][bin])
-            tab_a[bin] = suf;
+    // ---- the exact cut: radix select on the patterns relative to klo (two passes in the usual case) ----
+    uint32_t prefix = 0u;
+    int need = need_around;
+    {
+        const int bits = 32 - __builtin_clz(khi - klo);
+        int fixed = bits, shift = bits > kDigit ? bits - kDigit : 0;
+        for (;;) {
+            for (int i = threadIdx.x; i < (1 << kDigit); i += kSelThreads) hist[i] = 0;
+            __syncthreads();
+            each_around([&](uint32_t key, int) {
+                const uint32_t rel = key - klo;
+                if (fixed >= 32 || (rel >> fixed) == (prefix >> fixed))
+                    atomicAdd(&hist[(rel >> shift) & ((1u << (fixed - shift)) - 1u)], 1);
+            });
+            __syncthreads();
+            const int c0 = hist[2 * threadIdx.x], c1 = hist[2 * threadIdx.x + 1];
+            const int above = sum_after(c0 + c1, swave);
+            if (above < need && above + c1 >= need) { s_prefix = 2u * threadIdx.x + 1u; s_need = need - above; }
+            else if (above + c1 < need && above + c1 + c0 >= need) { s_prefix = 2u * threadIdx.x; s_need = need - above - c1; }
+            __syncthreads();
+            prefix |= __builtin_amdgcn_readfirstlane(s_prefix) << shift;
+            need = __builtin_amdgcn_readfirstlane(s_need);
+            if (shift == 0) break;
+            fixed = shift;
+            shift = shift > kDigit ? shift - kDigit : 0;
         }
-        __syncthreads();
-        if (wave < 4) {
-            const int bin = threadIdx.x;
-            int above = tab_a[bin] - hist[0][bin];        // candidates in higher bins of this wave's 64
-            for (int w = wave + 1; w < 4; ++w) above += swave[w];
-            if (above < need && above + hist[0][bin] >= need) {   // exactly one bin satisfies this
-                s_need = need - above;
-                s_prefix = prefix | ((uint32_t)bin << shift);
-            }
-        }
-        __syncthreads();
     }
-    const float cut = __uint_as_float(s_prefix + kmin);
-    const int need_at_cut = s_need;   // how many candidates equal to the cut are taken (binary32 rule)
+    const uint32_t cut_key = klo + prefix;
+    const float cut = __uint_as_float(cut_key);
+    const int need_at_cut = need;     // how many candidates equal to the cut are taken (binary32 rule)
     // band of scores that binary32 rounding could move across the cut
     const float lo = cut * (1.0f - kBandRel), hi = cut * (1.0f + kBandRel);
 
-    // ---- per-(row, wave) counts: sure survivors (> hi) and band members ----
-    KVQP_FOR_ROWS(
-        const unsigned long long bs = __builtin_amdgcn_ballot_w64(v > hi);
-        const unsigned long long bb = __builtin_amdgcn_ballot_w64(v >= lo && v <= hi);
-        if (lane == 0) { tab_a[row * kSelWaves + wave] = __popcll(bs); tab_b[row * kSelWaves + wave] = __popcll(bb); }
-        (void)j;
-    )
+    // ---- survivors above the band, and the band itself in position order ----
+    int* band_raw = tab;                                                   // [kMaxBand] as found
+    int* band_pos = tab + kMaxBand;                                        // [kMaxBand] ascending
+    double* band_score = reinterpret_cast<double*>(tab + 2 * kMaxBand);    // [kMaxBand]
+    static_assert(4 * kMaxBand <= 2 * kSelThreads, "the band fits the table");
+    if (threadIdx.x == 0) s_sure = 0;
     __syncthreads();
-    const int tot_sure = scan_table(tab_a, n_rows * kSelWaves, swave);
-    const int tot_band = scan_table(tab_b, n_rows * kSelWaves, swave);
-    const int n_parts = (a.rows + 31) / 32;       // a wave re-scores 32 window rows of one position
+    each_around([&](uint32_t key, int j) {
+        const float v = __uint_as_float(key);
+        if (v > hi) { set_keep(j); atomicAdd(&s_sure, 1); }
+        else if (v >= lo) {
+            const int e = atomicAdd(&s_band, 1);
+            if (e < kMaxBand) band_raw[e] = j;
+        }
+    });
+    __syncthreads();
+    const int tot_band = __builtin_amdgcn_readfirstlane(s_band);
+    const int take = need_around - __builtin_amdgcn_readfirstlane(s_sure);   // members of the band that survive
     bool refine = tot_band <= kMaxBand;
-    double* part_vote = reinterpret_cast<double*>(&hist[0][0]);   // kVoteSlots partial votes of a batch of positions
-    double* pos_vote = reinterpret_cast<double*>(&stage[0]);        // kVoteSlots votes, one per distinct position
-    int n_pos = 0;
-
     if (refine) {
-        // ---- band members in position order ----
-        KVQP_FOR_ROWS(
-            const bool inb = v >= lo && v <= hi;
-            const unsigned long long bb = __builtin_amdgcn_ballot_w64(inb);
-            if (inb) band_idx[tab_b[row * kSelWaves + wave] + __popcll(bb & lt_mask)] = j;
-        )
-        __syncthreads();
-        // ---- the positions whose votes are needed, each once: member c owns those of its pool
-        // window that no earlier member's window covers ----
-        for (int c = threadIdx.x; c < tot_band; c += kSelThreads) {
-            const int jc = band_idx[c];
-            int st = jc - r > 0 ? jc - r : 0;
-            if (c > 0) st = max(st, band_idx[c - 1] + r + 1);
-            const int en = min(jc + r, P - 1);
-            band_start[c] = st;
-            band_off[c] = en >= st ? en - st + 1 : 0;
+        for (int e = threadIdx.x; e < tot_band; e += kSelThreads) {
+            const int j = band_raw[e];
+            int rank = 0;
+            for (int o = 0; o < tot_band; ++o) rank += band_raw[o] < j;
+            band_pos[rank] = j;
         }
         __syncthreads();
-        if (threadIdx.x == 0) {   // exclusive prefix over at most kMaxBand counts
-            int run = 0;
-            for (int c = 0; c < tot_band; ++c) { const int t = band_off[c]; band_off[c] = run; run += t; }
-            band_off[tot_band] = run;
+    }
+    int* hot_pos = hist;                                                   // [kVoteSlots]
+    int n_hot = 0;
+    if (refine && take < tot_band) {
+        // ---- the positions whose votes decide: a member's pooled score is the vote of a position in its
+        // window that lies in the band itself (with a margin for the edge), so only such votes are
+        // scored again, each once -- by the member whose window no earlier member's window covers.  If
+        // one position stands behind the whole band (the usual case: a plateau of the max-pool), its
+        // members are equal in any precision and nothing needs to be scored.
+        const float lo2 = lo * (1.0f - 1.0e-6f), hi2 = hi * (1.0f + 1.0e-6f);
+        const int span = 2 * r + 1;
+        for (int item = threadIdx.x; item < tot_band * span; item += kSelThreads) {
+            const int m = item / span, j = band_pos[m] - r + item % span;
+            if (j < 0 || j >= P || (m > 0 && j <= band_pos[m - 1] + r)) continue;
+            const float v = vote[j];
+            if (v >= lo2 && v <= hi2) {
+                const int e = atomicAdd(&s_hot, 1);
+                if (e < kVoteSlots) hot_pos[e] = j;
+            }
         }
         __syncthreads();
-        n_pos = band_off[tot_band];
-        refine = n_pos <= kVoteSlots;
+        n_hot = __builtin_amdgcn_readfirstlane(s_hot);
+        refine = n_hot <= kVoteSlots;
     }
     if (refine) {
-        // ---- binary64 re-scoring: one wave per (position, 32 window rows); the parts of a position land
-        // in the histogram's LDS and are summed in ascending order into the position's vote, which is kept
-        // in the pooling stage's LDS (both are free by now).  Positions go in batches that fit the parts. ----
-        const int batch = kVoteSlots / n_parts;           // positions per batch (n_parts <= 8)
-        for (int p0 = 0; p0 < n_pos; p0 += batch) {
-            const int np = min(batch, n_pos - p0);
-            for (int item = wave; item < np * n_parts; item += kSelWaves) {
-                const int pos = p0 + item / n_parts, part = item % n_parts;
-                int lo_c = 0, hi_c = tot_band - 1;           // owner: last member with band_off <= pos
-                while (lo_c < hi_c) {
-                    const int mid = (lo_c + hi_c + 1) >> 1;
-                    if (band_off[mid] <= pos) lo_c = mid; else hi_c = mid - 1;
+        if (n_hot > 1) {
+            // ---- binary64 re-scoring: one wave per (position, 32 window rows); the parts of a position are
+            // summed in ascending order.  Positions go in batches that fit the parts. ----
+            double* part_vote = reinterpret_cast<double*>(big);                      // [kPartSlots]
+            double* pos_vote = reinterpret_cast<double*>(big) + kPartSlots;          // [kVoteSlots]
+            const int n_parts = (a.rows + 31) / 32;           // (at most 8)
+            const int batch = kPartSlots / n_parts;
+            for (int p0 = 0; p0 < n_hot; p0 += batch) {
+                const int np = min(batch, n_hot - p0);
+                for (int item = wave; item < np * n_parts; item += kSelWaves) {
+                    const double v = vote_f64_part(a, head, hot_pos[p0 + item / n_parts], 32 * (item % n_parts));
+                    if (lane == 0) part_vote[item] = v;
                 }
-                const int j = band_start[lo_c] + (pos - band_off[lo_c]);
-                const double v = vote_f64_part(a, head, j, 32 * part);
-                if (lane == 0) part_vote[item] = v;
+                __syncthreads();
+                for (int i = threadIdx.x; i < np; i += kSelThreads) {
+                    double sum = 0.0;
+                    for (int q = 0; q < n_parts; ++q) sum += part_vote[i * n_parts + q];
+                    pos_vote[p0 + i] = sum;
+                }
+                __syncthreads();
+            }
+            // ---- pooled binary64 score of each member, and its rank by (score desc, position asc) ----
+            for (int m = threadIdx.x; m < tot_band; m += kSelThreads) {
+                const int j = band_pos[m];
+                double best = 0.0;                            // votes are >= 0
+                for (int i = 0; i < n_hot; ++i)
+                    if (abs(hot_pos[i] - j) <= r) best = fmax(best, pos_vote[i]);
+                band_score[m] = best;
             }
             __syncthreads();
-            for (int i = threadIdx.x; i < np; i += kSelThreads) {
-                double sum = 0.0;
-                for (int q = 0; q < n_parts; ++q) sum += part_vote[i * n_parts + q];
-                pos_vote[p0 + i] = sum;
+            for (int m = threadIdx.x; m < tot_band; m += kSelThreads) {
+                const double sc = band_score[m];
+                int rank = 0;
+                for (int o = 0; o < tot_band; ++o) rank += (band_score[o] > sc) || (band_score[o] == sc && o < m);
+                if (rank < take) set_keep(band_pos[m]);
             }
-            __syncthreads();
-        }
-        // ---- pooled binary64 score of each member ----
-        for (int c = threadIdx.x; c < tot_band; c += kSelThreads) {
-            const int jc = band_idx[c];
-            double best = 0.0;                            // votes are >= 0
-            int o = c;
-            for (int t = r; t >= -r; --t) {               // descending positions: the owner index only falls
-                const int j = jc + t;
-                if (j < 0 || j >= P) continue;
-                while (o > 0 && j < band_start[o]) --o;
-                best = fmax(best, pos_vote[band_off[o] + (j - band_start[o])]);
-            }
-            band_score[c] = best;
+        } else {                                              // all taken, or all equal: by position
+            for (int m = threadIdx.x; m < min(take, tot_band); m += kSelThreads) set_keep(band_pos[m]);
         }
         __syncthreads();
-        // rank inside the band by (score desc, position asc); band_idx is ascending
-        const int take = k - tot_sure;
-        for (int c = threadIdx.x; c < tot_band; c += kSelThreads) {
-            const double sc = band_score[c];
-            int rank = 0;
-            for (int o = 0; o < tot_band; ++o) rank += (band_score[o] > sc) || (band_score[o] == sc && o < c);
-            band_take[c] = rank < take;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int run = 0;
-            for (int c = 0; c < tot_band; ++c) { const int t = band_take[c]; band_take[c] = run; run += t; }
-            band_take[tot_band] = run;
-        }
-        __syncthreads();
-        // ---- ordered compaction ----
-        KVQP_FOR_ROWS(
-            const bool sure = v > hi, inb = v >= lo && v <= hi;
-            const unsigned long long bs = __builtin_amdgcn_ballot_w64(sure);
-            const unsigned long long bb = __builtin_amdgcn_ballot_w64(inb);
-            const int sure_before = tab_a[row * kSelWaves + wave] + __popcll(bs & lt_mask);
-            const int band_before = tab_b[row * kSelWaves + wave] + __popcll(bb & lt_mask);
-            bool keep = sure;
-            if (inb) keep = band_take[band_before + 1] > band_take[band_before];
-            if (keep) idx[sure_before + band_take[band_before]] = j;
-        )
     } else {
         // binary32 decides: everything above the cut, then the first need_at_cut equal to it
         if (a.unrefined && threadIdx.x == 0) a.unrefined[head] = tot_band;
-        KVQP_FOR_ROWS(
-            const unsigned long long bs = __builtin_amdgcn_ballot_w64(v > cut);
-            const unsigned long long bb = __builtin_amdgcn_ballot_w64(v == cut);
-            if (lane == 0) { tab_a[row * kSelWaves + wave] = __popcll(bs); tab_b[row * kSelWaves + wave] = __popcll(bb); }
-            (void)j;
-        )
+        uint32_t* ties = reinterpret_cast<uint32_t*>(big);      // mask of the candidates equal to the cut
+        const int n_words = (P + 31) / 32;
+        each_around([&](uint32_t key, int j) { if (key > cut_key) set_keep(j); });
+        __syncthreads();                                        // (the list is read to its end before its place is taken)
+        // (candidates are pooled again here: the list may not hold them all, and its place is needed)
+        for (int i = threadIdx.x; i < n_words; i += kSelThreads) ties[i] = 0u;
         __syncthreads();
-        (void)scan_table(tab_a, n_rows * kSelWaves, swave);
-        (void)scan_table(tab_b, n_rows * kSelWaves, swave);
-        KVQP_FOR_ROWS(
-            const bool above = v > cut, eq = v == cut;
-            const unsigned long long bs = __builtin_amdgcn_ballot_w64(above);
-            const unsigned long long bb = __builtin_amdgcn_ballot_w64(eq);
-            const int above_before = tab_a[row * kSelWaves + wave] + __popcll(bs & lt_mask);
-            const int eq_before = tab_b[row * kSelWaves + wave] + __popcll(bb & lt_mask);
-            if (above) idx[above_before + min(eq_before, need_at_cut)] = j;
-            else if (eq && eq_before < need_at_cut) idx[above_before + eq_before] = j;
-        )
+        if constexpr (ONE) {
+            each_around([&](uint32_t key, int j) { if (key == cut_key) atomicOr(&ties[j >> 5], 1u << (j & 31)); });
+        } else {
+            for (int j = threadIdx.x; j < P; j += kSelThreads)
+                if (code[code_at(j)] == (cut_key >> kCodeShift) && pooled_key(j) == cut_key) atomicOr(&ties[j >> 5], 1u << (j & 31));
+        }
+        __syncthreads();
+        const int per = (n_words + kSelThreads - 1) / kSelThreads;   // mask words of a thread, in position order
+        int mine = 0;
+        for (int i = 0; i < per; ++i) {
+            const int w = (int)threadIdx.x * per + i;
+            if (w < n_words) mine += __popc(ties[w]);
+        }
+        int left = need_at_cut - sum_before(mine, swave);
+        for (int i = 0; i < per && left > 0; ++i) {
+            const int w = (int)threadIdx.x * per + i;
+            if (w >= n_words) break;
+            for (uint32_t m = ties[w]; m && left > 0; m &= m - 1u, --left) set_keep(32 * w + __builtin_ctz(m));
+        }
+        __syncthreads();
+    }
+
+    // ---- ordered compaction: a wave owns consecutive 64-bit mask words and stores the positions of one
+    // at a time, side by side (a thread that walks the bits of its own mask bytes writes every line
+    // in many pieces: 17 instead of 5 us when 256 heads do it at once; collecting positions in LDS
+    // for 16-byte stores gains nothing: the loop issues instructions, it does not wait for stores) ----
+    const int n_words = (P + 63) / 64, per = (n_words + kSelWaves - 1) / kSelWaves;      // (per <= 128)
+    const int w0 = wave * per, w1 = min(w0 + per, n_words);
+    uint32_t word[4] = {0u, 0u, 0u, 0u};                     // lane l: words w0 + l and w0 + 64 + l
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int w = w0 + 64 * h + lane;
+        if (w < w1) { word[2 * h] = keep[2 * w]; word[2 * h + 1] = 2 * w + 1 < (P + 31) / 32 ? keep[2 * w + 1] : 0u; }
+    }
+    int at = __builtin_amdgcn_readfirstlane(sum_before(__popc(word[0]) + __popc(word[1]) + __popc(word[2]) + __popc(word[3]), swave));
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int n = min(w1 - w0 - 64 * h, 64);
+        for (int u = 0; u < n; ++u) {
+            const uint32_t lo = __builtin_amdgcn_readlane(word[2 * h], u), hi = __builtin_amdgcn_readlane(word[2 * h + 1], u);
+            const unsigned long long m = lo | ((unsigned long long)hi << 32);
+            const int below = (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+            if (__builtin_amdgcn_inverse_ballot_w64(m)) (idx + at)[below] = 64 * (w0 + 64 * h + u) + lane;
+            at += __popcll(m);
+        }
     }
 }
-#undef KVQP_FOR_ROWS
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -713,11 +893,22 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
     p.n_row_slabs = nrw;
     const size_t n_parts = (size_t)p.n_wg * ks;
     size_t off = 0;
-    p.off_stats_part = off; off = align_up(off + (size_t)heads * n_parts * rows_pad * sizeof(float2), 256);
+    // pooling workgroups per head: enough to fill the chip, whole pooling tiles each
+    const int tiles = p.P > 0 ? (p.P + kPoolTile - 1) / kPoolTile : 1;
+    int segs = (512 + heads - 1) / heads;
+    if (segs > kMaxSegs) segs = kMaxSegs;
+    if (segs > tiles) segs = tiles;
+    p.seg_tiles = (tiles + segs - 1) / segs;
+    if (p.seg_tiles > kMaxSegTiles) p.seg_tiles = kMaxSegTiles;
+    p.n_seg = (tiles + p.seg_tiles - 1) / p.seg_tiles;
+    p.p_stride = p.P > 0 ? (p.P + 7) / 8 * 8 : 8;
+    // (the row statistics of the scoring workgroups are dead when the pooled scores are counted)
+    const size_t part_bytes = (size_t)heads * n_parts * rows_pad * sizeof(float2);
+    const size_t bins_bytes = tiles > 1 ? (size_t)heads * p.n_seg * kBins * sizeof(uint16_t) : 0;
+    p.off_stats_part = off; off = align_up(off + (part_bytes > bins_bytes ? part_bytes : bins_bytes), 256);
     p.off_stats = off;      off = align_up(off + (size_t)heads * rows_pad * (sizeof(float2) + sizeof(double)), 256);
     p.off_vote = off;       off = align_up(off + (size_t)heads * (p.P > 0 ? p.P : 1) * sizeof(float), 256);
-    p.off_pooled = off;     off = align_up(off + (size_t)heads * (p.P > 0 ? p.P : 1) * sizeof(float), 256);
-    p.off_sel = off;
+    p.off_pooled = off;     off = align_up(off + (size_t)heads * p.p_stride * sizeof(uint16_t), 256);
     p.off_idx = off;        off = align_up(off + (size_t)heads * (p.n_kept > 0 ? p.n_kept : 1) * sizeof(int32_t), 256);
     p.total = off;
     return p;
@@ -758,12 +949,19 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
         if (e != hipSuccess) return e;
     }
     SelectArgs s;
-    s.vote = a.vote; s.pooled = reinterpret_cast<float*>(base + plan.off_pooled); s.idx = idx; s.unrefined = unrefined; s.head_n = head_n;
+    s.vote = a.vote; s.code = reinterpret_cast<uint16_t*>(base + plan.off_pooled); s.idx = idx; s.unrefined = unrefined; s.head_n = head_n;
     s.q_obs = a.q_obs; s.k = a.k; s.stats = stats; s.zsum = zsum;
     s.P = plan.P; s.L = cfg.seq_len; s.W = cfg.window; s.n_kept = plan.n_kept; s.pool = cfg.pool_kernel;
     s.gq = a.gq; s.n_q_heads = cfg.n_q_heads; s.n_kv_heads = cfg.n_kv_heads; s.rows = a.rows; s.rows_pad = a.rows_pad;
     s.scale_log2 = a.scale_log2; s.sm_scale = cfg.sm_scale;
-    hipLaunchKernelGGL(select_topk, dim3(heads), dim3(kSelThreads), 0, stream, s);
+    s.bins = reinterpret_cast<uint16_t*>(base + plan.off_stats_part);
+    s.p_stride = plan.p_stride; s.n_seg = plan.n_seg; s.seg_tiles = plan.seg_tiles;
+    if (plan.P <= kPoolTile) {
+        hipLaunchKernelGGL(select_topk<true>, dim3(heads), dim3(kSelThreads), 0, stream, s);
+    } else {
+        if (score) hipLaunchKernelGGL(pool_scores, dim3(plan.n_seg, heads), dim3(kSelThreads), 0, stream, s);
+        hipLaunchKernelGGL(select_topk<false>, dim3(heads), dim3(kSelThreads), 0, stream, s);
+    }
     return hipGetLastError();
 }
 

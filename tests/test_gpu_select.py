@@ -1,0 +1,83 @@
+"""Token selection at the sizes where its kernels change course (paper Section 3, "KV Pruning"):
+prefixes around the pooling tile of 4096 candidates (one kernel up to it, a pooling kernel of several
+workgroups beyond it), around the groups of eight candidates whose codes share 16 bytes, pooling
+windows up to the widest, cuts in the lowest score bin, and candidates around the cut that do not
+fit the list in LDS.  Indices against the checker, which scores in binary64."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2412_12706_amd import kvqp, synth
+from tests.gpu_util import dev
+from tests.test_gpu_compress import check_indices
+
+pytestmark = pytest.mark.gpu
+
+
+def select(orc, P, W, pool, budget, Gq=2, Hkv=2, sm_scale=None, outlier=10.0, keys=None, seed=60):
+    L, Hq = P + W, Hkv * Gq
+    q_obs, k, v = synth.prompt_host(1, Hq, Hkv, L, W, 128, outlier=outlier, config=seed)
+    if keys is not None:
+        keys(k)
+    cfg = kvqp.Cfg(batch=1, n_q_heads=Hq, n_kv_heads=Hkv, seq_len=L, window=W, pool_kernel=pool, budget=budget, bits=16,
+                   sm_scale=sm_scale or 128 ** -0.5)
+    _, idx, pooled = orc.compress(q_obs, k, v, window=W, pool=pool, budget=budget, bits=16, G=32, sm_scale=float(np.float32(cfg.sm_scale)))
+    gc = kvqp.alloc_cache(cfg)
+    got = torch.full((1, Hkv, cfg.n_kept), -1, dtype=torch.int32, device="cuda")
+    unrefined = torch.full((Hkv,), -1, dtype=torch.int32, device="cuda")
+    kvqp.compress(cfg, dev(q_obs), dev(k), dev(v), gc, idx_out=got, unrefined_out=unrefined)
+    torch.cuda.synchronize()
+    return got.cpu().numpy(), idx, pooled, unrefined.cpu().tolist()
+
+
+@pytest.mark.parametrize("P,pool,budget", [
+    (2, 1, 1), (7, 3, 3), (9, 7, 8), (64, 63, 10), (1025, 5, 1024), (4095, 7, 1000), (4096, 63, 4095), (4096, 1, 1),
+    (4097, 7, 1), (4104, 1, 4103), (8191, 13, 2000), (8193, 63, 513), (12289, 3, 6000), (40001, 7, 9001)])
+def test_survivors_match_the_checker(orc, P, pool, budget):
+    print(f"case P={P} pool={pool} budget={budget}", flush=True)
+    got, idx, pooled, unrefined = select(orc, P, 8, pool, budget, seed=60 + P % 7)
+    check_indices(got, idx, pooled)
+    assert unrefined == [0, 0]
+
+
+@pytest.mark.parametrize("P,budget", [(3000, 2850), (9000, 8700)])
+def test_cut_in_the_lowest_score_bin(orc, P, budget):
+    """A single sharp row spreads its votes over ninety factors of two: the cut lies below 2^-55, where
+    all scores share one bin, and the list of candidates around it is long."""
+    print(f"case low cut P={P} budget={budget}", flush=True)
+    got, idx, pooled, unrefined = select(orc, P, 1, 1, budget, Gq=1, sm_scale=0.7, outlier=1.0, seed=71)
+    assert all(np.sort(pooled[0, g])[-budget] < 2.0 ** -55 for g in range(2))
+    check_indices(got, idx, pooled)
+    assert unrefined == [0, 0]
+
+
+@pytest.mark.parametrize("P,budget,distinct", [(6000, 1500, 1), (9000, 4000, 2), (4090, 100, 1)])
+def test_more_ties_than_the_list_holds(orc, P, budget, distinct):
+    """Prefixes of one or two distinct key rows: thousands of scores tie at the cut exactly, more than
+    the list in LDS and the binary64 re-scoring hold; the lowest positions win and the call says how
+    many candidates binary32 decided."""
+    print(f"case ties P={P} budget={budget} distinct={distinct}", flush=True)
+
+    def keys(k):
+        for d in range(distinct):
+            k[:, :, d:P:distinct] = k[:, :, d:d + 1]
+    got, idx, _, unrefined = select(orc, P, 8, 1, budget, keys=keys, seed=73)
+    assert np.array_equal(got, idx)
+    assert unrefined == [-(-P // distinct)] * 2
+
+
+def test_clustered_scores_beyond_the_list_are_still_refined(orc):
+    """Six thousand scores within one percent of the cut but few within the band that binary32 could
+    misplace: the candidates do not fit the list, and the cut is binary64's all the same."""
+    P = 6500
+
+    def keys(k):
+        base = k[:, :, :1].astype(np.float32)
+        k[:, :, :P] = (base + 0.005 * k[:, :, :P].astype(np.float32)).astype(np.float16)
+    print("case clustered", flush=True)
+    got, idx, pooled, unrefined = select(orc, P, 8, 1, 3000, outlier=1.0, keys=keys, seed=75)
+    for g in range(2):
+        kth = np.sort(pooled[0, g])[-3000]
+        assert (np.abs(pooled[0, g] / kth - 1) < 0.004).sum() > 3840
+    check_indices(got, idx, pooled)
+    assert unrefined == [0, 0]

@@ -68,7 +68,8 @@ struct CompressPlan {
     int P, n_kept, rows;          // rows = Gq * W query rows per kv head
     int n_chunks;                 // key chunks of the scoring passes
     int n_wg, chunks_per_wg;      // scoring workgroups per kv head and their share
-    int n_row_slabs;              // 64-row slabs of query rows (1, 2 or 4)
+    int rows_pad;                 // rows the scoring kernels cover
+    int n_parts;                  // row statistics per kv head that the first scoring pass leaves
     int n_seg, seg_tiles;         // pooling workgroups per kv head and their share in pooling tiles
     int p_stride;                 // score codes of a head, padded to whole 16-byte pieces
     size_t off_stats_part, off_stats, off_vote, off_pooled, off_idx, total;

@@ -18,8 +18,11 @@
 //   select_topk        find the cut, ordered compaction; scores within a relative
 //                      2e-5 of the cut are first re-scored in binary64 so that
 //                      binary32 rounding cannot move the cut
-// Keys stream through LDS once per pass in 64- or 128-key chunks shared by the
-// four waves of a workgroup; query rows stay in registers as MFMA operands.
+// score_pass (up to 128 window rows): keys stream through LDS once per pass in 64- or
+// 128-key chunks shared by the four waves of a workgroup; query rows stay in registers as
+// MFMA operands.  score_wide (more rows): keys in registers, query rows in LDS.
+#include <algorithm>
+
 #include "kvqp_internal.h"
 
 namespace kvqp {
@@ -31,15 +34,16 @@ union Frag {
     h8v v;
     uint4 q;
 };
+template <int I> struct IntC { static constexpr int value = I; };
+template <bool B> struct BoolC { static constexpr bool value = B; };
 
 constexpr int kThreads = 256;
-// Query rows one wave owns (its MFMA A operands, register-resident): 32 when the group has up to
-// 128 window rows (small register footprint, four waves per SIMD), else 64.
-constexpr int rows_per_wave(int rows) { return rows <= 128 ? 32 : 64; }
+constexpr int kRowsPerWave = 32;        // score_pass: query rows one wave owns (its MFMA A operands, register-resident)
+constexpr int kNarrowRows = 4 * kRowsPerWave;   // window rows of a KV head it takes; more are score_wide's
 constexpr int kKeyStride = kHeadDim * 2 + 16;  // LDS bytes per key row; +16 B skews banks
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1.0e30f;
-constexpr float kLazy = 8.0f;           // pass 1 moves a row's reference only when a score beats it by 2^8
+constexpr float kLazy = 8.0f;           // score_pass moves a row's reference only when a score beats it by 2^8
 
 enum { PASS_STATS = 0, PASS_VOTES = 1 };
 
@@ -55,16 +59,17 @@ struct ScoreArgs {
     float scale_log2;       // sm_scale * log2(e)
 };
 
-// NRW = number of row slabs (1, 2, 4) of RPW rows; the 4 waves are NRW row slabs x KS key strips.
+// NRW = number of row slabs (1, 2, 4) of 32 rows; the 4 waves are NRW row slabs x KS key strips.
 template <int NRW> struct ScoreGeom {
     static constexpr int KS = 4 / NRW;
     static constexpr int CK = (KS == 1) ? 64 : 128;   // keys per chunk
     static constexpr int KT = CK / (16 * KS);         // key tiles per wave per chunk
 };
 
-template <int RPW, int NRW, int PASS>
-__global__ __launch_bounds__(kThreads, RPW == 32 ? 4 : 2) void score_pass(const ScoreArgs a) {
-    constexpr int kRowsPerWave = RPW, kMT = RPW / 16;
+// Up to 128 window rows.
+template <int NRW, int PASS>
+__global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
+    constexpr int kMT = kRowsPerWave / 16;
     using Gm = ScoreGeom<NRW>;
     constexpr int KS = Gm::KS, CK = Gm::CK, KT = Gm::KT;
     __shared__ __align__(16) unsigned char sk[CK * kKeyStride];
@@ -78,7 +83,7 @@ __global__ __launch_bounds__(kThreads, RPW == 32 ? 4 : 2) void score_pass(const 
     const int rw = wave % NRW, ks = wave / NRW;
     const uint16_t* kh = a.k + (size_t)head * a.L * kHeadDim;
 
-    // Query operand: rows 64*rw + 16*mt + (lane & 15), channels 32*s + 8*kb .. +8.
+    // Query operand: rows 32*rw + 16*mt + (lane & 15), channels 32*s + 8*kb .. +8.
     Frag qf[kMT][4];
 #pragma unroll
     for (int mt = 0; mt < kMT; ++mt) {
@@ -191,7 +196,7 @@ __global__ __launch_bounds__(kThreads, RPW == 32 ? 4 : 2) void score_pass(const 
 #pragma unroll
                     for (int i = 0; i < 4; ++i) z_run[mt][i] += __builtin_amdgcn_exp2f(e[mt][i]);
             } else {
-                // normalised probabilities summed over this wave's 64 rows, per key
+                // normalised probabilities summed over this wave's 32 rows, per key
                 float c0 = 0.f, c1 = 0.f;
 #pragma unroll
                 for (int mt = 0; mt < kMT; ++mt)
@@ -243,6 +248,229 @@ __global__ __launch_bounds__(kThreads, RPW == 32 ? 4 : 2) void score_pass(const 
                     a.stats_part[((size_t)head * a.n_parts + blockIdx.x * KS + ks) * a.rows_pad + r] = make_float2(m, z);
                 }
             }
+    }
+}
+
+// 129 to 256 window rows (RT tiles of 16).  Matrix instructions and exponentials, twice as many per key
+// as above, bound these passes unless something else gets in their way: with the keys in LDS for
+// four waves of 64 rows each, every key is read from LDS four times, the waves meet at two barriers
+// per 64 keys, and 64 query rows per wave in registers leave room for one matrix chain at a time.
+// So a wave owns its keys outright: 64 of them stay in its registers as the A operand, requested
+// from memory in operand layout (a load instruction covers 64 bytes of 16 rows) one step ahead, and
+// the query rows, the same for every wave, are read from LDS as the B operand, one read per four
+// matrix instructions.  No barrier in the loop, no key through LDS; the products of a row tile run
+// while the scores of the tile before it are exponentiated.  A lane's accumulators are keys of ONE
+// row, so a row's reference is one register.  8 heads, 131072 keys, 256 rows: 124 + 91 us (statistics +
+// votes) with score_pass's layout, 93 + 85 us this way; up to 128 rows score_pass is as fast or faster
+// (8 heads of 32768 keys: 23 + 19 against 24 + 21 us; of 4096 keys 10 + 7 against 12 + 9).
+constexpr int kWideTiles = 16;                 // row tiles
+constexpr int kKeyTiles = 4;                   // 16-key tiles a wave holds
+constexpr int kChunkKeys = 16 * kKeyTiles;     // keys of a wave's step
+constexpr int kScoreWaves = kThreads / 64;
+constexpr float kFarSum = 1.152921504606846976e18f;   // 2^60: a row's reference is moved when a sum relative to it passes this
+template <int PASS>
+__global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
+    constexpr int RT = kWideTiles;
+    __shared__ __align__(16) uint4 sq[RT * 4 * 64];      // query operand: [row tile][contraction step][lane]
+    const int head = blockIdx.y;
+    const int b = head / a.n_kv_heads, g = head % a.n_kv_heads;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, kb = lane >> 4;
+    const char* kh = reinterpret_cast<const char*>(a.k + (size_t)head * a.L * kHeadDim);
+
+    // ---- a wave's keys: tile kt, contraction step s -> key 16 kt + n, channels 32 s + 8 kb .. + 8 ----
+    typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+    struct Keys { u4v f[kKeyTiles][4]; };
+    auto load = [&](Keys& d, int chunk) {
+#pragma unroll
+        for (int kt = 0; kt < kKeyTiles; ++kt) {
+            const int key = min(chunk * kChunkKeys + 16 * kt + n, a.L - 1);      // (rows past the end are masked)
+            const u4v* p = reinterpret_cast<const u4v*>(kh + (uint32_t)key * (2u * kHeadDim) + 16u * kb);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                d.f[kt][s] = (PASS == PASS_VOTES) ? __builtin_nontemporal_load(p + 4 * s) : p[4 * s];   // last read of a key: streamed
+        }
+    };
+    const int c_end = min(a.n_chunks, ((int)blockIdx.x + 1) * a.chunks_per_wg);
+    int chunk = (int)blockIdx.x * a.chunks_per_wg + wave;
+    Keys keys;
+    if (chunk < c_end) load(keys, chunk);
+
+    // STATS: reference (log2 domain) and sum of exp2(score - reference) of row 16 rt + n over the
+    // lane's keys.  VOTES: m and 1/Z of the row.
+    float m_run[RT], z_run[RT];
+    if constexpr (PASS == PASS_STATS) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) { m_run[rt] = kNegBig; z_run[rt] = 0.f; }
+    } else {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            const int r = 16 * rt + n;
+            const float2 st = a.stats[(size_t)head * a.rows_pad + r];
+            m_run[rt] = st.x; z_run[rt] = (r < a.rows) ? st.y : 0.f;
+        }
+    }
+
+    // ---- query operand: row 16 rt + n, channels 32 s + 8 kb .. + 8 ----
+#pragma unroll 4
+    for (int item = threadIdx.x; item < RT * 4 * 64; item += kThreads) {
+        const int r = 16 * (item >> 8) + (item & 15), ch = 32 * ((item >> 6) & 3) + 8 * ((item >> 4) & 3);
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (r < a.rows) {
+            const int hl = r / a.W, i = r % a.W;
+            v = *reinterpret_cast<const uint4*>(a.q_obs + (((size_t)b * a.n_q_heads + g * a.gq + hl) * a.W + i) * kHeadDim + ch);
+        }
+        sq[item] = v;
+    }
+    __syncthreads();
+
+    const int w_first = n % a.W, w_step = 16 % a.W;               // window position of row n; from a row tile to the next
+    // A step comes in two forms without a branch inside (branches let the compiler start later tiles
+    // early, which do not fit the registers).  The careful one masks keys the rows may not see and
+    // moves the references to the rows' maxima; it takes a wave's first step, the steps that reach the
+    // window, and those of which the other one finds a sum out of range: scores are taken relative to
+    // the reference as it is, which costs no precision while their sums stay below kFarSum.
+    // Returns whether the step was out of range (then nothing has been added).
+    auto compute = [&](auto careful, const Keys& key_f, int c) -> bool {
+        constexpr bool CAREFUL = decltype(careful)::value;
+        float z_add[RT];
+        int at = lane, wr = w_first;
+        asm volatile("" : "+v"(at));                             // (the query operand is read again every step, not kept for the whole loop)
+        float vs[kKeyTiles][4];                                  // VOTES: the lane's row sums per key 16 kt + 4 kb + i
+#pragma unroll
+        for (int kt = 0; kt < kKeyTiles; ++kt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) vs[kt][i] = 0.f;
+        auto product = [&](f4v (&acc)[kKeyTiles], int rt) {      // scores of row tile rt
+            Frag qf[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) qf[s].q = sq[(rt * 4 + s) * 64 + at];
+#pragma unroll
+            for (int kt = 0; kt < kKeyTiles; ++kt) acc[kt] = (f4v){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int kt = 0; kt < kKeyTiles; ++kt)
+                    acc[kt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8v, key_f.f[kt][s]), qf[s].v, acc[kt], 0, 0, 0);
+        };
+        f4v acc[kKeyTiles], acc_next[kKeyTiles];                 // the next tile's product runs while this one's scores are used
+        product(acc, 0);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            if (rt + 1 < RT) product(acc_next, rt + 1);
+            if constexpr (CAREFUL) {                             // causal mask (raw scores; the scale is positive)
+                const int last = min(a.P + wr, a.L - 1) - c * kChunkKeys - 4 * kb;   // the row's last key, from the lane's first one
+#pragma unroll
+                for (int kt = 0; kt < kKeyTiles; ++kt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (16 * kt + i > last) acc[kt][i] = -INFINITY;
+                wr += w_step;                                    // (window position of row 16 (rt + 1) + n)
+                if (wr >= a.W) wr -= a.W;
+            }
+            if constexpr (PASS == PASS_STATS) {
+                if constexpr (CAREFUL) {
+                    float big = acc[0][0];
+#pragma unroll
+                    for (int kt = 0; kt < kKeyTiles; ++kt)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) big = fmaxf(big, acc[kt][i]);
+                    const float m_new = fmaxf(m_run[rt], big * a.scale_log2);
+                    z_run[rt] *= __builtin_amdgcn_exp2f(m_run[rt] - m_new);
+                    m_run[rt] = m_new;
+                }
+                float z0 = 0.f, z1 = 0.f;
+#pragma unroll
+                for (int kt = 0; kt < kKeyTiles; ++kt)
+#pragma unroll
+                    for (int i = 0; i < 4; i += 2) {
+                        z0 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[kt][i], a.scale_log2, -m_run[rt]));
+                        z1 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[kt][i + 1], a.scale_log2, -m_run[rt]));
+                    }
+                z_add[rt] = z0 + z1;
+                asm volatile("" : "+v"(z_add[rt]));              // (formed here and not where it is added: 16 registers per tile)
+            } else {
+#pragma unroll
+                for (int kt = 0; kt < kKeyTiles; ++kt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        vs[kt][i] = __builtin_fmaf(__builtin_amdgcn_exp2f(__builtin_fmaf(acc[kt][i], a.scale_log2, -m_run[rt])),
+                                                   z_run[rt], vs[kt][i]);
+            }
+#pragma unroll
+            for (int kt = 0; kt < kKeyTiles; ++kt) acc[kt] = acc_next[kt];
+            __builtin_amdgcn_sched_barrier(0);                   // (tiles started early would not fit the registers)
+        }
+        if constexpr (PASS == PASS_STATS) {
+            if constexpr (!CAREFUL) {
+                bool far = false;
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) far |= !(z_add[rt] < kFarSum);
+                if (__builtin_amdgcn_ballot_w64(far) != 0ull) return true;
+            }
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) z_run[rt] += z_add[rt];
+        } else {
+            // sum over the 16 lanes of a row of lanes, each ending up with one of the 16 values: lane n with
+            // (kt, i) = (n / 4, n % 4).  At every step a lane keeps the half of the values that its bit
+            // selects and receives its partner's sums of that half.
+            float x[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) x[e] = vs[e >> 2][e & 3];
+            auto fold = [&](auto half, auto ctrl, bool upper) {
+                constexpr int H = decltype(half)::value;
+#pragma unroll
+                for (int e = 0; e < H; ++e) {
+                    const float keep = upper ? x[e + H] : x[e], give = upper ? x[e] : x[e + H];
+                    x[e] = keep + __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(give), decltype(ctrl)::value, 0xf, 0xf, true));
+                }
+            };
+            fold(IntC<8>{}, IntC<0x140>{} /* row_mirror */, (n & 8) != 0);
+            fold(IntC<4>{}, IntC<0x141>{} /* row_half_mirror */, (n & 4) != 0);
+            fold(IntC<2>{}, IntC<0x4E>{} /* quad_perm [2,3,0,1] */, (n & 2) != 0);
+            fold(IntC<1>{}, IntC<0xB1>{} /* quad_perm [1,0,3,2] */, (n & 1) != 0);
+            const int key = c * kChunkKeys + 16 * (n >> 2) + 4 * kb + (n & 3);
+            if (key < a.P) a.vote[(size_t)head * a.P + key] = x[0];
+        }
+        return false;
+    };
+    bool first = PASS == PASS_STATS;
+    for (; chunk < c_end; chunk += kScoreWaves) {
+        Keys next;
+        if (chunk + kScoreWaves < c_end) load(next, chunk + kScoreWaves);
+        if (first || (chunk + 1) * kChunkKeys > a.P || compute(BoolC<false>{}, keys, chunk)) compute(BoolC<true>{}, keys, chunk);
+        first = false;
+        keys = next;
+    }
+
+    if constexpr (PASS == PASS_STATS) {
+        // merge the four lanes that share a row, then the waves through LDS
+        __syncthreads();                                         // (every wave is done with the query operand)
+        float2* s_st = reinterpret_cast<float2*>(sq);            // [wave][16 RT]
+        static_assert(kScoreWaves * 16 * RT * 8 <= sizeof(sq), "the statistics fit the query operand's place");
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            float m = m_run[rt], z = z_run[rt];
+#pragma unroll
+            for (int off = 16; off < 64; off <<= 1) {
+                const float mo = __shfl_xor(m, off), zo = __shfl_xor(z, off);
+                const float mn = fmaxf(m, mo);
+                z = z * __builtin_amdgcn_exp2f(m - mn) + zo * __builtin_amdgcn_exp2f(mo - mn);
+                m = mn;
+            }
+            if (kb == 0) s_st[wave * 16 * RT + 16 * rt + n] = make_float2(m, z);
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < 16 * RT) {
+            float2 v[kScoreWaves];
+            float m = kNegBig, z = 0.f;
+#pragma unroll
+            for (int w = 0; w < kScoreWaves; ++w) { v[w] = s_st[w * 16 * RT + threadIdx.x]; m = fmaxf(m, v[w].x); }
+#pragma unroll
+            for (int w = 0; w < kScoreWaves; ++w) z = __builtin_fmaf(v[w].y, __builtin_amdgcn_exp2f(v[w].x - m), z);
+            a.stats_part[((size_t)head * a.n_parts + blockIdx.x) * (16 * RT) + threadIdx.x] = make_float2(m, z);
+        }
     }
 }
 
@@ -855,20 +1083,18 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-int n_row_slabs(const kvqp_cfg& cfg) {
-    const int rows = (cfg.n_q_heads / cfg.n_kv_heads) * cfg.window;
-    const int rpw = rows_per_wave(rows);
-    const int slabs = (rows + rpw - 1) / rpw;
-    return slabs <= 1 ? 1 : slabs == 2 ? 2 : 4;
+// Slabs of 32 window rows score_pass covers: 1, 2 or 4.  0: more rows than it takes.
+int n_row_slabs(int rows) {
+    const int slabs = (rows + kRowsPerWave - 1) / kRowsPerWave;
+    return rows > kNarrowRows ? 0 : slabs <= 1 ? 1 : slabs == 2 ? 2 : 4;
 }
 
-template <int RPW, int NRW>
-hipError_t launch_scores(const ScoreArgs& a, int n_wg, int heads, hipStream_t stream, float2* stats, double* zsum) {
-    ScoreArgs s1 = a;
-    hipLaunchKernelGGL((score_pass<RPW, NRW, PASS_STATS>), dim3(n_wg, heads), dim3(kThreads), 0, stream, s1);
+template <class Stats, class Votes>
+hipError_t launch_scores(Stats stats_pass, Votes vote_pass, const ScoreArgs& a, int n_wg, int heads, hipStream_t stream, float2* stats, double* zsum) {
+    hipLaunchKernelGGL(stats_pass, dim3(n_wg, heads), dim3(kThreads), 0, stream, a);
     hipLaunchKernelGGL(stats_combine, dim3(heads, (a.rows_pad + 3) / 4), dim3(256), 0, stream, (const float2*)a.stats_part, stats, zsum,
                        a.n_parts, a.rows_pad);
-    hipLaunchKernelGGL((score_pass<RPW, NRW, PASS_VOTES>), dim3(n_wg, heads), dim3(kThreads), 0, stream, s1);
+    hipLaunchKernelGGL(vote_pass, dim3(n_wg, heads), dim3(kThreads), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -879,19 +1105,29 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
     p.P = cfg.seq_len - cfg.window;
     p.n_kept = cfg.budget < p.P ? cfg.budget : p.P;
     p.rows = (cfg.n_q_heads / cfg.n_kv_heads) * cfg.window;
-    const int nrw = n_row_slabs(cfg);
-    const int rows_pad = nrw * rows_per_wave(p.rows);
-    const int ks = 4 / nrw, ck = (ks == 1) ? 64 : 128;
-    const int heads = cfg.batch * cfg.n_kv_heads;
+    const int nrw = n_row_slabs(p.rows), heads = cfg.batch * cfg.n_kv_heads;
+    const bool wide = nrw == 0;
+    p.rows_pad = wide ? 16 * kWideTiles : nrw * kRowsPerWave;
+    const int ks = wide ? 1 : 4 / nrw;                   // statistics a workgroup leaves per row
+    const int ck = wide || ks == 1 ? 64 : 128;           // keys per chunk
     p.n_chunks = (cfg.seq_len + ck - 1) / ck;
-    // enough workgroups to fill the chip a few times over, at least 2 chunks each
-    int n_wg = (2048 + heads - 1) / heads;
-    if (n_wg > (p.n_chunks + 1) / 2) n_wg = (p.n_chunks + 1) / 2;
+    // A workgroup pays for staging its query rows and waits for its first keys alone, so it should have
+    // sixteen chunks (64 where the wave holds more rows), as long as that leaves two workgroups per CU;
+    // beyond eight per CU more only cost.  Statistics + votes, us, with 512 / 1024 / 2048 workgroups: 8
+    // heads of 32768 keys 23 + 19 / 26 + 19 / 32 + 22, 32 heads of 16384 37 + 34 / 39 + 32 / 46 + 35, 64 heads
+    // 62 + 59 / 61 + 55 / 68 + 57, 128 heads 117 + 122 / 117 + 110 / 118 + 108, 256 heads of 32768 431 + 494 /
+    // 419 + 419 / 415 + 418; with 256 rows 16 heads of 65536 keys 93 + 85 / 101 + 89 / 128 + 102.
+    const long long chunks = (long long)heads * p.n_chunks;
+    const int total = (int)std::min(2048LL, std::max(512LL, chunks / (wide ? 64 : 16)));
+    int n_wg = (total + heads - 1) / heads;
+    const int least = wide ? kScoreWaves : 2;
+    if (n_wg > (p.n_chunks + least - 1) / least) n_wg = (p.n_chunks + least - 1) / least;
     if (n_wg < 1) n_wg = 1;
     p.chunks_per_wg = (p.n_chunks + n_wg - 1) / n_wg;
     p.n_wg = (p.n_chunks + p.chunks_per_wg - 1) / p.chunks_per_wg;
-    p.n_row_slabs = nrw;
-    const size_t n_parts = (size_t)p.n_wg * ks;
+    p.n_parts = p.n_wg * ks;
+    const int rows_pad = p.rows_pad;
+    const size_t n_parts = (size_t)p.n_parts;
     size_t off = 0;
     // pooling workgroups per head: enough to fill the chip, whole pooling tiles each
     const int tiles = p.P > 0 ? (p.P + kPoolTile - 1) / kPoolTile : 1;
@@ -918,33 +1154,28 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
                          const CompressPlan& plan, const int32_t* head_n, bool score, hipStream_t stream) {
     char* base = static_cast<char*>(ws);
     const int heads = cfg.batch * cfg.n_kv_heads;
-    const int nrw = plan.n_row_slabs;
-    const int ks = 4 / nrw;
-    const int n_wg = plan.n_wg, cpw = plan.chunks_per_wg;
+    const int n_wg = plan.n_wg;
 
     ScoreArgs a;
     a.q_obs = (const uint16_t*)q_obs; a.k = (const uint16_t*)k;
     a.stats_part = reinterpret_cast<float2*>(base + plan.off_stats_part);
     float2* stats = reinterpret_cast<float2*>(base + plan.off_stats);
-    a.rows = plan.rows; a.rows_pad = nrw * rows_per_wave(plan.rows);
+    a.rows = plan.rows; a.rows_pad = plan.rows_pad;
     double* zsum = reinterpret_cast<double*>(base + plan.off_stats + (size_t)heads * a.rows_pad * sizeof(float2));
     a.stats = stats;
     a.vote = reinterpret_cast<float*>(base + plan.off_vote);
     a.L = cfg.seq_len; a.W = cfg.window; a.P = plan.P; a.gq = cfg.n_q_heads / cfg.n_kv_heads;
     a.n_q_heads = cfg.n_q_heads; a.n_kv_heads = cfg.n_kv_heads;
-    a.chunks_per_wg = cpw; a.n_chunks = plan.n_chunks; a.n_parts = n_wg * ks;
+    a.chunks_per_wg = plan.chunks_per_wg; a.n_chunks = plan.n_chunks; a.n_parts = plan.n_parts;
     a.scale_log2 = cfg.sm_scale * kLog2e;
 
     hipError_t e;
     if (score) {   // scores are needed only when something is dropped
-        if (rows_per_wave(plan.rows) == 32) {
-            switch (nrw) {
-                case 1: e = launch_scores<32, 1>(a, n_wg, heads, stream, stats, zsum); break;
-                case 2: e = launch_scores<32, 2>(a, n_wg, heads, stream, stats, zsum); break;
-                default: e = launch_scores<32, 4>(a, n_wg, heads, stream, stats, zsum); break;
-            }
-        } else {
-            e = launch_scores<64, 4>(a, n_wg, heads, stream, stats, zsum);   // 129..256 rows: four 64-row slabs
+        switch (n_row_slabs(plan.rows)) {
+            case 1: e = launch_scores(score_pass<1, PASS_STATS>, score_pass<1, PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
+            case 2: e = launch_scores(score_pass<2, PASS_STATS>, score_pass<2, PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
+            case 4: e = launch_scores(score_pass<4, PASS_STATS>, score_pass<4, PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
+            default: e = launch_scores(score_wide<PASS_STATS>, score_wide<PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
         }
         if (e != hipSuccess) return e;
     }

@@ -81,3 +81,28 @@ def test_clustered_scores_beyond_the_list_are_still_refined(orc):
         assert (np.abs(pooled[0, g] / kth - 1) < 0.004).sum() > 3840
     check_indices(got, idx, pooled)
     assert unrefined == [0, 0]
+
+
+@pytest.mark.parametrize("Gq,W", [(4, 64), (8, 17), (4, 32), (1, 5)])
+def test_scores_that_leave_the_first_keys_far_behind(orc, Gq, W):
+    """Keys that grow fourteenfold halfway through the prompt: row maxima pass the references taken from
+    a workgroup's first keys by more than 2^60, which makes the statistics pass of the wide kernel
+    (more than 128 window rows) do a step again with moved references."""
+    P = 4500
+    print(f"case growing keys Gq={Gq} W={W}", flush=True)
+
+    def keys(k):
+        k[:, :, P // 2:P] = (k[:, :, P // 2:P].astype(np.float32) * 14).astype(np.float16)
+    got, idx, pooled, unrefined = select(orc, P, W, 7, 300, Gq=Gq, Hkv=2, outlier=1.0, keys=keys, seed=77)
+    check_indices(got, idx, pooled)
+    assert unrefined == [0, 0]
+
+
+@pytest.mark.parametrize("P,Gq,W", [(1, 8, 32), (63, 4, 64), (191, 8, 17), (257, 8, 31), (4097, 4, 33)])
+def test_wide_windows_at_the_edges_of_a_step(orc, P, Gq, W):
+    """More than 128 window rows: key counts around the 64 keys of a wave's step, row counts that do not
+    fill a tile of 16."""
+    print(f"case wide P={P} Gq={Gq} W={W}", flush=True)
+    got, idx, pooled, unrefined = select(orc, P, W, 5, max(1, P // 3), Gq=Gq, seed=79)
+    check_indices(got, idx, pooled)
+    assert unrefined == [0, 0]

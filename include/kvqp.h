@@ -350,9 +350,10 @@ int kvqp_decode_workspace_init(const kvqp_cfg *cfg, void *workspace, size_t work
  * kvqp_decode_attn for callers that cannot allocate device memory or carry a
  * workspace: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same arguments, same result, no workspace: the partial
- * results and arrival counters of the token-axis splits live in an array of
- * KVQP_STATIC_SCRATCH_BYTES that the library owns (static device storage, one
- * copy per GPU the library runs on, held until the process ends).  The call
+ * results and arrival counters of the token-axis splits live in an array that
+ * the library owns (static device storage, KVQP_STATIC_SCRATCH_BYTES and room for
+ * every head's counter, one copy per GPU the library runs on, held until the
+ * process ends).  The call
  * allocates and frees nothing and never synchronises.
  *   - A launch whose splits need more than KVQP_STATIC_SCRATCH_BYTES (see
  *     kvqp_workspace_bytes' decode_bytes) returns KVQP_ERR_WORKSPACE and

@@ -27,6 +27,8 @@
 // and writes the output itself; otherwise a head is split over several
 // workgroups whose partial (m, l, O) go to the workspace, and the last one to
 // arrive merges them (no second kernel).
+#include <cmath>
+#include <initializer_list>
 #include <mutex>
 
 #include "kvqp_internal.h"
@@ -38,7 +40,7 @@
 // Each device's copy starts all zero (static storage) and every completed launch leaves the
 // arrival counters at its head zero again; they are nevertheless zeroed by a fill kernel when a
 // device's address is first taken.  Calls that use it share it: they must not overlap on one device.
-static __device__ __align__(256) unsigned char scratch[KVQP_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[kvqp::kStaticCounterBytes + kvqp::kStaticScratchBytes];
 
 namespace kvqp {
 namespace {
@@ -1479,7 +1481,27 @@ size_t decode_ws_bound(const kvqp_cfg& cfg) {
     return decode_ws_header_bytes(cfg) + (size_t)heads * splits * gq * kPartFloats * sizeof(float);
 }
 
+// Microseconds of a launch of `splits` workgroups of nw waves per head (equal heads), as measured over
+// 3100 shapes (4 to 512 heads of 290 to 20000 tokens, all bit widths, 2 to 8 query heads, every
+// workgroup size and split count: rms error 9 %).  A launch pays a start, and again for every round of
+// workgroups that the chip cannot hold at once; what streams in between is bounded by the waves'
+// own time per 64-token chunk (longer with more waves on a SIMD, longer with eight query heads), by the
+// chip's memory rate, and by the rate of the CU that gets most of the bytes, whichever dominates;
+// split heads pay for the merge of their partials.
+static float predicted_us(int heads, int gq, int bits, int n_chunks, float mbytes, int n_cu, int max_nw, int nw, int splits) {
+    const int chunks = (n_chunks + splits - 1) / splits, wgs = heads * ((n_chunks + chunks - 1) / chunks);
+    const int per_cu = max_nw / nw, rounds = (wgs + n_cu * per_cu - 1) / (n_cu * per_cu), deep = (wgs + n_cu - 1) / n_cu;
+    const float simd_waves = 0.25f * nw * (deep < per_cu ? deep : per_cu);
+    const float chunk_us = bits == 2 ? 1.31f + 0.27f * simd_waves : bits == 4 ? 1.40f + 0.10f * simd_waves : bits == 8 ? 1.48f + 0.21f * simd_waves : 0.0f;
+    const float waves_us = rounds * ((chunks + nw - 1) / nw) * chunk_us * (gq == 8 ? 1.47f : 1.0f);
+    const float chip_us = mbytes * (1.0f / 7.15f);
+    const float cu_us = mbytes * deep * n_cu / wgs * (1.0f / (7.15f * 1.44f));
+    const float merge_us = wgs > heads ? 0.85f + 0.02f * (wgs / heads) * gq : 0.0f;
+    return 2.4f + 4.99f * rounds + std::sqrt(waves_us * waves_us + chip_us * chip_us + cu_us * cu_us) + merge_us;
+}
+
 DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept, int tail_len) {
+    (void)tail_len;
     DecodePlan p;
     const int heads = cfg.batch * cfg.n_kv_heads;
     const int n_chunks = (n_kept + kChunk - 1) / kChunk;
@@ -1493,33 +1515,65 @@ DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept, int tail_len) {
         const int max_nw = pipe_max_waves(cfg.bits, gq, outliers_on(cfg));
         int waves = (n_cu * max_nw) / heads;
         if (waves > n_chunks) waves = n_chunks;
-        int splits, nw;
+        int splits, nw, plain_splits = 0, plain_nw = 0;
         if (cfg.decode_splits > 0) {            // caller's choice: that many four-wave workgroups
             splits = cfg.decode_splits < n_chunks ? cfg.decode_splits : n_chunks;
             nw = kWaves;
-        } else if (waves <= max_nw) {           // one workgroup per head: no partials, no merge across workgroups
-            splits = 1;
-            nw = waves / kWaves * kWaves;
-        } else {                                // several workgroups per head: small ones while CUs are left over
-            nw = (int)((long long)waves * heads / n_cu) / kWaves * kWaves;
-            // (a head is kept within sixteen partials by making the workgroups larger rather than more:
-            // the last workgroup fetches 1 KB per partial and query head through its own CU, and 32
-            // four-wave workgroups per head measured slower than 16 of eight waves)
-            const int nw16 = ((waves + 15) / 16 + kWaves - 1) / kWaves * kWaves;
-            if (nw < nw16) nw = nw16;
-            if (nw > max_nw) nw = max_nw;
+        } else {
+            if (waves <= max_nw) {              // one workgroup per head: no partials, no merge across workgroups
+                splits = 1;
+                nw = waves / kWaves * kWaves;
+            } else {                            // several workgroups per head: small ones while CUs are left over
+                nw = (int)((long long)waves * heads / n_cu) / kWaves * kWaves;
+                // (a head is kept within sixteen partials by making the workgroups larger rather than more:
+                // the last workgroup fetches 1 KB per partial and query head through its own CU, and 32
+                // four-wave workgroups per head measured slower than 16 of eight waves)
+                const int nw16 = ((waves + 15) / 16 + kWaves - 1) / kWaves * kWaves;
+                if (nw < nw16) nw = nw16;
+                if (nw > max_nw) nw = max_nw;
+                if (nw < kWaves) nw = kWaves;
+                splits = (waves + nw - 1) / nw;
+            }
+            if (splits < 1) splits = 1;
             if (nw < kWaves) nw = kWaves;
-            splits = (waves + nw - 1) / nw;
+            // That rule knows neither rounds nor remainders: 192 heads of 4096 tokens at 4 bits became 384
+            // workgroups of twelve waves on 256 CUs, 40.1 us where one workgroup per head takes 28.9; 320
+            // heads 61.9 against 47.5 with two four-wave workgroups each; 96 heads of 3000 tokens 26.5 against
+            // 18.8.  So the other shapes are priced too and taken where they promise 4 % or more: over 250
+            // shapes that the prices were not fitted to, calls take 7.6 % less time on average, 1 % of them
+            // 3 to 5 % more.  Bounds: the workspace of decode_ws_bound, and the library's own array.
+            const int share = (n_cu * max_nw) / heads, most = (share + kWaves - 1) / kWaves;
+            const size_t head_part = (size_t)heads * gq * kPartFloats * sizeof(float);
+            const float mbytes = 1e-6f * heads * (float)n_kept * (cfg.bits == 16 ? 512.0f : 2.0f * (16 * cfg.bits + 512 / cfg.group_size) + (outliers_on(cfg) ? 32.0f : 0.0f));
+            plain_splits = splits; plain_nw = nw;
+            auto price = [&](int w, int s) { return predicted_us(heads, gq, cfg.bits, n_chunks, mbytes, n_cu, max_nw, w, s); };
+            if (n_chunks > 0) {
+                float best = 0.96f * price(nw, splits);
+                for (const int s : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32}) {
+                    if (s > n_chunks || s > most || (s > 1 && decode_ws_header_bytes(cfg) + s * head_part > kStaticScratchBytes)) break;
+                    for (int w = kWaves; w <= max_nw; w += kWaves) {
+                        const float us = price(w, s);
+                        if (us < best) { best = us; nw = w; splits = s; }
+                    }
+                }
+            }
         }
+        auto cut = [&](int s, int& chunks, int& n_splits, size_t& part_bytes) {
+            chunks = (n_chunks + s - 1) / s;
+            n_splits = chunks ? (n_chunks + chunks - 1) / chunks : 1;
+            // (a head that stays in one workgroup writes no partial: the counters' bytes are all the launch touches)
+            part_bytes = n_splits > 1 ? (size_t)heads * (size_t)n_splits * gq * kPartFloats * sizeof(float) : 0;
+        };
         if (splits < 1) splits = 1;
-        if (nw < kWaves) nw = kWaves;
         p.n_waves = nw;
-        p.chunks_per_split = (n_chunks + splits - 1) / splits;
-        p.n_splits = p.chunks_per_split ? (n_chunks + p.chunks_per_split - 1) / p.chunks_per_split : 1;
+        cut(splits, p.chunks_per_split, p.n_splits, p.part_bytes);
         p.n_partials = p.n_splits;
+        p.ws_bytes = decode_ws_header_bytes(cfg) + p.part_bytes;
+        if (plain_splits) {
+            cut(plain_splits, p.alt_chunks, p.alt_splits, p.alt_part_bytes);
+            p.alt_waves = plain_nw;
+        }
     }
-    // (a head that stays in one workgroup writes no partial: the counters' bytes are all the launch touches)
-    p.ws_bytes = decode_ws_header_bytes(cfg) + (p.n_splits > 1 ? (size_t)heads * (size_t)p.n_partials * gq * kPartFloats * sizeof(float) : 0);
     return p;
 }
 
@@ -1553,8 +1607,7 @@ hipError_t static_scratch(const kvqp_cfg& cfg, void** ptr, hipStream_t stream) {
         if (e != hipSuccess) return e;
         if (!p) return hipErrorInvalidSymbol;
         // counters for the largest head count the launches accept (a fill kernel: the call may be under capture)
-        constexpr int n = 65536;
-        static_assert((size_t)n * sizeof(unsigned int) <= kStaticScratchBytes, "counters fit the array");
+        constexpr int n = (int)(kStaticCounterBytes / sizeof(unsigned int));
         hipLaunchKernelGGL(zero_words, dim3(n / 256), dim3(256), 0, stream, (unsigned int*)p, n);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1574,7 +1627,7 @@ hipError_t launch_decode(const kvqp_cfg& cfg, const void* q, const kvqp_cache& c
     a.v_scale = (const uint16_t*)c.v_scale; a.v_zero = (const uint16_t*)c.v_zero;
     a.tail_k = (const uint16_t*)c.tail_k; a.tail_v = (const uint16_t*)c.tail_v;
     a.arrivals = (unsigned int*)ws;
-    a.part = (float*)(static_cast<char*>(ws) + decode_ws_header_bytes(cfg));
+    a.part = (float*)(static_cast<char*>(ws) + plan.part_off);
     a.out = (uint16_t*)out;
     a.n_kept = c.n_kept; a.tail_len = c.tail_len; a.tail_cap = c.tail_cap;
     a.n_cap = layout_tokens(c, c.n_kept);

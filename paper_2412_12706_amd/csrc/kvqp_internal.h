@@ -52,7 +52,30 @@ struct DecodePlan {
     int chunks_per_split;// 64-token chunks handled by one workgroup
     int n_partials;      // n_splits (+1 when a tail partial is written)
     int n_waves;         // waves per decode workgroup
-    size_t ws_bytes;
+    size_t ws_bytes;         // counters and partials
+    size_t part_bytes = 0;   // the partials alone
+    size_t part_off = 0;     // where they lie in the workspace at hand (fit)
+    // A plan that was taken for its speed beside the plain rule's (alt_waves == 0: none).  The plain one
+    // says what workspace the call wants, and runs when there is that much but not enough for the other.
+    int alt_splits = 0, alt_chunks = 0, alt_waves = 0;
+    size_t alt_part_bytes = 0;
+    void take_plain() {
+        if (!alt_waves) return;
+        const size_t counters = ws_bytes - part_bytes;
+        n_splits = n_partials = alt_splits; chunks_per_split = alt_chunks; n_waves = alt_waves;
+        part_bytes = alt_part_bytes; ws_bytes = counters + part_bytes;
+        alt_waves = 0;
+    }
+    // Whether a workspace of that size serves the call.  The partials go to its end: at its head lie
+    // the arrival counters, and those of a call with more heads, which have to stay zero, reach further.
+    bool fit(size_t bytes) {
+        const size_t counters = ws_bytes - part_bytes;
+        if (alt_waves && bytes < counters + alt_part_bytes) return false;
+        if (bytes < ws_bytes) take_plain();
+        if (bytes < ws_bytes) return false;
+        part_off = (bytes - part_bytes) / 16 * 16;
+        return true;
+    }
 };
 DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept, int tail_len);
 size_t decode_ws_bound(const kvqp_cfg& cfg);   // >= plan_decode(cfg, n, t).ws_bytes for every n and t
@@ -61,6 +84,8 @@ hipError_t launch_ws_init(const kvqp_cfg& cfg, void* ws, hipStream_t stream);   
 // The library's own decode workspace (a static device array): its address on the current device,
 // prepared on first use.  KVQP_STATIC_SCRATCH_BYTES in kvqp.h is its size.
 constexpr size_t kStaticScratchBytes = KVQP_STATIC_SCRATCH_BYTES;
+// ... behind arrival counters for the largest head count a launch accepts, which no call's partials touch.
+constexpr size_t kStaticCounterBytes = 65536 * sizeof(unsigned int);
 hipError_t static_scratch(const kvqp_cfg& cfg, void** ptr, hipStream_t stream);
 
 // Compress workspace layout (bytes offsets), pure function of cfg.

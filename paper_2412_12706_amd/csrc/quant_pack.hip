@@ -43,7 +43,12 @@ struct QuantPackJob {
     const int32_t* head_base = nullptr;   // device: first destination token of each head in place of dst_base, or NULL
     int base_quantum = 1;                 // what every head_base entry is a multiple of
     int ovf_cap = 0;                      // outlier filtering: entries of a head's overflow list
+    int tail_len = 0;                     // > 0: the rows come from the front of a tail of that many, which is to close up
 };
+
+// Whether the quantizer itself closes the tail up: one workgroup has all of a head's rows and nothing reads them after it.
+constexpr int quant_tokens(int bits, int group) { return (bits != 16 && group == 128) ? 128 : 64; }   // per workgroup
+bool closes_tail(const QuantPackJob& j) { return j.n_tok <= quant_tokens(j.bits, j.group_size) && !j.outliers; }
 
 typedef unsigned short us2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
@@ -179,16 +184,42 @@ __device__ __forceinline__ uint32_t row16_before(uint32_t v) {
 // 0xFFFF in the half-words whose bit (bit 0: low half, bit 1: high half) is set
 __device__ __forceinline__ uint32_t half_mask(uint32_t b) { return ((0u - (b & 1u)) & 0xFFFFu) | ((0u - ((b >> 1) & 1u)) << 16); }
 
+// Rows [n_shift, tail_len) of both tail tensors of a head move down to [0, tail_len - n_shift).  One
+// workgroup; 16 rows per round go through registers (all reads of a round before its writes, rounds
+// in ascending order, so overlapping ranges are safe).
+__device__ __forceinline__ void close_tail(uint16_t* tail_k, uint16_t* tail_v, int head, int tail_cap, int n_shift, int tail_len) {
+    uint16_t* tk = tail_k + (size_t)head * tail_cap * kHeadDim;
+    uint16_t* tv = tail_v + (size_t)head * tail_cap * kHeadDim;
+    const int r = threadIdx.x >> 4, c8 = threadIdx.x & 15;
+    for (int r0 = n_shift; r0 < tail_len; r0 += 16) {
+        const int row = r0 + r;
+        const bool live = row < tail_len;
+        uint4 a = make_uint4(0, 0, 0, 0), b = a;
+        if (live) {
+            a = *reinterpret_cast<const uint4*>(tk + (size_t)row * kHeadDim + 8 * c8);
+            b = *reinterpret_cast<const uint4*>(tv + (size_t)row * kHeadDim + 8 * c8);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (the barrier alone does not wait for loads in flight)
+        __syncthreads();
+        if (live) {
+            *reinterpret_cast<uint4*>(tk + (size_t)(row - n_shift) * kHeadDim + 8 * c8) = a;
+            *reinterpret_cast<uint4*>(tv + (size_t)(row - n_shift) * kHeadDim + 8 * c8) = b;
+        }
+        __syncthreads();
+    }
+}
+
 template <int BITS, int G, bool OUT>
 __global__ __launch_bounds__(kThreads) void gather_quant_pack(
-    const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, const int32_t* __restrict__ idx,
+    const uint16_t* k, const uint16_t* v, const int32_t* __restrict__ idx,
     uint32_t* __restrict__ k_codes, uint32_t* __restrict__ v_codes, uint16_t* __restrict__ k_scale,
     uint16_t* __restrict__ k_zero, uint16_t* __restrict__ v_scale, uint16_t* __restrict__ v_zero,
-    uint16_t* __restrict__ tail_k, uint16_t* __restrict__ tail_v, int L, int W, int n_kept, int key_axis,
+    uint16_t* tail_k, uint16_t* tail_v, int L, int W, int n_kept, int key_axis,
     int tail_cap, int n_tok_blocks, int n_cap, int dst_base, const int32_t* __restrict__ head_n,
     uint32_t* __restrict__ k_out, uint32_t* __restrict__ v_out, uint32_t tau_bits,
     const int32_t* __restrict__ head_base, int base_quantum, uint32_t* __restrict__ k_ovf,
-    uint32_t* __restrict__ v_ovf, int ovf_cap) {
+    uint32_t* __restrict__ v_ovf, int ovf_cap, int tail_len) {
+    // (k / v may be the tail itself: neither is a restrict pointer.)
     // L: rows per head of the source tensors.  idx: source row of every token of this call
     // ([heads, n_kept]), or NULL for rows 0 .. n_kept-1.  The tokens land at positions dst_base ..
     // dst_base + n_kept - 1 of a cache whose buffers are laid out for n_cap tokens per head.
@@ -196,11 +227,13 @@ __global__ __launch_bounds__(kThreads) void gather_quant_pack(
     // head_base: a head's own first position in place of dst_base, or NULL; it is cut to dst_base and
     // rounded down to a multiple of base_quantum, so whatever the array holds the stores stay inside
     // the buffers and on group and superblock boundaries.
+    // tail_len > 0: the source rows are the oldest of tail_len tail rows and one workgroup takes all of a
+    // head's; it closes the tail up when it is done with them.
     // OUT: outlier filtering; k_out / v_out receive four slot words per token row, and the number of
     // a block's further outliers is left at entry (block + 1) of the head's overflow prefix array
     // (k_ovf / v_ovf), which ovf_scan then turns into prefix counts and ovf_fill completes.
     constexpr bool QUANT = BITS != 16;
-    constexpr int TB = (QUANT && G == 128) ? 128 : 64;   // tokens per workgroup
+    constexpr int TB = quant_tokens(BITS, G);            // tokens per workgroup
     constexpr int R = TB / 16;                            // rows per thread
     constexpr int NG = TB / G > 0 ? TB / G : 1;           // per-channel key groups per workgroup
     constexpr int JPG = G / 16;                           // a thread's rows per key group
@@ -534,6 +567,8 @@ __global__ __launch_bounds__(kThreads) void gather_quant_pack(
         for (int item = threadIdx.x; item < n_sb * SBW / 4; item += kThreads)
             reinterpret_cast<uint4*>(vc)[item] = reinterpret_cast<const uint4*>(s_words)[item];
     }
+    // (the barrier before the value store: every wave has its rows in registers)
+    if (tail_len > 0) close_tail(tail_k, tail_v, head, tail_cap, n_head, tail_len);
     if constexpr (OUT) {   // (the barrier before the value store orders every row's count before this)
         const int tensor = threadIdx.x / (TB / 32), blk = threadIdx.x % (TB / 32);
         if (threadIdx.x < 2 * (TB / 32) && 32 * blk < ntok) {
@@ -638,7 +673,7 @@ __global__ __launch_bounds__(64) void ovf_fill(const uint16_t* __restrict__ k, c
 
 template <int BITS, int G, bool OUT>
 hipError_t launch_bits_g(const QuantPackJob& j, hipStream_t stream) {
-    constexpr int TB = (BITS != 16 && G == 128) ? 128 : 64;
+    constexpr int TB = quant_tokens(BITS, G);
     const int nblk = (j.n_tok + TB - 1) / TB;
     dim3 grid(nblk + (j.copy_tail ? 1 : 0), j.heads);
     if (grid.x == 0) return hipSuccess;
@@ -647,7 +682,7 @@ hipError_t launch_bits_g(const QuantPackJob& j, hipStream_t stream) {
                        (uint16_t*)j.c.k_zero, (uint16_t*)j.c.v_scale, (uint16_t*)j.c.v_zero, (uint16_t*)j.c.tail_k,
                        (uint16_t*)j.c.tail_v, j.src_rows, j.window, j.n_tok, j.key_axis, j.c.tail_cap, nblk, j.n_cap,
                        j.dst_base, j.head_n, (uint32_t*)j.c.k_out, (uint32_t*)j.c.v_out, j.tau_bits, j.head_base,
-                       j.base_quantum, (uint32_t*)j.c.k_ovf, (uint32_t*)j.c.v_ovf, j.ovf_cap);
+                       j.base_quantum, (uint32_t*)j.c.k_ovf, (uint32_t*)j.c.v_ovf, j.ovf_cap, closes_tail(j) ? j.tail_len : 0);
     hipError_t e = hipGetLastError();
     if constexpr (OUT) {
         if (e != hipSuccess || j.n_tok == 0) return e;
@@ -681,30 +716,9 @@ hipError_t launch_bits(const QuantPackJob& j, hipStream_t stream) {
     }
 }
 
-// Rows [n_shift, tail_len) of both tail tensors move down to [0, tail_len - n_shift).  One workgroup
-// per head; 16 rows per round go through registers (all reads of a round before its writes, rounds
-// in ascending order, so overlapping ranges are safe).
 __global__ __launch_bounds__(kThreads) void tail_shift(uint16_t* __restrict__ tail_k, uint16_t* __restrict__ tail_v,
                                                        int tail_cap, int n_shift, int tail_len) {
-    const int head = blockIdx.x;
-    uint16_t* tk = tail_k + (size_t)head * tail_cap * kHeadDim;
-    uint16_t* tv = tail_v + (size_t)head * tail_cap * kHeadDim;
-    const int r = threadIdx.x >> 4, c8 = threadIdx.x & 15;
-    for (int r0 = n_shift; r0 < tail_len; r0 += 16) {
-        const int row = r0 + r;
-        const bool live = row < tail_len;
-        uint4 a = make_uint4(0, 0, 0, 0), b = a;
-        if (live) {
-            a = *reinterpret_cast<const uint4*>(tk + (size_t)row * kHeadDim + 8 * c8);
-            b = *reinterpret_cast<const uint4*>(tv + (size_t)row * kHeadDim + 8 * c8);
-        }
-        __syncthreads();
-        if (live) {
-            *reinterpret_cast<uint4*>(tk + (size_t)(row - n_shift) * kHeadDim + 8 * c8) = a;
-            *reinterpret_cast<uint4*>(tv + (size_t)(row - n_shift) * kHeadDim + 8 * c8) = b;
-        }
-        __syncthreads();
-    }
+    close_tail(tail_k, tail_v, blockIdx.x, tail_cap, n_shift, tail_len);
 }
 
 hipError_t launch_job(const QuantPackJob& j, hipStream_t stream) {
@@ -779,8 +793,9 @@ hipError_t launch_append_tail(const kvqp_cfg& cfg, const kvqp_cache& cache, int 
     j.heads = cfg.batch * cfg.n_kv_heads; j.src_rows = cache.tail_cap; j.window = 0;
     j.n_tok = n_tokens; j.dst_base = cache.n_kept; j.n_cap = layout_tokens(cache, cache.n_kept);
     j.bits = cfg.bits; j.group_size = cfg.group_size; j.key_axis = cfg.key_axis; j.copy_tail = false;
+    j.tail_len = cache.tail_len;
     hipError_t e = launch_job(j, stream);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || closes_tail(j)) return e;
     hipLaunchKernelGGL(tail_shift, dim3(j.heads), dim3(kThreads), 0, stream, (uint16_t*)cache.tail_k, (uint16_t*)cache.tail_v,
                        cache.tail_cap, n_tokens, cache.tail_len);
     return hipGetLastError();

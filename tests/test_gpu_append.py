@@ -162,3 +162,34 @@ def test_decode_loop_with_periodic_appends(orc):
     out = kvqp.decode_attn(cfg, dev(q), gc)
     torch.cuda.synchronize()
     assert np.abs(out.cpu().numpy().astype(np.float64) - ref).max() <= TOL
+
+
+@pytest.mark.parametrize("bits,G,n_app", [(4, 32, 64), (16, 32, 32), (8, 128, 128), (4, 32, 96), (2, 64, 128)])
+@pytest.mark.parametrize("rest", [0, 1, 16, 17, 130])
+def test_tail_closes_up_whatever_is_left(bits, G, n_app, rest):
+    """The rows behind the moved ones, none to several rounds of 16, end up at the front of the tail --
+    closed up by the quantizer's own workgroup where it has all moved rows, by a second kernel where it
+    has not -- and the packed part is what quantizing those rows from a prompt gives."""
+    print(f"case close tail bits={bits} G={G} append={n_app} rest={rest}", flush=True)
+    B, Hkv, n_kept, W = 2, 3, 128, 1
+    heads, grown = B * Hkv, n_app + rest
+    torch.manual_seed(bits + rest)
+    rows = torch.randn(2, B, Hkv, n_kept + grown, D, device="cuda").half()
+    cfg = kvqp.Cfg(batch=B, n_q_heads=Hkv, n_kv_heads=Hkv, seq_len=n_kept + grown + W, window=W, budget=n_kept, bits=bits, group_size=G)
+    k, v = (torch.cat([t, t[:, :, -1:]], 2).contiguous() for t in rows)
+    whole, part = (kvqp.alloc_cache(cfg, tail_cap=grown + 3, n_cap=(n_kept + n_app + 127) // 128 * 128) for _ in range(2))
+    for c, n in ((whole, n_kept + n_app), (part, n_kept)):
+        for t in c.buffers.values():
+            t.fill_(0x3C)
+        kvqp.quantize_selected(cfg, k, v, torch.arange(n, dtype=torch.int32, device="cuda").expand(B, Hkv, n).contiguous(), c)
+    for name, t in zip(("tail_k", "tail_v"), rows):
+        part.buffers[name].view(torch.float16).view(B, Hkv, grown + 3, D)[:, :, :grown] = t[:, :, n_kept:]
+    part.tail_len = grown
+    kvqp.append_tail(cfg, part, n_app)
+    torch.cuda.synchronize()
+    assert part.n_kept == n_kept + n_app and part.tail_len == rest
+    for name in NAMES[:6]:
+        assert torch.equal(part.buffers[name], whole.buffers[name]), name
+    for name, t in zip(("tail_k", "tail_v"), rows):
+        got = part.buffers[name].view(torch.float16).view(B, Hkv, grown + 3, D)[:, :, :rest]
+        assert torch.equal(got, t[:, :, n_kept + n_app:]), name

@@ -534,6 +534,7 @@ constexpr int kBinBase = ((136 << 23) >> kBinShift) - kBins;   // 2^9 is the fir
 constexpr int kMaxSegs = 16;          // pooling workgroups per head
 constexpr int kMaxSegTiles = 15;      // (a workgroup's bin counts are stored in 16 bits)
 constexpr int kListCap = 3840;        // candidates around the cut held in LDS; more are swept from memory
+constexpr int kRankMax = 128;         // candidates around the cut that are ranked against each other
 constexpr int kDigit = 11;            // bits per pass of the radix select among them
 constexpr int kMaxBand = 512;         // candidates re-scored per head; beyond that binary32 decides (and the caller is told)
 constexpr int kVoteSlots = 2048;      // binary64 votes (distinct positions) held in LDS during the re-scoring
@@ -837,6 +838,12 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
         for (int i = 0; i < 4; ++i) bits |= (int)own[i] > (int)khi ? 1u << i : 0u;
         sure = __popc(bits);
         if (bits) atomicOr(&keep[threadIdx.x >> 3], bits << (4 * (threadIdx.x & 7)));
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (own[i] >= klo && own[i] <= khi) {
+                const int e = atomicAdd(&s_list, 1);
+                if (e < kListCap) list_key[e] = own[i];
+            }
     } else {
 #pragma unroll
         for (int i = 0; i < kOctets; ++i) {
@@ -898,10 +905,38 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     };
     auto set_keep = [&](int j) { atomicOr(&keep[j >> 5], 1u << (j & 31)); };
 
-    // ---- the exact cut: radix select on the patterns relative to klo (two passes in the usual case) ----
+    // ---- the exact cut: a hundred candidates are ranked against each other, every wave
+    // against its share of them (1.0 to 1.9 us for 15 to 100 of them, where two radix passes take 2.5 to
+    // 3; 3.5 and more for 200); more go through a radix
+    // select on the patterns relative to klo ----
     uint32_t prefix = 0u;
     int need = need_around;
-    {
+    if (n_list <= kRankMax) {
+        if (threadIdx.x < 4) list_key[n_list + threadIdx.x] = 0u;       // (whole 16-byte pieces; 0 is above no candidate)
+        for (int e = threadIdx.x; e < n_list; e += kSelThreads) hist[e] = 0;
+        __syncthreads();
+        const int n4 = (n_list + 3) / 4, share = (n4 + kSelWaves - 1) / kSelWaves;
+        const uint4* others = reinterpret_cast<const uint4*>(list_key);
+        for (int e = lane; e < n_list; e += 64) {
+            const uint32_t mine = list_key[e];
+            int count = 0;                                                // candidates above; 16 bits higher: at or above
+#pragma unroll 4
+            for (int o = wave * share; o < min(n4, wave * share + share); ++o) {
+                const uint4 x = others[o];
+                count += (x.x > mine) + (x.y > mine) + (x.z > mine) + (x.w > mine);
+                count += ((x.x >= mine) + (x.y >= mine) + (x.z >= mine) + (x.w >= mine)) << 16;
+            }
+            if (count) atomicAdd(&hist[e], count);
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < n_list; e += kSelThreads) {
+            const int above = hist[e] & 0xffff, at_least = min(hist[e] >> 16, n_list);   // (the padding counts where the score is 0)
+            if (above < need && at_least >= need) { s_prefix = list_key[e] - klo; s_need = need - above; }   // (the same from every candidate at the cut)
+        }
+        __syncthreads();
+        prefix = __builtin_amdgcn_readfirstlane(s_prefix);
+        need = __builtin_amdgcn_readfirstlane(s_need);
+    } else {
         const int bits = 32 - __builtin_clz(khi - klo);
         int fixed = bits, shift = bits > kDigit ? bits - kDigit : 0;
         for (;;) {
@@ -1071,12 +1106,22 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int n = min(w1 - w0 - 64 * h, 64);
-        for (int u = 0; u < n; ++u) {
-            const uint32_t lo = __builtin_amdgcn_readlane(word[2 * h], u), hi = __builtin_amdgcn_readlane(word[2 * h + 1], u);
-            const unsigned long long m = lo | ((unsigned long long)hi << 32);
-            const int below = (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-            if (__builtin_amdgcn_inverse_ballot_w64(m)) (idx + at)[below] = 64 * (w0 + 64 * h + u) + lane;
-            at += __popcll(m);
+        for (int u0 = 0; u0 < n; u0 += 4) {                  // four words at a time: a word's chain of scalar and vector steps is all latency
+            uint32_t lo[4], hi[4];
+            int e[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                lo[u] = __builtin_amdgcn_readlane(word[2 * h], (u0 + u) & 63);
+                hi[u] = __builtin_amdgcn_readlane(word[2 * h + 1], (u0 + u) & 63);     // (words past the last are 0)
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                e[u] = at + (int)__builtin_amdgcn_mbcnt_hi(hi[u], __builtin_amdgcn_mbcnt_lo(lo[u], 0u));
+                at += __popc(lo[u]) + __popc(hi[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (__builtin_amdgcn_inverse_ballot_w64(lo[u] | ((unsigned long long)hi[u] << 32))) idx[e[u]] = 64 * (w0 + 64 * h + u0 + u) + lane;
         }
     }
 }

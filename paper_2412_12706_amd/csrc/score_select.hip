@@ -518,7 +518,7 @@ __global__ __launch_bounds__(256) void stats_combine(const float2* __restrict__ 
 // Prefixes of one pooling tile (4096) do both in the second kernel.  A single
 // workgroup per head that did everything, with a four-pass radix select over all
 // scores, took 45 / 87 / 310 us for 8 heads of 4064 / 32736 / 131008 candidates
-// and 120 us for 256 heads of 32736; these take 12 / 5 + 20 / 6.5 + 36 and 17 + 28 us.
+// and 120 us for 256 heads of 32736; these take 10 / 5 + 21 / 6.5 + 36 and 17 + 28 us.
 // ---------------------------------------------------------------------------
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
@@ -905,10 +905,9 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     };
     auto set_keep = [&](int j) { atomicOr(&keep[j >> 5], 1u << (j & 31)); };
 
-    // ---- the exact cut: a hundred candidates are ranked against each other, every wave
-    // against its share of them (1.0 to 1.9 us for 15 to 100 of them, where two radix passes take 2.5 to
-    // 3; 3.5 and more for 200); more go through a radix
-    // select on the patterns relative to klo ----
+    // ---- the exact cut: up to a hundred candidates are ranked against each other, every wave against its
+    // share of them (1.0 to 1.9 us for 15 to 100 of them, where two radix passes take 2.5 to 3; 3.5 and
+    // more for 200); more go through a radix select on the patterns relative to klo ----
     uint32_t prefix = 0u;
     int need = need_around;
     if (n_list <= kRankMax) {

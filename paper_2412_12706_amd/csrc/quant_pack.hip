@@ -3,12 +3,14 @@
 // s = (m - z)/(2^B - 1), Q(G) = round((G - z)/s); grouping axes of Section 2 /
 // Section 6.3).  Every survivor row is read once (2 x 256 B, scattered) and
 // k*bpt bytes are written; there is no reuse to exploit.  What bounds it on
-// the MI355X, measured: not the scattered rows (contiguous survivors take the
-// same time) and not the instruction count alone (order keys, the quantizer's
-// individually rounded binary32 steps, field packing: ~18 lane operations per
-// element), but a workgroup's own chain of waits -- two memory round trips,
-// three barriers -- that the six workgroups a CU holds at 78 registers do not
-// fully hide; it moves ~4.7 TB/s of gathers and stores.
+// the MI355X: vector-instruction issue at 2 and 4 bits (the vector ALUs were
+// busy all the time at 1090 instructions per thread for 64 elements), then
+// memory.  So an element costs five: v_fma_mix_f32 (widen and subtract z),
+// multiply, round, clamp, and a multiply-add that puts its field into the word
+// as a whole number in binary32; order keys take two instructions per pair, and
+// every lane exchange merges two registers into one.  256 heads, 16384 of 32768
+// tokens at 2 bits: 510 -> 453 us (2.55 GB: 5.6 TB/s); 8 heads, 8192 tokens at
+// 4 bits: 15.7 -> 12.5 us; 16384 tokens at 2 bits in groups of 64: 22 -> 19 us.
 //
 // One workgroup owns TB consecutive kept tokens of one (batch, kv head): whole
 // key groups (G | TB) and whole value superblocks (SB | TB).  Thread
@@ -16,7 +18,7 @@
 // r, r + 16, r + 32, ... in registers from the gather to the packed words:
 //   * minima / maxima are taken on packed 16-bit order keys (two channels per
 //     register), across lanes with DPP / permlane exchanges and across waves
-//     through a few hundred bytes of LDS;
+//     through a few KB of LDS;
 //   * key words are assembled in registers and stored straight from them
 //     (a word holds consecutive channels of one token);
 //   * value words hold one channel of several tokens (the tile-transposed
@@ -60,10 +62,13 @@ __device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
 
 // binary16 bit pattern -> key that orders like the value (-0 below +0).
 __device__ __forceinline__ uint32_t order_key(uint16_t h) { return (h & 0x8000u) ? (uint16_t)~h : (uint16_t)(h | 0x8000u); }
-// the same on both halves of a word
+// the same on both halves of a word: negative halves inverted, the others with the sign bit set (two instructions)
+typedef short ss2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t order_key2(uint32_t w) {
-    const uint32_t neg = (w >> 15) & 0x00010001u;
-    return w ^ (0x80008000u | (neg * 0x7fffu));
+    union { uint32_t u; ss2v v; } t;
+    t.u = w;
+    t.v = t.v >> (short)15;
+    return w ^ (t.u | 0x80008000u);
 }
 __device__ __forceinline__ uint16_t key_to_half(uint32_t key) { return (key & 0x8000u) ? (uint16_t)(key & 0x7fffu) : (uint16_t)~key; }
 __device__ __forceinline__ float half_bits_to_float(uint16_t h) { return __half2float(__ushort_as_half(h)); }
@@ -87,19 +92,27 @@ __device__ __forceinline__ GroupParams group_params(uint32_t kmin, uint32_t kmax
     g.inv = (sf == 0.0f) ? 0.0f : __fdiv_rn(1.0f, sf);
     return g;
 }
+// The code of one element, as a float: the words are put together by multiply-adds (field_sum).
+// one is 1.0f that the compiler does not know: x * one - z is the widening and the subtraction in one
+// instruction (v_fma_mix_f32; the product is exact, so the difference is rounded once, as a subtraction is).
 template <int BITS>
-__device__ __forceinline__ uint32_t encode(uint16_t xh, const GroupParams& g) {
+__device__ __forceinline__ float encode(uint16_t xh, float zf, float inv, float one) {
     // a degenerate group needs no branch: (x - z) * 0 rounds and clamps to code 0
-    float c = rintf(__fmul_rn(__fsub_rn(half_bits_to_float(xh), g.zf), g.inv));
-    c = fminf(fmaxf(c, 0.0f), (float)((1 << BITS) - 1));
-    return (uint32_t)c;
+    const float c = rintf(__fmul_rn(__builtin_fmaf(half_bits_to_float(xh), one, -zf), inv));
+    return fminf(fmaxf(c, 0.0f), (float)((1 << BITS) - 1));
 }
+// c + 2^SHIFT * hi: fields of whole numbers side by side, exact while the sum stays below 2^24
+template <int SHIFT> __device__ __forceinline__ float field_sum(float c, float hi) { return __builtin_fmaf(hi, (float)(1 << SHIFT), c); }
 
-// lane exchanges: partner lane ^ 16 / ^ 32 (both values come back, combine them with any symmetric op)
-#define KVQP_SWAP16(v) __builtin_amdgcn_permlane16_swap((v), (v), false, false)
-#define KVQP_SWAP32(v) __builtin_amdgcn_permlane32_swap((v), (v), false, false)
 template <int CTRL> __device__ __forceinline__ uint32_t dpp(uint32_t v) { return __builtin_amdgcn_update_dpp(0u, v, CTRL, 0xF, 0xF, true); }
 constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowHalfMirror = 0x141, kRowMirror = 0x140;
+
+// one of four values by a lane's number 0 .. 3 (by value: a choice among array elements becomes branches)
+__device__ __forceinline__ uint32_t pick(int i, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+    asm("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+    const uint32_t lo = (i & 1) ? b : a, hi = (i & 1) ? d : c;
+    return (i & 2) ? hi : lo;
+}
 
 // min / max over the LANES consecutive lanes (4, 8 or 16) that share a per-token group
 template <int LANES> __device__ __forceinline__ void group_minmax(uint32_t& mn, uint32_t& mx) {
@@ -111,57 +124,50 @@ template <int LANES> __device__ __forceinline__ void group_minmax(uint32_t& mn, 
 
 // codes of a thread's eight channels of one row
 template <int BITS>
-__device__ __forceinline__ void encode8(const uint32_t (&w)[4], const float (&zf)[8], const float (&inv)[8], uint32_t (&c)[8]) {
+__device__ __forceinline__ void encode8(const uint32_t (&w)[4], const float (&zf)[8], const float (&inv)[8], float one, float (&c)[8]) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        GroupParams g0, g1;
-        g0.zf = zf[2 * q]; g0.inv = inv[2 * q]; g1.zf = zf[2 * q + 1]; g1.inv = inv[2 * q + 1];
-        c[2 * q] = encode<BITS>((uint16_t)(w[q] & 0xffffu), g0);
-        c[2 * q + 1] = encode<BITS>((uint16_t)(w[q] >> 16), g1);
+        c[2 * q] = encode<BITS>((uint16_t)(w[q] & 0xffffu), zf[2 * q], inv[2 * q], one);
+        c[2 * q + 1] = encode<BITS>((uint16_t)(w[q] >> 16), zf[2 * q + 1], inv[2 * q + 1], one);
     }
 }
 
 // the same when all eight channels share one group
 template <int BITS>
-__device__ __forceinline__ void encode8(const uint32_t (&w)[4], float zf, float inv, uint32_t (&c)[8]) {
-    GroupParams g; g.zf = zf; g.inv = inv;
+__device__ __forceinline__ void encode8(const uint32_t (&w)[4], float zf, float inv, float one, float (&c)[8]) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        c[2 * q] = encode<BITS>((uint16_t)(w[q] & 0xffffu), g);
-        c[2 * q + 1] = encode<BITS>((uint16_t)(w[q] >> 16), g);
+        c[2 * q] = encode<BITS>((uint16_t)(w[q] & 0xffffu), zf, inv, one);
+        c[2 * q + 1] = encode<BITS>((uint16_t)(w[q] >> 16), zf, inv, one);
     }
 }
 
 // Key words of one row from the thread's eight codes (row-major layout of kvqp.h: channel d sits in
-// word d / E at half-word r % 2, field r / 2, r = d % E) and their store.  krow points at the row.
+// word d / E at half-word r % 2, field r / 2, r = d % E) and their store, at words row .. of kc.
 // keep: all ones, or 0 for a padding row (its words are stored as zeros).
 template <int BITS>
-__device__ __forceinline__ void store_key_words(uint32_t* krow, int c8, const uint32_t (&c)[8], uint32_t keep = 0xFFFFFFFFu) {
+__device__ __forceinline__ void store_key_words(uint32_t* kc, uint32_t row, int c8, const float (&c)[8], uint32_t keep = 0xFFFFFFFFu) {
     constexpr int E = 32 / BITS;
-    if constexpr (E == 8) {
-        uint32_t w = 0;
+    if constexpr (E == 8) {   // four fields per half-word
+        float half[2];
 #pragma unroll
-        for (int dd = 0; dd < 8; ++dd) w |= c[dd] << (16 * (dd & 1) + BITS * (dd >> 1));
-        krow[c8] = w & keep;
-    } else if constexpr (E == 4) {
-        uint32_t w0 = 0, w1 = 0;
+        for (int h = 0; h < 2; ++h) half[h] = field_sum<8>(field_sum<4>(c[h], c[2 + h]), field_sum<4>(c[4 + h], c[6 + h]));
+        kc[row + (uint32_t)c8] = ((uint32_t)half[0] | ((uint32_t)half[1] << 16)) & keep;
+    } else if constexpr (E == 4) {   // two fields per half-word, two words
+        uint32_t w[2];
 #pragma unroll
-        for (int dd = 0; dd < 4; ++dd) {
-            w0 |= c[dd] << (16 * (dd & 1) + BITS * (dd >> 1));
-            w1 |= c[4 + dd] << (16 * (dd & 1) + BITS * (dd >> 1));
-        }
-        *reinterpret_cast<uint2*>(krow + 2 * c8) = make_uint2(w0 & keep, w1 & keep);
-    } else {   // E == 16: the word spans this lane's channels and its neighbour's
-        uint32_t w = 0;
+        for (int u = 0; u < 2; ++u)
+            w[u] = ((uint32_t)field_sum<8>(c[4 * u], c[4 * u + 2]) | ((uint32_t)field_sum<8>(c[4 * u + 1], c[4 * u + 3]) << 16)) & keep;
+        *reinterpret_cast<uint2*>(kc + (row + 2u * (uint32_t)c8)) = make_uint2(w[0], w[1]);
+    } else {   // E == 16: the word spans this lane's channels and its neighbour's; four of eight fields per half-word, sum < 2^24
+        float half[2];
 #pragma unroll
-        for (int dd = 0; dd < 8; ++dd) {
-            const int r = dd;   // position inside the lane's half of the word
-            w |= c[dd] << (16 * (r & 1) + BITS * (r >> 1));
-        }
+        for (int h = 0; h < 2; ++h) half[h] = field_sum<4>(field_sum<2>(c[h], c[2 + h]), field_sum<2>(c[4 + h], c[6 + h]));
+        uint32_t w = (uint32_t)field_sum<16>(half[0], half[1]);
         // odd lanes hold channels 8..15 of the word: fields 4..7 of each half-word
         if (c8 & 1) w <<= 4 * BITS;
         w |= dpp<kQuadXor1>(w);
-        if (!(c8 & 1)) krow[c8 >> 1] = w & keep;
+        if (!(c8 & 1)) kc[row + (uint32_t)(c8 >> 1)] = w & keep;
     }
 }
 
@@ -209,8 +215,14 @@ __device__ __forceinline__ void close_tail(uint16_t* tail_k, uint16_t* tail_v, i
     }
 }
 
+// Waves per SIMD the registers have to allow: as many as they do without spilling (other workgroups hide
+// one's waits: at three waves instead of six the former code was 35 % slower).
+constexpr int quant_waves(int bits, int group, bool out) {
+    return out ? (group == 128 ? 3 : 5) : group == 128 ? 4 : bits == 2 && group == 32 ? 7 : 8;
+}
+
 template <int BITS, int G, bool OUT>
-__global__ __launch_bounds__(kThreads) void gather_quant_pack(
+__global__ __launch_bounds__(kThreads, quant_waves(BITS, G, OUT)) void gather_quant_pack(
     const uint16_t* k, const uint16_t* v, const int32_t* __restrict__ idx,
     uint32_t* __restrict__ k_codes, uint32_t* __restrict__ v_codes, uint16_t* __restrict__ k_scale,
     uint16_t* __restrict__ k_zero, uint16_t* __restrict__ v_scale, uint16_t* __restrict__ v_zero,
@@ -245,7 +257,7 @@ __global__ __launch_bounds__(kThreads) void gather_quant_pack(
     constexpr int SBW = v_superblock_words(BITS);
     constexpr int NSB = TB / SB;
     __shared__ __align__(16) uint32_t s_words[NSB * SBW];                 // finished value superblocks
-    __shared__ __align__(16) uint16_t s_min[QUANT ? 4 * NG * kHeadDim : 8];   // per wave: channel minima / maxima (order keys)
+    __shared__ __align__(16) uint16_t s_min[QUANT ? 4 * NG * kHeadDim : 8];   // per wave: channel minima (order keys) / maxima (inverted)
     __shared__ __align__(16) uint16_t s_max[QUANT ? 4 * NG * kHeadDim : 8];
     __shared__ __align__(16) float2 s_par[QUANT ? NG * kHeadDim : 1];     // (z, 1/s) per (key group, channel)
     __shared__ int s_cnt[2][OUT ? TB / 32 : 1];                           // OUT: outliers beyond the slots per 32-token block (keys, values)
@@ -288,34 +300,41 @@ __global__ __launch_bounds__(kThreads) void gather_quant_pack(
     // The row numbers come first, all of them, and then every row load leaves without waiting for
     // another (two round trips to memory instead of one per row); a row past the count reads the
     // block's last row instead, so no load depends on a branch, and is cleared afterwards. ----
+    // (Addresses here and below: a base that is the same for the workgroup and 32 bits per lane.)
     uint32_t kw[R][4], vw[R][4];
     bool live[R];
-    int pos[R];
+    uint32_t pos[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         live[j] = r + 16 * j < ntok;      // (the same for the 16 lanes of a token row)
-        pos[j] = t0 + min(r + 16 * j, ntok - 1);
+        pos[j] = (uint32_t)min(r + 16 * j, ntok - 1);
     }
-    if (idx) {                            // (uniform)
-        const int32_t* rows = idx + (size_t)head * n_kept;
+    const uint16_t *kb = kh, *vb = vh;
+    if (idx) {                            // (uniform; rows of a prompt: below 2^18)
+        const int32_t* rows = idx + (size_t)head * n_kept + t0;
 #pragma unroll
-        for (int j = 0; j < R; ++j) pos[j] = rows[pos[j]];
+        for (int j = 0; j < R; ++j) pos[j] = (uint32_t)rows[pos[j]];
+    } else {
+        kb += (size_t)t0 * kHeadDim;
+        vb += (size_t)t0 * kHeadDim;
     }
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         // (prompt rows are read once: non-temporal)
         typedef uint32_t u4v __attribute__((ext_vector_type(4)));
-        const u4v a = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(kh + (size_t)pos[j] * kHeadDim + 8 * c8));
-        const u4v b = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(vh + (size_t)pos[j] * kHeadDim + 8 * c8));
+        const u4v a = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(kb + (pos[j] * kHeadDim + 8u * c8)));
+        const u4v b = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(vb + (pos[j] * kHeadDim + 8u * c8)));
         kw[j][0] = a[0]; kw[j][1] = a[1]; kw[j][2] = a[2]; kw[j][3] = a[3];
         vw[j][0] = b[0]; vw[j][1] = b[1]; vw[j][2] = b[2]; vw[j][3] = b[3];
     }
     if (ntok < TB) {                      // (uniform) the head's last block: rows past the count are zeros
+        // (but a copy of the last row leaves the minima and maxima of per-channel groups alone)
+        const bool clear_k = !QUANT || OUT || key_axis != KVQP_KEY_PER_CHANNEL;
 #pragma unroll
         for (int j = 0; j < R; ++j)
             if (!live[j]) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) { kw[j][q] = 0u; vw[j][q] = 0u; }
+                for (int q = 0; q < 4; ++q) { kw[j][q] = clear_k ? 0u : kw[j][q]; vw[j][q] = 0u; }
             }
     }
 
@@ -367,12 +386,14 @@ __global__ __launch_bounds__(kThreads) void gather_quant_pack(
         }
     };
 
+    float one = 1.0f;                     // (see encode)
+    asm("" : "+s"(one));
     // Per-token groups (values always, keys on that axis): every row is complete inside GL lanes.
-    // Fills the codes of all rows and stores scale / zero.  Lane q of a quad derives the parameters
+    // Hands the codes of every row to sink(row, codes) and stores scale / zero.  Lane q of a quad derives the parameters
     // of rows q, q + 4, ... and hands them to the other three.  om: outlier bits (OUT); zrow: float
     // bits of the zero of the lane's own group, per row.
-    auto per_token = [&](const uint32_t (&w)[R][4], uint16_t* scale, uint16_t* zero, uint32_t (&codes)[R][8],
-                         const uint32_t (&om)[R], uint32_t (&zrow)[R]) {
+    auto per_token = [&](const uint32_t (&w)[R][4], uint16_t* scale, uint16_t* zero, const uint32_t (&om)[R],
+                         uint32_t (&zrow)[R], auto sink) {
         uint32_t mn[R], mx[R];
 #pragma unroll
         for (int j = 0; j < R; ++j) {
@@ -390,30 +411,33 @@ __global__ __launch_bounds__(kThreads) void gather_quant_pack(
         const int q4 = c8 & 3;
 #pragma unroll
         for (int jj = 0; jj < R / 4; ++jj) {
-            const uint32_t a = q4 == 0 ? mn[4 * jj] : q4 == 1 ? mn[4 * jj + 1] : q4 == 2 ? mn[4 * jj + 2] : mn[4 * jj + 3];
-            const uint32_t b = q4 == 0 ? mx[4 * jj] : q4 == 1 ? mx[4 * jj + 1] : q4 == 2 ? mx[4 * jj + 2] : mx[4 * jj + 3];
+            const uint32_t a = pick(q4, mn[4 * jj], mn[4 * jj + 1], mn[4 * jj + 2], mn[4 * jj + 3]);
+            const uint32_t b = pick(q4, mx[4 * jj], mx[4 * jj + 1], mx[4 * jj + 2], mx[4 * jj + 3]);
             const GroupParams gp = group_params<BITS>(a, b);
             const int t = r + 16 * (4 * jj + q4);
             if (t < ntok_pad && (c8 & (GL - 1)) < 4) {               // (a padding row of the last block was loaded as zeros: scale 0, zero +0)
-                const size_t m = ((size_t)head * n_cap + d0 + t) * CPT + c8 / GL;
-                scale[m] = gp.scale_h; zero[m] = gp.zero_h;
+                const size_t first = ((size_t)head * n_cap + d0) * CPT;
+                const uint32_t m = (uint32_t)(t * CPT + c8 / GL);
+                (scale + first)[m] = gp.scale_h; (zero + first)[m] = gp.zero_h;
             }
             const uint32_t zb = __float_as_uint(gp.zf), ib = __float_as_uint(gp.inv);
             const uint32_t zq[4] = {dpp<0x00>(zb), dpp<0x55>(zb), dpp<0xAA>(zb), dpp<0xFF>(zb)};
             const uint32_t iq[4] = {dpp<0x00>(ib), dpp<0x55>(ib), dpp<0xAA>(ib), dpp<0xFF>(ib)};
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                encode8<BITS>(w[4 * jj + u], __uint_as_float(zq[u]), __uint_as_float(iq[u]), codes[4 * jj + u]);
+                float c[8];
+                encode8<BITS>(w[4 * jj + u], __uint_as_float(zq[u]), __uint_as_float(iq[u]), one, c);
                 zrow[4 * jj + u] = zq[u];
                 if constexpr (OUT) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) codes[4 * jj + u][e] &= ((om[4 * jj + u] >> e) & 1u) - 1u;   // outliers: code 0
+                    for (int e = 0; e < 8; ++e) c[e] = (om[4 * jj + u] >> e) & 1u ? 0.0f : c[e];   // outliers: code 0
                 }
+                sink(4 * jj + u, c);
             }
         }
     };
     // ---------------- keys ----------------
-    uint32_t* kc_head = k_codes + (size_t)head * ((size_t)n_cap * kHeadDim / E);
+    uint32_t* kc = k_codes + ((size_t)head * n_cap + d0) * (kHeadDim / E);   // first row of this workgroup
     uint32_t om[R], zrow[R];   // outlier bits of the tensor at hand (OUT); zero of the lane's own per-token group
 #pragma unroll
     for (int j = 0; j < R; ++j) om[j] = 0u;
@@ -422,10 +446,15 @@ __global__ __launch_bounds__(kThreads) void gather_quant_pack(
 #pragma unroll
         for (int j = 0; j < R; ++j)
             if (r + 16 * j < ntok_pad)     // (rows past the count were loaded as zeros)
-                *reinterpret_cast<uint4*>(kc_head + (size_t)(d0 + r + 16 * j) * (kHeadDim / 2) + 4 * c8) = make_uint4(kw[j][0], kw[j][1], kw[j][2], kw[j][3]);
+                *reinterpret_cast<uint4*>(kc + (uint32_t)((r + 16 * j) * (kHeadDim / 2) + 4 * c8)) = make_uint4(kw[j][0], kw[j][1], kw[j][2], kw[j][3]);
     } else if (key_axis == KVQP_KEY_PER_CHANNEL) {
         // minima / maxima per channel over the G tokens of a group: own rows, the four row lanes of
         // the wave (lane ^ 16, ^ 32), then the four waves through LDS
+        // (the empty asm keeps the compiler from forming every word's order key ahead of the branch, for both axes)
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) asm("" : "+v"(kw[j][q]));
         uint32_t pmin[NG][4], pmax[NG][4];
 #pragma unroll
         for (int ug = 0; ug < NG; ++ug)
@@ -433,7 +462,7 @@ __global__ __launch_bounds__(kThreads) void gather_quant_pack(
             for (int q = 0; q < 4; ++q) { pmin[ug][q] = 0xffffffffu; pmax[ug][q] = 0u; }
 #pragma unroll
         for (int j = 0; j < R; ++j)
-            if (live[j]) {
+            if (!OUT || live[j]) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const uint32_t a = order_key2(kw[j][q]);
@@ -441,37 +470,52 @@ __global__ __launch_bounds__(kThreads) void gather_quant_pack(
                     pmin[j / JPG][q] = pk_min(pmin[j / JPG][q], a | ex); pmax[j / JPG][q] = pk_max(pmax[j / JPG][q], a & ~ex);
                 }
             }
+        // Maxima go on as minima of the inverted keys, and every lane exchange merges two registers into one:
+        // exchanged between neighbouring rows of 16 lanes, a minimum's and a maximum's register leave the even
+        // rows with the one and the odd rows with the other; exchanged between the halves of the wave, the two
+        // key groups' (or, with one group, two words') leave one to each half.
+        uint32_t red[NG][4];
 #pragma unroll
         for (int ug = 0; ug < NG; ++ug)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                auto s1 = KVQP_SWAP16(pmin[ug][q]); uint32_t a = pk_min(s1[0], s1[1]);
-                auto s2 = KVQP_SWAP32(a); pmin[ug][q] = pk_min(s2[0], s2[1]);
-                auto s3 = KVQP_SWAP16(pmax[ug][q]); uint32_t b = pk_max(s3[0], s3[1]);
-                auto s4 = KVQP_SWAP32(b); pmax[ug][q] = pk_max(s4[0], s4[1]);
+                const auto x = __builtin_amdgcn_permlane16_swap(pmin[ug][q], ~pmax[ug][q], false, false);
+                red[ug][q] = pk_min(x[0], x[1]);
             }
-        if (lane < 16) {
+        uint16_t* s_red = lane & 16 ? s_max : s_min;
+        if constexpr (NG == 2) {
+            uint32_t g[4];
 #pragma unroll
-            for (int ug = 0; ug < NG; ++ug) {
-                *reinterpret_cast<uint4*>(s_min + (wave * NG + ug) * kHeadDim + 8 * c8) = make_uint4(pmin[ug][0], pmin[ug][1], pmin[ug][2], pmin[ug][3]);
-                *reinterpret_cast<uint4*>(s_max + (wave * NG + ug) * kHeadDim + 8 * c8) = make_uint4(pmax[ug][0], pmax[ug][1], pmax[ug][2], pmax[ug][3]);
+            for (int q = 0; q < 4; ++q) {
+                const auto x = __builtin_amdgcn_permlane32_swap(red[0][q], red[1][q], false, false);
+                g[q] = pk_min(x[0], x[1]);
             }
+            *reinterpret_cast<uint4*>(s_red + (wave * 2 + (lane >> 5)) * kHeadDim + 8 * c8) = make_uint4(g[0], g[1], g[2], g[3]);
+        } else {
+            uint32_t g[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const auto x = __builtin_amdgcn_permlane32_swap(red[0][q], red[0][2 + q], false, false);
+                g[q] = pk_min(x[0], x[1]);
+            }
+            *reinterpret_cast<uint2*>(s_red + wave * kHeadDim + 8 * c8 + 4 * (lane >> 5)) = make_uint2(g[0], g[1]);
         }
         __syncthreads();
         for (int item = threadIdx.x; item < NG * kHeadDim; item += kThreads) {   // one (group, channel) each
             const int ug = item / kHeadDim, d = item % kHeadDim;
-            uint32_t a = 0xffffu, b = 0u;
+            uint32_t a = 0xffffu, b = 0xffffu;
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
                 a = min(a, (uint32_t)s_min[(w * NG + ug) * kHeadDim + d]);
-                b = max(b, (uint32_t)s_max[(w * NG + ug) * kHeadDim + d]);
+                b = min(b, (uint32_t)s_max[(w * NG + ug) * kHeadDim + d]);
             }
+            b = 0xffffu - b;
             if (OUT && a > b) { a = 0x8000u; b = 0x8000u; }   // every token of the group is an outlier here: zero +0, scale 0
             const GroupParams gp = group_params<BITS>(a, b);
             s_par[item] = make_float2(gp.zf, gp.inv);
             if (ug * G < ntok) {
-                const size_t m = ((size_t)head * ((n_cap + G - 1) / G) + (d0 / G + ug)) * kHeadDim + d;
-                k_scale[m] = gp.scale_h; k_zero[m] = gp.zero_h;
+                const size_t first = ((size_t)head * ((n_cap + G - 1) / G) + d0 / G) * kHeadDim;
+                (k_scale + first)[(uint32_t)item] = gp.scale_h; (k_zero + first)[(uint32_t)item] = gp.zero_h;
             }
         }
         __syncthreads();
@@ -486,25 +530,23 @@ __global__ __launch_bounds__(kThreads) void gather_quant_pack(
 #pragma unroll
             for (int jl = 0; jl < JPG && ug * JPG + jl < R; ++jl) {
                 const int j = ug * JPG + jl;
-                uint32_t c[8];
-                encode8<BITS>(kw[j], zf, inv, c);
+                float c[8];
+                encode8<BITS>(kw[j], zf, inv, one, c);
                 if constexpr (OUT) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) c[e] &= ((om[j] >> e) & 1u) - 1u;
+                    for (int e = 0; e < 8; ++e) c[e] = (om[j] >> e) & 1u ? 0.0f : c[e];
                 }
                 // (padding rows of the last block hold code 0)
-                if (r + 16 * j < ntok_pad) store_key_words<BITS>(kc_head + (size_t)(d0 + r + 16 * j) * (kHeadDim / E), c8, c, live[j] ? 0xFFFFFFFFu : 0u);
+                if (r + 16 * j < ntok_pad) store_key_words<BITS>(kc, (uint32_t)((r + 16 * j) * (kHeadDim / E)), c8, c, live[j] ? 0xFFFFFFFFu : 0u);
             }
         }
         if constexpr (OUT)   // the zero of (row j's key group, own channel 8 c8 + e) from the table the codes were made with
             store_slots(k_out, s_cnt[0], kw, om, [&](int j, int e) { return s_par[(j / JPG) * kHeadDim + 8 * c8 + e].x; });
     } else {
-        uint32_t codes[R][8];
-        per_token(kw, k_scale, k_zero, codes, om, zrow);
+        per_token(kw, k_scale, k_zero, om, zrow, [&](int j, const float (&c)[8]) {   // (a padding row was loaded as zeros: scale 0, all codes 0)
+            if (r + 16 * j < ntok_pad) store_key_words<BITS>(kc, (uint32_t)((r + 16 * j) * (kHeadDim / E)), c8, c);
+        });
         if constexpr (OUT) store_slots(k_out, s_cnt[0], kw, om, [&](int j, int) { return __uint_as_float(zrow[j]); });
-#pragma unroll
-        for (int j = 0; j < R; ++j)      // (a padding row was loaded as zeros: scale 0, all codes 0)
-            if (r + 16 * j < ntok_pad) store_key_words<BITS>(kc_head + (size_t)(d0 + r + 16 * j) * (kHeadDim / E), c8, codes[j]);
     }
 
     // ---------------- values ----------------
@@ -518,18 +560,27 @@ __global__ __launch_bounds__(kThreads) void gather_quant_pack(
 #pragma unroll
             for (int dd = 0; dd < 8; ++dd) part[sb][dd] = 0u;
         if constexpr (QUANT) {
-            uint32_t codes[R][8];
             if constexpr (OUT) mark(vw, om);
-            per_token(vw, v_scale, v_zero, codes, om, zrow);
+            // A lane's fields of a word sit at 16 H + 8 blk + BITS * (its own place), H = j % 2: the rows of a half-word
+            // add up as floats (blocks only at 2 bits), the lane's place is one shift at the end.  (A padding row's codes are all 0.)
+            float sum[R / 2][8];                       // rows 2 j2 and 2 j2 + 1: below 2^24
+            float even[8];
+            per_token(vw, v_scale, v_zero, om, zrow, [&](int j, const float (&c)[8]) {
+#pragma unroll
+                for (int dd = 0; dd < 8; ++dd) {
+                    if ((j & 1) == 0) even[dd] = c[dd];
+                    else sum[j >> 1][dd] = field_sum<16>(even[dd], c[dd]);
+                }
+            });
             if constexpr (OUT) store_slots(v_out, s_cnt[1], vw, om, [&](int j, int) { return __uint_as_float(zrow[j]); });
+            const uint32_t place = BITS * (i4 % (E / 2));
 #pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const int b32 = j >> 1, H = j & 1;
-                const int sb = (32 * b32) / SB, blk = b32 % (SB / 32);
-                const int p = (4 * blk + i4) % (E / 2);
+            for (int sb = 0; sb < NSB; ++sb)
 #pragma unroll
-                for (int dd = 0; dd < 8; ++dd) part[sb][dd] |= codes[j][dd] << (16 * H + BITS * p);   // (a padding row's codes are all 0)
-            }
+                for (int dd = 0; dd < 8; ++dd) {
+                    if constexpr (SB == 64) part[sb][dd] = ((uint32_t)sum[2 * sb][dd] | ((uint32_t)sum[2 * sb + 1][dd] << 8)) << place;
+                    else part[sb][dd] = (uint32_t)sum[sb][dd] << place;
+                }
         } else {
 #pragma unroll
             for (int j = 0; j < R; ++j) {
@@ -541,25 +592,42 @@ __global__ __launch_bounds__(kThreads) void gather_quant_pack(
                 }
             }
         }
-        constexpr int LANES_PER_WORD = (E / 2 >= 4) ? 4 : E / 2;   // row lanes whose fields share a word
-#pragma unroll
-        for (int sb = 0; sb < NSB; ++sb)
-#pragma unroll
-            for (int dd = 0; dd < 8; ++dd) {
-                if (LANES_PER_WORD >= 2) { auto s1 = KVQP_SWAP16(part[sb][dd]); part[sb][dd] = s1[0] | s1[1]; }
-                if (LANES_PER_WORD >= 4) { auto s2 = KVQP_SWAP32(part[sb][dd]); part[sb][dd] = s2[0] | s2[1]; }
-            }
+        // Row lanes whose fields share a word merge them, and every lane exchange merges two registers into one:
+        // a lane is left with 8 / LANES_PER_WORD of the channels, first + 0 .. (bit 2 of the channel by the lane's
+        // place among the neighbouring rows, bit 1 by the half of the wave).
+        constexpr int LANES_PER_WORD = (E / 2 >= 4) ? 4 : E / 2;
+        constexpr int NW = 8 / LANES_PER_WORD;
         const int wl = (E / 2 >= 4) ? 0 : i4 / (E / 2);          // run / (E/2) with blk = 0 (SB = 32 whenever E/2 < 4)
-        const bool writer = (i4 % LANES_PER_WORD) == 0;
-        if (writer) {
-            const int tile = c8 >> 1, y = tile * WPT + wl;
+        const int tile = c8 >> 1, y = tile * WPT + wl;
+        const int first = (LANES_PER_WORD >= 2 ? 4 * (i4 & 1) : 0) + (LANES_PER_WORD >= 4 ? 2 * (i4 >> 1) : 0);
 #pragma unroll
-            for (int sb = 0; sb < NSB; ++sb)
+        for (int sb = 0; sb < NSB; ++sb) {
+            uint32_t m[NW];
+            if constexpr (LANES_PER_WORD == 1) {
 #pragma unroll
-                for (int dd = 0; dd < 8; ++dd) {
-                    const int n = 8 * (c8 & 1) + dd;
-                    s_words[sb * SBW + ((y >> 2) * 64 + wave * 16 + n) * 4 + (y & 3)] = part[sb][dd];
+                for (int dd = 0; dd < 8; ++dd) m[dd] = part[sb][dd];
+            } else {
+                uint32_t h[4];
+#pragma unroll
+                for (int dd = 0; dd < 4; ++dd) {
+                    const auto x = __builtin_amdgcn_permlane16_swap(part[sb][dd], part[sb][4 + dd], false, false);
+                    h[dd] = x[0] | x[1];
                 }
+#pragma unroll
+                for (int dd = 0; dd < NW; ++dd) {
+                    if constexpr (LANES_PER_WORD == 4) {
+                        const auto x = __builtin_amdgcn_permlane32_swap(h[dd], h[2 + dd], false, false);
+                        m[dd] = x[0] | x[1];
+                    } else {
+                        m[dd] = h[dd];
+                    }
+                }
+            }
+#pragma unroll
+            for (int dd = 0; dd < NW; ++dd) {
+                const int n = 8 * (c8 & 1) + first + dd;
+                s_words[sb * SBW + ((y >> 2) * 64 + wave * 16 + n) * 4 + (y & 3)] = m[dd];
+            }
         }
         __syncthreads();
         const int n_sb = (ntok + SB - 1) / SB;
@@ -668,8 +736,6 @@ __global__ __launch_bounds__(64) void ovf_fill(const uint16_t* __restrict__ k, c
         at += total - 4u;
     }
 }
-#undef KVQP_SWAP16
-#undef KVQP_SWAP32
 
 template <int BITS, int G, bool OUT>
 hipError_t launch_bits_g(const QuantPackJob& j, hipStream_t stream) {

@@ -67,3 +67,31 @@ def test_quantizer_edge_values_bit_exact(orc):
         kvqp.quantize_selected(cfg, dev(k), dev(v), dev(idx), gc)
         torch.cuda.synchronize()
         assert_cache_equal(gc, oc)
+
+
+@pytest.mark.parametrize("n", [1, 33, 65, 129, 193])
+@pytest.mark.parametrize("bits,G,axis", [(2, 32, 0), (4, 32, 0), (8, 32, 0), (2, 64, 0), (8, 64, 0), (4, 128, 0), (8, 128, 0),
+                                         (2, 32, 1), (8, 64, 1), (4, 128, 1)])
+def test_extremes_in_every_row_bit_exact(orc, n, bits, G, axis):
+    """Where a group's minimum and maximum come from: every channel has its extremes in other rows and
+    every row in other channels, signs change from channel to channel (all negative, all positive,
+    around zero, signed zeros), rows past the survivors hold larger values, and the last key group and
+    block are partly filled."""
+    print(f"case extremes n={n} bits={bits} G={G} axis={axis}", flush=True)
+    W, L = 8, n + 40
+    rng = np.random.default_rng(n * 10 + bits)
+    k, v = [(rng.standard_normal((1, 2, L, 128)) * np.exp2(rng.integers(-16, 10, (1, 2, 1, 128)))
+             + rng.integers(-2, 3, (1, 2, 1, 128)) * np.exp2(rng.integers(-3, 13, (1, 2, 1, 128)))).astype(np.float16) for _ in range(2)]
+    for x in (k, v):
+        x[..., 5::16] = np.where(rng.random(x[..., 5::16].shape) < 0.5, np.float16(0.0), np.float16(-0.0))
+        x[..., 6::16] = -np.abs(x[..., 6::16])
+        x[:, :, n:] = np.float16(60000) * np.sign(x[:, :, n:] + np.float16(0.1))
+    idx = np.broadcast_to(np.arange(n, dtype=np.int32), (1, 2, n)).copy()
+    oc = orc.quantize_selected(k, v, idx, W=W, bits=bits, G=G, key_axis=axis)
+    cfg = kvqp.Cfg(batch=1, n_q_heads=4, n_kv_heads=2, seq_len=L, window=W, budget=n, bits=bits, group_size=G, key_axis=axis)
+    gc = kvqp.alloc_cache(cfg)
+    for t in gc.buffers.values():
+        t.fill_(0xA5)
+    kvqp.quantize_selected(cfg, dev(k), dev(v), dev(idx), gc)
+    torch.cuda.synchronize()
+    assert_cache_equal(gc, oc)

@@ -326,7 +326,10 @@ int kvqp_quantize_selected_ragged(const kvqp_cfg *cfg, const void *k, const void
  * Workspace: kvqp_workspace_bytes' decode_bytes, 16-byte aligned, prepared ONCE with
  * kvqp_decode_workspace_init before its first use.  It holds the partial results of
  * the token-axis splits and, at its head, one arrival counter per (batch, KV head)
- * that is zero between calls (the workgroup that merges a head puts it back).  Calls
+ * that is zero between calls (the workgroup that merges a head puts it back).  One
+ * workspace may serve calls of different batch sizes, models and bit widths in any
+ * order if it has the largest decode_bytes among them and was prepared for the
+ * most heads; their partial results stay clear of all their counters.  Calls
  * that use different workspaces are independent and may overlap in time (several
  * streams, several graphs in flight); calls that share one workspace must not
  * overlap (calls issued on one stream never do).

@@ -40,7 +40,7 @@
 // Each device's copy starts all zero (static storage) and every completed launch leaves the
 // arrival counters at its head zero again; they are nevertheless zeroed by a fill kernel when a
 // device's address is first taken.  Calls that use it share it: they must not overlap on one device.
-static __device__ __align__(256) unsigned char scratch[kvqp::kStaticCounterBytes + kvqp::kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kvqp::kCounterBytes + kvqp::kStaticScratchBytes];
 
 namespace kvqp {
 namespace {
@@ -1478,7 +1478,7 @@ size_t decode_ws_bound(const kvqp_cfg& cfg) {
     int splits = (share + kWaves - 1) / kWaves;
     if (cfg.decode_splits > splits) splits = cfg.decode_splits;
     if (splits < 1) splits = 1;
-    return decode_ws_header_bytes(cfg) + (size_t)heads * splits * gq * kPartFloats * sizeof(float);
+    return kCounterBytes + (size_t)heads * splits * gq * kPartFloats * sizeof(float);
 }
 
 // Microseconds of a launch of `splits` workgroups of nw waves per head (equal heads), as measured over
@@ -1607,7 +1607,7 @@ hipError_t static_scratch(const kvqp_cfg& cfg, void** ptr, hipStream_t stream) {
         if (e != hipSuccess) return e;
         if (!p) return hipErrorInvalidSymbol;
         // counters for the largest head count the launches accept (a fill kernel: the call may be under capture)
-        constexpr int n = (int)(kStaticCounterBytes / sizeof(unsigned int));
+        constexpr int n = (int)(kCounterBytes / sizeof(unsigned int));
         hipLaunchKernelGGL(zero_words, dim3(n / 256), dim3(256), 0, stream, (unsigned int*)p, n);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -321,10 +321,10 @@ int kvqp_decode_attn_static(const kvqp_cfg* cfg, const void* q, const kvqp_cache
     DecodePlan plan;
     const int rc = check_decode(cfg, q, cache, out, &plan);
     if (rc) return rc;
-    if (!plan.fit(kStaticScratchBytes)) return KVQP_ERR_WORKSPACE;   // beyond the library's array: use kvqp_decode_attn
+    if (plan.least_bytes() > kStaticScratchBytes || !plan.fit(kCounterBytes + kStaticScratchBytes))
+        return KVQP_ERR_WORKSPACE;   // beyond the library's array: use kvqp_decode_attn
     void* ws = nullptr;
     if (static_scratch(*cfg, &ws, (hipStream_t)hip_stream) != hipSuccess) return KVQP_ERR_HIP;
-    plan.part_off += kStaticCounterBytes;
     if (launch_decode(*cfg, q, *cache, out, ws, plan, (hipStream_t)hip_stream) != hipSuccess) return KVQP_ERR_HIP;
     return KVQP_OK;
 }

@@ -45,6 +45,10 @@ inline size_t k_meta_elems(int n_kept, int bits, int G, int key_axis) {
 }
 inline size_t v_meta_elems(int n_kept, int bits, int G) { return bits == 16 ? 0 : (size_t)rows32(n_kept) * (kHeadDim / G); }
 
+// Room for the arrival counters of the most heads a launch accepts.  It opens every decode workspace of
+// the size that kvqp_workspace_bytes states, and no call's partial results touch it.
+constexpr size_t kCounterBytes = 65536 * sizeof(unsigned int);
+
 // Decode split-K geometry, a pure function of the problem so that the
 // workspace query and the launch agree.
 struct DecodePlan {
@@ -56,36 +60,35 @@ struct DecodePlan {
     size_t part_bytes = 0;   // the partials alone
     size_t part_off = 0;     // where they lie in the workspace at hand (fit)
     // A plan that was taken for its speed beside the plain rule's (alt_waves == 0: none).  The plain one
-    // says what workspace the call wants, and runs when there is that much but not enough for the other.
+    // says what workspace the call accepts, and runs when there is that much but not enough for the other.
     int alt_splits = 0, alt_chunks = 0, alt_waves = 0;
     size_t alt_part_bytes = 0;
+    size_t least_bytes() const { return ws_bytes - part_bytes + (alt_waves ? alt_part_bytes : part_bytes); }
     void take_plain() {
         if (!alt_waves) return;
-        const size_t counters = ws_bytes - part_bytes;
+        ws_bytes = least_bytes();
         n_splits = n_partials = alt_splits; chunks_per_split = alt_chunks; n_waves = alt_waves;
-        part_bytes = alt_part_bytes; ws_bytes = counters + part_bytes;
+        part_bytes = alt_part_bytes;
         alt_waves = 0;
     }
-    // Whether a workspace of that size serves the call.  The partials go to its end: at its head lie
-    // the arrival counters, and those of a call with more heads, which have to stay zero, reach further.
+    // Whether a workspace of that size serves the call.  Partials lie behind the counters of every call
+    // that may share the workspace, not behind this call's alone: a counter of another one that is not
+    // zero when it starts is never reached, and that head is never merged.  A smaller workspace than
+    // stated takes the plain plan's partials at its end, as far from the counters as they go.
     bool fit(size_t bytes) {
-        const size_t counters = ws_bytes - part_bytes;
-        if (alt_waves && bytes < counters + alt_part_bytes) return false;
-        if (bytes < ws_bytes) take_plain();
-        if (bytes < ws_bytes) return false;
-        part_off = (bytes - part_bytes) / 16 * 16;
+        if (bytes < least_bytes()) return false;
+        if (part_bytes > 0 && bytes < kCounterBytes + part_bytes) take_plain();
+        part_off = bytes < kCounterBytes + part_bytes ? (bytes - part_bytes) / 16 * 16 : kCounterBytes;
         return true;
     }
 };
 DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept, int tail_len);
-size_t decode_ws_bound(const kvqp_cfg& cfg);   // >= plan_decode(cfg, n, t).ws_bytes for every n and t
+size_t decode_ws_bound(const kvqp_cfg& cfg);   // >= kCounterBytes + plan_decode(cfg, n, t).part_bytes for every n and t
 size_t decode_ws_header_bytes(const kvqp_cfg& cfg);   // arrival counters at the head of a decode workspace
 hipError_t launch_ws_init(const kvqp_cfg& cfg, void* ws, hipStream_t stream);   // zeroes them
 // The library's own decode workspace (a static device array): its address on the current device,
 // prepared on first use.  KVQP_STATIC_SCRATCH_BYTES in kvqp.h is its size.
-constexpr size_t kStaticScratchBytes = KVQP_STATIC_SCRATCH_BYTES;
-// ... behind arrival counters for the largest head count a launch accepts, which no call's partials touch.
-constexpr size_t kStaticCounterBytes = 65536 * sizeof(unsigned int);
+constexpr size_t kStaticScratchBytes = KVQP_STATIC_SCRATCH_BYTES;   // ... behind kCounterBytes of counters
 hipError_t static_scratch(const kvqp_cfg& cfg, void** ptr, hipStream_t stream);
 
 // Compress workspace layout (bytes offsets), pure function of cfg.

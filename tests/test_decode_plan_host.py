@@ -1,0 +1,70 @@
+"""Launch plans of the decode kernel (token-axis splits of Eq. (3)) and where their partial results
+lie in a workspace, from the library's own planning code; no GPU needed."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2412_12706_amd import kvqp
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+FIELDS = ("accepted", "splits", "waves", "part_bytes", "part_off", "counters", "stated")
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    """plans([(batch, hq, hkv, n, bits, group, outliers, decode_splits, workspace bytes), ...]) -> dicts"""
+    if shutil.which("hipcc") is None:
+        pytest.skip("no hipcc")
+    if not os.path.exists(kvqp.LIB_PATH):
+        from paper_2412_12706_amd import build
+        build.build()
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_driver")
+    lib_dir = os.path.dirname(kvqp.LIB_PATH)
+    r = subprocess.run(["hipcc", "-x", "hip", "--cuda-host-only", "-O1", "-std=c++17", "-I" + os.path.join(ROOT, "include"),
+                        "-I" + os.path.join(lib_dir, "csrc"), os.path.join(ROOT, "tests", "sanitize", "plan_driver.cpp"),
+                        "-L" + lib_dir, "-lkvqp", "-Wl,-rpath," + lib_dir, "-o", exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-3000:]
+
+    def ask(problems):
+        r = subprocess.run([exe], input="".join(" ".join(map(str, p)) + "\n" for p in problems), capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr[-3000:]
+        rows = [dict(zip(FIELDS, map(int, line.split()))) for line in r.stdout.splitlines()]
+        assert len(rows) == len(problems)
+        return rows
+    return ask
+
+
+@pytest.mark.parametrize("hq,hkv,n,bits,group,outliers,splits", [
+    (32, 8, 2048, 4, 32, 0, 0), (32, 8, 8192, 2, 32, 0, 0), (32, 8, 8192, 16, 32, 0, 0), (64, 8, 3000, 4, 128, 0, 0),
+    (16, 8, 1000, 8, 64, 0, 0), (8, 8, 4096, 4, 32, 0, 0), (32, 8, 5000, 4, 32, 1, 0), (32, 8, 4096, 4, 32, 0, 7)])
+def test_partials_stay_clear_of_every_counter_of_calls_that_share_a_workspace(plans, hq, hkv, n, bits, group, outliers, splits):
+    """One workspace of the larger stated size, two batch sizes in turn: neither call's partial
+    results may lie over the other's arrival counters, which have to be zero when it starts."""
+    def problem(b, ws=0):
+        return (b, hq, hkv, n, bits, group, outliers, splits, ws)
+    own = {b: r for b, r in zip(range(1, 65), plans([problem(b) for b in range(1, 65)]))}
+    pairs = [(a, b) for a in own for b in own if a != b]
+    shared = [max(own[a]["stated"], own[b]["stated"]) for a, b in pairs]
+    split = 0
+    for (a, b), ws, p in zip(pairs, shared, plans([problem(a, ws) for (a, _), ws in zip(pairs, shared)])):
+        assert p["accepted"] and p["splits"] == own[a]["splits"]
+        if p["splits"] > 1:
+            split += 1
+            assert p["part_off"] >= max(own[a]["counters"], own[b]["counters"]), (a, b, p)
+            assert p["part_off"] % 16 == 0 and p["part_off"] + p["part_bytes"] <= ws, (a, b, p)
+    assert split > 500
+
+
+@pytest.mark.parametrize("hq,hkv,n,bits", [(32, 8, 2048, 4), (16, 8, 1200, 4), (64, 8, 8192, 2)])
+def test_smaller_workspaces_than_stated_are_taken_and_not_overrun(plans, hq, hkv, n, bits):
+    """Down to the arrival counters and the plain rule's partials, and no further."""
+    for b in (1, 3, 12, 19, 40, 44):
+        whole = plans([(b, hq, hkv, n, bits, 32, 0, 0, 0)])[0]
+        sizes = sorted({whole["counters"] + i * whole["stated"] // 40 // 16 * 16 for i in range(40)} | {whole["stated"]})
+        rows = plans([(b, hq, hkv, n, bits, 32, 0, 0, ws) for ws in sizes])
+        taken = [(ws, p) for ws, p in zip(sizes, rows) if p["accepted"]]
+        assert taken and [p["accepted"] for p in rows] == sorted(p["accepted"] for p in rows)
+        for ws, p in taken:
+            assert p["part_bytes"] == 0 or (p["part_off"] >= p["counters"] and p["part_off"] + p["part_bytes"] <= ws), (b, ws, p)

@@ -71,3 +71,20 @@ def test_one_workspace_and_the_static_array_serve_head_counts_in_any_order(orc):
         out = torch.empty((cfg.batch, cfg.n_q_heads, 128), dtype=torch.float16, device="cuda")
         kvqp.decode_attn_static(cfg, q, gc, out)
         assert attn_excess(out, ref) <= 0
+
+
+@pytest.mark.parametrize("order", [(19, 44, 23, 43), (44, 19, 44, 23, 44)])
+def test_splits_that_fill_the_stated_workspace_leave_other_calls_counters_alone(orc, order):
+    """Batches whose splits use all the partials a workspace is stated for, on one workspace that is
+    prepared once: every call's counters have to be zero when it starts, whichever came before."""
+    jobs = {}
+    for b in set(order):
+        cfg, oc = cache_of(orc, b, 8, 2, 900, 4)
+        q = synth.decode_query_host(b, 16, 128, config=94)
+        jobs[b] = (cfg, upload_cache(oc), dev(q), orc.decode_attn(q, oc, float(np.float32(cfg.sm_scale))))
+    ws = kvqp.decode_workspace_init(jobs[max(order)][0], kvqp.alloc_workspace(max(kvqp.workspace_bytes(cfg)[1] for cfg, *_ in jobs.values())))
+    for b in order:
+        print(f"case shared workspace batch {b} of {order}", flush=True)
+        cfg, gc, q, ref = jobs[b]
+        out = torch.full((b, 16, 128), float("nan"), dtype=torch.float16, device="cuda")   # (a head that is not merged stays)
+        assert attn_excess(kvqp.decode_attn(cfg, q, gc, out, ws), ref) <= 0

@@ -144,7 +144,8 @@ typedef struct kvqp_cfg {
  *   r = float(m) - float(z);  s32 = r / float(2^bits - 1);  s = half(s32);
  *   s == 0  ->  all codes 0;  else inv = 1.0f / float(s),
  *   code = clamp(rint((float(x) - float(z)) * inv), 0, 2^bits - 1).
- * NaN inputs are not supported.
+ * NaN inputs are not supported (results are undefined; compression still keeps
+ * the stated number of positions, all of the prefix, in every head).
  *
  * Outlier filtering (Section 6.3, item (1); Appendix B: numbers whose absolute
  * value exceeds 6, about 1 %, are excluded from quantization).  With

@@ -558,6 +558,9 @@ struct SelectArgs {
     float sm_scale;
 };
 
+// Pooling starts from 0, which no vote is below: a vote that is not a number counts as 0, so a score's pattern is 0 ..
+// 0x7f800000 whatever the inputs hold.  Its code fits 16 bits, the bins and the sweep over the codes agree, and every
+// head gets exactly as many survivors as it is to have, all of them positions of the prefix.
 __device__ __forceinline__ uint32_t score_key(float v) { return __float_as_uint(v); }  // scores are >= 0: bits order like values
 __device__ __forceinline__ int score_bin(uint32_t key) { return min(max((int)(key >> kBinShift) - kBinBase, 0), kBins - 1); }
 
@@ -656,8 +659,8 @@ __device__ double vote_f64_part(const SelectArgs& a, int head, int key, int row_
     return acc;
 }
 
-// Max-pooling of one tile: the votes of candidates j0 - r .. j0 + kPoolTile + r go through LDS (-1,
-// below any vote, outside the prefix) and every thread pools four consecutive candidates, reading
+// Max-pooling of one tile: the votes of candidates j0 - r .. j0 + kPoolTile + r go through LDS (0
+// outside the prefix) and every thread pools four consecutive candidates, reading
 // the votes its windows share once (10 votes for a pool of 7, in three 16-byte reads).
 struct VoteTile { float v[5]; };
 __device__ __forceinline__ VoteTile fetch_votes(const float* vote, int P, int r, int j0) {
@@ -665,7 +668,7 @@ __device__ __forceinline__ VoteTile fetch_votes(const float* vote, int P, int r,
 #pragma unroll
     for (int u = 0; u < 5; ++u) {
         const int i = (int)threadIdx.x + u * kSelThreads, j = j0 - r + i;
-        t.v[u] = (i < kPoolTile + 2 * r && j >= 0 && j < P) ? vote[j] : -1.0f;
+        t.v[u] = (i < kPoolTile + 2 * r && j >= 0 && j < P) ? vote[j] : 0.0f;
     }
     return t;
 }
@@ -678,7 +681,7 @@ __device__ __forceinline__ void stage_votes(const VoteTile& t, float* stage) {
 }
 __device__ __forceinline__ float4 pool_four(const float* stage, int r) {
     const float4* s = reinterpret_cast<const float4*>(stage) + threadIdx.x;
-    float o[4] = {-1.0f, -1.0f, -1.0f, -1.0f};
+    float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int q = 0; 4 * q <= 2 * r + 3; ++q) {
         const float4 x4 = s[q];
         const float x[4] = {x4.x, x4.y, x4.z, x4.w};
@@ -872,7 +875,7 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     // the pooled score of a candidate, from the votes
     auto pooled_key = [&](int j) -> uint32_t {
         const int t1 = min(j + r, P - 1);
-        float best = -1.0f;
+        float best = 0.0f;
         for (int t = max(j - r, 0); t <= t1; t += 8) {      // (eight votes in flight; past the window its last one again)
             float x[8];
 #pragma unroll

@@ -106,3 +106,31 @@ def test_wide_windows_at_the_edges_of_a_step(orc, P, Gq, W):
     got, idx, pooled, unrefined = select(orc, P, W, 5, max(1, P // 3), Gq=Gq, seed=79)
     check_indices(got, idx, pooled)
     assert unrefined == [0, 0]
+
+
+@pytest.mark.parametrize("where,word", [("query", float("nan")), ("key", float("nan")), ("query", float("inf")), ("key", -float("inf"))])
+@pytest.mark.parametrize("P,Gq,W,pool,budget", [(700, 2, 8, 7, 100), (4096, 4, 32, 1, 4095), (5000, 2, 8, 7, 513), (9001, 4, 64, 63, 2000)])
+def test_votes_that_are_not_numbers_still_give_every_survivor(P, Gq, W, pool, budget, where, word):
+    """Such inputs have no defined scores, but every head still gets its count of ascending positions
+    of the prefix (the quantizer gathers at them), and the other heads are not touched.  A row of a
+    head that is not finite takes all its votes away (query, NaN) or leaves them at zero: the lowest positions."""
+    print(f"case {where} {word} P={P} Gq={Gq} W={W} pool={pool} budget={budget}", flush=True)
+    L, Hkv = P + W, 3
+    q_obs, k, v = (dev(t) for t in synth.prompt_host(1, Hkv * Gq, Hkv, L, W, 128, config=81))
+    cfg = kvqp.Cfg(batch=1, n_q_heads=Hkv * Gq, n_kv_heads=Hkv, seq_len=L, window=W, pool_kernel=pool, budget=budget, bits=4, group_size=32)
+
+    def survivors():
+        got = torch.full((1, Hkv, budget), -1, dtype=torch.int32, device="cuda")
+        kvqp.compress(cfg, q_obs, k, v, kvqp.alloc_cache(cfg), idx_out=got)
+        torch.cuda.synchronize()
+        return got.cpu()[0]
+    clean = survivors()
+    if where == "query":
+        q_obs[0, Gq:2 * Gq, :, 5] = word
+    else:
+        k[0, 1, P // 3, 9] = word
+    got = survivors()
+    assert torch.equal(got[0], clean[0]) and torch.equal(got[2], clean[2])
+    assert bool((got[1].diff() > 0).all()) and int(got[1, 0]) >= 0 and int(got[1, -1]) < P
+    if word != word:
+        assert torch.equal(got[1], torch.arange(budget, dtype=torch.int32))

@@ -43,7 +43,7 @@ constexpr int kNarrowRows = 4 * kRowsPerWave;   // window rows of a KV head it t
 constexpr int kKeyStride = kHeadDim * 2 + 16;  // LDS bytes per key row; +16 B skews banks
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1.0e30f;
-constexpr float kLazy = 8.0f;           // score_pass moves a row's reference only when a score beats it by 2^8
+constexpr float kLazy = 8.0f;           // a row's reference moves only when a score beats it by 2^8 (an exponential's argument is rounded at its own magnitude: here to 2^-22, with references moved at 2^60 to 2^-19)
 
 enum { PASS_STATS = 0, PASS_VOTES = 1 };
 
@@ -261,13 +261,12 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
 // matrix instructions.  No barrier in the loop, no key through LDS; the products of a row tile run
 // while the scores of the tile before it are exponentiated.  A lane's accumulators are keys of ONE
 // row, so a row's reference is one register.  8 heads, 131072 keys, 256 rows: 124 + 91 us (statistics +
-// votes) with score_pass's layout, 93 + 85 us this way; up to 128 rows score_pass is as fast or faster
+// votes) with score_pass's layout, 97 + 86 us this way; up to 128 rows score_pass is as fast or faster
 // (8 heads of 32768 keys: 23 + 19 against 24 + 21 us; of 4096 keys 10 + 7 against 12 + 9).
 constexpr int kWideTiles = 16;                 // row tiles
 constexpr int kKeyTiles = 4;                   // 16-key tiles a wave holds
 constexpr int kChunkKeys = 16 * kKeyTiles;     // keys of a wave's step
 constexpr int kScoreWaves = kThreads / 64;
-constexpr float kFarSum = 1.152921504606846976e18f;   // 2^60: a row's reference is moved when a sum relative to it passes this
 template <int PASS>
 __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
     constexpr int RT = kWideTiles;
@@ -327,16 +326,15 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
 
     const int w_first = n % a.W, w_step = 16 % a.W;               // window position of row n; from a row tile to the next
     // A step comes in two forms without a branch inside (branches let the compiler start later tiles
-    // early, which do not fit the registers).  The careful one masks keys the rows may not see and
-    // moves the references to the rows' maxima; it takes a wave's first step, the steps that reach the
-    // window, and those of which the other one finds a sum out of range: scores are taken relative to
-    // the reference as it is, which costs no precision while their sums stay below kFarSum.
-    // Returns whether the step was out of range (then nothing has been added).
-    auto compute = [&](auto careful, const Keys& key_f, int c) -> bool {
-        constexpr bool CAREFUL = decltype(careful)::value;
-        float z_add[RT];
+    // early, which do not fit the registers); the one with MASK hides the keys that the rows may not see and
+    // takes the steps that reach the window.  The references move as in score_pass, a lane's by the scores of
+    // its 16 keys, by selects: 94 -> 97 us of the statistics pass.  (Left alone until a step's sum passed 2^60, and the step
+    // done again, they made a row's sum, and with it the binary64 re-scoring, wrong by up to 1.4e-6 instead of
+    // 4e-7; done again at 2^8, strong outlier channels took 62 us more of the 93 at 131072 keys.)
+    auto compute = [&](auto mask, const Keys& key_f, int c) {
+        constexpr bool MASK = decltype(mask)::value;
         int at = lane, wr = w_first;
-        asm volatile("" : "+v"(at));                             // (the query operand is read again every step, not kept for the whole loop)
+        asm volatile("" : "+v"(at), "+v"(wr));                   // (the query operand is read, and the masks formed, again every step, not kept for the whole loop)
         float vs[kKeyTiles][4];                                  // VOTES: the lane's row sums per key 16 kt + 4 kb + i
 #pragma unroll
         for (int kt = 0; kt < kKeyTiles; ++kt)
@@ -359,7 +357,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             if (rt + 1 < RT) product(acc_next, rt + 1);
-            if constexpr (CAREFUL) {                             // causal mask (raw scores; the scale is positive)
+            if constexpr (MASK) {                                // causal mask (raw scores; the scale is positive)
                 const int last = min(a.P + wr, a.L - 1) - c * kChunkKeys - 4 * kb;   // the row's last key, from the lane's first one
 #pragma unroll
                 for (int kt = 0; kt < kKeyTiles; ++kt)
@@ -370,16 +368,14 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
                 if (wr >= a.W) wr -= a.W;
             }
             if constexpr (PASS == PASS_STATS) {
-                if constexpr (CAREFUL) {
-                    float big = acc[0][0];
+                float big = acc[0][0];
 #pragma unroll
-                    for (int kt = 0; kt < kKeyTiles; ++kt)
+                for (int kt = 0; kt < kKeyTiles; ++kt)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) big = fmaxf(big, acc[kt][i]);
-                    const float m_new = fmaxf(m_run[rt], big * a.scale_log2);
-                    z_run[rt] *= __builtin_amdgcn_exp2f(m_run[rt] - m_new);
-                    m_run[rt] = m_new;
-                }
+                    for (int i = 0; i < 4; ++i) big = fmaxf(big, acc[kt][i]);
+                const float top = big * a.scale_log2, m_new = top > m_run[rt] + kLazy ? top : m_run[rt];
+                z_run[rt] *= __builtin_amdgcn_exp2f(m_run[rt] - m_new);
+                m_run[rt] = m_new;
                 float z0 = 0.f, z1 = 0.f;
 #pragma unroll
                 for (int kt = 0; kt < kKeyTiles; ++kt)
@@ -388,8 +384,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
                         z0 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[kt][i], a.scale_log2, -m_run[rt]));
                         z1 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[kt][i + 1], a.scale_log2, -m_run[rt]));
                     }
-                z_add[rt] = z0 + z1;
-                asm volatile("" : "+v"(z_add[rt]));              // (formed here and not where it is added: 16 registers per tile)
+                z_run[rt] += z0 + z1;
             } else {
 #pragma unroll
                 for (int kt = 0; kt < kKeyTiles; ++kt)
@@ -402,16 +397,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
             for (int kt = 0; kt < kKeyTiles; ++kt) acc[kt] = acc_next[kt];
             __builtin_amdgcn_sched_barrier(0);                   // (tiles started early would not fit the registers)
         }
-        if constexpr (PASS == PASS_STATS) {
-            if constexpr (!CAREFUL) {
-                bool far = false;
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt) far |= !(z_add[rt] < kFarSum);
-                if (__builtin_amdgcn_ballot_w64(far) != 0ull) return true;
-            }
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) z_run[rt] += z_add[rt];
-        } else {
+        if constexpr (PASS == PASS_VOTES) {
             // sum over the 16 lanes of a row of lanes, each ending up with one of the 16 values: lane n with
             // (kt, i) = (n / 4, n % 4).  At every step a lane keeps the half of the values that its bit
             // selects and receives its partner's sums of that half.
@@ -433,14 +419,12 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
             const int key = c * kChunkKeys + 16 * (n >> 2) + 4 * kb + (n & 3);
             if (key < a.P) a.vote[(size_t)head * a.P + key] = x[0];
         }
-        return false;
     };
-    bool first = PASS == PASS_STATS;
     for (; chunk < c_end; chunk += kScoreWaves) {
         Keys next;
         if (chunk + kScoreWaves < c_end) load(next, chunk + kScoreWaves);
-        if (first || (chunk + 1) * kChunkKeys > a.P || compute(BoolC<false>{}, keys, chunk)) compute(BoolC<true>{}, keys, chunk);
-        first = false;
+        if ((chunk + 1) * kChunkKeys > a.P) compute(BoolC<true>{}, keys, chunk);
+        else compute(BoolC<false>{}, keys, chunk);
         keys = next;
     }
 
@@ -1163,7 +1147,8 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
     // beyond eight per CU more only cost.  Statistics + votes, us, with 512 / 1024 / 2048 workgroups: 8
     // heads of 32768 keys 23 + 19 / 26 + 19 / 32 + 22, 32 heads of 16384 37 + 34 / 39 + 32 / 46 + 35, 64 heads
     // 62 + 59 / 61 + 55 / 68 + 57, 128 heads 117 + 122 / 117 + 110 / 118 + 108, 256 heads of 32768 431 + 494 /
-    // 419 + 419 / 415 + 418; with 256 rows 16 heads of 65536 keys 93 + 85 / 101 + 89 / 128 + 102.
+    // 419 + 419 / 415 + 418; with 256 rows 16 heads of 65536 keys 93 + 85 / 101 + 89 / 128 + 102 (the statistics
+    // without moving references, 3 % of them).
     const long long chunks = (long long)heads * p.n_chunks;
     const int total = (int)std::min(2048LL, std::max(512LL, chunks / (wide ? 64 : 16)));
     int n_wg = (total + heads - 1) / heads;

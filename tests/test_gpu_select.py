@@ -85,9 +85,8 @@ def test_clustered_scores_beyond_the_list_are_still_refined(orc):
 
 @pytest.mark.parametrize("Gq,W", [(4, 64), (8, 17), (4, 32), (1, 5)])
 def test_scores_that_leave_the_first_keys_far_behind(orc, Gq, W):
-    """Keys that grow fourteenfold halfway through the prompt: row maxima pass the references taken from
-    a workgroup's first keys by more than 2^60, which makes the statistics pass of the wide kernel
-    (more than 128 window rows) do a step again with moved references."""
+    """Keys that grow fourteenfold halfway through the prompt: row maxima of later workgroups pass those of
+    earlier ones by more than 2^60, and the statistics of the latter vanish in the merge."""
     P = 4500
     print(f"case growing keys Gq={Gq} W={W}", flush=True)
 
@@ -134,3 +133,43 @@ def test_votes_that_are_not_numbers_still_give_every_survivor(P, Gq, W, pool, bu
     assert bool((got[1].diff() > 0).all()) and int(got[1, 0]) >= 0 and int(got[1, -1]) < P
     if word != word:
         assert torch.equal(got[1], torch.arange(budget, dtype=torch.int32))
+
+
+@pytest.mark.parametrize("Gq,W", [(4, 64), (8, 24), (4, 32)])
+@pytest.mark.parametrize("key", [5.0, 14.0, 24.0, 38.0])
+def test_row_sums_keep_their_precision_when_a_late_key_dominates(Gq, W, key):
+    """Statistics of the window rows (the divisors of every vote, in the re-scoring too) when one key, the
+    last of a wave's share, beats all earlier ones by 4 to 55 factors of two.  One channel is in use, so
+    the products are exact and only exponentials and sums are rounded: with arguments up to 8 (a
+    reference never lags further) 2^-22 ln 2 for the rounding of the argument, 2^-23 for the exponential and 2^-24
+    for each of at most eleven additions behind the large term, together 9.4e-7 of the sum.  Arguments of 32
+    to 64, as a reference left at the first keys gives, are rounded to 1.3e-6 alone.  The statistics lie in the
+    workspace before the votes, the pooled scores' codes and the survivors (each padded to 256 bytes)."""
+    B, Hkv, P, budget = 8, 8, 4500, 100
+    heads, rows = B * Hkv, Gq * W
+    rows_pad = 128 if rows <= 128 else 256
+    print(f"case late key {key} Gq={Gq} W={W}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q = torch.zeros(B, Hkv * Gq, W, 128, dtype=torch.float16, device="cuda")
+    q[..., 0] = (0.5 + 0.5 * torch.rand(B, Hkv * Gq, W, generator=gen, device="cuda")).half()
+    k = torch.zeros(B, Hkv, P + W, 128, dtype=torch.float16, device="cuda")
+    k[:, :, 8 * 64 + 51, 0] = key
+    cfg = kvqp.Cfg(batch=B, n_q_heads=Hkv * Gq, n_kv_heads=Hkv, seq_len=P + W, window=W, pool_kernel=1, budget=budget, bits=16, sm_scale=1.0)
+    ws = kvqp.alloc_workspace(kvqp.workspace_bytes(cfg)[0])
+    kvqp.compress(cfg, q, k, torch.zeros_like(k), kvqp.alloc_cache(cfg), workspace=ws)
+    torch.cuda.synchronize()
+
+    def padded(n):
+        return -(-n // 256) * 256
+    at = kvqp.workspace_bytes(cfg)[0] - sum(padded(heads * n) for n in (budget * 4, -(-P // 8) * 16, P * 4, rows_pad * 16))
+    host = ws.cpu().numpy()
+    stats = host[at:at + heads * rows_pad * 8].view(np.float32).reshape(heads, rows_pad, 2)[:, :rows].astype(np.float64)
+    zsum = host[at + heads * rows_pad * 8:at + heads * rows_pad * 16].view(np.float64).reshape(heads, rows_pad)[:, :rows]
+    arg = q[..., 0].cpu().numpy().astype(np.float64).reshape(heads, rows) * key * np.float64(np.float32(np.log2(np.e)))
+    others = P + np.arange(rows) % W                                             # visible keys of score 0
+    assert np.ptp(arg) > 0.4 * key
+    err = zsum / (others[None] * np.exp2(-stats[..., 0]) + np.exp2(arg - stats[..., 0])) - 1
+    worst = np.abs(err).max()
+    print(f"worst {worst:.2e} rms {np.sqrt((err ** 2).mean()):.2e}", flush=True)
+    assert worst < 9.4e-7
+    assert np.allclose(stats[..., 1] * zsum, 1, rtol=1.2e-7)

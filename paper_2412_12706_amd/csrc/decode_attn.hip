@@ -27,6 +27,7 @@
 // and writes the output itself; otherwise a head is split over several
 // workgroups whose partial (m, l, O) go to the workspace, and the last one to
 // arrive merges them (no second kernel).
+#include <algorithm>
 #include <cmath>
 #include <initializer_list>
 #include <mutex>
@@ -1481,23 +1482,47 @@ size_t decode_ws_bound(const kvqp_cfg& cfg) {
     return kCounterBytes + (size_t)heads * splits * gq * kPartFloats * sizeof(float);
 }
 
-// Microseconds of a launch of `splits` workgroups of nw waves per head (equal heads), as measured over
-// 3100 shapes (4 to 512 heads of 290 to 20000 tokens, all bit widths, 2 to 8 query heads, every
+// Microseconds of a launch of some number of workgroups of nw waves per head (equal heads), as measured
+// over 3100 shapes (4 to 512 heads of 290 to 20000 tokens, all bit widths, 2 to 8 query heads, every
 // workgroup size and split count: rms error 9 %).  A launch pays a start, and again for every round of
 // workgroups that the chip cannot hold at once; what streams in between is bounded by the waves'
 // own time per 64-token chunk (longer with more waves on a SIMD, longer with eight query heads), by the
 // chip's memory rate, and by the rate of the CU that gets most of the bytes, whichever dominates;
 // split heads pay for the merge of their partials.
-static float predicted_us(int heads, int gq, int bits, int n_chunks, float mbytes, int n_cu, int max_nw, int nw, int splits) {
-    const int chunks = (n_chunks + splits - 1) / splits, wgs = heads * ((n_chunks + chunks - 1) / chunks);
-    const int per_cu = max_nw / nw, rounds = (wgs + n_cu * per_cu - 1) / (n_cu * per_cu), deep = (wgs + n_cu - 1) / n_cu;
-    const float simd_waves = 0.25f * nw * (deep < per_cu ? deep : per_cu);
-    const float chunk_us = bits == 2 ? 1.31f + 0.27f * simd_waves : bits == 4 ? 1.40f + 0.10f * simd_waves : bits == 8 ? 1.48f + 0.21f * simd_waves : 0.0f;
-    const float waves_us = rounds * ((chunks + nw - 1) / nw) * chunk_us * (gq == 8 ? 1.47f : 1.0f);
-    const float chip_us = mbytes * (1.0f / 7.15f);
-    const float cu_us = mbytes * deep * n_cu / wgs * (1.0f / (7.15f * 1.44f));
-    const float merge_us = wgs > heads ? 0.85f + 0.02f * (wgs / heads) * gq : 0.0f;
-    return 2.4f + 4.99f * rounds + std::sqrt(waves_us * waves_us + chip_us * chip_us + cu_us * cu_us) + merge_us;
+namespace {
+struct LaunchPrice {
+    int heads, n_chunks, n_cu, max_nw;
+    float merge_per_split, chunk_base, chunk_wave, chip_us;
+    // what the number of splits fixes, whatever the workgroup size
+    int chunks = 1, wgs = 1, deep = 1;
+    float cu_us = 0.0f, merge_us = 0.0f;
+    LaunchPrice(int heads_, int gq, int bits, int n_chunks_, float mbytes, int n_cu_, int max_nw_)
+        : heads(heads_), n_chunks(n_chunks_), n_cu(n_cu_), max_nw(max_nw_) {
+        const float slow = gq == 8 ? 1.47f : 1.0f;
+        merge_per_split = 0.02f * gq;
+        chunk_base = slow * (bits == 2 ? 1.31f : bits == 4 ? 1.40f : bits == 8 ? 1.48f : 0.0f);
+        chunk_wave = slow * (bits == 2 ? 0.27f : bits == 4 ? 0.10f : bits == 8 ? 0.21f : 0.0f);
+        chip_us = mbytes * (1.0f / 7.15f);
+    }
+    void set_splits(int splits) {
+        chunks = (n_chunks + splits - 1) / splits;
+        const int cut = (n_chunks + chunks - 1) / chunks;
+        wgs = heads * cut;
+        deep = (wgs + n_cu - 1) / n_cu;
+        cu_us = chip_us * (float)(deep * n_cu) / ((float)wgs * 1.44f);
+        merge_us = cut > 1 ? 0.85f + merge_per_split * cut : 0.0f;
+    }
+    float launch_us(int rounds, float waves_us, float busiest_cu_us) const {
+        return 2.4f + 4.99f * rounds + std::sqrt(waves_us * waves_us + chip_us * chip_us + busiest_cu_us * busiest_cu_us) + merge_us;
+    }
+    float us(int nw) const {
+        const int per_cu = max_nw / nw, rounds = (wgs + n_cu * per_cu - 1) / (n_cu * per_cu);
+        return launch_us(rounds, (float)(rounds * ((chunks + nw - 1) / nw)) * (chunk_base + chunk_wave * (0.25f * nw * std::min(deep, per_cu))), cu_us);
+    }
+    // no workgroup size takes less with this number of splits; nor with this or any larger number
+    float at_least() const { return launch_us(1, (float)((chunks + max_nw - 1) / max_nw) * (chunk_base + chunk_wave), cu_us); }
+    float at_least_from_here() const { return launch_us(1, chunk_base + chunk_wave, chip_us * (1.0f / 1.44f)); }
+};
 }
 
 DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept, int tail_len) {
@@ -1541,18 +1566,26 @@ DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept, int tail_len) {
             // heads 61.9 against 47.5 with two four-wave workgroups each; 96 heads of 3000 tokens 26.5 against
             // 18.8.  So the other shapes are priced too and taken where they promise 4 % or more: over 250
             // shapes that the prices were not fitted to, calls take 7.6 % less time on average, 1 % of them
-            // 3 to 5 % more.  Bounds: the workspace of decode_ws_bound, and the library's own array.
+            // 3 to 5 % more; of forms that the fit does not have (one query head per KV head, outlier caches)
+            // and of 16 bits and groups of 64 and 128, 140 shapes where the two differ take 17 % less, none
+            // more than 1.6 % more.  Bounds: the workspace of decode_ws_bound, and the library's own array.
+            // (Numbers of splits that no workgroup size can make good are passed over, most of them for a small
+            // call: 435 -> 87 ns of the host per call for 8 heads of 1024 tokens, 480 -> 212 for 8192.)
             const int share = (n_cu * max_nw) / heads, most = (share + kWaves - 1) / kWaves;
             const size_t head_part = (size_t)heads * gq * kPartFloats * sizeof(float);
             const float mbytes = 1e-6f * heads * (float)n_kept * (cfg.bits == 16 ? 512.0f : 2.0f * (16 * cfg.bits + 512 / cfg.group_size) + (outliers_on(cfg) ? 32.0f : 0.0f));
             plain_splits = splits; plain_nw = nw;
-            auto price = [&](int w, int s) { return predicted_us(heads, gq, cfg.bits, n_chunks, mbytes, n_cu, max_nw, w, s); };
             if (n_chunks > 0) {
-                float best = 0.96f * price(nw, splits);
+                LaunchPrice price(heads, gq, cfg.bits, n_chunks, mbytes, n_cu, max_nw);
+                price.set_splits(splits);
+                float best = 0.96f * price.us(nw);
                 for (const int s : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32}) {
                     if (s > n_chunks || s > most || (s > 1 && decode_ws_header_bytes(cfg) + s * head_part > kStaticScratchBytes)) break;
+                    price.set_splits(s);
+                    if (price.at_least_from_here() >= best) break;
+                    if (price.at_least() >= best) continue;
                     for (int w = kWaves; w <= max_nw; w += kWaves) {
-                        const float us = price(w, s);
+                        const float us = price.us(w);
                         if (us < best) { best = us; nw = w; splits = s; }
                     }
                 }

@@ -1,6 +1,7 @@
 """Launch plans of the decode kernel (token-axis splits of Eq. (3)) and where their partial results
 lie in a workspace, from the library's own planning code; no GPU needed."""
 import os
+import random
 import shutil
 import subprocess
 
@@ -68,3 +69,53 @@ def test_smaller_workspaces_than_stated_are_taken_and_not_overrun(plans, hq, hkv
         assert taken and [p["accepted"] for p in rows] == sorted(p["accepted"] for p in rows)
         for ws, p in taken:
             assert p["part_bytes"] == 0 or (p["part_off"] >= p["counters"] and p["part_off"] + p["part_bytes"] <= ws), (b, ws, p)
+
+
+def price(heads, gq, bits, group, outliers, n, waves, splits):
+    """Predicted microseconds of a launch, in 64 bits, and the number of splits it comes to."""
+    max_waves, n_cu = (12 if bits <= 4 and gq <= 4 and not outliers else 8), 256
+    n_chunks = -(-n // 64)
+    chunks = -(-n_chunks // splits)
+    cut = -(-n_chunks // chunks)
+    wgs, per_cu = heads * cut, max_waves // waves
+    rounds, deep = -(-wgs // (n_cu * per_cu)), -(-wgs // n_cu)
+    simd = 0.25 * waves * min(deep, per_cu)
+    chunk = {2: 1.31 + 0.27 * simd, 4: 1.40 + 0.10 * simd, 8: 1.48 + 0.21 * simd, 16: 0.0}[bits]
+    token = 512 if bits == 16 else 2 * (16 * bits + 512 // group) + (32 if outliers else 0)
+    chip = heads * n * token * 1e-6 / 7.15
+    streams = (rounds * -(-chunks // waves) * chunk * (1.47 if gq == 8 else 1)) ** 2 + chip ** 2 + (chip * deep * n_cu / wgs / 1.44) ** 2
+    return 2.4 + 4.99 * rounds + streams ** 0.5 + (0.85 + 0.02 * cut * gq if cut > 1 else 0), cut
+
+
+def test_the_search_passes_over_no_better_launch_shape(plans):
+    """The planner's search, which leaves out numbers of splits that cannot win, against all pairs."""
+    rng = random.Random(17)
+    problems = []
+    for _ in range(4000):
+        bits = rng.choice([2, 4, 8, 16])
+        problems.append((rng.randint(1, 80), rng.choice([1, 2, 4, 8]), rng.choice([1, 4, 8]), int(2 ** rng.uniform(0, 17)), bits,
+                         rng.choice([32, 64, 128]), rng.choice([0, 0, 1]) if bits < 16 else 0))
+    rows = plans([(b, hkv * gq, hkv, n, bits, g, o, 0, 0) for b, gq, hkv, n, bits, g, o in problems])
+    other = 0
+    for (b, gq, hkv, n, bits, g, o), row in zip(problems, rows):
+        heads, max_waves, n_chunks = b * hkv, (12 if bits <= 4 and gq <= 4 and not o else 8), -(-n // 64)
+        share = 256 * max_waves // heads
+        waves = min(share, n_chunks)                                         # the plain rule
+        if waves <= max_waves:
+            plain = (max(4, waves // 4 * 4), 1)
+        else:
+            nw = max(4, min(max_waves, max(waves * heads // 256 // 4 * 4, -(-(-(-waves // 16)) // 4) * 4)))
+            plain = (nw, -(-waves // nw))
+        part = heads * gq * 1024                                             # bytes of a split's partials
+        choice = [price(heads, gq, bits, g, o, n, w, s) for s in (1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32)
+                  if s <= n_chunks and s <= -(-share // 4) and (s == 1 or row["counters"] + s * part <= 8 << 20)
+                  for w in range(4, max_waves + 1, 4)]
+        here = price(heads, gq, bits, g, o, n, row["waves"], row["splits"])[0]
+        best = min([p for p, _ in choice], default=1e9)
+        was, cut = price(heads, gq, bits, g, o, n, *plain)
+        if best < 0.96 * was * (1 - 1e-5):
+            other += 1
+            assert here <= best * (1 + 1e-5), (b, gq, hkv, n, bits, g, o, row)
+        elif best > 0.96 * was * (1 + 1e-5):
+            assert (row["waves"], row["splits"]) == (plain[0], cut), (b, gq, hkv, n, bits, g, o, row)
+    assert other > 800

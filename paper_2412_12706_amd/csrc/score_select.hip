@@ -527,8 +527,9 @@ constexpr float kBandRel = 2.0e-5f;   // >> the binary32 error of a vote (a few 
 
 struct SelectArgs {
     const float* vote;      // [heads, P]
-    uint16_t* code;         // [heads, p_stride] codes of the pooled scores; candidate j at code_at(j)
+    uint16_t* code;         // [heads, p_stride] codes of the pooled scores, in groups of eight (codes_above)
     uint16_t* bins;         // [heads, n_seg, kBins] counts of every pooling workgroup
+    float* exact;           // [heads, p_stride] pooled scores, only where the candidates around the cut don't fit the list
     int32_t* idx;           // [heads, n_kept]
     int32_t* unrefined;     // [heads] or NULL: candidates near the cut that binary32 decided (0: all re-scored)
     const int32_t* head_n;  // a head's own cut (<= n_kept), or NULL for n_kept everywhere
@@ -550,7 +551,6 @@ __device__ __forceinline__ int score_bin(uint32_t key) { return min(max((int)(ke
 
 // Eight consecutive candidates share 16 bytes, candidates q and q + 4 the 32-bit word q (so that a
 // comparison of both halves of the four words yields their mask byte in order).
-__device__ __forceinline__ int code_at(int j) { return (j & ~7) | ((j & 3) << 1) | ((j >> 2) & 1); }
 typedef unsigned short us2v __attribute__((ext_vector_type(2)));
 // mask byte: bit i set where the code of candidate i exceeds t
 __device__ __forceinline__ uint32_t codes_above(const uint4& w4, uint32_t t) {
@@ -732,14 +732,15 @@ __global__ __launch_bounds__(kSelThreads) void pool_scores(const SelectArgs a) {
 template <bool ONE>
 __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     __shared__ __align__(16) uint32_t keep[(ONE ? kPoolTile : kMaxPrefix) / 32];
-    __shared__ __align__(16) int tab[2 * kSelThreads];            // the band
-    __shared__ int hist[1 << kDigit];                             // radix digits; later the positions to re-score
-    __shared__ __align__(16) unsigned char big[kListCap * 8];     // candidates around the cut; before that the pooling stage and the bins (ONE); later the binary64 votes, or the mask of the ties
+    __shared__ __align__(16) int tab[2 * kSelThreads + (1 << kDigit)];   // the band, then:
+    int* hist = tab + 2 * kSelThreads;                            // radix digits; later the positions to re-score
+    uint32_t* ties = reinterpret_cast<uint32_t*>(tab);            // where binary32 decides: the mask of the candidates equal to the cut
+    __shared__ __align__(16) unsigned char big[kListCap * 8];     // candidates around the cut, or (too many) the pooling stage; before that the pooling stage and the bins (ONE); later the binary64 votes
     __shared__ int swave[kSelWaves];
     __shared__ int s_bin, s_list, s_sure, s_need, s_band, s_hot;
     __shared__ uint32_t s_prefix;
     static_assert(kListCap * 8 >= kStage * 4 && kListCap * 8 >= kBins * 4 && kListCap * 8 >= (kPartSlots + kVoteSlots) * 8 &&
-                  kListCap * 8 >= kMaxPrefix / 8 && kVoteSlots <= (1 << kDigit), "aliases fit");
+                  sizeof(tab) >= kMaxPrefix / 8 && kVoteSlots <= (1 << kDigit), "aliases fit");
 
     const int head = blockIdx.x;
     const int P = a.P, k = a.head_n ? a.head_n[head] : a.n_kept;
@@ -873,20 +874,49 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
         if (n_list <= kListCap)
             for (int e = threadIdx.x; e < n_list; e += kSelThreads) list_key[e] = pooled_key(list_pos[e]);   // (read back by the same thread only)
     }
+    // Where the list is too short (thousands of scores within two percent of the cut), the whole prefix is
+    // pooled once more, tile by tile, into memory; a thread reads back only what it has stored itself.
+    // (Whole calls with 8 heads, pool 7: all keys alike, 32736 / 131008 candidates, 134 / 412 us, where
+    // pooling every candidate by itself on every visit took 214 / 726; scores spread evenly over 0.1 %,
+    // 132 / 406 against 184 / 613.)
+    float* exact = a.exact + (size_t)head * a.p_stride;
+    if constexpr (!ONE) {
+        if (__builtin_expect(n_list > kListCap, 0)) {
+            float* stage = reinterpret_cast<float*>(big);
+            VoteTile next = fetch_votes(vote, P, r, 0);
+            for (int j0 = 0; j0 < P; j0 += kPoolTile) {
+                __syncthreads();
+                stage_votes(next, stage);
+                __syncthreads();
+                if (j0 + kPoolTile < P) next = fetch_votes(vote, P, r, j0 + kPoolTile);
+                const float4 o = pool_four(stage, r);
+                if (j0 + 4 * (int)threadIdx.x < P) *reinterpret_cast<float4*>(exact + j0 + 4 * threadIdx.x) = o;
+            }
+        }
+    }
     // every candidate around the cut: from the thread's own scores (ONE), from the list (in no
-    // particular order), or, where the list is too short (thousands of scores within two percent of
-    // the cut), from the codes
+    // particular order) or from all pooled scores
     auto each_around = [&](auto visit) {
         if constexpr (ONE) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 if (own[i] >= klo && own[i] <= khi) visit(own[i], 4 * (int)threadIdx.x + i);
-        } else if (n_list <= kListCap) {
+        } else if (__builtin_expect(n_list <= kListCap, 1)) {
             for (int e = threadIdx.x; e < n_list; e += kSelThreads) visit(list_key[e], list_pos[e]);
         } else {
-            for (int j = threadIdx.x; j < P; j += kSelThreads) {
-                const uint32_t cd = code[code_at(j)];
-                if (cd >= clo && cd <= chi) visit(pooled_key(j), j);
+            const int last = (P - 1) & ~3;
+            int j = 4 * (int)threadIdx.x;
+            float4 next = *reinterpret_cast<const float4*>(exact + min(j, last));
+#pragma unroll 1
+            for (; j < P; j += kPoolTile) {
+                float4 o = next;
+                next = *reinterpret_cast<const float4*>(exact + min(j + kPoolTile, last));
+#pragma unroll 1
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t key = score_key(o.x);
+                    if (j + i < P && key >= klo && key <= khi) visit(key, j + i);
+                    o.x = o.y; o.y = o.z; o.z = o.w;
+                }
             }
         }
     };
@@ -897,7 +927,7 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     // more for 200); more go through a radix select on the patterns relative to klo ----
     uint32_t prefix = 0u;
     int need = need_around;
-    if (n_list <= kRankMax) {
+    if (__builtin_expect(n_list <= kRankMax, 1)) {
         if (threadIdx.x < 4) list_key[n_list + threadIdx.x] = 0u;       // (whole 16-byte pieces; 0 is above no candidate)
         for (int e = threadIdx.x; e < n_list; e += kSelThreads) hist[e] = 0;
         __syncthreads();
@@ -930,8 +960,12 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
             __syncthreads();
             each_around([&](uint32_t key, int) {
                 const uint32_t rel = key - klo;
-                if (fixed >= 32 || (rel >> fixed) == (prefix >> fixed))
-                    atomicAdd(&hist[(rel >> shift) & ((1u << (fixed - shift)) - 1u)], 1);
+                if (fixed >= 32 || (rel >> fixed) == (prefix >> fixed)) {
+                    const int digit = (int)((rel >> shift) & ((1u << (fixed - shift)) - 1u)), some = __builtin_amdgcn_readfirstlane(digit);
+                    const unsigned long long alike = __builtin_amdgcn_ballot_w64(digit == some);     // (ties: one of the lanes counts them all)
+                    if (digit != some) atomicAdd(&hist[digit], 1);
+                    else if (lane == __builtin_ctzll(alike)) atomicAdd(&hist[some], __popcll(alike));
+                }
             });
             __syncthreads();
             const int c0 = hist[2 * threadIdx.x], c1 = hist[2 * threadIdx.x + 1];
@@ -1003,7 +1037,7 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
         n_hot = __builtin_amdgcn_readfirstlane(s_hot);
         refine = n_hot <= kVoteSlots;
     }
-    if (refine) {
+    if (__builtin_expect(refine, 1)) {
         if (n_hot > 1) {
             // ---- binary64 re-scoring: one wave per (position, 32 window rows); the parts of a position are
             // summed in ascending order.  Positions go in batches that fit the parts. ----
@@ -1047,19 +1081,13 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     } else {
         // binary32 decides: everything above the cut, then the first need_at_cut equal to it
         if (a.unrefined && threadIdx.x == 0) a.unrefined[head] = tot_band;
-        uint32_t* ties = reinterpret_cast<uint32_t*>(big);      // mask of the candidates equal to the cut
         const int n_words = (P + 31) / 32;
-        each_around([&](uint32_t key, int j) { if (key > cut_key) set_keep(j); });
-        __syncthreads();                                        // (the list is read to its end before its place is taken)
-        // (candidates are pooled again here: the list may not hold them all, and its place is needed)
         for (int i = threadIdx.x; i < n_words; i += kSelThreads) ties[i] = 0u;
         __syncthreads();
-        if constexpr (ONE) {
-            each_around([&](uint32_t key, int j) { if (key == cut_key) atomicOr(&ties[j >> 5], 1u << (j & 31)); });
-        } else {
-            for (int j = threadIdx.x; j < P; j += kSelThreads)
-                if (code[code_at(j)] == (cut_key >> kCodeShift) && pooled_key(j) == cut_key) atomicOr(&ties[j >> 5], 1u << (j & 31));
-        }
+        each_around([&](uint32_t key, int j) {
+            if (key > cut_key) set_keep(j);
+            else if (key == cut_key) atomicOr(&ties[j >> 5], 1u << (j & 31));
+        });
         __syncthreads();
         const int per = (n_words + kSelThreads - 1) / kSelThreads;   // mask words of a thread, in position order
         int mine = 0;
@@ -1174,6 +1202,7 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
     const size_t part_bytes = (size_t)heads * n_parts * rows_pad * sizeof(float2);
     const size_t bins_bytes = tiles > 1 ? (size_t)heads * p.n_seg * kBins * sizeof(uint16_t) : 0;
     p.off_stats_part = off; off = align_up(off + (part_bytes > bins_bytes ? part_bytes : bins_bytes), 256);
+    p.off_exact = off;      off = align_up(off + (tiles > 1 ? (size_t)heads * p.p_stride * sizeof(float) : 0), 256);
     p.off_stats = off;      off = align_up(off + (size_t)heads * rows_pad * (sizeof(float2) + sizeof(double)), 256);
     p.off_vote = off;       off = align_up(off + (size_t)heads * (p.P > 0 ? p.P : 1) * sizeof(float), 256);
     p.off_pooled = off;     off = align_up(off + (size_t)heads * p.p_stride * sizeof(uint16_t), 256);
@@ -1218,6 +1247,7 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
     s.gq = a.gq; s.n_q_heads = cfg.n_q_heads; s.n_kv_heads = cfg.n_kv_heads; s.rows = a.rows; s.rows_pad = a.rows_pad;
     s.scale_log2 = a.scale_log2; s.sm_scale = cfg.sm_scale;
     s.bins = reinterpret_cast<uint16_t*>(base + plan.off_stats_part);
+    s.exact = reinterpret_cast<float*>(base + plan.off_exact);
     s.p_stride = plan.p_stride; s.n_seg = plan.n_seg; s.seg_tiles = plan.seg_tiles;
     if (plan.P <= kPoolTile) {
         hipLaunchKernelGGL(select_topk<true>, dim3(heads), dim3(kSelThreads), 0, stream, s);

@@ -173,3 +173,25 @@ def test_row_sums_keep_their_precision_when_a_late_key_dominates(Gq, W, key):
     print(f"worst {worst:.2e} rms {np.sqrt((err ** 2).mean()):.2e}", flush=True)
     assert worst < 9.4e-7
     assert np.allclose(stats[..., 1] * zsum, 1, rtol=1.2e-7)
+
+
+@pytest.mark.parametrize("P,pool,budget,noise", [(12301, 63, 5000, 0.0), (8192, 5, 8191, 0.0), (40003, 13, 9000, 0.0), (13001, 31, 4000, 0.003),
+                                                 (20481, 1, 12000, 0.002)])
+def test_more_candidates_around_the_cut_than_the_list_holds_under_wide_windows(orc, P, pool, budget, noise):
+    """Prompts whose keys are alike (or nearly): the candidates around the cut are visited by pooling the
+    prefix once more, tile by tile, and their windows reach across the tiles' edges."""
+    print(f"case alike P={P} pool={pool} budget={budget} noise={noise}", flush=True)
+
+    def keys(k):
+        base = k[:, :, :1].astype(np.float32)
+        k[:, :, :P] = (base + noise * k[:, :, :P].astype(np.float32)).astype(np.float16)
+    got, idx, pooled, unrefined = select(orc, P, 8, pool, budget, outlier=1.0, keys=keys, seed=83)
+    if noise == 0.0:
+        assert np.array_equal(got[0], np.tile(np.arange(budget), (2, 1))) and unrefined == [P, P]
+    else:
+        for g in range(2):
+            kth = np.sort(pooled[0, g])[-budget]
+            assert (np.abs(pooled[0, g] / kth - 1) < 0.004).sum() > 3840
+            assert unrefined[g] == 0 or unrefined[g] > 512
+        if unrefined == [0, 0]:
+            check_indices(got, idx, pooled)

@@ -226,7 +226,7 @@ struct DecodeArgs {
     const uint16_t* v_zero;
     const uint16_t* tail_k;
     const uint16_t* tail_v;
-    float* part;              // [B*Hkv, n_partials, GQ, D+2]
+    float* part;              // [B*Hkv, n_splits, GQ, 2 D]
     unsigned int* arrivals;   // [B*Hkv] arrival counters at the head of the workspace, zero between launches
     uint16_t* out;            // [B, Hq, D]
     int n_kept, tail_len, tail_cap;
@@ -238,7 +238,7 @@ struct DecodeArgs {
     const uint32_t* v_ovf;
     int ovf_cap;                  // entries of a head's overflow list
     int n_q_heads, n_kv_heads;
-    int n_splits, chunks_per_split, n_partials;
+    int n_splits, chunks_per_split;
     int n_waves;              // waves per workgroup of the pipelined kernel
     int group;                // G
     int stream_from;          // chunks from this one on are loaded with the non-temporal hint
@@ -318,8 +318,8 @@ __device__ void merge_if_last(const DecodeArgs& a, int bh, int n_parts) {
     __syncthreads();
     if (!s_last) return;
     const int b = bh / a.n_kv_heads, g = bh % a.n_kv_heads;
-    const unsigned head_bytes = (unsigned)a.n_partials * GQ * kPartFloats * 4u;
-    const __amdgpu_buffer_rsrc_t rs = part_rsrc(a.part + (size_t)bh * a.n_partials * GQ * kPartFloats, head_bytes);
+    const unsigned head_bytes = (unsigned)a.n_splits * GQ * kPartFloats * 4u;
+    const __amdgpu_buffer_rsrc_t rs = part_rsrc(a.part + (size_t)bh * a.n_splits * GQ * kPartFloats, head_bytes);
     // Device-scope loads are slow (they go to the coherence point), so a whole batch of partials is
     // put in flight per round trip: one 16-byte load per partial and thread, a thread owning one
     // pair of output channels.
@@ -1346,7 +1346,7 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
     // the waves' states and this workgroup's share of the full-precision tail rows (the first four
     // waves' states in sT), then one pass that weighs and adds them.  All threads of a head read the
     // same references and sums (LDS broadcasts); nw is a multiple of 4.
-    const __amdgpu_buffer_rsrc_t part_rs = part_rsrc(a.part + (size_t)bh * a.n_partials * GQ * kPartFloats, (unsigned)a.n_partials * GQ * kPartFloats * 4u);
+    const __amdgpu_buffer_rsrc_t part_rs = part_rsrc(a.part + (size_t)bh * a.n_splits * GQ * kPartFloats, (unsigned)a.n_splits * GQ * kPartFloats * 4u);
     for (int item = threadIdx.x; item < GQ * kPartPairs; item += blockDim.x) {
         const int hh = item / kPartPairs, d = 2 * (item % kPartPairs);
         const int cg = d / G;
@@ -1413,7 +1413,7 @@ static int stream_from_chunk(const kvqp_cfg& cfg, int n_kept) {
 
 template <int BITS, int GQ, int NCG>
 hipError_t launch_axis(const kvqp_cfg& cfg, const DecodeArgs& a, hipStream_t stream) {
-    const dim3 grid(a.n_partials, cfg.batch * cfg.n_kv_heads);
+    const dim3 grid(a.n_splits, cfg.batch * cfg.n_kv_heads);
     const bool out = BITS != 16 && a.k_out != nullptr;
     const bool token_keys = BITS != 16 && cfg.key_axis == KVQP_KEY_PER_TOKEN;
     const unsigned lds_bytes = (out ? pipe_lds_bytes(a.n_waves, PipeGeom<BITS, NCG, true>::STRIP, GQ, true)
@@ -1525,8 +1525,7 @@ struct LaunchPrice {
 };
 }
 
-DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept, int tail_len) {
-    (void)tail_len;
+DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept) {
     DecodePlan p;
     const int heads = cfg.batch * cfg.n_kv_heads;
     const int n_chunks = (n_kept + kChunk - 1) / kChunk;
@@ -1600,7 +1599,6 @@ DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept, int tail_len) {
         if (splits < 1) splits = 1;
         p.n_waves = nw;
         cut(splits, p.chunks_per_split, p.n_splits, p.part_bytes);
-        p.n_partials = p.n_splits;
         p.ws_bytes = decode_ws_header_bytes(cfg) + p.part_bytes;
         if (plain_splits) {
             cut(plain_splits, p.alt_chunks, p.alt_splits, p.alt_part_bytes);
@@ -1671,7 +1669,7 @@ hipError_t launch_decode(const kvqp_cfg& cfg, const void* q, const kvqp_cache& c
     a.v_ovf = outliers_on(cfg) ? (const uint32_t*)c.v_ovf : nullptr;
     a.ovf_cap = cfg.outlier_overflow_cap;
     a.n_q_heads = cfg.n_q_heads; a.n_kv_heads = cfg.n_kv_heads;
-    a.n_splits = plan.n_splits; a.chunks_per_split = plan.chunks_per_split; a.n_partials = plan.n_partials;
+    a.n_splits = plan.n_splits; a.chunks_per_split = plan.chunks_per_split;
     a.n_waves = plan.n_waves;
     a.group = cfg.group_size; a.sm_scale = cfg.sm_scale;
     a.stream_from = stream_from_chunk(cfg, c.n_kept);

@@ -299,7 +299,7 @@ static int check_decode(const kvqp_cfg* cfg, const void* q, const kvqp_cache* ca
     if (cache->head_n_kept && cache->tail_len < 1) return KVQP_ERR_INVALID_ARG;   // a head may hold no packed token at all
     if ((rc = check_n_kept(cfg, cache->n_kept))) return rc;
     if ((rc = check_cache_ptrs(cfg, cache, cache->n_kept, cache->tail_len > 0))) return rc;
-    *plan = plan_decode(*cfg, cache->n_kept, cache->tail_len);
+    *plan = plan_decode(*cfg, cache->n_kept);
     // (the other plan's price is that of equal heads; where their counts differ, and the host does not
     // know them, it came out slower on one shape in eight, by up to 20 %)
     if (cache->head_n_kept) plan->take_plain();

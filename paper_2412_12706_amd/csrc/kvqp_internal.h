@@ -54,7 +54,6 @@ constexpr size_t kCounterBytes = 65536 * sizeof(unsigned int);
 struct DecodePlan {
     int n_splits;        // token-axis splits of the packed part
     int chunks_per_split;// 64-token chunks handled by one workgroup
-    int n_partials;      // n_splits (+1 when a tail partial is written)
     int n_waves;         // waves per decode workgroup
     size_t ws_bytes;         // counters and partials
     size_t part_bytes = 0;   // the partials alone
@@ -67,7 +66,7 @@ struct DecodePlan {
     void take_plain() {
         if (!alt_waves) return;
         ws_bytes = least_bytes();
-        n_splits = n_partials = alt_splits; chunks_per_split = alt_chunks; n_waves = alt_waves;
+        n_splits = alt_splits; chunks_per_split = alt_chunks; n_waves = alt_waves;
         part_bytes = alt_part_bytes;
         alt_waves = 0;
     }
@@ -82,8 +81,8 @@ struct DecodePlan {
         return true;
     }
 };
-DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept, int tail_len);
-size_t decode_ws_bound(const kvqp_cfg& cfg);   // >= kCounterBytes + plan_decode(cfg, n, t).part_bytes for every n and t
+DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept);
+size_t decode_ws_bound(const kvqp_cfg& cfg);   // >= kCounterBytes + plan_decode(cfg, n).part_bytes for every n
 size_t decode_ws_header_bytes(const kvqp_cfg& cfg);   // arrival counters at the head of a decode workspace
 hipError_t launch_ws_init(const kvqp_cfg& cfg, void* ws, hipStream_t stream);   // zeroes them
 // The library's own decode workspace (a static device array): its address on the current device,

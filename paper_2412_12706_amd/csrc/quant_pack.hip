@@ -60,9 +60,8 @@ __device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
     union { uint32_t u; us2v v; } x, y, z; x.u = a; y.u = b; z.v = __builtin_elementwise_max(x.v, y.v); return z.u;
 }
 
-// binary16 bit pattern -> key that orders like the value (-0 below +0).
-__device__ __forceinline__ uint32_t order_key(uint16_t h) { return (h & 0x8000u) ? (uint16_t)~h : (uint16_t)(h | 0x8000u); }
-// the same on both halves of a word: negative halves inverted, the others with the sign bit set (two instructions)
+// binary16 bit patterns -> keys that order like the values (-0 below +0), on both halves of a word:
+// negative halves inverted, the others with the sign bit set (two instructions)
 typedef short ss2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t order_key2(uint32_t w) {
     union { uint32_t u; ss2v v; } t;
@@ -171,12 +170,6 @@ __device__ __forceinline__ void store_key_words(uint32_t* kc, uint32_t row, int 
     }
 }
 
-// all 16 lanes of a row of lanes (one token row) get the largest value among them
-__device__ __forceinline__ uint32_t row16_max(uint32_t v) {
-    v = max(v, dpp<kQuadXor1>(v)); v = max(v, dpp<kQuadXor2>(v));
-    v = max(v, dpp<kRowHalfMirror>(v)); v = max(v, dpp<kRowMirror>(v));
-    return v;
-}
 // sum over the 16 lanes of a row, in every lane; and the sum over the lanes before this one
 __device__ __forceinline__ uint32_t row16_sum(uint32_t v) {
     v += dpp<kQuadXor1>(v); v += dpp<kQuadXor2>(v); v += dpp<kRowHalfMirror>(v); v += dpp<kRowMirror>(v);

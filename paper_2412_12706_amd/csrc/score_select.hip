@@ -539,7 +539,6 @@ struct SelectArgs {
     const double* zsum;     // Z binary64
     int P, p_stride, L, W, n_kept, pool, gq, n_q_heads, n_kv_heads, rows, rows_pad;
     int n_seg, seg_tiles;   // pooling workgroups per head and their pooling tiles
-    float scale_log2;
     float sm_scale;
 };
 
@@ -1245,7 +1244,7 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
     s.q_obs = a.q_obs; s.k = a.k; s.stats = stats; s.zsum = zsum;
     s.P = plan.P; s.L = cfg.seq_len; s.W = cfg.window; s.n_kept = plan.n_kept; s.pool = cfg.pool_kernel;
     s.gq = a.gq; s.n_q_heads = cfg.n_q_heads; s.n_kv_heads = cfg.n_kv_heads; s.rows = a.rows; s.rows_pad = a.rows_pad;
-    s.scale_log2 = a.scale_log2; s.sm_scale = cfg.sm_scale;
+    s.sm_scale = cfg.sm_scale;
     s.bins = reinterpret_cast<uint16_t*>(base + plan.off_stats_part);
     s.exact = reinterpret_cast<float*>(base + plan.off_exact);
     s.p_stride = plan.p_stride; s.n_seg = plan.n_seg; s.seg_tiles = plan.seg_tiles;

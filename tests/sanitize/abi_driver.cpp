@@ -19,9 +19,9 @@ static int g_launches = 0;      // calls that would have enqueued work
 static long long g_count_sum = 0;
 
 namespace kvqp {
-DecodePlan plan_decode(const kvqp_cfg& cfg, int, int) {
+DecodePlan plan_decode(const kvqp_cfg& cfg, int) {
     DecodePlan p{};
-    p.n_splits = p.n_partials = 2;
+    p.n_splits = 2;
     p.chunks_per_split = 1;
     p.n_waves = 4;
     p.ws_bytes = decode_ws_header_bytes(cfg) + 4096;

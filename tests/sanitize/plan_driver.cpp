@@ -15,7 +15,7 @@ int main() {
         c.batch = batch; c.n_q_heads = hq; c.n_kv_heads = hkv; c.head_dim = 128; c.bits = bits; c.group_size = group;
         c.outlier_threshold = outliers ? 6.0f : 0.0f; c.decode_splits = splits; c.sm_scale = 0.088f;
         const size_t stated = kvqp::decode_ws_bound(c);
-        kvqp::DecodePlan p = kvqp::plan_decode(c, n, 32);
+        kvqp::DecodePlan p = kvqp::plan_decode(c, n);
         const bool ok = p.fit(bytes ? bytes : stated);
         std::printf("%d %d %d %zu %zu %zu %zu\n", (int)ok, p.n_splits, p.n_waves, p.part_bytes, p.part_off,
                     kvqp::decode_ws_header_bytes(c), stated);

@@ -189,8 +189,11 @@ def alloc_cache(cfg: Cfg, tail_cap: int | None = None, device="cuda", n_cap: int
 
 def _stream_ptr(stream):
     import torch
-    if stream is None:      # the handle alone: the object that torch.cuda.current_stream() makes costs 3 us a call
-        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+    if stream is None:
+        try:                # the handle alone: the object that torch.cuda.current_stream() makes costs 3 us a call
+            return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+        except AttributeError:      # (undocumented names: a torch without them takes the public way)
+            stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream)
 
 

@@ -278,3 +278,18 @@ def test_decode_workspace_init_and_static_entry_validate_on_the_host(lib):
     big = kvqp.Cfg(batch=16, n_q_heads=64, n_kv_heads=8, seq_len=4096, window=32, budget=1024, bits=4, decode_splits=16)
     assert kvqp.workspace_bytes(big)[1] > (8 << 20)
     assert lib.kvqp_decode_attn_static(C.byref(big.struct()), fake, C.byref(cs), fake, None) == -3
+
+
+@pytest.mark.parametrize("missing", [None, "_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_the_undocumented_torch_names(monkeypatch, missing):
+    """The binding asks torch for the current stream's handle by names that are not documented; a torch
+    without one of them is asked for its current stream instead."""
+    import types
+    import torch
+    for name, value in (("_cuda_getDevice", lambda: 3), ("_cuda_getCurrentRawStream", lambda device: 0x5000 + device)):
+        monkeypatch.setattr(torch._C, name, value, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x7007))
+    if missing:
+        monkeypatch.delattr(torch._C, missing)
+    assert kvqp._stream_ptr(None).value == (0x7007 if missing else 0x5003)
+    assert kvqp._stream_ptr(types.SimpleNamespace(cuda_stream=0x9009)).value == 0x9009

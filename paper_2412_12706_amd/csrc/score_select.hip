@@ -502,7 +502,7 @@ __global__ __launch_bounds__(256) void stats_combine(const float2* __restrict__ 
 // Prefixes of one pooling tile (4096) do both in the second kernel.  A single
 // workgroup per head that did everything, with a four-pass radix select over all
 // scores, took 45 / 87 / 310 us for 8 heads of 4064 / 32736 / 131008 candidates
-// and 120 us for 256 heads of 32736; these take 10 / 5 + 21 / 6.5 + 36 and 17 + 28 us.
+// and 120 us for 256 heads of 32736; these take 9 / 5 + 21 / 5 + 35 and 12 + 29 us.
 // ---------------------------------------------------------------------------
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
@@ -542,7 +542,7 @@ struct SelectArgs {
     float sm_scale;
 };
 
-// Pooling starts from 0, which no vote is below: a vote that is not a number counts as 0, so a score's pattern is 0 ..
+// Pooling ends with a maximum with 0, which no vote is below: a vote that is not a number counts as 0, so a score's pattern is 0 ..
 // 0x7f800000 whatever the inputs hold.  Its code fits 16 bits, the bins and the sweep over the codes agree, and every
 // head gets exactly as many survivors as it is to have, all of them positions of the prefix.
 __device__ __forceinline__ uint32_t score_key(float v) { return __float_as_uint(v); }  // scores are >= 0: bits order like values
@@ -662,25 +662,42 @@ __device__ __forceinline__ void stage_votes(const VoteTile& t, float* stage) {
         if (i < kStage) stage[i] = t.v[u];
     }
 }
+// Votes 3 .. 2 r of the thread's 2 r + 4 lie in all four windows; the votes before them leave the windows one by one,
+// those after them enter.  (Branches on r alone, the same for the whole launch.  256 heads of 32736 candidates, pool 7:
+// pool_scores 12 us; with every vote tested against every window 17.)
 __device__ __forceinline__ float4 pool_four(const float* stage, int r) {
     const float4* s = reinterpret_cast<const float4*>(stage) + threadIdx.x;
-    float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int q = 0; 4 * q <= 2 * r + 3; ++q) {
-        const float4 x4 = s[q];
-        const float x[4] = {x4.x, x4.y, x4.z, x4.w};
-        if (q > 0 && 4 * q + 3 <= 2 * r) {           // inside all four windows
-            const float m = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = fmaxf(o[i], m);
-        } else {
-#pragma unroll
-            for (int w = 0; w < 4; ++w)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (4 * q + w >= i && 4 * q + w <= 2 * r + i) o[i] = fmaxf(o[i], x[w]);   // (uniform)
+    const float4 a = s[0];
+    float4 o;
+    if (r >= 2) {
+        const int m = r >> 1;                          // 2 r = 4 m or 4 m + 2
+        float mid = a.w;
+        for (int q = 1; q < m; ++q) {
+            const float4 x = s[q];
+            mid = fmaxf(mid, fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w)));
         }
+        const float4 b = s[m];
+        float t0 = b.y, t1 = b.z, t2 = b.w;
+        mid = fmaxf(mid, b.x);
+        if (r & 1) {
+            const float4 c = s[m + 1];
+            mid = fmaxf(mid, fmaxf(b.y, b.z));
+            t0 = b.w; t1 = c.x; t2 = c.y;
+        }
+        o.x = fmaxf(fmaxf(a.x, a.y), fmaxf(a.z, mid));
+        o.y = fmaxf(fmaxf(a.y, a.z), fmaxf(mid, t0));
+        o.z = fmaxf(fmaxf(a.z, mid), fmaxf(t0, t1));
+        o.w = fmaxf(fmaxf(mid, t0), fmaxf(t1, t2));
+    } else if (r == 1) {
+        const float4 c = s[1];
+        o.x = fmaxf(fmaxf(a.x, a.y), a.z);
+        o.y = fmaxf(fmaxf(a.y, a.z), a.w);
+        o.z = fmaxf(fmaxf(a.z, a.w), c.x);
+        o.w = fmaxf(fmaxf(a.w, c.x), c.y);
+    } else {
+        o = a;
     }
-    return make_float4(o[0], o[1], o[2], o[3]);
+    return make_float4(fmaxf(o.x, 0.0f), fmaxf(o.y, 0.0f), fmaxf(o.z, 0.0f), fmaxf(o.w, 0.0f));
 }
 
 // Pooled scores and their bin counts; workgroup x of a head takes seg_tiles consecutive tiles.
@@ -875,9 +892,9 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     }
     // Where the list is too short (thousands of scores within two percent of the cut), the whole prefix is
     // pooled once more, tile by tile, into memory; a thread reads back only what it has stored itself.
-    // (Whole calls with 8 heads, pool 7: all keys alike, 32736 / 131008 candidates, 134 / 412 us, where
+    // (Whole calls with 8 heads, pool 7: all keys alike, 32736 / 131008 candidates, 127 / 388 us, where
     // pooling every candidate by itself on every visit took 214 / 726; scores spread evenly over 0.1 %,
-    // 132 / 406 against 184 / 613.)
+    // 125 / 379 against 184 / 613.)
     float* exact = a.exact + (size_t)head * a.p_stride;
     if constexpr (!ONE) {
         if (__builtin_expect(n_list > kListCap, 0)) {

@@ -214,7 +214,8 @@ int kvqp_outlier_sizes(const kvqp_cfg *cfg, int32_t n_cap, size_t sizes_out[4]);
 /* Workspace bytes needed by kvqp_compress and kvqp_decode_attn for this cfg
  * (either pointer may be NULL).  decode_bytes depends on batch, heads, bits,
  * decode_splits and outlier_threshold only: it serves a cache of any token
- * count, also one that kvqp_append_tail has grown.  Host only. */
+ * count, also one that kvqp_append_tail has grown.  Both have room that a call
+ * uses for its speed; somewhat smaller workspaces are taken too.  Host only. */
 int kvqp_workspace_bytes(const kvqp_cfg *cfg, size_t *compress_bytes, size_t *decode_bytes);
 
 /*

@@ -151,7 +151,10 @@ int kvqp_workspace_bytes(const kvqp_cfg* cfg, size_t* compress_bytes, size_t* de
     if ((rc = check_prompt(cfg))) return rc;
     const int n_kept = n_kept_of(cfg);
     if ((rc = check_n_kept(cfg, n_kept))) return rc;
-    if (compress_bytes) *compress_bytes = plan_compress(*cfg).total;
+    if (compress_bytes) {
+        const CompressPlan plan = plan_compress(*cfg);
+        *compress_bytes = plan.total + plan.exact_bytes;
+    }
     // decode: covers every token count, so a cache that grows by appended tokens never outgrows it
     if (decode_bytes) *decode_bytes = decode_ws_bound(*cfg);
     return KVQP_OK;
@@ -218,8 +221,9 @@ static int compress_impl(const kvqp_cfg* cfg, const void* q_obs, const void* k, 
         for (int h = 0; h < heads; ++h)
             if (head_budget[h] > 0 && head_budget[h] < cfg->seq_len - cfg->window) score = true;
     }
-    const CompressPlan plan = plan_compress(*cfg);
+    CompressPlan plan = plan_compress(*cfg);
     if (!workspace || workspace_bytes < plan.total) return KVQP_ERR_WORKSPACE;
+    if (workspace_bytes < plan.total + plan.exact_bytes) plan.exact_bytes = 0;   // (slower on some prompts)
     if (((uintptr_t)workspace & 15) != 0) return KVQP_ERR_INVALID_ARG;
     hipStream_t stream = (hipStream_t)hip_stream;
     int32_t* idx = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + plan.off_idx);

@@ -99,7 +99,8 @@ struct CompressPlan {
     int n_parts;                  // row statistics per kv head that the first scoring pass leaves
     int n_seg, seg_tiles;         // pooling workgroups per kv head and their share in pooling tiles
     int p_stride;                 // score codes of a head, padded to whole 16-byte pieces
-    size_t off_stats_part, off_exact, off_stats, off_vote, off_pooled, off_idx, total;
+    size_t off_stats_part, off_stats, off_vote, off_pooled, off_idx, total;
+    size_t exact_bytes;           // further room, behind `total`, that a call uses for its speed where it is there
 };
 CompressPlan plan_compress(const kvqp_cfg& cfg);
 

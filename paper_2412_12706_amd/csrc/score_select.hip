@@ -529,7 +529,7 @@ struct SelectArgs {
     const float* vote;      // [heads, P]
     uint16_t* code;         // [heads, p_stride] codes of the pooled scores, in groups of eight (codes_above)
     uint16_t* bins;         // [heads, n_seg, kBins] counts of every pooling workgroup
-    float* exact;           // [heads, p_stride] pooled scores, only where the candidates around the cut don't fit the list
+    float* exact;           // [heads, p_stride] pooled scores, only where the candidates around the cut don't fit the list; or NULL
     int32_t* idx;           // [heads, n_kept]
     int32_t* unrefined;     // [heads] or NULL: candidates near the cut that binary32 decided (0: all re-scored)
     const int32_t* head_n;  // a head's own cut (<= n_kept), or NULL for n_kept everywhere
@@ -891,13 +891,14 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
             for (int e = threadIdx.x; e < n_list; e += kSelThreads) list_key[e] = pooled_key(list_pos[e]);   // (read back by the same thread only)
     }
     // Where the list is too short (thousands of scores within two percent of the cut), the whole prefix is
-    // pooled once more, tile by tile, into memory; a thread reads back only what it has stored itself.
+    // pooled once more, tile by tile, into memory; a thread reads back only what it has stored itself.  (In a
+    // workspace without that room every visit pools every candidate.)
     // (Whole calls with 8 heads, pool 7: all keys alike, 32736 / 131008 candidates, 127 / 388 us, where
     // pooling every candidate by itself on every visit took 214 / 726; scores spread evenly over 0.1 %,
     // 125 / 379 against 184 / 613.)
-    float* exact = a.exact + (size_t)head * a.p_stride;
+    float* exact = a.exact ? a.exact + (size_t)head * a.p_stride : nullptr;
     if constexpr (!ONE) {
-        if (__builtin_expect(n_list > kListCap, 0)) {
+        if (__builtin_expect(n_list > kListCap && exact, 0)) {
             float* stage = reinterpret_cast<float*>(big);
             VoteTile next = fetch_votes(vote, P, r, 0);
             for (int j0 = 0; j0 < P; j0 += kPoolTile) {
@@ -919,6 +920,11 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
                 if (own[i] >= klo && own[i] <= khi) visit(own[i], 4 * (int)threadIdx.x + i);
         } else if (__builtin_expect(n_list <= kListCap, 1)) {
             for (int e = threadIdx.x; e < n_list; e += kSelThreads) visit(list_key[e], list_pos[e]);
+        } else if (!exact) {
+            for (int j = threadIdx.x; j < P; j += kSelThreads) {
+                const uint32_t key = pooled_key(j);
+                if (key >= klo && key <= khi) visit(key, j);
+            }
         } else {
             const int last = (P - 1) & ~3;
             int j = 4 * (int)threadIdx.x;
@@ -1218,12 +1224,12 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
     const size_t part_bytes = (size_t)heads * n_parts * rows_pad * sizeof(float2);
     const size_t bins_bytes = tiles > 1 ? (size_t)heads * p.n_seg * kBins * sizeof(uint16_t) : 0;
     p.off_stats_part = off; off = align_up(off + (part_bytes > bins_bytes ? part_bytes : bins_bytes), 256);
-    p.off_exact = off;      off = align_up(off + (tiles > 1 ? (size_t)heads * p.p_stride * sizeof(float) : 0), 256);
     p.off_stats = off;      off = align_up(off + (size_t)heads * rows_pad * (sizeof(float2) + sizeof(double)), 256);
     p.off_vote = off;       off = align_up(off + (size_t)heads * (p.P > 0 ? p.P : 1) * sizeof(float), 256);
     p.off_pooled = off;     off = align_up(off + (size_t)heads * p.p_stride * sizeof(uint16_t), 256);
     p.off_idx = off;        off = align_up(off + (size_t)heads * (p.n_kept > 0 ? p.n_kept : 1) * sizeof(int32_t), 256);
     p.total = off;
+    p.exact_bytes = tiles > 1 ? (size_t)heads * p.p_stride * sizeof(float) : 0;
     return p;
 }
 
@@ -1263,7 +1269,7 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
     s.gq = a.gq; s.n_q_heads = cfg.n_q_heads; s.n_kv_heads = cfg.n_kv_heads; s.rows = a.rows; s.rows_pad = a.rows_pad;
     s.sm_scale = cfg.sm_scale;
     s.bins = reinterpret_cast<uint16_t*>(base + plan.off_stats_part);
-    s.exact = reinterpret_cast<float*>(base + plan.off_exact);
+    s.exact = plan.exact_bytes > 0 ? reinterpret_cast<float*>(base + plan.total) : nullptr;
     s.p_stride = plan.p_stride; s.n_seg = plan.n_seg; s.seg_tiles = plan.seg_tiles;
     if (plan.P <= kPoolTile) {
         hipLaunchKernelGGL(select_topk<true>, dim3(heads), dim3(kSelThreads), 0, stream, s);

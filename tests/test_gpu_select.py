@@ -144,7 +144,8 @@ def test_row_sums_keep_their_precision_when_a_late_key_dominates(Gq, W, key):
     reference never lags further) 2^-22 ln 2 for the rounding of the argument, 2^-23 for the exponential and 2^-24
     for each of at most eleven additions behind the large term, together 9.4e-7 of the sum.  Arguments of 32
     to 64, as a reference left at the first keys gives, are rounded to 1.3e-6 alone.  The statistics lie in the
-    workspace before the votes, the pooled scores' codes and the survivors (each padded to 256 bytes)."""
+    workspace before the votes, the pooled scores' codes, the survivors (each padded to 256 bytes) and room for
+    all pooled scores."""
     B, Hkv, P, budget = 8, 8, 4500, 100
     heads, rows = B * Hkv, Gq * W
     rows_pad = 128 if rows <= 128 else 256
@@ -161,7 +162,7 @@ def test_row_sums_keep_their_precision_when_a_late_key_dominates(Gq, W, key):
 
     def padded(n):
         return -(-n // 256) * 256
-    at = kvqp.workspace_bytes(cfg)[0] - sum(padded(heads * n) for n in (budget * 4, -(-P // 8) * 16, P * 4, rows_pad * 16))
+    at = kvqp.workspace_bytes(cfg)[0] - heads * -(-P // 8) * 32 - sum(padded(heads * n) for n in (budget * 4, -(-P // 8) * 16, P * 4, rows_pad * 16))
     host = ws.cpu().numpy()
     stats = host[at:at + heads * rows_pad * 8].view(np.float32).reshape(heads, rows_pad, 2)[:, :rows].astype(np.float64)
     zsum = host[at + heads * rows_pad * 8:at + heads * rows_pad * 16].view(np.float64).reshape(heads, rows_pad)[:, :rows]
@@ -195,3 +196,24 @@ def test_more_candidates_around_the_cut_than_the_list_holds_under_wide_windows(o
             assert unrefined[g] == 0 or unrefined[g] > 512
         if unrefined == [0, 0]:
             check_indices(got, idx, pooled)
+
+
+def test_a_compress_workspace_without_room_for_all_pooled_scores_gives_the_same_survivors():
+    """The stated size has four bytes per candidate for prompts whose scores cluster around the cut; a
+    workspace that holds everything else is taken, and a smaller one is not."""
+    print("case smaller compress workspace", flush=True)
+    P, W, Hkv, budget = 9003, 8, 2, 3000
+    q_obs, k, v = (dev(t) for t in synth.prompt_host(1, Hkv * 2, Hkv, P + W, W, 128, outlier=1.0, config=85))
+    k[:, :, :P] = (k[:, :, :1].float() + 0.002 * k[:, :, :P].float()).half()
+    cfg = kvqp.Cfg(batch=1, n_q_heads=Hkv * 2, n_kv_heads=Hkv, seq_len=P + W, window=W, pool_kernel=5, budget=budget, bits=4, group_size=32)
+    stated = kvqp.workspace_bytes(cfg)[0]
+    least = stated - Hkv * -(-P // 8) * 32
+    got = []
+    for size in (stated, least):
+        idx = torch.full((1, Hkv, budget), -1, dtype=torch.int32, device="cuda")
+        kvqp.compress(cfg, q_obs, k, v, kvqp.alloc_cache(cfg), idx_out=idx, workspace=kvqp.alloc_workspace(stated)[:size])
+        torch.cuda.synchronize()
+        got.append(idx)
+    assert torch.equal(got[0], got[1]) and bool((got[0].diff() > 0).all())
+    with pytest.raises(kvqp.KvqpError):
+        kvqp.compress(cfg, q_obs, k, v, kvqp.alloc_cache(cfg), workspace=kvqp.alloc_workspace(stated)[:least - 16])

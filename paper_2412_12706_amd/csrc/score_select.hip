@@ -18,8 +18,8 @@
 //   select_topk        find the cut, ordered compaction; scores within a relative
 //                      2e-5 of the cut are first re-scored in binary64 so that
 //                      binary32 rounding cannot move the cut
-// score_pass (up to 128 window rows): keys stream through LDS once per pass in 64- or
-// 128-key chunks shared by the four waves of a workgroup; query rows stay in registers as
+// score_pass (up to 128 window rows): keys stream through LDS once per pass in chunks of 64
+// shared by the four waves of a workgroup; query rows stay in registers as
 // MFMA operands.  score_wide (more rows): keys in registers, query rows in LDS.
 #include <algorithm>
 
@@ -30,9 +30,11 @@ namespace {
 
 typedef _Float16 h8v __attribute__((ext_vector_type(8)));
 typedef float f4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 union Frag {
     h8v v;
     uint4 q;
+    u4v u;
 };
 template <int I> struct IntC { static constexpr int value = I; };
 template <bool B> struct BoolC { static constexpr bool value = B; };
@@ -40,10 +42,18 @@ template <bool B> struct BoolC { static constexpr bool value = B; };
 constexpr int kThreads = 256;
 constexpr int kRowsPerWave = 32;        // score_pass: query rows one wave owns (its MFMA A operands, register-resident)
 constexpr int kNarrowRows = 4 * kRowsPerWave;   // window rows of a KV head it takes; more are score_wide's
-constexpr int kKeyStride = kHeadDim * 2 + 16;  // LDS bytes per key row; +16 B skews banks
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1.0e30f;
 constexpr float kLazy = 8.0f;           // a row's reference moves only when a score beats it by 2^8 (an exponential's argument is rounded at its own magnitude: here to 2^-22, with references moved at 2^60 to 2^-19)
+
+constexpr float kLazySum = 256.0f;        // ... as the sum of a few exponentials sees it
+
+// The chip's memory-side cache.  The vote pass and the quantizer read keys again: the statistics stream the keys of all but the
+// last heads past this cache, whose keys fill it, and the vote pass, which streams, leaves them there for the quantizer.  256
+// heads of 32768 keys (2.15 GB), us, statistics + votes + quantizer: all keys through the cache 409 + 370 + 452, none
+// 349 + 396 + 506 (what the quantizer has written leaves the cache while it runs), the last 128 MB 393 + 386 + 489, 192 MB
+// 405 + 384 + 463, 256 MB 394 + 363 + 452, 448 MB 412 + 367 + 451.  Keys that fit: 8 heads of 32768, votes 15.1 instead of 17.8.
+constexpr size_t kSideCache = (size_t)256 << 20;
 
 enum { PASS_STATS = 0, PASS_VOTES = 1 };
 
@@ -56,24 +66,48 @@ struct ScoreArgs {
     int L, W, P, gq, n_q_heads, n_kv_heads;
     int rows, rows_pad;     // Gq*W and the rows the waves cover (a multiple of 32 or 64)
     int chunks_per_wg, n_chunks, n_parts;
+    int stream_heads;       // STATS: heads below it are streamed past the memory-side cache
     float scale_log2;       // sm_scale * log2(e)
 };
 
-// NRW = number of row slabs (1, 2, 4) of 32 rows; the 4 waves are NRW row slabs x KS key strips.
-template <int NRW> struct ScoreGeom {
-    static constexpr int KS = 4 / NRW;
-    static constexpr int CK = (KS == 1) ? 64 : 128;   // keys per chunk
-    static constexpr int KT = CK / (16 * KS);         // key tiles per wave per chunk
-};
+constexpr int kChunk = 64;              // keys of a chunk
+constexpr int kChunkBytes = kChunk * kHeadDim * 2;
+constexpr int kRing = 2;                // chunks in LDS
 
-// Up to 128 window rows.
+// Request 1 KB of a chunk (four key rows) straight into LDS: lane l's 16 bytes from `base + off` land at dst + 16 l.
+// Nothing is left in a register, so the only thing to wait for is the counter (arrived()).
+template <bool STREAM>
+__device__ __forceinline__ void request_rows(uint32_t dst, uint32_t off, const void* base) {
+    if (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(dst), "v"(off), "s"(base) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(base) : "memory");
+}
+// Wait until at most LEFT of this wave's memory operations are outstanding and its LDS operations are done; BARRIER: meet the other waves.
+template <int LEFT, bool BARRIER>
+__device__ __forceinline__ void arrived() {
+    if (BARRIER) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LEFT) : "memory");
+}
+
+// Up to 128 window rows.  The four waves are NRW row slabs x KS key strips.  What bounds a pass is memory (K once per
+// pass) as long as requests stay in flight while a chunk is computed.  So chunks go from memory into LDS without
+// passing through registers, two places deep, and the waves meet once per chunk: behind that barrier the chunk has
+// arrived for all of them and the place of the one before it is free for the next request.  A wave forms all its
+// scores of a chunk before it uses any (sixteen independent matrix chains), and the one rare branch of the
+// statistics stands per chunk.  The statistics take keys as the first operand, so that a lane's scores belong to one row
+// (one reference and one sum to keep, two lane exchanges at the end); the votes take queries first: a key's rows are added up
+// in the lane, and two exchanges per chunk merge its four tiles.  Before (chunks through registers, two
+// barriers per chunk, a branch per 16 keys) -> now, us, statistics + votes: 8 heads of 4096 keys 10.0 + 7.2 -> 6.5 + 5.2,
+// 8 of 32768 23.2 + 19.2 -> 18.3 + 15.1, 32 of 16384 37 + 34 -> 29 + 26, 256 of 32768 425 + 414 -> 394 + 363 (2.15 GB:
+// 5.5 and 5.9 TB/s), 32 of 20011 with 32 rows 32.6 + 25.4 -> 31.6 + 24.6.  Three and four places in LDS are no better
+// (8 heads of 32768: 19.2 + 15.9 and 20.2 + 17.0): fewer workgroups fit a CU.
 template <int NRW, int PASS>
 __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     constexpr int kMT = kRowsPerWave / 16;
-    using Gm = ScoreGeom<NRW>;
-    constexpr int KS = Gm::KS, CK = Gm::CK, KT = Gm::KT;
-    __shared__ __align__(16) unsigned char sk[CK * kKeyStride];
-    __shared__ float svote[(PASS == PASS_VOTES) ? NRW * CK : 1];
+    constexpr int KS = 4 / NRW, KT = 4 / KS;          // key strips; 16-key tiles of a wave per chunk
+    constexpr int kLoads = 4;                         // requests of a wave per chunk
+    constexpr bool SHARED = NRW > 1;                  // a wave reads keys that other waves have requested
+    __shared__ __align__(16) unsigned char sk[kRing * kChunkBytes];
+    __shared__ float svote[(PASS == PASS_VOTES && NRW > 1) ? 2 * NRW * kChunk : 1];
 
     const int head = blockIdx.y;
     const int b = head / a.n_kv_heads, g = head % a.n_kv_heads;
@@ -82,6 +116,8 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     const int n = lane & 15, kb = lane >> 4;
     const int rw = wave % NRW, ks = wave / NRW;
     const uint16_t* kh = a.k + (size_t)head * a.L * kHeadDim;
+    const int c_begin = blockIdx.x * a.chunks_per_wg;
+    const int c_end = min(a.n_chunks, c_begin + a.chunks_per_wg);
 
     // Query operand: rows 32*rw + 16*mt + (lane & 15), channels 32*s + 8*kb .. +8.
     Frag qf[kMT][4];
@@ -96,11 +132,14 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
             qf[mt][s].q = live ? *reinterpret_cast<const uint4*>(qp + 32 * s) : make_uint4(0, 0, 0, 0);
         }
     }
-    float m_run[kMT][4], z_run[kMT][4];   // STATS: reference (log2 domain) and sum of exp2(score - reference).  VOTES: m and 1/Z of the row.
+    // STATS: a lane's scores belong to row 16 mt + n: reference (log2 domain) and sum of exp2(score - reference).
+    // VOTES: to rows 16 mt + 4 kb + i: m and 1/Z.
+    constexpr int NR = PASS == PASS_STATS ? 1 : 4;
+    float m_run[kMT][NR], z_run[kMT][NR];
 #pragma unroll
     for (int mt = 0; mt < kMT; ++mt)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < NR; ++i) {
             if (PASS == PASS_STATS) {
                 m_run[mt][i] = kNegBig; z_run[mt][i] = 0.f;
             } else {
@@ -110,144 +149,184 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
             }
         }
 
-    const int c_begin = blockIdx.x * a.chunks_per_wg;
-    const int c_end = min(a.n_chunks, c_begin + a.chunks_per_wg);
-
-    // The chunk after the one being computed is already on its way from HBM into registers;
-    // it is parked in LDS only when every wave has finished reading the current one.
-    constexpr int NPRE = CK * 16 / kThreads;
-    typedef uint32_t u4v __attribute__((ext_vector_type(4)));
-    u4v pre[NPRE];
-    const int pre_row = threadIdx.x >> 4, pre_col = threadIdx.x & 15;   // item i of a thread: key row pre_row + 16 i
-#define KVQP_ISSUE(chunk_)                                                                             \
-    _Pragma("unroll") for (int i_ = 0; i_ < NPRE; ++i_) {                                              \
-        const int key_ = min((chunk_) * CK + pre_row + 16 * i_, a.L - 1); /* rows past the end are masked */ \
-        const u4v* src_ = reinterpret_cast<const u4v*>(kh + (size_t)key_ * kHeadDim + pre_col * 8);    \
-        pre[i_] = (PASS == PASS_VOTES) ? __builtin_nontemporal_load(src_) : *src_; /* last read of a key: streamed */ \
+    // Chunk c lies in ring place c % kRing, its rows unpadded; the 16-byte piece p of row r is stored at place
+    // p ^ (r % 16), so that the operand reads below meet every bank equally.  Wave w requests rows 16 w .. 16 w + 15.
+    const uint32_t sk_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sk;
+    const int row_in = 16 * wave + kb;                                    // request i: row row_in + 4 i
+    auto request = [&](int chunk, int place) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int key = min(chunk * kChunk + row_in + 4 * i, a.L - 1);         // rows past the end are masked
+            const uint32_t piece = (uint32_t)(n ^ ((4 * i + kb) & 15));
+            const uint32_t dst = sk_at + place * kChunkBytes + (16 * wave + 4 * i) * (2 * kHeadDim), off = (uint32_t)key * (2u * kHeadDim) + 16u * piece;
+            if (PASS == PASS_VOTES || head < a.stream_heads) request_rows<true>(dst, off, kh);
+            else request_rows<false>(dst, off, kh);
+        }
+    };
+    request(c_begin, 0);
+    // (the first chunk and the query rows arrive together; the compiler's wait for the latter stands here, not in the loop)
+#pragma unroll
+    for (int mt = 0; mt < kMT; ++mt) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(qf[mt][s].u));
+        if (PASS == PASS_VOTES)
+#pragma unroll
+            for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(m_run[mt][i]), "+v"(z_run[mt][i]));
     }
-#define KVQP_COMMIT()                                                                                  \
-    _Pragma("unroll") for (int i_ = 0; i_ < NPRE; ++i_)                                                \
-        *reinterpret_cast<u4v*>(sk + (pre_row + 16 * i_) * kKeyStride + pre_col * 16) = pre[i_];
-    KVQP_ISSUE(min(c_begin, a.n_chunks - 1))
-    KVQP_COMMIT()
-    __syncthreads();
+#pragma unroll
+    for (int c = 1; c < kRing - 1; ++c)
+        if (c_begin + c < c_end) request(c_begin + c, c);
 
+    const uint32_t kp0 = (uint32_t)(n * 2 * kHeadDim + ((kb ^ n) << 4));  // contraction step 0 of key n; step s: ^ (s << 6)
+    int place = 0;
+    auto store_votes = [&](int chunk) {               // the chunk's votes over all slabs (one wave's work)
+        float v = 0.f;
+#pragma unroll
+        for (int r = 0; r < NRW; ++r) v += svote[((chunk & 1) * NRW + r) * kChunk + lane];
+        const int key = chunk * kChunk + lane;
+        if (key < a.P) a.vote[(size_t)head * a.P + key] = v;
+    };
     for (int chunk = c_begin; chunk < c_end; ++chunk) {
-        const int key0 = chunk * CK;
-        KVQP_ISSUE(min(chunk + 1, c_end - 1))
+        // this chunk has arrived, every wave is done with the one before it
+        if (chunk + kRing - 2 < c_end) arrived<kLoads * (kRing - 2), SHARED>();
+        else arrived<0, SHARED>();
+        if (chunk + kRing - 1 < c_end) request(chunk + kRing - 1, place == 0 ? kRing - 1 : place - 1);
+        if (PASS == PASS_VOTES && NRW > 1)
+            if (chunk > c_begin && wave == (chunk & 3)) store_votes(chunk - 1);
 
-        // one 16-key tile at a time keeps the accumulators at 16 registers
+        const unsigned char* kp = sk + place * kChunkBytes + 16 * KT * ks * (2 * kHeadDim);
+        f4v acc[KT][kMT];
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) {
             Frag kf[4];
-            const unsigned char* kp = sk + (16 * (ks * KT + kt) + n) * kKeyStride + 16 * kb;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) kf[s].q = *reinterpret_cast<const uint4*>(kp + 64 * s);
-            f4v acc[kMT];
+            for (int s = 0; s < 4; ++s) kf[s].q = *reinterpret_cast<const uint4*>(kp + 16 * kt * (2 * kHeadDim) + (kp0 ^ (s << 6)));
 #pragma unroll
             for (int mt = 0; mt < kMT; ++mt) {
                 f4v c = (f4v){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(qf[mt][s].v, kf[s].v, c, 0, 0, 0);
-                acc[mt] = c;
+                for (int s = 0; s < 4; ++s)
+                    c = PASS == PASS_STATS ? __builtin_amdgcn_mfma_f32_16x16x32_f16(kf[s].v, qf[mt][s].v, c, 0, 0, 0)
+                                           : __builtin_amdgcn_mfma_f32_16x16x32_f16(qf[mt][s].v, kf[s].v, c, 0, 0, 0);
+                acc[kt][mt] = c;
             }
-            // causal mask only where the tile reaches the window (raw scores; the scale is positive)
-            const int tile0 = key0 + 16 * (ks * KT + kt);
-            if (tile0 + 16 > a.P) {
-                const int key = tile0 + n;
+        }
+        float col[KT];
+        if constexpr (PASS == PASS_STATS) {
+            // causal mask only where the chunk reaches the window (raw scores; the scale is positive)
+            if ((chunk + 1) * kChunk > a.P) {
                 int w = a.W;
                 asm volatile("" : "+s"(w));   // keeps the window positions out of the loop's live registers
 #pragma unroll
-                for (int mt = 0; mt < kMT; ++mt)
+                for (int mt = 0; mt < kMT; ++mt) {
+                    const int r = kRowsPerWave * rw + 16 * mt + n;
+                    const int last = min(a.P + (r < a.rows ? r % w : -1), a.L - 1) - (chunk * kChunk + 16 * KT * ks + 4 * kb);   // padding rows see the prefix only
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int r = kRowsPerWave * rw + 16 * mt + 4 * kb + i;
-                        const int wr = (r < a.rows) ? r % w : -1;   // padding rows see the prefix only
-                        if (key > a.P + wr || key >= a.L) acc[mt][i] = -INFINITY;
-                    }
+                    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (16 * kt + i > last) acc[kt][mt][i] = -INFINITY;
+                }
             }
-            if (PASS == PASS_STATS) {
-                // m_run is a reference, not the exact maximum: it moves only when a score beats it
-                // by more than 2^kLazy, so the common path is one fused multiply-add and one exp2
-                float e[kMT][4];
-                float big = -INFINITY;
+            // m_run is a reference, not the exact maximum: it moves only when a score beats it by
+            // 2^kLazy or several come near (then the sum of the chunk's exponentials does), so the common path
+            // is one fused multiply-add, one exp2 and one add
+            float t[kMT];
+            auto sums = [&] {
 #pragma unroll
-                for (int mt = 0; mt < kMT; ++mt)
+                for (int mt = 0; mt < kMT; ++mt) {
+                    float x[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        e[mt][i] = __builtin_fmaf(acc[mt][i], a.scale_log2, -m_run[mt][i]);
-                        big = fmaxf(big, e[mt][i]);
-                    }
-                if (__builtin_amdgcn_ballot_w64(big > kLazy) != 0ull) {   // rare after the first tiles
-#pragma unroll
-                    for (int mt = 0; mt < kMT; ++mt)
+                    for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            const float sc = acc[mt][i] * a.scale_log2;
-                            if (sc > m_run[mt][i]) {
-                                z_run[mt][i] *= __builtin_amdgcn_exp2f(m_run[mt][i] - sc);
-                                m_run[mt][i] = sc;
-                            }
-                            e[mt][i] = __builtin_fmaf(acc[mt][i], a.scale_log2, -m_run[mt][i]);
+                            const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[kt][mt][i], a.scale_log2, -m_run[mt][0]));
+                            x[i] = kt == 0 ? e : x[i] + e;
                         }
+                    t[mt] = (x[0] + x[1]) + (x[2] + x[3]);
                 }
+            };
+            sums();
+            if (__builtin_amdgcn_ballot_w64(fmaxf(t[0], t[1]) > kLazySum) != 0ull) {   // rare after the first chunks
 #pragma unroll
-                for (int mt = 0; mt < kMT; ++mt)
+                for (int mt = 0; mt < kMT; ++mt) {
+                    float top = acc[0][mt][0];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) z_run[mt][i] += __builtin_amdgcn_exp2f(e[mt][i]);
-            } else {
-                // normalised probabilities summed over this wave's 32 rows, per key
+                    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) top = fmaxf(top, acc[kt][mt][i]);
+                    top *= a.scale_log2;
+                    if (top > m_run[mt][0]) {
+                        z_run[mt][0] *= __builtin_amdgcn_exp2f(m_run[mt][0] - top);
+                        m_run[mt][0] = top;
+                    }
+                }
+                sums();
+            }
+#pragma unroll
+            for (int mt = 0; mt < kMT; ++mt) z_run[mt][0] += t[mt];
+        } else {
+            // normalised probabilities summed over this lane's rows, per key (the window's own keys get votes nobody reads)
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt) {
                 float c0 = 0.f, c1 = 0.f;
 #pragma unroll
                 for (int mt = 0; mt < kMT; ++mt)
 #pragma unroll
                     for (int i = 0; i < 4; i += 2) {
-                        c0 = __builtin_fmaf(__builtin_amdgcn_exp2f(__builtin_fmaf(acc[mt][i], a.scale_log2, -m_run[mt][i])),
+                        c0 = __builtin_fmaf(__builtin_amdgcn_exp2f(__builtin_fmaf(acc[kt][mt][i], a.scale_log2, -m_run[mt][i])),
                                             z_run[mt][i], c0);
-                        c1 = __builtin_fmaf(__builtin_amdgcn_exp2f(__builtin_fmaf(acc[mt][i + 1], a.scale_log2, -m_run[mt][i + 1])),
+                        c1 = __builtin_fmaf(__builtin_amdgcn_exp2f(__builtin_fmaf(acc[kt][mt][i + 1], a.scale_log2, -m_run[mt][i + 1])),
                                             z_run[mt][i + 1], c1);
                     }
-                float col = c0 + c1;
-                // rows 4kb+i of all four lane quads
-                col += __shfl_xor(col, 16);
-                col += __shfl_xor(col, 32);
-                if (kb == 0) svote[rw * CK + 16 * (ks * KT + kt) + n] = col;
+                col[kt] = c0 + c1;
             }
         }
-        __syncthreads();                 // all waves are done with this chunk's keys (and votes are parked)
-        if (PASS == PASS_VOTES) {
-            for (int kk = threadIdx.x; kk < CK; kk += kThreads) {
-                float v = 0.f;
-#pragma unroll
-                for (int r = 0; r < NRW; ++r) v += svote[r * CK + kk];
-                if (key0 + kk < a.P) a.vote[(size_t)head * a.P + key0 + kk] = v;
+        if constexpr (PASS == PASS_VOTES) {
+            // sum over the four rows of 16 lanes; an exchange merges two tiles into one register
+            auto swap16 = [](float x, float y) {
+                const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+                return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+            };
+            auto swap32 = [](float x, float y) {
+                const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+                return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+            };
+            if constexpr (KT == 4) {          // row q of lanes: tile q
+                svote[((chunk & 1) * NRW + rw) * kChunk + lane] = swap32(swap16(col[0], col[1]), swap16(col[2], col[3]));
+            } else if constexpr (KT == 2) {   // rows 0 and 1: tiles 0 and 1; rows 2 and 3 the same again
+                const float x = swap16(col[0], col[1]), v = swap32(x, x);
+                if (lane < 32) svote[((chunk & 1) * NRW + rw) * kChunk + 32 * ks + lane] = v;
+            } else {
+                const float x = swap16(col[0], col[0]), v = swap32(x, x);
+                const int key = chunk * kChunk + 16 * ks + n;
+                if (kb == 0 && key < a.P) a.vote[(size_t)head * a.P + key] = v;
             }
         }
-        KVQP_COMMIT()
-        __syncthreads();
+        place = place == kRing - 1 ? 0 : place + 1;
     }
-#undef KVQP_ISSUE
-#undef KVQP_COMMIT
+    if (PASS == PASS_VOTES && NRW > 1) {
+        arrived<0, SHARED>();
+        if (wave == 0) store_votes(c_end - 1);
+    }
 
     if (PASS == PASS_STATS) {
-        // merge the 16 key columns a row is spread over, then one lane per row writes
+        // merge the four lanes that share a row, then one of them writes
 #pragma unroll
-        for (int mt = 0; mt < kMT; ++mt)
+        for (int mt = 0; mt < kMT; ++mt) {
+            float m = m_run[mt][0], z = z_run[mt][0];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float m = m_run[mt][i], z = z_run[mt][i];
-#pragma unroll
-                for (int off = 1; off < 16; off <<= 1) {
-                    const float mo = __shfl_xor(m, off), zo = __shfl_xor(z, off);
-                    const float mn = fmaxf(m, mo);
-                    z = z * __builtin_amdgcn_exp2f(m - mn) + zo * __builtin_amdgcn_exp2f(mo - mn);
-                    m = mn;
-                }
-                if (n == 0) {
-                    const int r = kRowsPerWave * rw + 16 * mt + 4 * kb + i;
-                    a.stats_part[((size_t)head * a.n_parts + blockIdx.x * KS + ks) * a.rows_pad + r] = make_float2(m, z);
-                }
+            for (int off = 16; off < 64; off <<= 1) {
+                const float mo = __shfl_xor(m, off), zo = __shfl_xor(z, off);
+                const float mn = fmaxf(m, mo);
+                z = z * __builtin_amdgcn_exp2f(m - mn) + zo * __builtin_amdgcn_exp2f(mo - mn);
+                m = mn;
             }
+            if (kb == 0) {
+                const int r = kRowsPerWave * rw + 16 * mt + n;
+                a.stats_part[((size_t)head * a.n_parts + blockIdx.x * KS + ks) * a.rows_pad + r] = make_float2(m, z);
+            }
+        }
     }
 }
 
@@ -261,8 +340,8 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
 // matrix instructions.  No barrier in the loop, no key through LDS; the products of a row tile run
 // while the scores of the tile before it are exponentiated.  A lane's accumulators are keys of ONE
 // row, so a row's reference is one register.  8 heads, 131072 keys, 256 rows: 124 + 91 us (statistics +
-// votes) with score_pass's layout, 97 + 86 us this way; up to 128 rows score_pass is as fast or faster
-// (8 heads of 32768 keys: 23 + 19 against 24 + 21 us; of 4096 keys 10 + 7 against 12 + 9).
+// votes) with an earlier score_pass's layout, 97 + 86 us this way; up to 128 rows score_pass is faster
+// (8 heads of 32768 keys: 18 + 15 against 24 + 21 us; of 4096 keys 6.5 + 5.2 against 12 + 9).
 constexpr int kWideTiles = 16;                 // row tiles
 constexpr int kKeyTiles = 4;                   // 16-key tiles a wave holds
 constexpr int kChunkKeys = 16 * kKeyTiles;     // keys of a wave's step
@@ -279,7 +358,6 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
     const char* kh = reinterpret_cast<const char*>(a.k + (size_t)head * a.L * kHeadDim);
 
     // ---- a wave's keys: tile kt, contraction step s -> key 16 kt + n, channels 32 s + 8 kb .. + 8 ----
-    typedef uint32_t u4v __attribute__((ext_vector_type(4)));
     struct Keys { u4v f[kKeyTiles][4]; };
     auto load = [&](Keys& d, int chunk) {
 #pragma unroll
@@ -1190,14 +1268,12 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
     const bool wide = nrw == 0;
     p.rows_pad = wide ? 16 * kWideTiles : nrw * kRowsPerWave;
     const int ks = wide ? 1 : 4 / nrw;                   // statistics a workgroup leaves per row
-    const int ck = wide || ks == 1 ? 64 : 128;           // keys per chunk
-    p.n_chunks = (cfg.seq_len + ck - 1) / ck;
+    p.n_chunks = (cfg.seq_len + 63) / 64;                // keys per chunk: 64
     // A workgroup pays for staging its query rows and waits for its first keys alone, so it should have
     // sixteen chunks (64 where the wave holds more rows), as long as that leaves two workgroups per CU;
     // beyond eight per CU more only cost.  Statistics + votes, us, with 512 / 1024 / 2048 workgroups: 8
-    // heads of 32768 keys 23 + 19 / 26 + 19 / 32 + 22, 32 heads of 16384 37 + 34 / 39 + 32 / 46 + 35, 64 heads
-    // 62 + 59 / 61 + 55 / 68 + 57, 128 heads 117 + 122 / 117 + 110 / 118 + 108, 256 heads of 32768 431 + 494 /
-    // 419 + 419 / 415 + 418; with 256 rows 16 heads of 65536 keys 93 + 85 / 101 + 89 / 128 + 102 (the statistics
+    // heads of 32768 keys 18.4 + 14.8 / 19.5 + 16.2 / 22.0 + 17.3; 32 heads of 16384 29 + 26, 64 heads 55 + 46 and
+    // 128 heads 100 + 92 with any of them; with 256 rows 16 heads of 65536 keys 93 + 85 / 101 + 89 / 128 + 102 (the statistics
     // without moving references, 3 % of them).
     const long long chunks = (long long)heads * p.n_chunks;
     const int total = (int)std::min(2048LL, std::max(512LL, chunks / (wide ? 64 : 16)));
@@ -1251,6 +1327,7 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
     a.n_q_heads = cfg.n_q_heads; a.n_kv_heads = cfg.n_kv_heads;
     a.chunks_per_wg = plan.chunks_per_wg; a.n_chunks = plan.n_chunks; a.n_parts = plan.n_parts;
     a.scale_log2 = cfg.sm_scale * kLog2e;
+    a.stream_heads = std::max(0, heads - (int)(kSideCache / ((size_t)cfg.seq_len * kHeadDim * 2)));
 
     hipError_t e;
     if (score) {   // scores are needed only when something is dropped

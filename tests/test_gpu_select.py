@@ -107,6 +107,17 @@ def test_wide_windows_at_the_edges_of_a_step(orc, P, Gq, W):
     assert unrefined == [0, 0]
 
 
+@pytest.mark.parametrize("L,Gq,W", [(9, 1, 5), (64, 2, 17), (65, 4, 8), (127, 8, 16), (129, 4, 31), (193, 2, 64), (4159, 4, 16), (4161, 4, 32), (20011, 1, 33)])
+def test_scores_at_the_edges_of_a_chunk(orc, L, Gq, W):
+    """Up to 128 window rows: key counts around the chunks of 64 that take turns in LDS (one, two and more of them
+    per workgroup), row counts that do not fill the one, two or four slabs of 32 rows."""
+    print(f"case chunks L={L} Gq={Gq} W={W}", flush=True)
+    P = L - W
+    got, idx, pooled, unrefined = select(orc, P, W, 3, max(1, P // 4), Gq=Gq, seed=83)
+    check_indices(got, idx, pooled)
+    assert unrefined == [0, 0]
+
+
 @pytest.mark.parametrize("where,word", [("query", float("nan")), ("key", float("nan")), ("query", float("inf")), ("key", -float("inf"))])
 @pytest.mark.parametrize("P,Gq,W,pool,budget", [(700, 2, 8, 7, 100), (4096, 4, 32, 1, 4095), (5000, 2, 8, 7, 513), (9001, 4, 64, 63, 2000)])
 def test_votes_that_are_not_numbers_still_give_every_survivor(P, Gq, W, pool, budget, where, word):

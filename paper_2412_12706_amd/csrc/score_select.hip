@@ -18,9 +18,9 @@
 //   select_topk        find the cut, ordered compaction; scores within a relative
 //                      2e-5 of the cut are first re-scored in binary64 so that
 //                      binary32 rounding cannot move the cut
-// score_pass (up to 128 window rows): keys stream through LDS once per pass in chunks of 64
-// shared by the four waves of a workgroup; query rows stay in registers as
-// MFMA operands.  score_wide (more rows): keys in registers, query rows in LDS.
+// score_pass (up to 128 window rows) and score_wide (more rows): keys stream through LDS once per
+// pass in chunks of 64 shared by the four waves of a workgroup; query rows stay in registers as
+// MFMA operands.
 #include <algorithm>
 
 #include "kvqp_internal.h"
@@ -36,7 +36,7 @@ union Frag {
     uint4 q;
     u4v u;
 };
-template <int I> struct IntC { static constexpr int value = I; };
+
 template <bool B> struct BoolC { static constexpr bool value = B; };
 
 constexpr int kThreads = 256;
@@ -44,9 +44,7 @@ constexpr int kRowsPerWave = 32;        // score_pass: query rows one wave owns 
 constexpr int kNarrowRows = 4 * kRowsPerWave;   // window rows of a KV head it takes; more are score_wide's
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1.0e30f;
-constexpr float kLazy = 8.0f;           // a row's reference moves only when a score beats it by 2^8 (an exponential's argument is rounded at its own magnitude: here to 2^-22, with references moved at 2^60 to 2^-19)
-
-constexpr float kLazySum = 256.0f;        // ... as the sum of a few exponentials sees it
+constexpr float kLazySum = 256.0f;      // a row's reference moves only when the exponentials of a lane's tiles add up to more, so no score is further than 2^8 above it (an exponential's argument is rounded at its own magnitude: here to 2^-22, with references moved at 2^60 to 2^-19)
 
 // The chip's memory-side cache.  The vote pass and the quantizer read keys again: the statistics stream the keys of all but the
 // last heads past this cache, whose keys fill it, and the vote pass, which streams, leaves them there for the quantizer.  256
@@ -88,6 +86,26 @@ __device__ __forceinline__ void arrived() {
     else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LEFT) : "memory");
 }
 
+// Request a chunk.  Its rows lie unpadded in LDS; the 16-byte piece p of row r is stored at place p ^ (r % 16), so that
+// the operand reads meet every bank equally.  Wave w requests rows 16 w .. 16 w + 15.
+constexpr int kLoads = 4;               // requests of a wave per chunk
+template <int PASS>
+__device__ __forceinline__ void request_chunk(const ScoreArgs& a, int head, const void* kh, uint32_t sk_at, int chunk, int place) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, kb = lane >> 4;
+    auto rows = [&](auto stream) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int row = 16 * wave + 4 * i;
+            const int key = min(chunk * kChunk + row + kb, a.L - 1);                // rows past the end are masked
+            request_rows<decltype(stream)::value>(sk_at + place * kChunkBytes + row * (2 * kHeadDim),
+                                                  (uint32_t)key * (2u * kHeadDim) + 16u * (uint32_t)(n ^ ((4 * i + kb) & 15)), kh);
+        }
+    };
+    if (PASS == PASS_VOTES || head < a.stream_heads) rows(BoolC<true>{});
+    else rows(BoolC<false>{});
+}
+
 // Up to 128 window rows.  The four waves are NRW row slabs x KS key strips.  What bounds a pass is memory (K once per
 // pass) as long as requests stay in flight while a chunk is computed.  So chunks go from memory into LDS without
 // passing through registers, two places deep, and the waves meet once per chunk: behind that barrier the chunk has
@@ -104,7 +122,6 @@ template <int NRW, int PASS>
 __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     constexpr int kMT = kRowsPerWave / 16;
     constexpr int KS = 4 / NRW, KT = 4 / KS;          // key strips; 16-key tiles of a wave per chunk
-    constexpr int kLoads = 4;                         // requests of a wave per chunk
     constexpr bool SHARED = NRW > 1;                  // a wave reads keys that other waves have requested
     __shared__ __align__(16) unsigned char sk[kRing * kChunkBytes];
     __shared__ float svote[(PASS == PASS_VOTES && NRW > 1) ? 2 * NRW * kChunk : 1];
@@ -149,20 +166,8 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
             }
         }
 
-    // Chunk c lies in ring place c % kRing, its rows unpadded; the 16-byte piece p of row r is stored at place
-    // p ^ (r % 16), so that the operand reads below meet every bank equally.  Wave w requests rows 16 w .. 16 w + 15.
     const uint32_t sk_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sk;
-    const int row_in = 16 * wave + kb;                                    // request i: row row_in + 4 i
-    auto request = [&](int chunk, int place) {
-#pragma unroll
-        for (int i = 0; i < kLoads; ++i) {
-            const int key = min(chunk * kChunk + row_in + 4 * i, a.L - 1);         // rows past the end are masked
-            const uint32_t piece = (uint32_t)(n ^ ((4 * i + kb) & 15));
-            const uint32_t dst = sk_at + place * kChunkBytes + (16 * wave + 4 * i) * (2 * kHeadDim), off = (uint32_t)key * (2u * kHeadDim) + 16u * piece;
-            if (PASS == PASS_VOTES || head < a.stream_heads) request_rows<true>(dst, off, kh);
-            else request_rows<false>(dst, off, kh);
-        }
-    };
+    auto request = [&](int chunk, int place) { request_chunk<PASS>(a, head, kh, sk_at, chunk, place); };
     request(c_begin, 0);
     // (the first chunk and the query rows arrive together; the compiler's wait for the latter stands here, not in the loop)
 #pragma unroll
@@ -229,7 +234,7 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
                 }
             }
             // m_run is a reference, not the exact maximum: it moves only when a score beats it by
-            // 2^kLazy or several come near (then the sum of the chunk's exponentials does), so the common path
+            // 2^8 or several come near (the sum of the chunk's exponentials tells), so the common path
             // is one fused multiply-add, one exp2 and one add
             float t[kMT];
             auto sums = [&] {
@@ -330,208 +335,208 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     }
 }
 
-// 129 to 256 window rows (RT tiles of 16).  Matrix instructions and exponentials, twice as many per key
-// as above, bound these passes unless something else gets in their way: with the keys in LDS for
-// four waves of 64 rows each, every key is read from LDS four times, the waves meet at two barriers
-// per 64 keys, and 64 query rows per wave in registers leave room for one matrix chain at a time.
-// So a wave owns its keys outright: 64 of them stay in its registers as the A operand, requested
-// from memory in operand layout (a load instruction covers 64 bytes of 16 rows) one step ahead, and
-// the query rows, the same for every wave, are read from LDS as the B operand, one read per four
-// matrix instructions.  No barrier in the loop, no key through LDS; the products of a row tile run
-// while the scores of the tile before it are exponentiated.  A lane's accumulators are keys of ONE
-// row, so a row's reference is one register.  8 heads, 131072 keys, 256 rows: 124 + 91 us (statistics +
-// votes) with an earlier score_pass's layout, 97 + 86 us this way; up to 128 rows score_pass is faster
-// (8 heads of 32768 keys: 18 + 15 against 24 + 21 us; of 4096 keys 6.5 + 5.2 against 12 + 9).
-constexpr int kWideTiles = 16;                 // row tiles
-constexpr int kKeyTiles = 4;                   // 16-key tiles a wave holds
-constexpr int kChunkKeys = 16 * kKeyTiles;     // keys of a wave's step
-constexpr int kScoreWaves = kThreads / 64;
+// 129 to 256 window rows: four waves of 64 rows.  Here the matrix cores and the exponentials bound a pass: 67 us for the
+// products of 8 heads, 131072 keys and 256 rows at the rate of a large matrix product, and the vector unit stands still for
+// most of a 16x16x32 instruction (two of them with 8 fused multiply-adds and 4 exponentials: 33.9 ns, the latter
+// alone 27.5; 8 multiply-adds 26.1 and 10.0).  One 32x32x16 instruction does the same work and lets more of it
+// through (31.1 and 20.1 ns).  So tiles are 32 keys x 32 rows, and the product of a tile runs while the scores of the one
+// before it are exponentiated, across chunks too: the waves meet when all have a chunk's last keys in registers.  Keys arrive as in
+// score_pass.  131072 keys, 8 heads, 256 rows, us, statistics + votes: keys in registers, queries in LDS, 16x16x32, a
+// reference moved by selects in every step: 95 + 83; score_pass with 64 rows per wave 94 + 78; 32x32x16 without the next tile's product
+// 82 + 78; this 82 + 76.  (The matrix cores are busy for half of that; the clock falls to 1.8 GHz.  Three or four chunks in
+// LDS 87 + 79 and 87 + 82; a fixed mixture of matrix and vector instructions 84 + 77.)  What the references cost where
+// strong outlier channels make them move: 5 us; a moved reference is shared by the two lanes of a row.
+typedef float f16v __attribute__((ext_vector_type(16)));
+constexpr int kWideRows = 256;
 template <int PASS>
 __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
-    constexpr int RT = kWideTiles;
-    __shared__ __align__(16) uint4 sq[RT * 4 * 64];      // query operand: [row tile][contraction step][lane]
+    constexpr int MT = 2;                             // row tiles of a wave
+    constexpr int kWaveRows = 32 * MT;
+    constexpr int kSteps = kHeadDim / 16;             // contraction steps
+    __shared__ __align__(16) unsigned char sk[kRing * kChunkBytes];
+    __shared__ float svote[PASS == PASS_VOTES ? 2 * 4 * kChunk : 1];
+
     const int head = blockIdx.y;
     const int b = head / a.n_kv_heads, g = head % a.n_kv_heads;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n = lane & 15, kb = lane >> 4;
-    const char* kh = reinterpret_cast<const char*>(a.k + (size_t)head * a.L * kHeadDim);
+    const int n = lane & 31, hi = lane >> 5;
+    const uint16_t* kh = a.k + (size_t)head * a.L * kHeadDim;
+    const int c_begin = blockIdx.x * a.chunks_per_wg;
+    const int c_end = min(a.n_chunks, c_begin + a.chunks_per_wg);
 
-    // ---- a wave's keys: tile kt, contraction step s -> key 16 kt + n, channels 32 s + 8 kb .. + 8 ----
-    struct Keys { u4v f[kKeyTiles][4]; };
-    auto load = [&](Keys& d, int chunk) {
+    // Query operand: row kWaveRows * wave + 32 * mt + n, channels 16 * s + 8 * hi .. +8.
+    Frag qf[MT][kSteps];
 #pragma unroll
-        for (int kt = 0; kt < kKeyTiles; ++kt) {
-            const int key = min(chunk * kChunkKeys + 16 * kt + n, a.L - 1);      // (rows past the end are masked)
-            const u4v* p = reinterpret_cast<const u4v*>(kh + (uint32_t)key * (2u * kHeadDim) + 16u * kb);
+    for (int mt = 0; mt < MT; ++mt) {
+        const int r = kWaveRows * wave + 32 * mt + n;
+        const bool live = r < a.rows;
+        const int hl = live ? r / a.W : 0, i = live ? r % a.W : 0;
+        const uint16_t* qp = a.q_obs + (((size_t)b * a.n_q_heads + g * a.gq + hl) * a.W + i) * kHeadDim + 8 * hi;
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                d.f[kt][s] = (PASS == PASS_VOTES) ? __builtin_nontemporal_load(p + 4 * s) : p[4 * s];   // last read of a key: streamed
-        }
-    };
-    const int c_end = min(a.n_chunks, ((int)blockIdx.x + 1) * a.chunks_per_wg);
-    int chunk = (int)blockIdx.x * a.chunks_per_wg + wave;
-    Keys keys;
-    if (chunk < c_end) load(keys, chunk);
-
-    // STATS: reference (log2 domain) and sum of exp2(score - reference) of row 16 rt + n over the
-    // lane's keys.  VOTES: m and 1/Z of the row.
-    float m_run[RT], z_run[RT];
-    if constexpr (PASS == PASS_STATS) {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) { m_run[rt] = kNegBig; z_run[rt] = 0.f; }
-    } else {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const int r = 16 * rt + n;
-            const float2 st = a.stats[(size_t)head * a.rows_pad + r];
-            m_run[rt] = st.x; z_run[rt] = (r < a.rows) ? st.y : 0.f;
+        for (int s = 0; s < kSteps; ++s) {
+            qf[mt][s].q = live ? *reinterpret_cast<const uint4*>(qp + 16 * s) : make_uint4(0, 0, 0, 0);
         }
     }
-
-    // ---- query operand: row 16 rt + n, channels 32 s + 8 kb .. + 8 ----
-#pragma unroll 4
-    for (int item = threadIdx.x; item < RT * 4 * 64; item += kThreads) {
-        const int r = 16 * (item >> 8) + (item & 15), ch = 32 * ((item >> 6) & 3) + 8 * ((item >> 4) & 3);
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (r < a.rows) {
-            const int hl = r / a.W, i = r % a.W;
-            v = *reinterpret_cast<const uint4*>(a.q_obs + (((size_t)b * a.n_q_heads + g * a.gq + hl) * a.W + i) * kHeadDim + ch);
-        }
-        sq[item] = v;
-    }
-    __syncthreads();
-
-    const int w_first = n % a.W, w_step = 16 % a.W;               // window position of row n; from a row tile to the next
-    // A step comes in two forms without a branch inside (branches let the compiler start later tiles
-    // early, which do not fit the registers); the one with MASK hides the keys that the rows may not see and
-    // takes the steps that reach the window.  The references move as in score_pass, a lane's by the scores of
-    // its 16 keys, by selects: 94 -> 97 us of the statistics pass.  (Left alone until a step's sum passed 2^60, and the step
-    // done again, they made a row's sum, and with it the binary64 re-scoring, wrong by up to 1.4e-6 instead of
-    // 4e-7; done again at 2^8, strong outlier channels took 62 us more of the 93 at 131072 keys.)
-    auto compute = [&](auto mask, const Keys& key_f, int c) {
-        constexpr bool MASK = decltype(mask)::value;
-        int at = lane, wr = w_first;
-        asm volatile("" : "+v"(at), "+v"(wr));                   // (the query operand is read, and the masks formed, again every step, not kept for the whole loop)
-        float vs[kKeyTiles][4];                                  // VOTES: the lane's row sums per key 16 kt + 4 kb + i
+    // STATS: a lane's scores belong to row 32 mt + n.  VOTES: to rows 32 mt + 8 (i / 4) + 4 hi + i % 4.
+    constexpr int NR = PASS == PASS_STATS ? 1 : 16;
+    float m_run[MT][NR], z_run[MT][NR];
 #pragma unroll
-        for (int kt = 0; kt < kKeyTiles; ++kt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) vs[kt][i] = 0.f;
-        auto product = [&](f4v (&acc)[kKeyTiles], int rt) {      // scores of row tile rt
-            Frag qf[4];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) qf[s].q = sq[(rt * 4 + s) * 64 + at];
-#pragma unroll
-            for (int kt = 0; kt < kKeyTiles; ++kt) acc[kt] = (f4v){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int kt = 0; kt < kKeyTiles; ++kt)
-                    acc[kt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8v, key_f.f[kt][s]), qf[s].v, acc[kt], 0, 0, 0);
-        };
-        f4v acc[kKeyTiles], acc_next[kKeyTiles];                 // the next tile's product runs while this one's scores are used
-        product(acc, 0);
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            if (rt + 1 < RT) product(acc_next, rt + 1);
-            if constexpr (MASK) {                                // causal mask (raw scores; the scale is positive)
-                const int last = min(a.P + wr, a.L - 1) - c * kChunkKeys - 4 * kb;   // the row's last key, from the lane's first one
-#pragma unroll
-                for (int kt = 0; kt < kKeyTiles; ++kt)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (16 * kt + i > last) acc[kt][i] = -INFINITY;
-                wr += w_step;                                    // (window position of row 16 (rt + 1) + n)
-                if (wr >= a.W) wr -= a.W;
-            }
-            if constexpr (PASS == PASS_STATS) {
-                float big = acc[0][0];
-#pragma unroll
-                for (int kt = 0; kt < kKeyTiles; ++kt)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) big = fmaxf(big, acc[kt][i]);
-                const float top = big * a.scale_log2, m_new = top > m_run[rt] + kLazy ? top : m_run[rt];
-                z_run[rt] *= __builtin_amdgcn_exp2f(m_run[rt] - m_new);
-                m_run[rt] = m_new;
-                float z0 = 0.f, z1 = 0.f;
-#pragma unroll
-                for (int kt = 0; kt < kKeyTiles; ++kt)
-#pragma unroll
-                    for (int i = 0; i < 4; i += 2) {
-                        z0 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[kt][i], a.scale_log2, -m_run[rt]));
-                        z1 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[kt][i + 1], a.scale_log2, -m_run[rt]));
-                    }
-                z_run[rt] += z0 + z1;
+        for (int i = 0; i < NR; ++i) {
+            if (PASS == PASS_STATS) {
+                m_run[mt][i] = kNegBig; z_run[mt][i] = 0.f;
             } else {
-#pragma unroll
-                for (int kt = 0; kt < kKeyTiles; ++kt)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        vs[kt][i] = __builtin_fmaf(__builtin_amdgcn_exp2f(__builtin_fmaf(acc[kt][i], a.scale_log2, -m_run[rt])),
-                                                   z_run[rt], vs[kt][i]);
+                const int r = kWaveRows * wave + 32 * mt + 8 * (i >> 2) + 4 * hi + (i & 3);
+                const float2 st = a.stats[(size_t)head * a.rows_pad + r];
+                m_run[mt][i] = st.x; z_run[mt][i] = (r < a.rows) ? st.y : 0.f;
             }
-#pragma unroll
-            for (int kt = 0; kt < kKeyTiles; ++kt) acc[kt] = acc_next[kt];
-            __builtin_amdgcn_sched_barrier(0);                   // (tiles started early would not fit the registers)
         }
-        if constexpr (PASS == PASS_VOTES) {
-            // sum over the 16 lanes of a row of lanes, each ending up with one of the 16 values: lane n with
-            // (kt, i) = (n / 4, n % 4).  At every step a lane keeps the half of the values that its bit
-            // selects and receives its partner's sums of that half.
-            float x[16];
+
+    const uint32_t sk_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sk;
+    auto request = [&](int chunk, int place) { request_chunk<PASS>(a, head, kh, sk_at, chunk, place); };
+    request(c_begin, 0);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) x[e] = vs[e >> 2][e & 3];
-            auto fold = [&](auto half, auto ctrl, bool upper) {
-                constexpr int H = decltype(half)::value;
+    for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
-                for (int e = 0; e < H; ++e) {
-                    const float keep = upper ? x[e + H] : x[e], give = upper ? x[e] : x[e + H];
-                    x[e] = keep + __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(give), decltype(ctrl)::value, 0xf, 0xf, true));
-                }
-            };
-            fold(IntC<8>{}, IntC<0x140>{} /* row_mirror */, (n & 8) != 0);
-            fold(IntC<4>{}, IntC<0x141>{} /* row_half_mirror */, (n & 4) != 0);
-            fold(IntC<2>{}, IntC<0x4E>{} /* quad_perm [2,3,0,1] */, (n & 2) != 0);
-            fold(IntC<1>{}, IntC<0xB1>{} /* quad_perm [1,0,3,2] */, (n & 1) != 0);
-            const int key = c * kChunkKeys + 16 * (n >> 2) + 4 * kb + (n & 3);
-            if (key < a.P) a.vote[(size_t)head * a.P + key] = x[0];
-        }
-    };
-    for (; chunk < c_end; chunk += kScoreWaves) {
-        Keys next;
-        if (chunk + kScoreWaves < c_end) load(next, chunk + kScoreWaves);
-        if ((chunk + 1) * kChunkKeys > a.P) compute(BoolC<true>{}, keys, chunk);
-        else compute(BoolC<false>{}, keys, chunk);
-        keys = next;
+        for (int s = 0; s < kSteps; ++s) asm volatile("" : "+v"(qf[mt][s].u));
+        if (PASS == PASS_VOTES)
+#pragma unroll
+            for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(m_run[mt][i]), "+v"(z_run[mt][i]));
     }
 
-    if constexpr (PASS == PASS_STATS) {
-        // merge the four lanes that share a row, then the waves through LDS
-        __syncthreads();                                         // (every wave is done with the query operand)
-        float2* s_st = reinterpret_cast<float2*>(sq);            // [wave][16 RT]
-        static_assert(kScoreWaves * 16 * RT * 8 <= sizeof(sq), "the statistics fit the query operand's place");
+    const uint32_t kp0 = (uint32_t)(n * 2 * kHeadDim + ((hi ^ (n & 15)) << 4));  // contraction step 0 of key n; step s: ^ (s << 5)
+    struct Tile { f16v f[MT]; };
+    auto product = [&](Tile& acc, int place, int kt) {
+        const unsigned char* kp = sk + place * kChunkBytes + 32 * kt * (2 * kHeadDim);
+        Frag kf[kSteps];
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            float m = m_run[rt], z = z_run[rt];
+        for (int s = 0; s < kSteps; ++s) kf[s].q = *reinterpret_cast<const uint4*>(kp + (kp0 ^ (s << 5)));
 #pragma unroll
-            for (int off = 16; off < 64; off <<= 1) {
-                const float mo = __shfl_xor(m, off), zo = __shfl_xor(z, off);
-                const float mn = fmaxf(m, mo);
-                z = z * __builtin_amdgcn_exp2f(m - mn) + zo * __builtin_amdgcn_exp2f(mo - mn);
-                m = mn;
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc.f[mt][i] = 0.f;
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                acc.f[mt] = PASS == PASS_STATS ? __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[s].v, qf[mt][s].v, acc.f[mt], 0, 0, 0)
+                                               : __builtin_amdgcn_mfma_f32_32x32x16_f16(qf[mt][s].v, kf[s].v, acc.f[mt], 0, 0, 0);
+    };
+    // STATS: the tile's scores enter the lane's sums
+    auto sums = [&](const Tile& acc, float (&t)[MT]) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            float x[4];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(acc.f[mt][i], a.scale_log2, -m_run[mt][0]));
+                x[i & 3] = i < 4 ? e : x[i & 3] + e;
             }
-            if (kb == 0) s_st[wave * 16 * RT + 16 * rt + n] = make_float2(m, z);
+            t[mt] = (x[0] + x[1]) + (x[2] + x[3]);
         }
-        __syncthreads();
-        if ((int)threadIdx.x < 16 * RT) {
-            float2 v[kScoreWaves];
-            float m = kNegBig, z = 0.f;
+    };
+    // causal mask, only where the tile reaches the window
+    auto mask = [&](Tile& acc, int tile0) {
+        if (tile0 + 32 > a.P) {
+            int w = a.W;
+            asm volatile("" : "+s"(w));
 #pragma unroll
-            for (int w = 0; w < kScoreWaves; ++w) { v[w] = s_st[w * 16 * RT + threadIdx.x]; m = fmaxf(m, v[w].x); }
+            for (int mt = 0; mt < MT; ++mt) {
+                const int r = kWaveRows * wave + 32 * mt + n;
+                const int last = min(a.P + (r < a.rows ? r % w : -1), a.L - 1) - (tile0 + 4 * hi);
 #pragma unroll
-            for (int w = 0; w < kScoreWaves; ++w) z = __builtin_fmaf(v[w].y, __builtin_amdgcn_exp2f(v[w].x - m), z);
-            a.stats_part[((size_t)head * a.n_parts + blockIdx.x) * (16 * RT) + threadIdx.x] = make_float2(m, z);
+                for (int i = 0; i < 16; ++i)
+                    if (8 * (i >> 2) + (i & 3) > last) acc.f[mt][i] = -INFINITY;
+            }
+        }
+    };
+    // (references move as in score_pass)
+    auto count = [&](const Tile& acc, float (&t)[MT]) {
+        float peak = t[0];
+#pragma unroll
+        for (int mt = 1; mt < MT; ++mt) peak = fmaxf(peak, t[mt]);
+        if (__builtin_amdgcn_ballot_w64(peak > kLazySum) != 0ull) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                float top = acc.f[mt][0];
+#pragma unroll
+                for (int i = 1; i < 16; ++i) top = fmaxf(top, acc.f[mt][i]);
+                top = fmaxf(top, __shfl_xor(top, 32)) * a.scale_log2;
+                if (top > m_run[mt][0]) {
+                    z_run[mt][0] *= __builtin_amdgcn_exp2f(m_run[mt][0] - top);
+                    m_run[mt][0] = top;
+                }
+            }
+            sums(acc, t);
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) z_run[mt][0] += t[mt];
+    };
+    // VOTES: the key's probabilities summed over the lane's rows
+    auto column = [&](const Tile& acc) {
+        float c0 = 0.f, c1 = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 16; i += 2) {
+                c0 = __builtin_fmaf(__builtin_amdgcn_exp2f(__builtin_fmaf(acc.f[mt][i], a.scale_log2, -m_run[mt][i])),
+                                    z_run[mt][i], c0);
+                c1 = __builtin_fmaf(__builtin_amdgcn_exp2f(__builtin_fmaf(acc.f[mt][i + 1], a.scale_log2, -m_run[mt][i + 1])),
+                                    z_run[mt][i + 1], c1);
+            }
+        return c0 + c1;
+    };
+    int place = 0;
+    auto store_votes = [&](int chunk) {
+        float v = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v += svote[((chunk & 1) * 4 + r) * kChunk + lane];
+        const int key = chunk * kChunk + lane;
+        if (key < a.P) a.vote[(size_t)head * a.P + key] = v;
+    };
+    Tile even, odd;                              // scores of a chunk's two tiles
+    arrived<0, true>();
+    if (c_begin + 1 < c_end) request(c_begin + 1, 1);
+    product(even, 0, 0);
+    for (int chunk = c_begin; chunk < c_end; ++chunk) {
+        float t[MT], col0, col1;
+        if (PASS == PASS_STATS) mask(even, chunk * kChunk);
+        __builtin_amdgcn_sched_barrier(0);
+        product(odd, place, 1);
+        if (PASS == PASS_STATS) sums(even, t); else col0 = column(even);
+        if (PASS == PASS_STATS) count(even, t);
+        arrived<0, true>();                    // the next chunk is there; every wave has this one in registers
+        if (chunk + 2 < c_end) request(chunk + 2, place);
+        if (PASS == PASS_VOTES)
+            if (chunk > c_begin && wave == (chunk & 3)) store_votes(chunk - 1);
+        place ^= 1;
+        if (PASS == PASS_STATS) mask(odd, chunk * kChunk + 32);
+        __builtin_amdgcn_sched_barrier(0);
+        product(even, place, 0);               // (past the last chunk: not used)
+        if (PASS == PASS_STATS) sums(odd, t); else col1 = column(odd);
+        if (PASS == PASS_STATS) count(odd, t);
+        if constexpr (PASS == PASS_VOTES) {   // halves of the wave: tiles 0 and 1
+            const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(col0), __float_as_uint(col1), false, false);
+            svote[((chunk & 1) * 4 + wave) * kChunk + lane] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+        }
+    }
+    if (PASS == PASS_VOTES) {
+        arrived<0, true>();
+        if (wave == 0) store_votes(c_end - 1);
+    }
+    if (PASS == PASS_STATS) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            float m = m_run[mt][0], z = z_run[mt][0];
+            const float mo = __shfl_xor(m, 32), zo = __shfl_xor(z, 32);
+            const float mn = fmaxf(m, mo);
+            z = z * __builtin_amdgcn_exp2f(m - mn) + zo * __builtin_amdgcn_exp2f(mo - mn);
+            if (hi == 0) {
+                const int r = kWaveRows * wave + 32 * mt + n;
+                a.stats_part[((size_t)head * a.n_parts + blockIdx.x) * a.rows_pad + r] = make_float2(mn, z);
+            }
         }
     }
 }
@@ -1266,19 +1271,18 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
     p.rows = (cfg.n_q_heads / cfg.n_kv_heads) * cfg.window;
     const int nrw = n_row_slabs(p.rows), heads = cfg.batch * cfg.n_kv_heads;
     const bool wide = nrw == 0;
-    p.rows_pad = wide ? 16 * kWideTiles : nrw * kRowsPerWave;
+    p.rows_pad = wide ? kWideRows : nrw * kRowsPerWave;
     const int ks = wide ? 1 : 4 / nrw;                   // statistics a workgroup leaves per row
     p.n_chunks = (cfg.seq_len + 63) / 64;                // keys per chunk: 64
     // A workgroup pays for staging its query rows and waits for its first keys alone, so it should have
     // sixteen chunks (64 where the wave holds more rows), as long as that leaves two workgroups per CU;
     // beyond eight per CU more only cost.  Statistics + votes, us, with 512 / 1024 / 2048 workgroups: 8
     // heads of 32768 keys 18.4 + 14.8 / 19.5 + 16.2 / 22.0 + 17.3; 32 heads of 16384 29 + 26, 64 heads 55 + 46 and
-    // 128 heads 100 + 92 with any of them; with 256 rows 16 heads of 65536 keys 93 + 85 / 101 + 89 / 128 + 102 (the statistics
-    // without moving references, 3 % of them).
+    // 128 heads 100 + 92 with any of them; with 256 rows 8 heads of 131072 keys 87 + 78 / 88 + 79.
     const long long chunks = (long long)heads * p.n_chunks;
     const int total = (int)std::min(2048LL, std::max(512LL, chunks / (wide ? 64 : 16)));
     int n_wg = (total + heads - 1) / heads;
-    const int least = wide ? kScoreWaves : 2;
+    const int least = 2;
     if (n_wg > (p.n_chunks + least - 1) / least) n_wg = (p.n_chunks + least - 1) / least;
     if (n_wg < 1) n_wg = 1;
     p.chunks_per_wg = (p.n_chunks + n_wg - 1) / n_wg;
@@ -1334,7 +1338,7 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
         switch (n_row_slabs(plan.rows)) {
             case 1: e = launch_scores(score_pass<1, PASS_STATS>, score_pass<1, PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
             case 2: e = launch_scores(score_pass<2, PASS_STATS>, score_pass<2, PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
-            case 4: e = launch_scores(score_pass<4, PASS_STATS>, score_pass<4, PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
+                        case 4: e = launch_scores(score_pass<4, PASS_STATS>, score_pass<4, PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
             default: e = launch_scores(score_wide<PASS_STATS>, score_wide<PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
         }
         if (e != hipSuccess) return e;

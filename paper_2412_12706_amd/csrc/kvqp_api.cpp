@@ -228,15 +228,21 @@ static int compress_impl(const kvqp_cfg* cfg, const void* q_obs, const void* k, 
     hipStream_t stream = (hipStream_t)hip_stream;
     // The selection writes the caller's list and the quantizer reads it there: a copy of it between the two is a launch
     // that both wait for (3.8 us of 30 with 8 heads of 4096 tokens, 4.6 of 70 with 32768, 6.3 with 256 heads).
-    const bool in_place = idx_out && ((uintptr_t)idx_out & 3) == 0;
+    // A list that lies over the workspace or the queries, which are dead only when it has been made, is copied there.
+    const size_t idx_bytes = (size_t)heads * n_kept * sizeof(int32_t);
+    auto apart = [&](const void* p, size_t bytes) {
+        const uintptr_t a = (uintptr_t)idx_out, b = (uintptr_t)p;
+        return a + idx_bytes <= b || b + bytes <= a;
+    };
+    const bool in_place = idx_out && ((uintptr_t)idx_out & 3) == 0 && apart(workspace, workspace_bytes) &&
+                          apart(q_obs, (size_t)cfg->batch * cfg->n_q_heads * cfg->window * kHeadDim * 2);
     int32_t* idx = in_place ? idx_out : reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + plan.off_idx);
     if (head_budget && upload_counts(cache->head_n_kept, head_budget, heads, stream) != hipSuccess) return KVQP_ERR_HIP;
     if (n_kept == 0 && unrefined_out && upload_counts(unrefined_out, nullptr, heads, stream) != hipSuccess) return KVQP_ERR_HIP;   // nothing is cut
     if (n_kept > 0) {
         if (launch_select(*cfg, q_obs, k, idx, unrefined_out, workspace, plan, cache->head_n_kept, score, stream) != hipSuccess) return KVQP_ERR_HIP;
         if (idx_out && !in_place) {
-            const size_t bytes = (size_t)heads * n_kept * sizeof(int32_t);
-            if (hipMemcpyAsync(idx_out, idx, bytes, hipMemcpyDeviceToDevice, stream) != hipSuccess) return KVQP_ERR_HIP;
+            if (hipMemcpyAsync(idx_out, idx, idx_bytes, hipMemcpyDeviceToDevice, stream) != hipSuccess) return KVQP_ERR_HIP;
         }
     }
     if (launch_quant_pack(*cfg, k, v, idx, n_kept, cache->head_n_kept, *cache, stream) != hipSuccess) return KVQP_ERR_HIP;

@@ -228,3 +228,23 @@ def test_a_compress_workspace_without_room_for_all_pooled_scores_gives_the_same_
     assert torch.equal(got[0], got[1]) and bool((got[0].diff() > 0).all())
     with pytest.raises(kvqp.KvqpError):
         kvqp.compress(cfg, q_obs, k, v, kvqp.alloc_cache(cfg), workspace=kvqp.alloc_workspace(stated)[:least - 16])
+
+
+@pytest.mark.parametrize("where", ["workspace", "query"])
+def test_a_survivor_list_over_memory_that_dies_during_the_call(where):
+    """The selection writes the caller's list itself; a list laid over the workspace or the queries, which are read
+    until the list is complete, still comes out as one in memory of its own, and so does the cache."""
+    print(f"case list over {where}", flush=True)
+    P, W, Hkv, Gq, budget = 5000, 16, 2, 4, 700
+    q_obs, k, v = (dev(t) for t in synth.prompt_host(1, Hkv * Gq, Hkv, P + W, W, 128, config=87))
+    cfg = kvqp.Cfg(batch=1, n_q_heads=Hkv * Gq, n_kv_heads=Hkv, seq_len=P + W, window=W, budget=budget, bits=4, group_size=32)
+    ws = kvqp.alloc_workspace(kvqp.workspace_bytes(cfg)[0])
+    want = torch.empty((1, Hkv, budget), dtype=torch.int32, device="cuda")
+    ca, cb = kvqp.alloc_cache(cfg), kvqp.alloc_cache(cfg)
+    kvqp.compress(cfg, q_obs, k, v, ca, idx_out=want, workspace=ws)
+    over = ws if where == "workspace" else q_obs.view(torch.uint8).view(-1)
+    got = over[:4 * Hkv * budget].view(torch.int32).view(1, Hkv, budget)
+    kvqp.compress(cfg, q_obs, k, v, cb, idx_out=got, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    assert all(torch.equal(ca.buffers[n], cb.buffers[n]) for n in ca.buffers)

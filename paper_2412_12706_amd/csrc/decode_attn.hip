@@ -322,41 +322,50 @@ __device__ void merge_if_last(const DecodeArgs& a, int bh, int n_parts) {
     const __amdgpu_buffer_rsrc_t rs = part_rsrc(a.part + (size_t)bh * a.n_splits * GQ * kPartFloats, head_bytes);
     // Device-scope loads are slow (they go to the coherence point), so a whole batch of partials is
     // put in flight per round trip: one 16-byte load per partial and thread, a thread owning one
-    // pair of output channels.
-    constexpr int kMergeBatch = 32;
-    for (int item = threadIdx.x; item < GQ * kPartPairs; item += blockDim.x) {
-        const int h = item / kPartPairs, j = item % kPartPairs;
-        float M = kNegBig, acc0 = 0.f, acc1 = 0.f, L = 0.f;
-        for (int s0 = 0; s0 < n_parts; s0 += kMergeBatch) {
-            u4v v[kMergeBatch];
+    // pair of output channels.  A batch costs its full length in exponentials and multiply-adds, on one wave per SIMD that
+    // nothing hides, so it is four, sixteen or 32 partials long by how many there are (always 32: 8 heads of 1024 tokens in
+    // four workgroups each 8.5 us instead of 8.1, of 8192 in sixteen 11.9 instead of 11.6, 128 heads of 4096 in two 22.1
+    // instead of 21.7).  (Not each wave for itself, without barriers, in a field of the counter's word: atomics on
+    // one word follow each other at 60 ns, and four times as many of them take 15.7 us for the sixteen workgroups.)
+    auto merge = [&](auto length) {
+        constexpr int kMergeBatch = decltype(length)::value;
+        for (int item = threadIdx.x; item < GQ * kPartPairs; item += blockDim.x) {
+            const int h = item / kPartPairs, j = item % kPartPairs;
+            float M = kNegBig, acc0 = 0.f, acc1 = 0.f, L = 0.f;
+            for (int s0 = 0; s0 < n_parts; s0 += kMergeBatch) {
+                u4v v[kMergeBatch];
 #pragma unroll
-            for (int u4 = 0; u4 < kMergeBatch; u4 += 4) {
-                if (s0 + u4 < n_parts) {          // (uniform: whole groups of four beyond the last partial are not fetched)
+                for (int u4 = 0; u4 < kMergeBatch; u4 += 4) {
+                    if (kMergeBatch == 4 || s0 + u4 < n_parts) {          // (uniform: whole groups of four beyond the last partial are not fetched)
 #pragma unroll
-                    for (int u = u4; u < u4 + 4; ++u)
-                        v[u] = ld_dev16(rs, (unsigned)((min(s0 + u, n_parts - 1) * GQ + h) * kPartPairs + j) * 16u);
-                } else {
+                        for (int u = u4; u < u4 + 4; ++u)
+                            v[u] = ld_dev16(rs, (unsigned)((min(s0 + u, n_parts - 1) * GQ + h) * kPartPairs + j) * 16u);
+                    } else {
 #pragma unroll
-                    for (int u = u4; u < u4 + 4; ++u) { v[u][0] = __float_as_uint(kNegBig); v[u][1] = 0u; v[u][2] = 0u; v[u][3] = 0u; }
+                        for (int u = u4; u < u4 + 4; ++u) { v[u][0] = __float_as_uint(kNegBig); v[u][1] = 0u; v[u][2] = 0u; v[u][3] = 0u; }
+                    }
                 }
-            }
-            float Mn = M;
+                float Mn = M;
 #pragma unroll
-            for (int u = 0; u < kMergeBatch; ++u) Mn = fmaxf(Mn, __uint_as_float(v[u][0]));
-            const float keep = __builtin_amdgcn_exp2f(M - Mn);
-            acc0 *= keep; acc1 *= keep; L *= keep;
+                for (int u = 0; u < kMergeBatch; ++u) Mn = fmaxf(Mn, __uint_as_float(v[u][0]));
+                const float keep = __builtin_amdgcn_exp2f(M - Mn);
+                acc0 *= keep; acc1 *= keep; L *= keep;
 #pragma unroll
-            for (int u = 0; u < kMergeBatch; ++u) {
-                const float wgt = (s0 + u < n_parts) ? __builtin_amdgcn_exp2f(__uint_as_float(v[u][0]) - Mn) : 0.f;
-                acc0 = __builtin_fmaf(wgt, __uint_as_float(v[u][2]), acc0);
-                acc1 = __builtin_fmaf(wgt, __uint_as_float(v[u][3]), acc1);
-                L = __builtin_fmaf(wgt, __uint_as_float(v[u][1]), L);
+                for (int u = 0; u < kMergeBatch; ++u) {
+                    const float wgt = (s0 + u < n_parts) ? __builtin_amdgcn_exp2f(__uint_as_float(v[u][0]) - Mn) : 0.f;
+                    acc0 = __builtin_fmaf(wgt, __uint_as_float(v[u][2]), acc0);
+                    acc1 = __builtin_fmaf(wgt, __uint_as_float(v[u][3]), acc1);
+                    L = __builtin_fmaf(wgt, __uint_as_float(v[u][1]), L);
+                }
+                M = Mn;
             }
-            M = Mn;
+            const uint32_t lo = __half_as_ushort(__float2half_rn(acc0 / L)), hi = __half_as_ushort(__float2half_rn(acc1 / L));
+            reinterpret_cast<uint32_t*>(a.out + ((size_t)b * a.n_q_heads + g * GQ + h) * kHeadDim)[j] = lo | (hi << 16);
         }
-        const uint32_t lo = __half_as_ushort(__float2half_rn(acc0 / L)), hi = __half_as_ushort(__float2half_rn(acc1 / L));
-        reinterpret_cast<uint32_t*>(a.out + ((size_t)b * a.n_q_heads + g * GQ + h) * kHeadDim)[j] = lo | (hi << 16);
-    }
+    };
+    if (n_parts <= 4) merge(BoolI<4>{});
+    else if (n_parts <= 16) merge(BoolI<16>{});
+    else merge(BoolI<32>{});
 }
 
 // Value of lane ^ 16 / lane ^ 32.
@@ -1345,55 +1354,61 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
     // One pair of output channels (head hh, channels d, d + 1) per thread: the common reference over
     // the waves' states and this workgroup's share of the full-precision tail rows (the first four
     // waves' states in sT), then one pass that weighs and adds them.  All threads of a head read the
-    // same references and sums (LDS broadcasts); nw is a multiple of 4.
+    // same references and sums (LDS broadcasts); nw is 4, 8 or 12.  Written out for each, so that every read is on its way
+    // before the first is used (a loop over groups of four waves: 8 heads of 8192 tokens 11.6 us instead of 11.45, 128 heads
+    // of 4096 21.6 instead of 21.5).
     const __amdgpu_buffer_rsrc_t part_rs = part_rsrc(a.part + (size_t)bh * a.n_splits * GQ * kPartFloats, (unsigned)a.n_splits * GQ * kPartFloats * 4u);
-    for (int item = threadIdx.x; item < GQ * kPartPairs; item += blockDim.x) {
-        const int hh = item / kPartPairs, d = 2 * (item % kPartPairs);
-        const int cg = d / G;
-        float M = kNegBig;
-        for (int w0 = 0; w0 < nw; w0 += kWaves)
+    auto merge_waves = [&](auto waves) {
+        constexpr int NW = decltype(waves)::value, NS = NW * SLOTS;
+        for (int item = threadIdx.x; item < GQ * kPartPairs; item += blockDim.x) {
+            const int hh = item / kPartPairs, d = 2 * (item % kPartPairs);
+            const int cg = d / G;
+            auto state = [&](int i) { return sS + ((i / SLOTS) * 16 + (i % SLOTS) * 8 + 2 * hh) * 6; };   // of wave i / SLOTS
+            auto tail = [&](int w) { return sT + (w * GQ + hh) * kPartStride; };
+            float2 ml[NS], tl[kWaves];
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w)
+            for (int i = 0; i < NS; ++i) ml[i] = *reinterpret_cast<const float2*>(state(i));
 #pragma unroll
-                for (int sl = 0; sl < SLOTS; ++sl) M = fmaxf(M, sS[((w0 + w) * 16 + sl * 8 + 2 * hh) * 6]);
+            for (int w = 0; w < kWaves; ++w) tl[w] = *reinterpret_cast<const float2*>(tail(w));
+            float M = kNegBig;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, sT[(w * GQ + hh) * kPartStride]);
-        float acc0 = 0.f, acc1 = 0.f, L = 0.f;
-        for (int w0 = 0; w0 < nw; w0 += kWaves)
+            for (int i = 0; i < NS; ++i) M = fmaxf(M, ml[i].x);
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w)
+            for (int w = 0; w < kWaves; ++w) M = fmaxf(M, tl[w].x);
+            float acc0 = 0.f, acc1 = 0.f, L = 0.f;
 #pragma unroll
-                for (int sl = 0; sl < SLOTS; ++sl) {
-                    const float* st = sS + ((w0 + w) * 16 + sl * 8 + 2 * hh) * 6;
-                    const float2 ml = *reinterpret_cast<const float2*>(st);
-                    const float wgt = __builtin_amdgcn_exp2f(ml.x - M);
-                    const float2 o2 = *reinterpret_cast<const float2*>(sO + ((w0 + w) * 8 + sl * 4 + hh) * kHeadDim + d);
-                    float o0 = o2.x * kCodeUnit + st[2 + cg], o1 = o2.y * kCodeUnit + st[2 + cg];
-                    if constexpr (OUT) {
-                        const float2 c2 = *reinterpret_cast<const float2*>(s_oc + ((w0 + w) * 8 + sl * 4 + hh) * kHeadDim + d);
-                        o0 += c2.x; o1 += c2.y;
-                    }
-                    acc0 = __builtin_fmaf(wgt, o0, acc0);
-                    acc1 = __builtin_fmaf(wgt, o1, acc1);
-                    L = __builtin_fmaf(wgt, ml.y, L);
+            for (int i = 0; i < NS; ++i) {
+                const float wgt = __builtin_amdgcn_exp2f(ml[i].x - M), z = state(i)[2 + cg];
+                const int at = ((i / SLOTS) * 8 + (i % SLOTS) * 4 + hh) * kHeadDim + d;
+                const float2 o2 = *reinterpret_cast<const float2*>(sO + at);
+                float o0 = o2.x * kCodeUnit + z, o1 = o2.y * kCodeUnit + z;
+                if constexpr (OUT) {
+                    const float2 c2 = *reinterpret_cast<const float2*>(s_oc + at);
+                    o0 += c2.x; o1 += c2.y;
                 }
+                acc0 = __builtin_fmaf(wgt, o0, acc0);
+                acc1 = __builtin_fmaf(wgt, o1, acc1);
+                L = __builtin_fmaf(wgt, ml[i].y, L);
+            }
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            const float* row = sT + (w * GQ + hh) * kPartStride;
-            const float2 ml = *reinterpret_cast<const float2*>(row);
-            const float2 o2 = *reinterpret_cast<const float2*>(row + 2 + d);
-            const float wgt = __builtin_amdgcn_exp2f(ml.x - M);
-            acc0 = __builtin_fmaf(wgt, o2.x, acc0);
-            acc1 = __builtin_fmaf(wgt, o2.y, acc1);
-            L = __builtin_fmaf(wgt, ml.y, L);
+            for (int w = 0; w < kWaves; ++w) {
+                const float2 o2 = *reinterpret_cast<const float2*>(tail(w) + 2 + d);
+                const float wgt = __builtin_amdgcn_exp2f(tl[w].x - M);
+                acc0 = __builtin_fmaf(wgt, o2.x, acc0);
+                acc1 = __builtin_fmaf(wgt, o2.y, acc1);
+                L = __builtin_fmaf(wgt, tl[w].y, L);
+            }
+            if (n_parts == 1) {      // the whole head was here: normalise, round once, done
+                const uint32_t lo = __half_as_ushort(__float2half_rn(acc0 / L)), hi = __half_as_ushort(__float2half_rn(acc1 / L));
+                reinterpret_cast<uint32_t*>(a.out + ((size_t)b * a.n_q_heads + g * GQ + hh) * kHeadDim)[d >> 1] = lo | (hi << 16);
+            } else {                 // this split's record of the pair, reference and sum beside it
+                st_dev16(part_rs, (unsigned)((blockIdx.x * GQ + hh) * kPartPairs + (d >> 1)) * 16u, M, L, acc0, acc1);
+            }
         }
-        if (n_parts == 1) {      // the whole head was here: normalise, round once, done
-            const uint32_t lo = __half_as_ushort(__float2half_rn(acc0 / L)), hi = __half_as_ushort(__float2half_rn(acc1 / L));
-            reinterpret_cast<uint32_t*>(a.out + ((size_t)b * a.n_q_heads + g * GQ + hh) * kHeadDim)[d >> 1] = lo | (hi << 16);
-        } else {                 // this split's record of the pair, reference and sum beside it
-            st_dev16(part_rs, (unsigned)((blockIdx.x * GQ + hh) * kPartPairs + (d >> 1)) * 16u, M, L, acc0, acc1);
-        }
-    }
+    };
+    if (nw == 4) merge_waves(BoolI<4>{});
+    else if (pipe_max_waves(BITS, GQ, OUT) <= 8 || nw == 8) merge_waves(BoolI<8>{});
+    else merge_waves(BoolI<12>{});
     if (n_parts == 1) return;
     merge_if_last<GQ>(a, bh, n_parts);
 }

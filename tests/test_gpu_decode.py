@@ -103,6 +103,19 @@ def test_more_partials_than_one_merge_round(orc, bits, Gq, n_kept, splits):
     assert err <= TOL
 
 
+@pytest.mark.parametrize("bits,Gq,splits", [(4, 4, 4), (4, 4, 5), (2, 8, 16), (8, 1, 17), (4, 2, 32), (4, 4, 33)])
+def test_partials_around_the_lengths_of_a_merge_batch(orc, bits, Gq, splits):
+    """A head's partials are fetched four, sixteen or 32 at a time by how many there are: one more or less than
+    each, every (batch, KV head) equal to the checker."""
+    print(f"case batch bits={bits} Gq={Gq} splits={splits}", flush=True)
+    cfg, oc = build_case(orc, bits, 32, 0, Gq, 64 * splits - 32 * (bits != 2), 16, 1, 2)
+    cfg.decode_splits = splits
+    gc = upload_cache(oc)
+    q = synth.decode_query_host(1, cfg.n_q_heads, 128, config=51, step=splits)
+    out = kvqp.decode_attn(cfg, dev(q), gc).cpu().numpy().astype(np.float64)
+    assert np.abs(out - orc.decode_attn(q, oc, cfg.sm_scale)).max() <= TOL
+
+
 def test_peaked_attention_and_large_logits(orc):
     """One key strongly aligned with the query (softmax mass on one token) and
     x20 outlier channels: the hi/lo operand split has to hold up."""

@@ -31,6 +31,7 @@ namespace kvqp {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr uint32_t kBlockCount = 0x80000000u;   // overflow prefix array, until ovf_fill has been there: a block's own count
 
 // One launch of the quantize-and-pack kernel: n_tok rows per head of (k, v) -- rows idx[...] or, with
 // idx == NULL, rows 0 .. n_tok-1 -- land at tokens dst_base .. of a cache laid out for n_cap tokens.
@@ -236,7 +237,7 @@ __global__ __launch_bounds__(kThreads, quant_waves(BITS, G, OUT)) void gather_qu
     // head's; it closes the tail up when it is done with them.
     // OUT: outlier filtering; k_out / v_out receive four slot words per token row, and the number of
     // a block's further outliers is left at entry (block + 1) of the head's overflow prefix array
-    // (k_ovf / v_ovf), which ovf_scan then turns into prefix counts and ovf_fill completes.
+    // (k_ovf / v_ovf), which ovf_fill turns into prefix counts before it writes the entries.
     constexpr bool QUANT = BITS != 16;
     constexpr int TB = quant_tokens(BITS, G);            // tokens per workgroup
     constexpr int R = TB / 16;                            // rows per thread
@@ -634,44 +635,19 @@ __global__ __launch_bounds__(kThreads, quant_waves(BITS, G, OUT)) void gather_qu
         const int tensor = threadIdx.x / (TB / 32), blk = threadIdx.x % (TB / 32);
         if (threadIdx.x < 2 * (TB / 32) && 32 * blk < ntok) {
             uint32_t* ovf = (tensor ? v_ovf : k_ovf) + (size_t)head * ovf_words(n_cap, ovf_cap);
-            ovf[d0 / 32 + blk + 1] = (uint32_t)s_cnt[tensor][blk];
+            ovf[d0 / 32 + blk + 1] = (uint32_t)s_cnt[tensor][blk] | kBlockCount;
         }
     }
 }
 
-// Raw block counts -> prefix counts, in place: entry b + 1 of a head's prefix array holds the
-// number of overflow outliers of block b (left there by the quantizer) for blocks first .. first +
-// n - 1, and entry `first` the prefix so far (set to 0 here when first == 0).  One wave per (head,
-// tensor); 64 blocks per round.
-__global__ __launch_bounds__(64) void ovf_scan(uint32_t* __restrict__ k_ovf, uint32_t* __restrict__ v_ovf, int n_cap, int ovf_cap,
-                                               int dst_base, int n_tok, const int32_t* __restrict__ head_n,
-                                               const int32_t* __restrict__ head_base, int base_quantum) {
-    const int head = blockIdx.x, lane = threadIdx.x;
-    uint32_t* start = (blockIdx.y ? v_ovf : k_ovf) + (size_t)head * ovf_words(n_cap, ovf_cap);
-    int base = dst_base;
-    if (head_base) {
-        base = min(max(head_base[head], 0), dst_base);
-        base -= base % base_quantum;
-    }
-    const int n_head = head_n ? min(max(head_n[head], 0), n_tok) : n_tok;
-    const int first = base / 32, n = (n_head + 31) / 32;
-    if (first == 0 && lane == 0) start[0] = 0u;
-    __syncthreads();
-    uint32_t carry = start[first];
-    for (int b0 = 0; b0 < n; b0 += 64) {
-        const int b = b0 + lane;
-        uint32_t v = b < n ? start[first + b + 1] : 0u;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t o = __shfl_up(v, off);
-            if (lane >= off) v += o;
-        }
-        if (b < n) start[first + b + 1] = carry + v;
-        carry += __shfl(v, 63);
-    }
-}
-
-// The overflow entries of one block of 32 tokens (one wave): the block's rows are read again, the
+// The prefix counts and overflow entries of one block of 32 tokens (one wave).  The quantizer has left every
+// block's own number of overflow outliers, marked by kBlockCount, at the block's entry + 1 of the head's prefix
+// array; here the mark goes and the number becomes the prefix count.  An entry of the array is
+// one or the other at any time and tells which, so a wave adds up the blocks before its own, backwards
+// up to the first prefix count that it meets, without waiting for anyone: a prefix count that was stored
+// meanwhile only saves it the rest.  (A kernel of its own for the prefix counts, one wave per head and
+// tensor, was a launch between two others and went through a long head 64 blocks at a time.)
+// Then the block's rows are read again, the
 // outliers beyond a row's fourth found in channel order, and written as (word, token) at the block's
 // place in the head's list -- position = prefix count of the block + entries of the block's earlier
 // rows -- unless they lie beyond the list's capacity.  Most blocks have none and leave at once.
@@ -690,11 +666,37 @@ __global__ __launch_bounds__(64) void ovf_fill(const uint16_t* __restrict__ k, c
     }
     const int n_head = head_n ? min(max(head_n[head], 0), n_kept) : n_kept;
     const int t0 = 32 * blockIdx.x;
-    if (t0 >= n_head) return;
     uint32_t* ovf = (tensor ? v_ovf : k_ovf) + (size_t)head * ovf_words(n_cap, ovf_cap);
-    const int blk = (base + t0) / 32;
-    uint32_t at = ovf[blk];
-    if (ovf[blk + 1] == at) return;                  // (wave-uniform) nothing beyond the slots in this block
+    const int first = base / 32, blk = first + (int)blockIdx.x;
+    if (first == 0 && t0 == 0 && lane == 0) ovf[0] = 0u;
+    if (t0 >= n_head) return;
+    auto entry = [&](int i) { return __hip_atomic_load(ovf + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+    const uint32_t own = entry(blk + 1) & ~kBlockCount;
+    uint32_t at = 0u;                                // entries of the blocks before this one
+    constexpr int kAhead = 4;                        // entries per lane and step: 256 blocks
+    for (int top = blk; ; top -= 64 * kAhead) {      // entries top, top - 1, ...; entry `first` is a prefix count (0 at a head's start)
+        uint32_t v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int i = top - 64 * u - lane;
+            const uint32_t x = entry(max(i, first));
+            v[u] = i > first ? x : first > 0 ? x & ~kBlockCount : 0u;
+        }
+        bool known = false;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const unsigned long long done = __builtin_amdgcn_ballot_w64((v[u] & kBlockCount) == 0u);    // prefix counts
+            const int last = done ? __builtin_ctzll(done) : 63;
+            uint32_t add = known || lane > last ? 0u : v[u] & ~kBlockCount;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) add += __shfl_xor(add, off);
+            at += add;
+            known = known || done != 0ull;
+        }
+        if (known) break;
+    }
+    if (lane == 0) __hip_atomic_store(ovf + blk + 1, at + own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (own == 0u) return;                           // (wave-uniform) nothing beyond the slots in this block
     uint32_t* entries = ovf + ovf_start_words(n_cap);
     const uint16_t* src = (tensor ? v : k) + (size_t)head * L * kHeadDim;
     const unsigned long long lt_mask = (1ull << lane) - 1ull;
@@ -745,8 +747,6 @@ hipError_t launch_bits_g(const QuantPackJob& j, hipStream_t stream) {
     hipError_t e = hipGetLastError();
     if constexpr (OUT) {
         if (e != hipSuccess || j.n_tok == 0) return e;
-        hipLaunchKernelGGL(ovf_scan, dim3(j.heads, 2), dim3(64), 0, stream, (uint32_t*)j.c.k_ovf, (uint32_t*)j.c.v_ovf, j.n_cap,
-                           j.ovf_cap, j.dst_base, j.n_tok, j.head_n, j.head_base, j.base_quantum);
         hipLaunchKernelGGL((ovf_fill<G>), dim3((j.n_tok + 31) / 32, j.heads, 2), dim3(64), 0, stream, (const uint16_t*)j.k,
                            (const uint16_t*)j.v, j.idx, (const uint16_t*)j.c.k_zero, (const uint16_t*)j.c.v_zero,
                            (uint32_t*)j.c.k_ovf, (uint32_t*)j.c.v_ovf, j.src_rows, j.n_tok, j.key_axis, j.n_cap, j.dst_base,

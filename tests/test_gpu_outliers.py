@@ -183,6 +183,37 @@ def test_head_level_counts_and_append_with_outliers(orc):
     del grow_ref
 
 
+@pytest.mark.parametrize("n", [33, 2048, 2081, 8192, 8225, 16449])
+def test_prefix_counts_over_many_blocks(orc, n):
+    """The waves that fill the list add up the counts of the blocks before their own, 64 at a time and four times as many in
+    flight: lists of one block more or fewer than that, nearly every block with entries; and heads with counts of their own."""
+    print(f"case blocks n={n}", flush=True)
+    W, cap = 8, 4 * n
+    _, k, v = prompt(1, 2, 2, n + W, W, config=88, extra_k_channels=(50, 51, 90))
+    idx = np.broadcast_to(np.arange(n, dtype=np.int32), (1, 2, n)).copy()
+    oc = orc.quantize_selected(k, v, idx, W=W, bits=4, G=32, key_axis=1, tau=TAU, ovf_cap=cap)
+    cfg = kvqp.Cfg(batch=1, n_q_heads=2, n_kv_heads=2, seq_len=n + W, window=W, budget=n, bits=4, group_size=32, key_axis=1,
+                   outlier_threshold=TAU, outlier_overflow_cap=cap)
+    gc = kvqp.alloc_cache(cfg)
+    for t in gc.buffers.values():
+        t.fill_(0xA5)
+    kvqp.quantize_selected(cfg, dev(k), dev(v), dev(idx), gc)
+    torch.cuda.synchronize()
+    assert_cache_equal(gc, oc)
+    counts = [n // 2 + 1, 0]
+    rc = kvqp.alloc_cache(cfg, ragged=True)
+    for t in rc.buffers.values():
+        t.fill_(0xA5)
+    kvqp.quantize_selected_ragged(cfg, dev(k), dev(v), dev(idx), counts, rc)
+    torch.cuda.synchronize()
+    half = orc.quantize_selected(k[:, :1], v[:, :1], idx[:, :1, :counts[0]], W=W, bits=4, G=32, key_axis=1, tau=TAU, ovf_cap=cap)
+    nb = -(-counts[0] // 32)
+    for nm in ("k_ovf", "v_ovf"):
+        got = rc.buffers[nm].cpu().numpy().view(np.uint32).reshape(2, -1)
+        assert_overflow_equal(got[0], n, getattr(half, nm)[0, 0], counts[0], cap, nm)
+        assert got[1][0] == 0
+
+
 def test_list_that_is_too_short_shows_its_shortfall(orc):
     """A caller that sizes the overflow list too small loses the entries beyond it -- those elements
     read as their group's zero -- and sees it: the last prefix count is the number needed.  Library

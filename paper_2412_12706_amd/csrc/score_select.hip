@@ -582,7 +582,7 @@ __global__ __launch_bounds__(256) void stats_combine(const float2* __restrict__ 
 //                sweep over the 16-bit codes leaves a mask bit per sure survivor and
 //                collects the few candidates of that bin, whose scores are pooled
 //                again and give the exact cut; survivors leave through the mask.
-// Prefixes of one pooling tile (4096) do both in the second kernel.  A single
+// Prefixes of up to three pooling tiles (4096) do both in the second kernel.  A single
 // workgroup per head that did everything, with a four-pass radix select over all
 // scores, took 45 / 87 / 310 us for 8 heads of 4064 / 32736 / 131008 candidates
 // and 120 us for 256 heads of 32736; these take 9 / 5 + 21 / 5 + 35 and 12 + 29 us.
@@ -826,19 +826,20 @@ __global__ __launch_bounds__(kSelThreads) void pool_scores(const SelectArgs a) {
 }
 
 // One workgroup per (batch, kv head).  keep: the survivor mask, bit j % 8 of byte j / 8.
-// ONE: the whole prefix is one pooling tile, pooled and counted here; thread t keeps the scores of
-// candidates 4 t .. 4 t + 3.
-template <bool ONE>
+// T > 0: the prefix is at most T pooling tiles, pooled and counted here; of every tile thread t keeps the scores of
+// candidates 4 t .. 4 t + 3.  T = 0: pool_scores has left codes and counts.
+template <int T>
 __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
-    __shared__ __align__(16) uint32_t keep[(ONE ? kPoolTile : kMaxPrefix) / 32];
-    __shared__ __align__(16) int tab[2 * kSelThreads + (1 << kDigit)];   // the band, then:
+    constexpr bool OWN = T > 0;
+    __shared__ __align__(16) uint32_t keep[(OWN ? T * kPoolTile : kMaxPrefix) / 32];
+    __shared__ __align__(16) int tab[2 * kSelThreads + (1 << kDigit)];   // the counts of the bins (OWN); later the band, then:
     int* hist = tab + 2 * kSelThreads;                            // radix digits; later the positions to re-score
     uint32_t* ties = reinterpret_cast<uint32_t*>(tab);            // where binary32 decides: the mask of the candidates equal to the cut
-    __shared__ __align__(16) unsigned char big[kListCap * 8];     // candidates around the cut, or (too many) the pooling stage; before that the pooling stage and the bins (ONE); later the binary64 votes
+    __shared__ __align__(16) unsigned char big[T > 1 ? 2 * kStage * 4 : kListCap * 8];     // candidates around the cut, or (too many) the pooling stage; before that the pooling stage (OWN); later the binary64 votes
     __shared__ int swave[kSelWaves];
     __shared__ int s_bin, s_list, s_sure, s_need, s_band, s_hot;
     __shared__ uint32_t s_prefix;
-    static_assert(kListCap * 8 >= kStage * 4 && kListCap * 8 >= kBins * 4 && kListCap * 8 >= (kPartSlots + kVoteSlots) * 8 &&
+    static_assert(kListCap * 8 >= kStage * 4 && sizeof(tab) >= kBins * 4 && kListCap * 8 >= (kPartSlots + kVoteSlots) * 8 &&
                   sizeof(tab) >= kMaxPrefix / 8 && kVoteSlots <= (1 << kDigit), "aliases fit");
 
     const int head = blockIdx.x;
@@ -859,27 +860,39 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
 
     // ---- the bin of the k-th largest score ----
     const int n_oct = (P + 7) / 8;
-    uint4 oct[ONE ? 1 : kOctets];                  // the thread's octets of codes: thread + 1024 i
-    uint32_t own[4];                               // ONE: the thread's scores (all ones past the end: neither above nor around the cut)
+    uint4 oct[OWN ? 1 : kOctets];                  // the thread's octets of codes: thread + 1024 i
+    uint32_t own[OWN ? 4 * T : 1];                 // OWN: the thread's scores (all ones past the end: neither above nor around the cut)
+    auto own_at = [&](int i) { return (i >> 2) * kPoolTile + 4 * (int)threadIdx.x + (i & 3); };   // ... and their candidates
     int c[4] = {0, 0, 0, 0};                       // counts of bins 4 thread .. 4 thread + 3
-    if constexpr (ONE) {
-        float* stage = reinterpret_cast<float*>(big);
-        stage_votes(fetch_votes(vote, P, r, 0), stage);
-        if (threadIdx.x < kPoolTile / 32) keep[threadIdx.x] = 0u;
-        __syncthreads();
-        const float4 o = pool_four(stage, r);
-        __syncthreads();
-        const float ov[4] = {o.x, o.y, o.z, o.w};
-        int* bins = reinterpret_cast<int*>(big);
-        *reinterpret_cast<int4*>(bins + 4 * threadIdx.x) = make_int4(0, 0, 0, 0);
-        __syncthreads();
+    if constexpr (OWN) {
+        const int n_tiles = (P + kPoolTile - 1) / kPoolTile;
+        // (two places for a tile's votes, one barrier per tile; two tiles' votes on their way while one is pooled)
+        VoteTile next[2] = {fetch_votes(vote, P, r, 0), {}};
+        if (T > 1 && n_tiles > 1) next[1] = fetch_votes(vote, P, r, kPoolTile);
+        for (int i = threadIdx.x; i < T * kPoolTile / 32; i += kSelThreads) keep[i] = 0u;
+        *reinterpret_cast<int4*>(tab + 4 * threadIdx.x) = make_int4(0, 0, 0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            own[i] = 4 * (int)threadIdx.x + i < P ? score_key(ov[i]) : 0xffffffffu;
-            if (4 * (int)threadIdx.x + i < P) atomicAdd(&bins[score_bin(own[i])], 1);
+        for (int q = 0; q < T; ++q) {
+            if (q < n_tiles) {
+                float* stage = reinterpret_cast<float*>(big) + (q & 1) * kStage;
+                stage_votes(next[q & 1], stage);
+                __syncthreads();
+                if (q + 2 < T && q + 2 < n_tiles) next[q & 1] = fetch_votes(vote, P, r, (q + 2) * kPoolTile);
+                const float4 o = pool_four(stage, r);
+                const float ov[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool in = own_at(4 * q + i) < P;
+                    own[4 * q + i] = in ? score_key(ov[i]) : 0xffffffffu;
+                    if (in) atomicAdd(&tab[score_bin(own[4 * q + i])], 1);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) own[4 * q + i] = 0xffffffffu;
+            }
         }
         __syncthreads();
-        const int4 b = *reinterpret_cast<const int4*>(bins + 4 * threadIdx.x);
+        const int4 b = *reinterpret_cast<const int4*>(tab + 4 * threadIdx.x);
         c[0] = b.x; c[1] = b.y; c[2] = b.z; c[3] = b.w;
     } else {
         const uint2* bins = reinterpret_cast<const uint2*>(a.bins + (size_t)head * a.n_seg * kBins) + threadIdx.x;
@@ -919,18 +932,21 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     uint32_t* list_key = reinterpret_cast<uint32_t*>(big);
     int* list_pos = reinterpret_cast<int*>(big + kListCap * 4);
     int sure = 0;
-    if constexpr (ONE) {
-        uint32_t bits = 0u;
+    if constexpr (OWN) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) bits |= (int)own[i] > (int)khi ? 1u << i : 0u;
-        sure = __popc(bits);
-        if (bits) atomicOr(&keep[threadIdx.x >> 3], bits << (4 * (threadIdx.x & 7)));
+        for (int q = 0; q < T; ++q) {
+            uint32_t bits = 0u;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (own[i] >= klo && own[i] <= khi) {
-                const int e = atomicAdd(&s_list, 1);
-                if (e < kListCap) list_key[e] = own[i];
-            }
+            for (int i = 0; i < 4; ++i) bits |= (int)own[4 * q + i] > (int)khi ? 1u << i : 0u;
+            sure += __popc(bits);
+            if (bits) atomicOr(&keep[q * (kPoolTile / 32) + (threadIdx.x >> 3)], bits << (4 * (threadIdx.x & 7)));
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (own[4 * q + i] >= klo && own[4 * q + i] <= khi) {
+                    const int e = atomicAdd(&s_list, 1);
+                    if (e < kListCap) list_key[e] = own[4 * q + i];
+                }
+        }
     } else {
 #pragma unroll
         for (int i = 0; i < kOctets; ++i) {
@@ -969,7 +985,7 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
         }
         return score_key(best);
     };
-    if constexpr (!ONE) {
+    if constexpr (!OWN) {
         if (n_list <= kListCap)
             for (int e = threadIdx.x; e < n_list; e += kSelThreads) list_key[e] = pooled_key(list_pos[e]);   // (read back by the same thread only)
     }
@@ -980,7 +996,7 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     // pooling every candidate by itself on every visit took 214 / 726; scores spread evenly over 0.1 %,
     // 125 / 379 against 184 / 613.)
     float* exact = a.exact ? a.exact + (size_t)head * a.p_stride : nullptr;
-    if constexpr (!ONE) {
+    if constexpr (!OWN) {
         if (__builtin_expect(n_list > kListCap && exact, 0)) {
             float* stage = reinterpret_cast<float*>(big);
             VoteTile next = fetch_votes(vote, P, r, 0);
@@ -994,13 +1010,13 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
             }
         }
     }
-    // every candidate around the cut: from the thread's own scores (ONE), from the list (in no
+    // every candidate around the cut: from the thread's own scores (OWN), from the list (in no
     // particular order) or from all pooled scores
     auto each_around = [&](auto visit) {
-        if constexpr (ONE) {
+        if constexpr (OWN) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (own[i] >= klo && own[i] <= khi) visit(own[i], 4 * (int)threadIdx.x + i);
+            for (int i = 0; i < 4 * T; ++i)
+                if (own[i] >= klo && own[i] <= khi) visit(own[i], own_at(i));
         } else if (__builtin_expect(n_list <= kListCap, 1)) {
             for (int e = threadIdx.x; e < n_list; e += kSelThreads) visit(list_key[e], list_pos[e]);
         } else if (!exact) {
@@ -1352,11 +1368,17 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
     s.bins = reinterpret_cast<uint16_t*>(base + plan.off_stats_part);
     s.exact = plan.exact_bytes > 0 ? reinterpret_cast<float*>(base + plan.total) : nullptr;
     s.p_stride = plan.p_stride; s.n_seg = plan.n_seg; s.seg_tiles = plan.seg_tiles;
-    if (plan.P <= kPoolTile) {
-        hipLaunchKernelGGL(select_topk<true>, dim3(heads), dim3(kSelThreads), 0, stream, s);
-    } else {
+    auto own = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(heads), dim3(kSelThreads), 0, stream, s); };
+    // Up to three pooling tiles per workgroup: the launch before it and the codes' way through memory are worth more than
+    // the workgroups that pool side by side (whole calls, us, two kernels -> one: 8 heads of 8192 keys 41.3 -> 35.1, of 12000 43.7 ->
+    // 38.9, 32 heads 68.8 -> 62.1 and 88.5 -> 84.5, 128 heads 184.6 -> 177.5 and 241.7 -> 239.2).  From four on the votes, four
+    // bytes each through one CU, take longer: 8 heads of 16384 keys 51.1 -> 52.3, of 20000 60.3 -> 65.7, 32 heads 117.4 -> 118.9.
+    if (plan.P <= kPoolTile) own(select_topk<1>);
+    else if (plan.P <= 2 * kPoolTile) own(select_topk<2>);
+    else if (plan.P <= 3 * kPoolTile) own(select_topk<3>);
+    else {
         if (score) hipLaunchKernelGGL(pool_scores, dim3(plan.n_seg, heads), dim3(kSelThreads), 0, stream, s);
-        hipLaunchKernelGGL(select_topk<false>, dim3(heads), dim3(kSelThreads), 0, stream, s);
+        own(select_topk<0>);
     }
     return hipGetLastError();
 }

@@ -40,6 +40,16 @@ def test_survivors_match_the_checker(orc, P, pool, budget):
     assert unrefined == [0, 0]
 
 
+@pytest.mark.parametrize("P,pool,budget", [(4097, 63, 4096), (8192, 7, 3000), (8193, 1, 8192), (9001, 5, 1), (12288, 63, 2500), (12289, 7, 12288)])
+def test_prefixes_of_two_and_three_pooling_tiles(orc, P, pool, budget):
+    """Up to three tiles the selection pools and counts by itself, beyond them a kernel before it does: both sides of
+    each line, windows that reach into the next tile, cuts at either end."""
+    print(f"case tiles P={P} pool={pool} budget={budget}", flush=True)
+    got, idx, pooled, unrefined = select(orc, P, 8, pool, budget, seed=90 + P % 5)
+    check_indices(got, idx, pooled)
+    assert unrefined == [0, 0]
+
+
 @pytest.mark.parametrize("P,budget", [(3000, 2850), (9000, 8700)])
 def test_cut_in_the_lowest_score_bin(orc, P, budget):
     """A single sharp row spreads its votes over ninety factors of two: the cut lies below 2^-55, where
@@ -248,3 +258,22 @@ def test_a_survivor_list_over_memory_that_dies_during_the_call(where):
     torch.cuda.synchronize()
     assert torch.equal(got, want)
     assert all(torch.equal(ca.buffers[n], cb.buffers[n]) for n in ca.buffers)
+
+
+def test_a_compress_workspace_without_room_for_all_pooled_scores_beyond_three_tiles():
+    """The same where the pooled scores pass through memory: prefixes of more than three pooling tiles, more
+    candidates around the cut than the list holds."""
+    print("case smaller compress workspace, long", flush=True)
+    P, W, Hkv, budget = 13003, 8, 2, 5000
+    q_obs, k, v = (dev(t) for t in synth.prompt_host(1, Hkv * 2, Hkv, P + W, W, 128, outlier=1.0, config=93))
+    k[:, :, :P] = (k[:, :, :1].float() + 0.002 * k[:, :, :P].float()).half()
+    cfg = kvqp.Cfg(batch=1, n_q_heads=Hkv * 2, n_kv_heads=Hkv, seq_len=P + W, window=W, pool_kernel=5, budget=budget, bits=4, group_size=32)
+    stated = kvqp.workspace_bytes(cfg)[0]
+    least = stated - Hkv * -(-P // 8) * 32
+    got = []
+    for size in (stated, least):
+        idx = torch.full((1, Hkv, budget), -1, dtype=torch.int32, device="cuda")
+        kvqp.compress(cfg, q_obs, k, v, kvqp.alloc_cache(cfg), idx_out=idx, workspace=kvqp.alloc_workspace(stated)[:size])
+        torch.cuda.synchronize()
+        got.append(idx)
+    assert torch.equal(got[0], got[1]) and bool((got[0].diff() > 0).all())

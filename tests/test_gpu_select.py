@@ -277,3 +277,10 @@ def test_a_compress_workspace_without_room_for_all_pooled_scores_beyond_three_ti
         torch.cuda.synchronize()
         got.append(idx)
     assert torch.equal(got[0], got[1]) and bool((got[0].diff() > 0).all())
+
+
+def test_unusual_cuts_beyond_three_tiles(orc):
+    """The lowest score bin, ties beyond the list and votes that are not numbers, where codes and counts pass through memory."""
+    test_cut_in_the_lowest_score_bin(orc, 13500, 13100)
+    test_more_ties_than_the_list_holds(orc, 14000, 4000, 2)
+    test_votes_that_are_not_numbers_still_give_every_survivor(13001, 4, 32, 7, 4000, "query", float("nan"))

@@ -322,7 +322,8 @@ __device__ void merge_if_last(const DecodeArgs& a, int bh, int n_parts) {
     const __amdgpu_buffer_rsrc_t rs = part_rsrc(a.part + (size_t)bh * a.n_splits * GQ * kPartFloats, head_bytes);
     // Device-scope loads are slow (they go to the coherence point), so a whole batch of partials is
     // put in flight per round trip: one 16-byte load per partial and thread, a thread owning one
-    // pair of output channels.  A batch costs its full length in exponentials and multiply-adds, on one wave per SIMD that
+    // pair of output channels (reference and sum apart from the channels, half the bytes in twice the loads: 11.5 -> 11.8 us
+    // for sixteen partials).  A batch costs its full length in exponentials and multiply-adds, on one wave per SIMD that
     // nothing hides, so it is four, sixteen or 32 partials long by how many there are (always 32: 8 heads of 1024 tokens in
     // four workgroups each 8.5 us instead of 8.1, of 8192 in sixteen 11.9 instead of 11.6, 128 heads of 4096 in two 22.1
     // instead of 21.7).  (Not each wave for itself, without barriers, in a field of the counter's word: atomics on
@@ -1359,44 +1360,91 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
     // of 4096 21.6 instead of 21.5).
     const __amdgpu_buffer_rsrc_t part_rs = part_rsrc(a.part + (size_t)bh * a.n_splits * GQ * kPartFloats, (unsigned)a.n_splits * GQ * kPartFloats * 4u);
     auto merge_waves = [&](auto waves) {
-        constexpr int NW = decltype(waves)::value, NS = NW * SLOTS;
-        for (int item = threadIdx.x; item < GQ * kPartPairs; item += blockDim.x) {
+        // Up to four query heads, which occupy four waves at most: every four waves are a group that merges the states of
+        // its own waves (the first one the tail rows' too); the groups beyond the first leave their sums where their own first
+        // two states were, which no other thread reads, and the first group adds them up (128 heads of 4096 tokens, twelve
+        // waves: 21.5 -> 21.25 us; the first four waves alone went through 28 states there, 1.2 us of the launch's end).
+        constexpr int NW = decltype(waves)::value, GROUPS = GQ <= 4 ? NW / kWaves : 1, WPG = NW / GROUPS, NS = WPG * SLOTS;
+        constexpr int THREADS = 64 * WPG, ITEMS = (GQ * kPartPairs + THREADS - 1) / THREADS;     // of a group; of a thread
+        const int grp = GROUPS > 1 ? wave / kWaves : 0, t = GROUPS > 1 ? threadIdx.x & (THREADS - 1) : threadIdx.x;
+        float2 acc[ITEMS], ML[ITEMS];
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const int item = t + it * THREADS;
+            if (item >= GQ * kPartPairs) break;
             const int hh = item / kPartPairs, d = 2 * (item % kPartPairs);
             const int cg = d / G;
-            auto state = [&](int i) { return sS + ((i / SLOTS) * 16 + (i % SLOTS) * 8 + 2 * hh) * 6; };   // of wave i / SLOTS
+            auto state = [&](int i) { return sS + ((grp * WPG + i / SLOTS) * 16 + (i % SLOTS) * 8 + 2 * hh) * 6; };   // of wave i / SLOTS of the group
+            auto place = [&](int i) { return ((grp * WPG + i / SLOTS) * 8 + (i % SLOTS) * 4 + hh) * kHeadDim + d; };
             auto tail = [&](int w) { return sT + (w * GQ + hh) * kPartStride; };
             float2 ml[NS], tl[kWaves];
 #pragma unroll
             for (int i = 0; i < NS; ++i) ml[i] = *reinterpret_cast<const float2*>(state(i));
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) tl[w] = *reinterpret_cast<const float2*>(tail(w));
             float M = kNegBig;
 #pragma unroll
             for (int i = 0; i < NS; ++i) M = fmaxf(M, ml[i].x);
+            if (grp == 0) {
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) M = fmaxf(M, tl[w].x);
+                for (int w = 0; w < kWaves; ++w) { tl[w] = *reinterpret_cast<const float2*>(tail(w)); M = fmaxf(M, tl[w].x); }
+            }
             float acc0 = 0.f, acc1 = 0.f, L = 0.f;
 #pragma unroll
             for (int i = 0; i < NS; ++i) {
                 const float wgt = __builtin_amdgcn_exp2f(ml[i].x - M), z = state(i)[2 + cg];
-                const int at = ((i / SLOTS) * 8 + (i % SLOTS) * 4 + hh) * kHeadDim + d;
-                const float2 o2 = *reinterpret_cast<const float2*>(sO + at);
+                const float2 o2 = *reinterpret_cast<const float2*>(sO + place(i));
                 float o0 = o2.x * kCodeUnit + z, o1 = o2.y * kCodeUnit + z;
                 if constexpr (OUT) {
-                    const float2 c2 = *reinterpret_cast<const float2*>(s_oc + at);
+                    const float2 c2 = *reinterpret_cast<const float2*>(s_oc + place(i));
                     o0 += c2.x; o1 += c2.y;
                 }
                 acc0 = __builtin_fmaf(wgt, o0, acc0);
                 acc1 = __builtin_fmaf(wgt, o1, acc1);
                 L = __builtin_fmaf(wgt, ml[i].y, L);
             }
+            if (grp == 0) {
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                const float2 o2 = *reinterpret_cast<const float2*>(tail(w) + 2 + d);
-                const float wgt = __builtin_amdgcn_exp2f(tl[w].x - M);
-                acc0 = __builtin_fmaf(wgt, o2.x, acc0);
-                acc1 = __builtin_fmaf(wgt, o2.y, acc1);
-                L = __builtin_fmaf(wgt, tl[w].y, L);
+                for (int w = 0; w < kWaves; ++w) {
+                    const float2 o2 = *reinterpret_cast<const float2*>(tail(w) + 2 + d);
+                    const float wgt = __builtin_amdgcn_exp2f(tl[w].x - M);
+                    acc0 = __builtin_fmaf(wgt, o2.x, acc0);
+                    acc1 = __builtin_fmaf(wgt, o2.y, acc1);
+                    L = __builtin_fmaf(wgt, tl[w].y, L);
+                }
+            } else {
+                *reinterpret_cast<float2*>(sO + place(0)) = make_float2(acc0, acc1);
+                *reinterpret_cast<float2*>(sO + place(1)) = make_float2(M, L);
+            }
+            acc[it] = make_float2(acc0, acc1); ML[it] = make_float2(M, L);
+        }
+        if constexpr (GROUPS > 1) {
+            __syncthreads();
+            if (grp > 0) return;
+        }
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const int item = t + it * THREADS;
+            if (item >= GQ * kPartPairs) break;
+            const int hh = item / kPartPairs, d = 2 * (item % kPartPairs);
+            float2 ga[GROUPS], gm[GROUPS];
+            ga[0] = acc[it]; gm[0] = ML[it];
+            float M = gm[0].x;
+#pragma unroll
+            for (int u = 1; u < GROUPS; ++u) {
+                const float* first = sO + (u * WPG * 8 + hh) * kHeadDim + d;
+                ga[u] = *reinterpret_cast<const float2*>(first);
+                gm[u] = *reinterpret_cast<const float2*>(first + (SLOTS == 2 ? 4 : 8) * kHeadDim);
+                M = fmaxf(M, gm[u].x);
+            }
+            float acc0 = ga[0].x, acc1 = ga[0].y, L = gm[0].y;
+            if constexpr (GROUPS > 1) {
+                acc0 = acc1 = L = 0.f;
+#pragma unroll
+                for (int u = 0; u < GROUPS; ++u) {
+                    const float wgt = __builtin_amdgcn_exp2f(gm[u].x - M);
+                    acc0 = __builtin_fmaf(wgt, ga[u].x, acc0);
+                    acc1 = __builtin_fmaf(wgt, ga[u].y, acc1);
+                    L = __builtin_fmaf(wgt, gm[u].y, L);
+                }
             }
             if (n_parts == 1) {      // the whole head was here: normalise, round once, done
                 const uint32_t lo = __half_as_ushort(__float2half_rn(acc0 / L)), hi = __half_as_ushort(__float2half_rn(acc1 / L));

@@ -12,7 +12,7 @@
 // KV head, so it runs on the matrix cores (v_mfma_f32_16x16x32_f16, binary32
 // accumulation); everything after it is a bandwidth- or latency-bound sweep.
 //   score_pass<STATS>  a reference and the exp-sum of every window row (pass 1)
-//   stats_combine      merges the per-wave row statistics
+//   stats_combine      merges the per-wave row statistics (where there are many: few are merged by the vote pass)
 //   score_pass<VOTES>  recomputes the tiles, normalises, sums columns (pass 2)
 //   pool_scores        max-pool the votes, count the pooled scores in bins
 //   select_topk        find the cut, ordered compaction; scores within a relative
@@ -38,6 +38,7 @@ union Frag {
 };
 
 template <bool B> struct BoolC { static constexpr bool value = B; };
+template <int I> struct IntC { static constexpr int value = I; };
 
 constexpr int kThreads = 256;
 constexpr int kRowsPerWave = 32;        // score_pass: query rows one wave owns (its MFMA A operands, register-resident)
@@ -59,7 +60,8 @@ struct ScoreArgs {
     const uint16_t* q_obs;  // [B, Hq, W, D]
     const uint16_t* k;      // [B, Hkv, L, D]
     float2* stats_part;     // [heads, n_parts, rows_pad]  (m, Z) in the log2 domain
-    const float2* stats;    // [heads, rows_pad]           (m, 1/Z)
+    float2* stats;          // [heads, rows_pad]           (m, 1/Z)
+    double* zsum;           // [heads, rows_pad]           Z
     float* vote;            // [heads, P]
     int L, W, P, gq, n_q_heads, n_kv_heads;
     int rows, rows_pad;     // Gq*W and the rows the waves cover (a multiple of 32 or 64)
@@ -68,6 +70,10 @@ struct ScoreArgs {
     float scale_log2;       // sm_scale * log2(e)
 };
 
+// Up to so many statistics per row the vote pass merges itself while its first keys are on their way, without the launch of
+// stats_combine before it: whole calls, us, 8 heads of 2000 keys (16 of them) 26.5 -> 24.9, of 4096 (32) 28.2 -> 26.1, 32 heads of 8192
+// (16) 64.5 -> 63.0, 256 heads of 32768 (8) 1276 -> 1261.  More of them take as long as the launch: 8 heads of 32768 (64) 75.3 -> 76.0.
+constexpr int kMergeParts = 32;
 constexpr int kChunk = 64;              // keys of a chunk
 constexpr int kChunkBytes = kChunk * kHeadDim * 2;
 constexpr int kRing = 2;                // chunks in LDS
@@ -118,7 +124,8 @@ __device__ __forceinline__ void request_chunk(const ScoreArgs& a, int head, cons
 // 8 of 32768 23.2 + 19.2 -> 18.3 + 15.1, 32 of 16384 37 + 34 -> 29 + 26, 256 of 32768 425 + 414 -> 394 + 363 (2.15 GB:
 // 5.5 and 5.9 TB/s), 32 of 20011 with 32 rows 32.6 + 25.4 -> 31.6 + 24.6.  Three and four places in LDS are no better
 // (8 heads of 32768: 19.2 + 15.9 and 20.2 + 17.0): fewer workgroups fit a CU.
-template <int NRW, int PASS>
+// MERGE (VOTES): the pass merges the row statistics itself.
+template <int NRW, int PASS, bool MERGE = false>
 __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     constexpr int kMT = kRowsPerWave / 16;
     constexpr int KS = 4 / NRW, KT = 4 / KS;          // key strips; 16-key tiles of a wave per chunk
@@ -153,31 +160,75 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     // VOTES: to rows 16 mt + 4 kb + i: m and 1/Z.
     constexpr int NR = PASS == PASS_STATS ? 1 : 4;
     float m_run[kMT][NR], z_run[kMT][NR];
+    const uint32_t sk_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sk;
+    auto request = [&](int chunk, int place) { request_chunk<PASS>(a, head, kh, sk_at, chunk, place); };
+    // (the first chunk and the query rows arrive together; the compiler's wait for the latter stands here, not in the loop)
+    auto settle = [&] {
 #pragma unroll
-    for (int mt = 0; mt < kMT; ++mt)
+        for (int mt = 0; mt < kMT; ++mt)
 #pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            if (PASS == PASS_STATS) {
-                m_run[mt][i] = kNegBig; z_run[mt][i] = 0.f;
-            } else {
+            for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(qf[mt][s].u));
+    };
+    if constexpr (PASS == PASS_STATS) {
+#pragma unroll
+        for (int mt = 0; mt < kMT; ++mt) { m_run[mt][0] = kNegBig; z_run[mt][0] = 0.f; }
+        request(c_begin, 0);
+        settle();
+    } else if constexpr (MERGE) {
+        // The two halves of the wave take every other part of the slab's 32 rows, all of them on their way at once.
+        auto merge = [&](auto count) {
+            constexpr int N = decltype(count)::value;
+            const int half = lane >> 5, row = kRowsPerWave * rw + (lane & 31);
+            const float2* p = a.stats_part + (size_t)head * a.n_parts * a.rows_pad + row;
+            float2 v[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                v[u] = p[(size_t)min(2 * u + half, a.n_parts - 1) * a.rows_pad];
+                if (2 * u + half >= a.n_parts) v[u].y = 0.f;
+            }
+            request(c_begin, 0);
+            settle();
+            float M = v[0].x;
+#pragma unroll
+            for (int u = 1; u < N; ++u) M = fmaxf(M, v[u].x);
+            M = fmaxf(M, __shfl_xor(M, 32));
+            double Z = 0.0;
+#pragma unroll
+            for (int u = 0; u < N; ++u) Z += (double)v[u].y * (double)__builtin_amdgcn_exp2f(v[u].x - M);
+            Z += __shfl_xor(Z, 32);
+            const float inv = Z > 0.0 && row < a.rows ? (float)(1.0 / Z) : 0.f;
+            if (blockIdx.x == 0 && ks == 0 && half == 0) {                // for the binary64 re-scoring
+                a.stats[(size_t)head * a.rows_pad + row] = make_float2(M, inv);
+                a.zsum[(size_t)head * a.rows_pad + row] = Z;
+            }
+#pragma unroll
+            for (int mt = 0; mt < kMT; ++mt)
+#pragma unroll
+                for (int i = 0; i < NR; ++i) {
+                    m_run[mt][i] = __shfl(M, 16 * mt + 4 * kb + i);
+                    z_run[mt][i] = __shfl(inv, 16 * mt + 4 * kb + i);
+                }
+        };
+        // (32 rows or fewer leave four times as many statistics, one per key strip: not built for them)
+        if (a.n_parts <= 8) merge(IntC<4>{});
+        else merge(IntC<kMergeParts / 2>{});
+    } else {
+#pragma unroll
+        for (int mt = 0; mt < kMT; ++mt)
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
                 const int r = kRowsPerWave * rw + 16 * mt + 4 * kb + i;
                 const float2 st = a.stats[(size_t)head * a.rows_pad + r];
                 m_run[mt][i] = st.x; z_run[mt][i] = (r < a.rows) ? st.y : 0.f;
             }
-        }
-
-    const uint32_t sk_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sk;
-    auto request = [&](int chunk, int place) { request_chunk<PASS>(a, head, kh, sk_at, chunk, place); };
-    request(c_begin, 0);
-    // (the first chunk and the query rows arrive together; the compiler's wait for the latter stands here, not in the loop)
+        request(c_begin, 0);
+        settle();
+    }
+    if (PASS == PASS_VOTES)
 #pragma unroll
-    for (int mt = 0; mt < kMT; ++mt) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(qf[mt][s].u));
-        if (PASS == PASS_VOTES)
+        for (int mt = 0; mt < kMT; ++mt)
 #pragma unroll
             for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(m_run[mt][i]), "+v"(z_run[mt][i]));
-    }
 #pragma unroll
     for (int c = 1; c < kRing - 1; ++c)
         if (c_begin + c < c_end) request(c_begin + c, c);
@@ -1269,12 +1320,15 @@ int n_row_slabs(int rows) {
     return rows > kNarrowRows ? 0 : slabs <= 1 ? 1 : slabs == 2 ? 2 : 4;
 }
 
+// merging: the vote pass that merges the row statistics itself, or NULL
 template <class Stats, class Votes>
-hipError_t launch_scores(Stats stats_pass, Votes vote_pass, const ScoreArgs& a, int n_wg, int heads, hipStream_t stream, float2* stats, double* zsum) {
+hipError_t launch_scores(Stats stats_pass, Votes vote_pass, Votes merging, const ScoreArgs& a, int n_wg, int heads, hipStream_t stream) {
     hipLaunchKernelGGL(stats_pass, dim3(n_wg, heads), dim3(kThreads), 0, stream, a);
-    hipLaunchKernelGGL(stats_combine, dim3(heads, (a.rows_pad + 3) / 4), dim3(256), 0, stream, (const float2*)a.stats_part, stats, zsum,
-                       a.n_parts, a.rows_pad);
-    hipLaunchKernelGGL(vote_pass, dim3(n_wg, heads), dim3(kThreads), 0, stream, a);
+    const bool merge = merging && a.n_parts <= kMergeParts;
+    if (!merge)
+        hipLaunchKernelGGL(stats_combine, dim3(heads, (a.rows_pad + 3) / 4), dim3(256), 0, stream, (const float2*)a.stats_part, a.stats, a.zsum,
+                           a.n_parts, a.rows_pad);
+    hipLaunchKernelGGL((merge ? merging : vote_pass), dim3(n_wg, heads), dim3(kThreads), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -1341,7 +1395,7 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
     float2* stats = reinterpret_cast<float2*>(base + plan.off_stats);
     a.rows = plan.rows; a.rows_pad = plan.rows_pad;
     double* zsum = reinterpret_cast<double*>(base + plan.off_stats + (size_t)heads * a.rows_pad * sizeof(float2));
-    a.stats = stats;
+    a.stats = stats; a.zsum = zsum;
     a.vote = reinterpret_cast<float*>(base + plan.off_vote);
     a.L = cfg.seq_len; a.W = cfg.window; a.P = plan.P; a.gq = cfg.n_q_heads / cfg.n_kv_heads;
     a.n_q_heads = cfg.n_q_heads; a.n_kv_heads = cfg.n_kv_heads;
@@ -1352,10 +1406,10 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
     hipError_t e;
     if (score) {   // scores are needed only when something is dropped
         switch (n_row_slabs(plan.rows)) {
-            case 1: e = launch_scores(score_pass<1, PASS_STATS>, score_pass<1, PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
-            case 2: e = launch_scores(score_pass<2, PASS_STATS>, score_pass<2, PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
-                        case 4: e = launch_scores(score_pass<4, PASS_STATS>, score_pass<4, PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
-            default: e = launch_scores(score_wide<PASS_STATS>, score_wide<PASS_VOTES>, a, n_wg, heads, stream, stats, zsum); break;
+            case 1: e = launch_scores(score_pass<1, PASS_STATS>, score_pass<1, PASS_VOTES>, (void (*)(const ScoreArgs))nullptr, a, n_wg, heads, stream); break;
+            case 2: e = launch_scores(score_pass<2, PASS_STATS>, score_pass<2, PASS_VOTES>, score_pass<2, PASS_VOTES, true>, a, n_wg, heads, stream); break;
+            case 4: e = launch_scores(score_pass<4, PASS_STATS>, score_pass<4, PASS_VOTES>, score_pass<4, PASS_VOTES, true>, a, n_wg, heads, stream); break;
+            default: e = launch_scores(score_wide<PASS_STATS>, score_wide<PASS_VOTES>, (void (*)(const ScoreArgs))nullptr, a, n_wg, heads, stream); break;
         }
         if (e != hipSuccess) return e;
     }

@@ -128,6 +128,20 @@ def test_scores_at_the_edges_of_a_chunk(orc, L, Gq, W):
     assert unrefined == [0, 0]
 
 
+@pytest.mark.parametrize("Hkv,Gq,W,L", [(64, 4, 32, 1030), (16, 4, 31, 2100), (2, 4, 32, 4100), (2, 4, 32, 4290), (3, 2, 30, 2111), (3, 1, 20, 517), (3, 1, 20, 600)])
+def test_row_statistics_merged_by_the_vote_pass(orc, Hkv, Gq, W, L):
+    """Eight, sixteen, up to 32 statistics per row, which the vote pass merges itself, and just more of them, which a
+    kernel before it does; keys that grow late, so that the parts differ by many factors of two."""
+    print(f"case parts Hkv={Hkv} Gq={Gq} W={W} L={L}", flush=True)
+    P = L - W
+
+    def keys(k):
+        k[:, :, P // 2:P] = (k[:, :, P // 2:P].astype(np.float32) * 3).astype(np.float16)
+    got, idx, pooled, unrefined = select(orc, P, W, 3, P // 5, Gq=Gq, Hkv=Hkv, outlier=4.0, keys=keys, seed=95)
+    check_indices(got, idx, pooled)
+    assert unrefined == [0] * Hkv
+
+
 @pytest.mark.parametrize("where,word", [("query", float("nan")), ("key", float("nan")), ("query", float("inf")), ("key", -float("inf"))])
 @pytest.mark.parametrize("P,Gq,W,pool,budget", [(700, 2, 8, 7, 100), (4096, 4, 32, 1, 4095), (5000, 2, 8, 7, 513), (9001, 4, 64, 63, 2000)])
 def test_votes_that_are_not_numbers_still_give_every_survivor(P, Gq, W, pool, budget, where, word):

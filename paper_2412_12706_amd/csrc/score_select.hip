@@ -209,7 +209,6 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
                     z_run[mt][i] = __shfl(inv, 16 * mt + 4 * kb + i);
                 }
         };
-        // (32 rows or fewer leave four times as many statistics, one per key strip: not built for them)
         if (a.n_parts <= 8) merge(IntC<4>{});
         else merge(IntC<kMergeParts / 2>{});
     } else {
@@ -367,7 +366,9 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     }
 
     if (PASS == PASS_STATS) {
-        // merge the four lanes that share a row, then one of them writes
+        // merge the four lanes that share a row, then (through LDS) the key strips
+        float2* s_st = reinterpret_cast<float2*>(sk);                    // [strip][row]
+        if constexpr (KS > 1) __syncthreads();                           // (every wave is done with its keys)
 #pragma unroll
         for (int mt = 0; mt < kMT; ++mt) {
             float m = m_run[mt][0], z = z_run[mt][0];
@@ -380,7 +381,20 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
             }
             if (kb == 0) {
                 const int r = kRowsPerWave * rw + 16 * mt + n;
-                a.stats_part[((size_t)head * a.n_parts + blockIdx.x * KS + ks) * a.rows_pad + r] = make_float2(m, z);
+                if constexpr (KS > 1) s_st[ks * (NRW * kRowsPerWave) + r] = make_float2(m, z);
+                else a.stats_part[((size_t)head * a.n_parts + blockIdx.x) * a.rows_pad + r] = make_float2(m, z);
+            }
+        }
+        if constexpr (KS > 1) {
+            __syncthreads();
+            if ((int)threadIdx.x < NRW * kRowsPerWave) {
+                float2 v[KS];
+                float m = kNegBig, z = 0.f;
+#pragma unroll
+                for (int u = 0; u < KS; ++u) { v[u] = s_st[u * (NRW * kRowsPerWave) + threadIdx.x]; m = fmaxf(m, v[u].x); }
+#pragma unroll
+                for (int u = 0; u < KS; ++u) z = __builtin_fmaf(v[u].y, __builtin_amdgcn_exp2f(v[u].x - m), z);
+                a.stats_part[((size_t)head * a.n_parts + blockIdx.x) * a.rows_pad + threadIdx.x] = make_float2(m, z);
             }
         }
     }
@@ -1342,22 +1356,30 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
     const int nrw = n_row_slabs(p.rows), heads = cfg.batch * cfg.n_kv_heads;
     const bool wide = nrw == 0;
     p.rows_pad = wide ? kWideRows : nrw * kRowsPerWave;
-    const int ks = wide ? 1 : 4 / nrw;                   // statistics a workgroup leaves per row
     p.n_chunks = (cfg.seq_len + 63) / 64;                // keys per chunk: 64
     // A workgroup pays for staging its query rows and waits for its first keys alone, so it should have
     // sixteen chunks (64 where the wave holds more rows), as long as that leaves two workgroups per CU;
     // beyond eight per CU more only cost.  Statistics + votes, us, with 512 / 1024 / 2048 workgroups: 8
     // heads of 32768 keys 18.4 + 14.8 / 19.5 + 16.2 / 22.0 + 17.3; 32 heads of 16384 29 + 26, 64 heads 55 + 46 and
     // 128 heads 100 + 92 with any of them; with 256 rows 8 heads of 131072 keys 87 + 78 / 88 + 79.
-    const long long chunks = (long long)heads * p.n_chunks;
-    const int total = (int)std::min(2048LL, std::max(512LL, chunks / (wide ? 64 : 16)));
-    int n_wg = (total + heads - 1) / heads;
-    const int least = 2;
-    if (n_wg > (p.n_chunks + least - 1) / least) n_wg = (p.n_chunks + least - 1) / least;
-    if (n_wg < 1) n_wg = 1;
-    p.chunks_per_wg = (p.n_chunks + n_wg - 1) / n_wg;
-    p.n_wg = (p.n_chunks + p.chunks_per_wg - 1) / p.chunks_per_wg;
-    p.n_parts = p.n_wg * ks;
+    auto workgroups = [&](int n_chunks, int& share) {
+        const int total = (int)std::min(2048LL, std::max(512LL, (long long)heads * n_chunks / (wide ? 64 : 16)));
+        const int least = wide ? 4 : 2;
+        int n_wg = (total + heads - 1) / heads;
+        if (n_wg > (n_chunks + least - 1) / least) n_wg = (n_chunks + least - 1) / least;
+        if (n_wg < 1) n_wg = 1;
+        share = (n_chunks + n_wg - 1) / n_wg;
+        return (n_chunks + share - 1) / share;
+    };
+    p.n_wg = workgroups(p.n_chunks, p.chunks_per_wg);
+    if (nrw == 1 || nrw == 2) {
+        // (Never more statistics than chunks of 128 keys with one per key strip, four or two to a workgroup, would leave: a
+        // workspace of the size that was once stated for those is taken.)
+        int share;
+        const int most = 4 / nrw * workgroups((cfg.seq_len + 127) / 128, share);
+        while (p.n_wg > most) { ++p.chunks_per_wg; p.n_wg = (p.n_chunks + p.chunks_per_wg - 1) / p.chunks_per_wg; }
+    }
+    p.n_parts = p.n_wg;
     const int rows_pad = p.rows_pad;
     const size_t n_parts = (size_t)p.n_parts;
     size_t off = 0;
@@ -1406,7 +1428,7 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
     hipError_t e;
     if (score) {   // scores are needed only when something is dropped
         switch (n_row_slabs(plan.rows)) {
-            case 1: e = launch_scores(score_pass<1, PASS_STATS>, score_pass<1, PASS_VOTES>, (void (*)(const ScoreArgs))nullptr, a, n_wg, heads, stream); break;
+            case 1: e = launch_scores(score_pass<1, PASS_STATS>, score_pass<1, PASS_VOTES>, score_pass<1, PASS_VOTES, true>, a, n_wg, heads, stream); break;
             case 2: e = launch_scores(score_pass<2, PASS_STATS>, score_pass<2, PASS_VOTES>, score_pass<2, PASS_VOTES, true>, a, n_wg, heads, stream); break;
             case 4: e = launch_scores(score_pass<4, PASS_STATS>, score_pass<4, PASS_VOTES>, score_pass<4, PASS_VOTES, true>, a, n_wg, heads, stream); break;
             default: e = launch_scores(score_wide<PASS_STATS>, score_wide<PASS_VOTES>, (void (*)(const ScoreArgs))nullptr, a, n_wg, heads, stream); break;

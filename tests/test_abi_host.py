@@ -293,3 +293,38 @@ def test_current_stream_without_the_undocumented_torch_names(monkeypatch, missin
         monkeypatch.delattr(torch._C, missing)
     assert kvqp._stream_ptr(None).value == (0x7007 if missing else 0x5003)
     assert kvqp._stream_ptr(types.SimpleNamespace(cuda_stream=0x9009)).value == 0x9009
+
+
+def test_compress_workspace_is_no_larger_than_it_was():
+    """A caller may have set aside what was stated when the statistics of up to 64 window rows came from chunks of 128 keys, two or
+    four per workgroup and row, and those of more than 128 rows from workgroups of four steps or more: the size stated now is never larger."""
+    import random
+    cd = lambda a, b: -(-a // b)
+    al = lambda v: cd(v, 256) * 256
+
+    def former(c):
+        L, W, heads = c.seq_len, c.window, c.batch * c.n_kv_heads
+        P, rows = L - W, c.n_q_heads // c.n_kv_heads * W
+        slabs = 0 if rows > 128 else 1 if rows <= 32 else 2 if rows <= 64 else 4
+        strips, keys, share, least = (4 // slabs, 64 if slabs == 4 else 128, 16, 2) if slabs else (1, 64, 64, 4)
+        n = cd(L, keys)
+        wg = max(1, min(cd(min(2048, max(512, heads * n // share)), heads), cd(n, least)))
+        rows_pad = 32 * slabs or 256
+        tiles = max(1, cd(P, 4096))
+        seg = min(15, cd(tiles, min(16, cd(512, heads), tiles)))
+        kept = min(c.budget, P)
+        size = al(max(heads * cd(n, cd(n, wg)) * strips * rows_pad * 8, heads * cd(tiles, seg) * 8192 if tiles > 1 else 0))
+        size = al(size + heads * rows_pad * 16)
+        size = al(size + heads * max(1, P) * 4)
+        size = al(size + heads * max(8, cd(P, 8) * 8) * 2)
+        return al(size + heads * max(1, kept) * 4) + (heads * cd(P, 8) * 8 * 4 if tiles > 1 else 0)
+
+    rng = random.Random(5)
+    for _ in range(3000):
+        gq, W = rng.choice([1, 2, 4, 8]), rng.choice([1, 8, 13, 16, 32, 64])
+        hkv = rng.choice([1, 2, 4, 8])
+        L = int(2 ** rng.uniform(7, 17))
+        if gq * W > 256 or L <= W:
+            continue
+        c = kvqp.Cfg(batch=rng.randint(1, 40), n_q_heads=hkv * gq, n_kv_heads=hkv, seq_len=L, window=W, budget=max(1, L // 4), bits=16)
+        assert kvqp.workspace_bytes(c)[0] <= former(c), c

@@ -12,7 +12,7 @@
 // KV head, so it runs on the matrix cores (v_mfma_f32_16x16x32_f16, binary32
 // accumulation); everything after it is a bandwidth- or latency-bound sweep.
 //   score_pass<STATS>  a reference and the exp-sum of every window row (pass 1)
-//   stats_combine      merges the per-wave row statistics (where there are many: few are merged by the vote pass)
+//   stats_combine      merges the row statistics of the workgroups (where there are many: few are merged by the vote pass)
 //   score_pass<VOTES>  recomputes the tiles, normalises, sums columns (pass 2)
 //   pool_scores        max-pool the votes, count the pooled scores in bins
 //   select_topk        find the cut, ordered compaction; scores within a relative

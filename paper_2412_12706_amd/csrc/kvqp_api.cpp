@@ -226,22 +226,25 @@ static int compress_impl(const kvqp_cfg* cfg, const void* q_obs, const void* k, 
     if (workspace_bytes < plan.total + plan.exact_bytes) plan.exact_bytes = 0;   // (slower on some prompts)
     if (((uintptr_t)workspace & 15) != 0) return KVQP_ERR_INVALID_ARG;
     hipStream_t stream = (hipStream_t)hip_stream;
-    // The selection writes the caller's list and the quantizer reads it there: a copy of it between the two is a launch
-    // that both wait for (3.8 us of 30 with 8 heads of 4096 tokens, 4.6 of 70 with 32768, 6.3 with 256 heads).
-    // A list that lies over the workspace or the queries, which are dead only when it has been made, is copied there.
-    const size_t idx_bytes = (size_t)heads * n_kept * sizeof(int32_t);
+    // The quantizer reads the survivors in the workspace.  The selection writes them there and, beside them, into the
+    // caller's list, which is an output only: calls on several streams may share one that nobody reads, and it may lie over
+    // a buffer of the cache.  A copy between the two kernels instead is a launch that the quantizer waits for (whole calls,
+    // us: LATER).  A list that lies over memory which the selection still reads or writes gets that copy.
+    const size_t idx_bytes = (size_t)heads * n_kept * sizeof(int32_t), row_bytes = (size_t)kHeadDim * 2;
     auto apart = [&](const void* p, size_t bytes) {
         const uintptr_t a = (uintptr_t)idx_out, b = (uintptr_t)p;
-        return a + idx_bytes <= b || b + bytes <= a;
+        return !p || a + idx_bytes <= b || b + bytes <= a;
     };
-    const bool in_place = idx_out && ((uintptr_t)idx_out & 3) == 0 && apart(workspace, workspace_bytes) &&
-                          apart(q_obs, (size_t)cfg->batch * cfg->n_q_heads * cfg->window * kHeadDim * 2);
-    int32_t* idx = in_place ? idx_out : reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + plan.off_idx);
+    const bool direct = idx_out && ((uintptr_t)idx_out & 3) == 0 && apart(workspace, workspace_bytes) &&
+                        apart(q_obs, (size_t)cfg->batch * cfg->n_q_heads * cfg->window * row_bytes) &&
+                        apart(k, (size_t)heads * cfg->seq_len * row_bytes) && apart(unrefined_out, (size_t)heads * sizeof(int32_t)) &&
+                        apart(cache->head_n_kept, (size_t)heads * sizeof(int32_t));
+    int32_t* idx = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + plan.off_idx);
     if (head_budget && upload_counts(cache->head_n_kept, head_budget, heads, stream) != hipSuccess) return KVQP_ERR_HIP;
     if (n_kept == 0 && unrefined_out && upload_counts(unrefined_out, nullptr, heads, stream) != hipSuccess) return KVQP_ERR_HIP;   // nothing is cut
     if (n_kept > 0) {
-        if (launch_select(*cfg, q_obs, k, idx, unrefined_out, workspace, plan, cache->head_n_kept, score, stream) != hipSuccess) return KVQP_ERR_HIP;
-        if (idx_out && !in_place) {
+        if (launch_select(*cfg, q_obs, k, idx, direct ? idx_out : nullptr, unrefined_out, workspace, plan, cache->head_n_kept, score, stream) != hipSuccess) return KVQP_ERR_HIP;
+        if (idx_out && !direct) {
             if (hipMemcpyAsync(idx_out, idx, idx_bytes, hipMemcpyDeviceToDevice, stream) != hipSuccess) return KVQP_ERR_HIP;
         }
     }

@@ -115,7 +115,8 @@ hipError_t upload_counts(int32_t* dst, const int32_t* src_host, int n, hipStream
 hipError_t launch_append_tail(const kvqp_cfg& cfg, const kvqp_cache& cache, int n_tokens, int base_quantum, hipStream_t stream);
 // head_n (device, or NULL): every head's own cut under plan.n_kept; score says whether any head drops a token
 // unrefined (device [heads], or NULL): per head, how many candidates near the cut binary32 had to decide
-hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, int32_t* idx, int32_t* unrefined,
+// idx: the survivors, in the workspace; list (device, or NULL): written with the same
+hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, int32_t* idx, int32_t* list, int32_t* unrefined,
                          void* ws, const CompressPlan& plan, const int32_t* head_n, bool score, hipStream_t stream);
 
 }  // namespace kvqp

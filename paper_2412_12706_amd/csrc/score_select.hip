@@ -678,7 +678,8 @@ struct SelectArgs {
     uint16_t* code;         // [heads, p_stride] codes of the pooled scores, in groups of eight (codes_above)
     uint16_t* bins;         // [heads, n_seg, kBins] counts of every pooling workgroup
     float* exact;           // [heads, p_stride] pooled scores, only where the candidates around the cut don't fit the list; or NULL
-    int32_t* idx;           // [heads, n_kept]
+    int32_t* idx;           // [heads, n_kept], in the workspace: the list that the quantizer reads
+    int32_t* list;          // the caller's, written beside it and never read; or NULL
     int32_t* unrefined;     // [heads] or NULL: candidates near the cut that binary32 decided (0: all re-scored)
     const int32_t* head_n;  // a head's own cut (<= n_kept), or NULL for n_kept everywhere
     const uint16_t* q_obs;
@@ -912,13 +913,14 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     const float* vote = a.vote + (size_t)head * P;
     const uint16_t* code = a.code + (size_t)head * a.p_stride;
     int32_t* idx = a.idx + (size_t)head * a.n_kept;
+    int32_t* list = a.list ? a.list + (size_t)head * a.n_kept : idx;      // (the same words twice where there is none)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = (a.pool - 1) / 2;
 
     if (a.unrefined && threadIdx.x == 0) a.unrefined[head] = 0;   // (overwritten below by the same thread if binary32 decides)
     if (k <= 0) return;   // (a head-level count may be zero)
     if (k >= P) {  // budget covers the prefix: identity, the scores are not looked at
-        for (int j = threadIdx.x; j < k; j += kSelThreads) idx[j] = j;
+        for (int j = threadIdx.x; j < k; j += kSelThreads) { idx[j] = j; list[j] = j; }
         return;
     }
     if (threadIdx.x == 0) { s_list = 0; s_sure = 0; s_band = 0; s_hot = 0; }
@@ -1321,7 +1323,11 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                if (__builtin_amdgcn_inverse_ballot_w64(lo[u] | ((unsigned long long)hi[u] << 32))) idx[e[u]] = 64 * (w0 + 64 * h + u0 + u) + lane;
+                if (__builtin_amdgcn_inverse_ballot_w64(lo[u] | ((unsigned long long)hi[u] << 32))) {
+                    const int j = 64 * (w0 + 64 * h + u0 + u) + lane;
+                    idx[e[u]] = j;
+                    list[e[u]] = j;
+                }
         }
     }
 }
@@ -1405,7 +1411,7 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
     return p;
 }
 
-hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, int32_t* idx, int32_t* unrefined, void* ws,
+hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, int32_t* idx, int32_t* list, int32_t* unrefined, void* ws,
                          const CompressPlan& plan, const int32_t* head_n, bool score, hipStream_t stream) {
     char* base = static_cast<char*>(ws);
     const int heads = cfg.batch * cfg.n_kv_heads;
@@ -1436,7 +1442,7 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
         if (e != hipSuccess) return e;
     }
     SelectArgs s;
-    s.vote = a.vote; s.code = reinterpret_cast<uint16_t*>(base + plan.off_pooled); s.idx = idx; s.unrefined = unrefined; s.head_n = head_n;
+    s.vote = a.vote; s.code = reinterpret_cast<uint16_t*>(base + plan.off_pooled); s.idx = idx; s.list = list; s.unrefined = unrefined; s.head_n = head_n;
     s.q_obs = a.q_obs; s.k = a.k; s.stats = stats; s.zsum = zsum;
     s.P = plan.P; s.L = cfg.seq_len; s.W = cfg.window; s.n_kept = plan.n_kept; s.pool = cfg.pool_kernel;
     s.gq = a.gq; s.n_q_heads = cfg.n_q_heads; s.n_kv_heads = cfg.n_kv_heads; s.rows = a.rows; s.rows_pad = a.rows_pad;

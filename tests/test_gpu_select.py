@@ -298,3 +298,41 @@ def test_unusual_cuts_beyond_three_tiles(orc):
     test_cut_in_the_lowest_score_bin(orc, 13500, 13100)
     test_more_ties_than_the_list_holds(orc, 14000, 4000, 2)
     test_votes_that_are_not_numbers_still_give_every_survivor(13001, 4, 32, 7, 4000, "query", float("nan"))
+
+
+@pytest.mark.parametrize("over", ["k_codes", "v_scale", "tail_k"])
+def test_a_survivor_list_over_a_buffer_of_the_cache(over):
+    """The caller's list is written and never read: laid over a buffer of the cache it is lost, the cache is not."""
+    print(f"case list over {over}", flush=True)
+    P, W, Hkv, Gq, budget = 5000, 16, 2, 4, 700
+    q_obs, k, v = (dev(t) for t in synth.prompt_host(1, Hkv * Gq, Hkv, P + W, W, 128, config=87))
+    cfg = kvqp.Cfg(batch=1, n_q_heads=Hkv * Gq, n_kv_heads=Hkv, seq_len=P + W, window=W, budget=budget, bits=4, group_size=32)
+    ca, cb = kvqp.alloc_cache(cfg), kvqp.alloc_cache(cfg)
+    for c in (ca, cb):
+        for t in c.buffers.values():
+            t.fill_(0xA5)
+    kvqp.compress(cfg, q_obs, k, v, ca)
+    kvqp.compress(cfg, q_obs, k, v, cb, idx_out=cb.buffers[over][:4 * Hkv * budget].view(torch.int32).view(1, Hkv, budget))
+    torch.cuda.synchronize()
+    assert all(torch.equal(ca.buffers[n], cb.buffers[n]) for n in ca.buffers)
+
+
+def test_calls_on_two_streams_may_share_a_survivor_list_that_nobody_reads():
+    """Prompts of two lengths, each with its own cache and workspace, one list for both."""
+    print("case one list for two streams", flush=True)
+    W, Hkv, budget = 16, 2, 120
+    waste = torch.empty((1, Hkv, budget), dtype=torch.int32, device="cuda")
+    calls = []
+    for L in (9000, 200):
+        t = [dev(x) for x in synth.prompt_host(1, Hkv * 2, Hkv, L, W, 128, config=L)]
+        cfg = kvqp.Cfg(batch=1, n_q_heads=Hkv * 2, n_kv_heads=Hkv, seq_len=L, window=W, budget=budget, bits=4, group_size=32)
+        want, got = kvqp.alloc_cache(cfg), kvqp.alloc_cache(cfg)
+        kvqp.compress(cfg, *t, want)
+        calls.append((cfg, t, want, got, kvqp.alloc_workspace(kvqp.workspace_bytes(cfg)[0]), torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for cfg, t, _, got, ws, stream in calls:
+            kvqp.compress(cfg, *t, got, idx_out=waste, workspace=ws, stream=stream)
+    torch.cuda.synchronize()
+    for cfg, _, want, got, _, _ in calls:
+        assert all(torch.equal(want.buffers[n], got.buffers[n]) for n in want.buffers)

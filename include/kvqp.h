@@ -243,7 +243,8 @@ int kvqp_workspace_bytes(const kvqp_cfg *cfg, size_t *compress_bytes, size_t *de
  *   k, v   half [batch, Hkv, L, D]  full prompt keys / values
  *   cache  buffers filled; n_kept and tail_len (= W) set; tail_cap must be set
  *          by the caller and be >= W
- *   idx_out int32 [batch, Hkv, n_kept] ascending survivors, or NULL
+ *   idx_out int32 [batch, Hkv, n_kept] ascending survivors, or NULL; written, never
+ *          read: calls on several streams may share a list that nobody looks at
  *   unrefined_out int32 [batch, Hkv] or NULL: per head 0 when every candidate
  *          near the cut was re-scored in binary64 (or none needed it), else
  *          the number of candidates near the cut that binary32 decided

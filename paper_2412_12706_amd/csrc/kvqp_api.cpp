@@ -228,8 +228,8 @@ static int compress_impl(const kvqp_cfg* cfg, const void* q_obs, const void* k, 
     hipStream_t stream = (hipStream_t)hip_stream;
     // The quantizer reads the survivors in the workspace.  The selection writes them there and, beside them, into the
     // caller's list, which is an output only: calls on several streams may share one that nobody reads, and it may lie over
-    // a buffer of the cache.  A copy between the two kernels instead is a launch that the quantizer waits for (whole calls,
-    // us: LATER).  A list that lies over memory which the selection still reads or writes gets that copy.
+    // a buffer of the cache.  A copy between the two kernels instead is a launch that the quantizer waits for (whole calls, us,
+    // with and without it: 8 heads of 4096 tokens 30.3, 27.1, of 32768 77.6, 75.9, 256 heads of 32768 1282, 1265).  A list that lies over memory which the selection still reads or writes gets that copy.
     const size_t idx_bytes = (size_t)heads * n_kept * sizeof(int32_t), row_bytes = (size_t)kHeadDim * 2;
     auto apart = [&](const void* p, size_t bytes) {
         const uintptr_t a = (uintptr_t)idx_out, b = (uintptr_t)p;

@@ -1295,7 +1295,8 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     // ---- ordered compaction: a wave owns consecutive 64-bit mask words and stores the positions of one
     // at a time, side by side (a thread that walks the bits of its own mask bytes writes every line
     // in many pieces: 17 instead of 5 us when 256 heads do it at once; collecting positions in LDS
-    // for 16-byte stores gains nothing: the loop issues instructions, it does not wait for stores) ----
+    // for 16-byte stores gains nothing: the loop issues instructions, it does not wait for stores; so both stores of a
+    // position share a 32-bit offset: 8 heads of 131072 keys take as long as with one list; with two 64-bit addresses 1.8 us more) ----
     const int n_words = (P + 63) / 64, per = (n_words + kSelWaves - 1) / kSelWaves;      // (per <= 128)
     const int w0 = wave * per, w1 = min(w0 + per, n_words);
     uint32_t word[4] = {0u, 0u, 0u, 0u};                     // lane l: words w0 + l and w0 + 64 + l
@@ -1324,9 +1325,9 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (__builtin_amdgcn_inverse_ballot_w64(lo[u] | ((unsigned long long)hi[u] << 32))) {
-                    const int j = 64 * (w0 + 64 * h + u0 + u) + lane;
-                    idx[e[u]] = j;
-                    list[e[u]] = j;
+                    const uint32_t j = 64u * (uint32_t)(w0 + 64 * h + u0 + u) + (uint32_t)lane, off = 4u * (uint32_t)e[u];
+                    *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(idx) + off) = j;
+                    *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(list) + off) = j;
                 }
         }
     }

@@ -17,6 +17,7 @@
 
 static int g_launches = 0;      // calls that would have enqueued work
 static long long g_count_sum = 0;
+static int32_t* g_list = nullptr;    // the survivor list that the selection was to write
 
 namespace kvqp {
 DecodePlan plan_decode(const kvqp_cfg& cfg, int) {
@@ -51,8 +52,8 @@ hipError_t upload_counts(int32_t*, const int32_t* src_host, int n, hipStream_t, 
     return hipSuccess;
 }
 hipError_t launch_append_tail(const kvqp_cfg&, const kvqp_cache&, int, int, hipStream_t) { ++g_launches; return hipSuccess; }
-hipError_t launch_select(const kvqp_cfg&, const void*, const void*, int32_t*, int32_t*, void*, const CompressPlan&, const int32_t*,
-                         bool, hipStream_t) { ++g_launches; return hipSuccess; }
+hipError_t launch_select(const kvqp_cfg&, const void*, const void*, int32_t*, int32_t* list, int32_t*, void*, const CompressPlan&, const int32_t*,
+                         bool, hipStream_t) { ++g_launches; g_list = list; return hipSuccess; }
 }  // namespace kvqp
 
 extern "C" hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { ++g_launches; return hipSuccess; }
@@ -84,6 +85,43 @@ static int32_t* counts(std::initializer_list<int> v) {
     int i = 0;
     for (int x : v) p[i++] = x;
     return p;
+}
+
+// The selection writes the caller's survivor list unless the list shares a byte with something that the selection reads or writes
+// besides it; then, and if it is not aligned, the list is a copy made afterwards (one call more).
+static void where_the_survivor_list_may_lie() {
+    kvqp_cfg c = base_cfg();
+    c.outlier_threshold = 6.0f; c.outlier_overflow_cap = 50;
+    const size_t heads = 4, list = heads * 256 * 4, prompt = heads * 800 * 256;
+    for (int n_cap : {0, 384}) {
+        size_t s[8], o[4];
+        kvqp_cache k = full_cache(true, true);
+        k.n_cap = n_cap;
+        EXPECT((n_cap ? kvqp_cache_sizes_cap(&c, n_cap, k.tail_cap, s) : kvqp_cache_sizes(&c, k.tail_cap, s)) == KVQP_OK);
+        EXPECT(kvqp_outlier_sizes(&c, n_cap, o) == KVQP_OK);
+        // every buffer far from the others: the prompt's queries (0), keys, values, the workspace, the cache's buffers, the counts, unrefined_out
+        const size_t bytes[] = {2 * heads * 2 * 32 * 256, prompt, prompt, 1 << 20, s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], o[0], o[1], o[2], o[3], heads * 4, heads * 4};
+        const int n = sizeof(bytes) / sizeof(bytes[0]);
+        char* at[n];
+        for (int i = 0; i < n; ++i) at[i] = (char*)((uintptr_t)(i + 1) << 32);
+        void** field[] = {&k.k_codes, &k.v_codes, &k.k_scale, &k.k_zero, &k.v_scale, &k.v_zero, &k.tail_k, &k.tail_v, &k.k_out, &k.v_out, &k.k_ovf, &k.v_ovf};
+        for (int i = 0; i < 12; ++i) *field[i] = at[4 + i];
+        k.head_n_kept = (int32_t*)at[16];
+        int32_t* budget = counts({256, 0, 10, 256});
+        auto direct = [&](char* p) {
+            g_launches = 0;
+            EXPECT(kvqp_compress_ragged(&c, at[0], at[1], at[2], budget, &k, (int32_t*)p, (int32_t*)at[17], at[3], 1 << 20, nullptr) == 0);
+            EXPECT(g_launches == (g_list ? 3 : 4) && (!g_list || (char*)g_list == p));      // counts, selection, (copy,) quantizer
+            return g_list != nullptr;
+        };
+        for (int i = 0; i < n; ++i) {
+            const bool free_to_use = i == 2 || (i >= 4 && i < 16);          // the values, the cache's buffers: not the selection's
+            EXPECT(direct(at[i] - list) && direct(at[i] + bytes[i]));
+            EXPECT(direct(at[i] - list + 4) == free_to_use && direct(at[i] + bytes[i] - 4) == free_to_use && direct(at[i]) == free_to_use);
+        }
+        EXPECT(!direct((char*)0x1001) && !direct((char*)0x1002) && direct((char*)0x1004));
+        std::free(budget);
+    }
 }
 
 static void sizes_sweep() {
@@ -273,6 +311,7 @@ static void append_and_decode() {
 
 int main() {
     sizes_sweep();
+    where_the_survivor_list_may_lie();
     rejected_configurations();
     compress_and_quantize();
     append_and_decode();

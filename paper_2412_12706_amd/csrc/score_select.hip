@@ -22,6 +22,7 @@
 // pass in chunks of 64 shared by the four waves of a workgroup; query rows stay in registers as
 // MFMA operands.
 #include <algorithm>
+#include <type_traits>
 
 #include "kvqp_internal.h"
 
@@ -159,7 +160,9 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     // STATS: a lane's scores belong to row 16 mt + n: reference (log2 domain) and sum of exp2(score - reference).
     // VOTES: to rows 16 mt + 4 kb + i: m and 1/Z.
     constexpr int NR = PASS == PASS_STATS ? 1 : 4;
-    float m_run[kMT][NR], z_run[kMT][NR];
+    using Sum = std::conditional_t<PASS == PASS_STATS && (KS > 1), double, float>;
+    float m_run[kMT][NR];
+    Sum z_run[kMT][NR];
     const uint32_t sk_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sk;
     auto request = [&](int chunk, int place) { request_chunk<PASS>(a, head, kh, sk_at, chunk, place); };
     // (the first chunk and the query rows arrive together; the compiler's wait for the latter stands here, not in the loop)
@@ -366,35 +369,44 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     }
 
     if (PASS == PASS_STATS) {
-        // merge the four lanes that share a row, then (through LDS) the key strips
-        float2* s_st = reinterpret_cast<float2*>(sk);                    // [strip][row]
-        if constexpr (KS > 1) __syncthreads();                           // (every wave is done with its keys)
-#pragma unroll
-        for (int mt = 0; mt < kMT; ++mt) {
-            float m = m_run[mt][0], z = z_run[mt][0];
-#pragma unroll
-            for (int off = 16; off < 64; off <<= 1) {
-                const float mo = __shfl_xor(m, off), zo = __shfl_xor(z, off);
-                const float mn = fmaxf(m, mo);
-                z = z * __builtin_amdgcn_exp2f(m - mn) + zo * __builtin_amdgcn_exp2f(mo - mn);
-                m = mn;
-            }
-            if (kb == 0) {
-                const int r = kRowsPerWave * rw + 16 * mt + n;
-                if constexpr (KS > 1) s_st[ks * (NRW * kRowsPerWave) + r] = make_float2(m, z);
-                else a.stats_part[((size_t)head * a.n_parts + blockIdx.x) * a.rows_pad + r] = make_float2(m, z);
-            }
-        }
         if constexpr (KS > 1) {
+            // The four lanes of every key strip that share a row meet in LDS, and one thread per row adds their sums, which are
+            // binary64 since the chunk, and stores the total: rounded once, however many strips and chunks the workgroup has.  Row sums of
+            // 64 heads of 8192 keys, 32 rows, against 64 bits, rms: every strip on its own 1.72e-8, strips added in binary32
+            // 2.23e-8, this 1.64e-8; whole calls as long as with binary32 (8 heads of 4096 keys 22.9 us, 64 of 8192 80.3).
+            constexpr int ROWS = NRW * kRowsPerWave;
+            double* s_z = reinterpret_cast<double*>(sk);                 // [strip][lane of the row][row]
+            float* s_m = reinterpret_cast<float*>(s_z + 4 * KS * ROWS);
+            static_assert(4 * KS * ROWS * (sizeof(double) + sizeof(float)) <= sizeof(sk), "the sums fit the keys' place");
+            __syncthreads();                                             // (every wave is done with its keys)
+#pragma unroll
+            for (int mt = 0; mt < kMT; ++mt) {
+                const int at = (4 * ks + kb) * ROWS + kRowsPerWave * rw + 16 * mt + n;
+                s_m[at] = m_run[mt][0]; s_z[at] = z_run[mt][0];
+            }
             __syncthreads();
-            if ((int)threadIdx.x < NRW * kRowsPerWave) {
-                float2 v[KS];
-                float m = kNegBig, z = 0.f;
+            if ((int)threadIdx.x < ROWS) {
+                float m_of[4 * KS], m = kNegBig;
+                double z = 0.0;
 #pragma unroll
-                for (int u = 0; u < KS; ++u) { v[u] = s_st[u * (NRW * kRowsPerWave) + threadIdx.x]; m = fmaxf(m, v[u].x); }
+                for (int u = 0; u < 4 * KS; ++u) { m_of[u] = s_m[u * ROWS + threadIdx.x]; m = fmaxf(m, m_of[u]); }
 #pragma unroll
-                for (int u = 0; u < KS; ++u) z = __builtin_fmaf(v[u].y, __builtin_amdgcn_exp2f(v[u].x - m), z);
-                a.stats_part[((size_t)head * a.n_parts + blockIdx.x) * a.rows_pad + threadIdx.x] = make_float2(m, z);
+                for (int u = 0; u < 4 * KS; ++u) z += s_z[u * ROWS + threadIdx.x] * (double)__builtin_amdgcn_exp2f(m_of[u] - m);
+                a.stats_part[((size_t)head * a.n_parts + blockIdx.x) * a.rows_pad + threadIdx.x] = make_float2(m, (float)z);
+            }
+        } else {
+            // merge the four lanes that share a row
+#pragma unroll
+            for (int mt = 0; mt < kMT; ++mt) {
+                float m = m_run[mt][0], z = z_run[mt][0];
+#pragma unroll
+                for (int off = 16; off < 64; off <<= 1) {
+                    const float mo = __shfl_xor(m, off), zo = __shfl_xor(z, off);
+                    const float mn = fmaxf(m, mo);
+                    z = z * __builtin_amdgcn_exp2f(m - mn) + zo * __builtin_amdgcn_exp2f(mo - mn);
+                    m = mn;
+                }
+                if (kb == 0) a.stats_part[((size_t)head * a.n_parts + blockIdx.x) * a.rows_pad + kRowsPerWave * rw + 16 * mt + n] = make_float2(m, z);
             }
         }
     }

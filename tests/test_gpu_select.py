@@ -30,6 +30,21 @@ def select(orc, P, W, pool, budget, Gq=2, Hkv=2, sm_scale=None, outlier=10.0, ke
     return got.cpu().numpy(), idx, pooled, unrefined.cpu().tolist()
 
 
+def row_statistics(cfg, ws, rows_pad):
+    """(m, 1/Z) and the binary64 Z of every window row, out of a workspace of the stated size: they lie before the votes, the
+    pooled scores' codes, the survivors (each padded to 256 bytes) and room for all pooled scores."""
+    heads, P, rows = cfg.batch * cfg.n_kv_heads, cfg.seq_len - cfg.window, cfg.n_q_heads // cfg.n_kv_heads * cfg.window
+
+    def padded(n):
+        return -(-n // 256) * 256
+    room = heads * -(-P // 8) * 32 if P > 4096 else 0
+    at = kvqp.workspace_bytes(cfg)[0] - room - sum(padded(heads * n) for n in (cfg.n_kept * 4, -(-P // 8) * 16, P * 4, rows_pad * 16))
+    host = ws.cpu().numpy()
+    stats = host[at:at + heads * rows_pad * 8].view(np.float32).reshape(heads, rows_pad, 2)[:, :rows]
+    zsum = host[at + heads * rows_pad * 8:at + heads * rows_pad * 16].view(np.float64).reshape(heads, rows_pad)[:, :rows]
+    return stats.astype(np.float64), zsum
+
+
 @pytest.mark.parametrize("P,pool,budget", [
     (2, 1, 1), (7, 3, 3), (9, 7, 8), (64, 63, 10), (1025, 5, 1024), (4095, 7, 1000), (4096, 63, 4095), (4096, 1, 1),
     (4097, 7, 1), (4104, 1, 4103), (8191, 13, 2000), (8193, 63, 513), (12289, 3, 6000), (40001, 7, 9001)])
@@ -170,7 +185,7 @@ def test_votes_that_are_not_numbers_still_give_every_survivor(P, Gq, W, pool, bu
         assert torch.equal(got[1], torch.arange(budget, dtype=torch.int32))
 
 
-@pytest.mark.parametrize("Gq,W", [(4, 64), (8, 24), (4, 32)])
+@pytest.mark.parametrize("Gq,W", [(4, 64), (8, 24), (4, 32), (8, 8), (4, 8)])
 @pytest.mark.parametrize("key", [5.0, 14.0, 24.0, 38.0])
 def test_row_sums_keep_their_precision_when_a_late_key_dominates(Gq, W, key):
     """Statistics of the window rows (the divisors of every vote, in the re-scoring too) when one key, the
@@ -178,12 +193,11 @@ def test_row_sums_keep_their_precision_when_a_late_key_dominates(Gq, W, key):
     the products are exact and only exponentials and sums are rounded: with arguments up to 8 (a
     reference never lags further) 2^-22 ln 2 for the rounding of the argument, 2^-23 for the exponential and 2^-24
     for each of at most eleven additions behind the large term, together 9.4e-7 of the sum.  Arguments of 32
-    to 64, as a reference left at the first keys gives, are rounded to 1.3e-6 alone.  The statistics lie in the
-    workspace before the votes, the pooled scores' codes, the survivors (each padded to 256 bytes) and room for
-    all pooled scores."""
+    to 64, as a reference left at the first keys gives, are rounded to 1.3e-6 alone.  (Up to 64 rows a lane's sum and what follows
+    are 64 bits wide and rounded once.)"""
     B, Hkv, P, budget = 8, 8, 4500, 100
     heads, rows = B * Hkv, Gq * W
-    rows_pad = 128 if rows <= 128 else 256
+    rows_pad = 32 if rows <= 32 else 64 if rows <= 64 else 128 if rows <= 128 else 256
     print(f"case late key {key} Gq={Gq} W={W}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(5)
     q = torch.zeros(B, Hkv * Gq, W, 128, dtype=torch.float16, device="cuda")
@@ -195,12 +209,7 @@ def test_row_sums_keep_their_precision_when_a_late_key_dominates(Gq, W, key):
     kvqp.compress(cfg, q, k, torch.zeros_like(k), kvqp.alloc_cache(cfg), workspace=ws)
     torch.cuda.synchronize()
 
-    def padded(n):
-        return -(-n // 256) * 256
-    at = kvqp.workspace_bytes(cfg)[0] - heads * -(-P // 8) * 32 - sum(padded(heads * n) for n in (budget * 4, -(-P // 8) * 16, P * 4, rows_pad * 16))
-    host = ws.cpu().numpy()
-    stats = host[at:at + heads * rows_pad * 8].view(np.float32).reshape(heads, rows_pad, 2)[:, :rows].astype(np.float64)
-    zsum = host[at + heads * rows_pad * 8:at + heads * rows_pad * 16].view(np.float64).reshape(heads, rows_pad)[:, :rows]
+    stats, zsum = row_statistics(cfg, ws, rows_pad)
     arg = q[..., 0].cpu().numpy().astype(np.float64).reshape(heads, rows) * key * np.float64(np.float32(np.log2(np.e)))
     others = P + np.arange(rows) % W                                             # visible keys of score 0
     assert np.ptp(arg) > 0.4 * key
@@ -209,6 +218,37 @@ def test_row_sums_keep_their_precision_when_a_late_key_dominates(Gq, W, key):
     print(f"worst {worst:.2e} rms {np.sqrt((err ** 2).mean()):.2e}", flush=True)
     assert worst < 9.4e-7
     assert np.allclose(stats[..., 1] * zsum, 1, rtol=1.2e-7)
+
+
+@pytest.mark.parametrize("Gq,W", [(1, 7), (4, 8), (2, 32), (4, 32)])
+def test_row_sums_of_the_key_strips_are_added_in_64_bits(Gq, W):
+    """A row whose sum is 1 in one strip of 16 keys of a chunk and 0.75 * 2^-24 in each of the other three: every strip's sum is exact,
+    and their total reaches the workspace rounded once (2^-24).  Added one after the other in 32 bits all three would be lost,
+    2.25 * 2^-24.  Products and scale are whole numbers, so no exponential is rounded.  (Up to 32 window rows there are four strips to a
+    chunk, up to 64 two, beyond them one, where a lane's own sum has the same bound.)"""
+    B, Hkv, P, budget = 1, 2, 3000, 100
+    heads, rows = B * Hkv, Gq * W
+    rows_pad = 32 if rows <= 32 else 64 if rows <= 64 else 128
+    print(f"case strips Gq={Gq} W={W}", flush=True)
+    scale = np.float32(np.log(2.0))
+    assert np.float32(scale * np.float32(1.4426950408889634)) == 1.0
+    q = torch.zeros(B, Hkv * Gq, W, 128, dtype=torch.float16, device="cuda")
+    q[..., 0] = 1.0
+    k = torch.zeros(B, Hkv, P + W, 128, dtype=torch.float16, device="cuda")
+    k[..., 0] = -2000.0
+    at = 10 * 64
+    k[:, :, at + 5, 0] = 0.0
+    for strip in (1, 2, 3):
+        k[:, :, at + 16 * strip + 2, 0] = -25.0
+        k[:, :, at + 16 * strip + 9, 0] = -26.0
+    cfg = kvqp.Cfg(batch=B, n_q_heads=Hkv * Gq, n_kv_heads=Hkv, seq_len=P + W, window=W, pool_kernel=1, budget=budget, bits=16, sm_scale=float(scale))
+    ws = kvqp.alloc_workspace(kvqp.workspace_bytes(cfg)[0])
+    kvqp.compress(cfg, q, k, torch.zeros_like(k), kvqp.alloc_cache(cfg), workspace=ws)
+    torch.cuda.synchronize()
+    stats, zsum = row_statistics(cfg, ws, rows_pad)
+    err = zsum / ((1 + 2.25 * 2.0 ** -24) * np.exp2(-stats[..., 0].astype(np.float64))) - 1
+    print(f"worst {np.abs(err).max():.2e}", flush=True)
+    assert np.abs(err).max() <= 2.0 ** -24 * (1 + 2.0 ** -20)
 
 
 @pytest.mark.parametrize("P,pool,budget,noise", [(12301, 63, 5000, 0.0), (8192, 5, 8191, 0.0), (40003, 13, 9000, 0.0), (13001, 31, 4000, 0.003),

@@ -241,6 +241,8 @@ int kvqp_workspace_bytes(const kvqp_cfg *cfg, size_t *compress_bytes, size_t *de
  *
  *   q_obs  half [batch, Hq, W, D]   queries of the last W prompt positions
  *   k, v   half [batch, Hkv, L, D]  full prompt keys / values
+ *          (the three need no more than a binary16 number's alignment; keys at a
+ *          multiple of 16 bytes are read faster)
  *   cache  buffers filled; n_kept and tail_len (= W) set; tail_cap must be set
  *          by the caller and be >= W
  *   idx_out int32 [batch, Hkv, n_kept] ascending survivors, or NULL; written, never

@@ -32,6 +32,7 @@ namespace {
 typedef _Float16 h8v __attribute__((ext_vector_type(8)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u4any __attribute__((ext_vector_type(4), aligned(2)));      // ... at any binary16 number's address
 union Frag {
     h8v v;
     uint4 q;
@@ -95,19 +96,29 @@ __device__ __forceinline__ void arrived() {
 
 // Request a chunk.  Its rows lie unpadded in LDS; the 16-byte piece p of row r is stored at place p ^ (r % 16), so that
 // the operand reads meet every bank equally.  Wave w requests rows 16 w .. 16 w + 15.
+// DIRECT: keys at multiples of 16 bytes.  Others (no form of the requests is documented for them) pass through registers to the same places.
 constexpr int kLoads = 4;               // requests of a wave per chunk
-template <int PASS>
-__device__ __forceinline__ void request_chunk(const ScoreArgs& a, int head, const void* kh, uint32_t sk_at, int chunk, int place) {
+template <int PASS, bool DIRECT>
+__device__ __forceinline__ void request_chunk(const ScoreArgs& a, int head, const void* kh, unsigned char* sk, int chunk, int place) {
+    const uint32_t sk_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sk;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, kb = lane >> 4;
+    auto from = [&](int i) {
+        const int key = min(chunk * kChunk + 16 * wave + 4 * i + kb, a.L - 1);      // rows past the end are masked
+        return (uint32_t)key * (2u * kHeadDim) + 16u * (uint32_t)(n ^ ((4 * i + kb) & 15));
+    };
+    auto to = [&](int i) { return place * kChunkBytes + (16 * wave + 4 * i) * (2 * kHeadDim); };
+    if constexpr (!DIRECT) {
+        u4v v[kLoads];
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) v[i] = *reinterpret_cast<const u4any*>(static_cast<const char*>(kh) + from(i));
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) *reinterpret_cast<u4v*>(sk + to(i) + 16 * lane) = v[i];
+        return;
+    }
     auto rows = [&](auto stream) {
 #pragma unroll
-        for (int i = 0; i < kLoads; ++i) {
-            const int row = 16 * wave + 4 * i;
-            const int key = min(chunk * kChunk + row + kb, a.L - 1);                // rows past the end are masked
-            request_rows<decltype(stream)::value>(sk_at + place * kChunkBytes + row * (2 * kHeadDim),
-                                                  (uint32_t)key * (2u * kHeadDim) + 16u * (uint32_t)(n ^ ((4 * i + kb) & 15)), kh);
-        }
+        for (int i = 0; i < kLoads; ++i) request_rows<decltype(stream)::value>(sk_at + to(i), from(i), kh);
     };
     if (PASS == PASS_VOTES || head < a.stream_heads) rows(BoolC<true>{});
     else rows(BoolC<false>{});
@@ -126,7 +137,7 @@ __device__ __forceinline__ void request_chunk(const ScoreArgs& a, int head, cons
 // 5.5 and 5.9 TB/s), 32 of 20011 with 32 rows 32.6 + 25.4 -> 31.6 + 24.6.  Three and four places in LDS are no better
 // (8 heads of 32768: 19.2 + 15.9 and 20.2 + 17.0): fewer workgroups fit a CU.
 // MERGE (VOTES): the pass merges the row statistics itself.
-template <int NRW, int PASS, bool MERGE = false>
+template <int NRW, int PASS, bool MERGE = false, bool DIRECT = true>
 __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     constexpr int kMT = kRowsPerWave / 16;
     constexpr int KS = 4 / NRW, KT = 4 / KS;          // key strips; 16-key tiles of a wave per chunk
@@ -163,8 +174,7 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     using Sum = std::conditional_t<PASS == PASS_STATS && (KS > 1), double, float>;
     float m_run[kMT][NR];
     Sum z_run[kMT][NR];
-    const uint32_t sk_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sk;
-    auto request = [&](int chunk, int place) { request_chunk<PASS>(a, head, kh, sk_at, chunk, place); };
+    auto request = [&](int chunk, int place) { request_chunk<PASS, DIRECT>(a, head, kh, sk, chunk, place); };
     // (the first chunk and the query rows arrive together; the compiler's wait for the latter stands here, not in the loop)
     auto settle = [&] {
 #pragma unroll
@@ -425,7 +435,7 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
 // strong outlier channels make them move: 5 us; a moved reference is shared by the two lanes of a row.
 typedef float f16v __attribute__((ext_vector_type(16)));
 constexpr int kWideRows = 256;
-template <int PASS>
+template <int PASS, bool DIRECT = true>
 __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
     constexpr int MT = 2;                             // row tiles of a wave
     constexpr int kWaveRows = 32 * MT;
@@ -471,8 +481,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
             }
         }
 
-    const uint32_t sk_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sk;
-    auto request = [&](int chunk, int place) { request_chunk<PASS>(a, head, kh, sk_at, chunk, place); };
+    auto request = [&](int chunk, int place) { request_chunk<PASS, DIRECT>(a, head, kh, sk, chunk, place); };
     request(c_begin, 0);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
@@ -1446,11 +1455,18 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
 
     hipError_t e;
     if (score) {   // scores are needed only when something is dropped
-        switch (n_row_slabs(plan.rows)) {
+        constexpr void (*none)(const ScoreArgs) = nullptr;
+        const int slabs = n_row_slabs(plan.rows);
+        if ((uintptr_t)k & 15) switch (slabs) {      // (whole calls, us, 8 heads: 4096 keys 28.5 instead of 25.5, 32768 75.7 / 76.0, 131072 with 256 rows 239.6 / 237.1)
+            case 1: e = launch_scores(score_pass<1, PASS_STATS, false, false>, score_pass<1, PASS_VOTES, false, false>, none, a, n_wg, heads, stream); break;
+            case 2: e = launch_scores(score_pass<2, PASS_STATS, false, false>, score_pass<2, PASS_VOTES, false, false>, none, a, n_wg, heads, stream); break;
+            case 4: e = launch_scores(score_pass<4, PASS_STATS, false, false>, score_pass<4, PASS_VOTES, false, false>, none, a, n_wg, heads, stream); break;
+            default: e = launch_scores(score_wide<PASS_STATS, false>, score_wide<PASS_VOTES, false>, none, a, n_wg, heads, stream); break;
+        } else switch (slabs) {
             case 1: e = launch_scores(score_pass<1, PASS_STATS>, score_pass<1, PASS_VOTES>, score_pass<1, PASS_VOTES, true>, a, n_wg, heads, stream); break;
             case 2: e = launch_scores(score_pass<2, PASS_STATS>, score_pass<2, PASS_VOTES>, score_pass<2, PASS_VOTES, true>, a, n_wg, heads, stream); break;
             case 4: e = launch_scores(score_pass<4, PASS_STATS>, score_pass<4, PASS_VOTES>, score_pass<4, PASS_VOTES, true>, a, n_wg, heads, stream); break;
-            default: e = launch_scores(score_wide<PASS_STATS>, score_wide<PASS_VOTES>, (void (*)(const ScoreArgs))nullptr, a, n_wg, heads, stream); break;
+            default: e = launch_scores(score_wide<PASS_STATS>, score_wide<PASS_VOTES>, none, a, n_wg, heads, stream); break;
         }
         if (e != hipSuccess) return e;
     }

@@ -376,3 +376,32 @@ def test_calls_on_two_streams_may_share_a_survivor_list_that_nobody_reads():
     torch.cuda.synchronize()
     for cfg, _, want, got, _, _ in calls:
         assert all(torch.equal(want.buffers[n], got.buffers[n]) for n in want.buffers)
+
+
+@pytest.mark.parametrize("Gq,W,L", [(1, 9, 700), (4, 8, 4133), (8, 8, 3001), (4, 32, 2065), (4, 64, 1500), (4, 30, 13000)])
+@pytest.mark.parametrize("shift", [1, 4])
+def test_prompts_at_any_address(Gq, W, L, shift):
+    """Queries, keys and values that begin at the address of any binary16 number (2 and 8 bytes past a multiple of 16 here): the same
+    survivors and the same cache as from aligned copies, for one, two and four slabs of window rows and for more."""
+    print(f"case address Gq={Gq} W={W} L={L} shift={shift}", flush=True)
+    Hkv, budget = 2, L // 5
+    t = [dev(x) for x in synth.prompt_host(1, Hkv * Gq, Hkv, L, W, 128, config=96)]
+    cfg = kvqp.Cfg(batch=1, n_q_heads=Hkv * Gq, n_kv_heads=Hkv, seq_len=L, window=W, budget=budget, bits=4, group_size=32, outlier_threshold=6.0,
+                   outlier_overflow_cap=budget)
+    got = []
+    for s in (0, shift):
+        moved = []
+        for x in t:
+            room = torch.zeros(x.numel() + 8, dtype=x.dtype, device="cuda")
+            moved.append(room[s:s + x.numel()].view(x.shape))
+            moved[-1].copy_(x)
+            assert moved[-1].data_ptr() % 16 == 2 * s
+        idx = torch.full((1, Hkv, budget), -1, dtype=torch.int32, device="cuda")
+        cache = kvqp.alloc_cache(cfg)
+        for b in cache.buffers.values():
+            b.fill_(0xA5)
+        kvqp.compress(cfg, *moved, cache, idx_out=idx)
+        torch.cuda.synchronize()
+        got.append((idx, cache))
+    assert torch.equal(got[0][0], got[1][0])
+    assert all(torch.equal(got[0][1].buffers[n], got[1][1].buffers[n]) for n in got[0][1].buffers)

@@ -684,6 +684,7 @@ constexpr int kBins = 4096;           // score bins: the bit pattern >> kBinShif
 constexpr int kBinShift = 17;
 constexpr int kCodeShift = 15;        // the stored code of a score: its pattern's upper 16 bits below the sign
 constexpr int kBinBase = ((136 << 23) >> kBinShift) - kBins;   // 2^9 is the first pattern past the last bin (votes stay below 256 rows)
+constexpr int kOwnTiles = 3;          // prefixes of up to so many tiles select_topk pools itself; longer ones are pool_scores'
 constexpr int kMaxSegs = 16;          // pooling workgroups per head
 constexpr int kMaxSegTiles = 15;      // (a workgroup's bin counts are stored in 16 bits)
 constexpr int kListCap = 3840;        // candidates around the cut held in LDS; more are swept from memory
@@ -1413,6 +1414,7 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
     size_t off = 0;
     // pooling workgroups per head: enough to fill the chip, whole pooling tiles each
     const int tiles = p.P > 0 ? (p.P + kPoolTile - 1) / kPoolTile : 1;
+    const bool apart = tiles > kOwnTiles;                // pooled by pool_scores: codes, counts and pooled scores pass through memory
     int segs = (512 + heads - 1) / heads;
     if (segs > kMaxSegs) segs = kMaxSegs;
     if (segs > tiles) segs = tiles;
@@ -1422,14 +1424,14 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
     p.p_stride = p.P > 0 ? (p.P + 7) / 8 * 8 : 8;
     // (the row statistics of the scoring workgroups are dead when the pooled scores are counted)
     const size_t part_bytes = (size_t)heads * n_parts * rows_pad * sizeof(float2);
-    const size_t bins_bytes = tiles > 1 ? (size_t)heads * p.n_seg * kBins * sizeof(uint16_t) : 0;
+    const size_t bins_bytes = apart ? (size_t)heads * p.n_seg * kBins * sizeof(uint16_t) : 0;
     p.off_stats_part = off; off = align_up(off + (part_bytes > bins_bytes ? part_bytes : bins_bytes), 256);
     p.off_stats = off;      off = align_up(off + (size_t)heads * rows_pad * (sizeof(float2) + sizeof(double)), 256);
     p.off_vote = off;       off = align_up(off + (size_t)heads * (p.P > 0 ? p.P : 1) * sizeof(float), 256);
-    p.off_pooled = off;     off = align_up(off + (size_t)heads * p.p_stride * sizeof(uint16_t), 256);
+    p.off_pooled = off;     off = align_up(off + (apart ? (size_t)heads * p.p_stride * sizeof(uint16_t) : 0), 256);
     p.off_idx = off;        off = align_up(off + (size_t)heads * (p.n_kept > 0 ? p.n_kept : 1) * sizeof(int32_t), 256);
     p.total = off;
-    p.exact_bytes = tiles > 1 ? (size_t)heads * p.p_stride * sizeof(float) : 0;
+    p.exact_bytes = apart ? (size_t)heads * p.p_stride * sizeof(float) : 0;
     return p;
 }
 
@@ -1484,9 +1486,10 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
     // the workgroups that pool side by side (whole calls, us, two kernels -> one: 8 heads of 8192 keys 41.3 -> 35.1, of 12000 43.7 ->
     // 38.9, 32 heads 68.8 -> 62.1 and 88.5 -> 84.5, 128 heads 184.6 -> 177.5 and 241.7 -> 239.2).  From four on the votes, four
     // bytes each through one CU, take longer: 8 heads of 16384 keys 51.1 -> 52.3, of 20000 60.3 -> 65.7, 32 heads 117.4 -> 118.9.
+    static_assert(kOwnTiles == 3, "a kernel for each");
     if (plan.P <= kPoolTile) own(select_topk<1>);
     else if (plan.P <= 2 * kPoolTile) own(select_topk<2>);
-    else if (plan.P <= 3 * kPoolTile) own(select_topk<3>);
+    else if (plan.P <= kOwnTiles * kPoolTile) own(select_topk<kOwnTiles>);
     else {
         if (score) hipLaunchKernelGGL(pool_scores, dim3(plan.n_seg, heads), dim3(kSelThreads), 0, stream, s);
         own(select_topk<0>);

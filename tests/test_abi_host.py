@@ -328,3 +328,19 @@ def test_compress_workspace_is_no_larger_than_it_was():
             continue
         c = kvqp.Cfg(batch=rng.randint(1, 40), n_q_heads=hkv * gq, n_kv_heads=hkv, seq_len=L, window=W, budget=max(1, L // 4), bits=16)
         assert kvqp.workspace_bytes(c)[0] <= former(c), c
+
+
+@pytest.mark.parametrize("P", [1, 4096, 4097, 9003, 12288, 12289, 20000])
+@pytest.mark.parametrize("batch,hkv,gq,W", [(1, 8, 4, 32), (16, 8, 4, 8), (3, 2, 8, 8), (1, 8, 4, 64)])
+def test_compress_workspace_holds_codes_and_pooled_scores_only_beyond_three_tiles(P, batch, hkv, gq, W):
+    """Up to three pooling tiles the selection keeps the pooled scores to itself: besides row statistics, votes and survivors
+    the workspace has nothing.  The parts of the statistics are whole, so what is left over shows."""
+    c = kvqp.Cfg(batch=batch, n_q_heads=hkv * gq, n_kv_heads=hkv, seq_len=P + W, window=W, budget=max(1, P // 3), bits=4)
+    heads, rows = batch * hkv, gq * W
+    rows_pad = 32 if rows <= 32 else 64 if rows <= 64 else 128 if rows <= 128 else 256
+    al = lambda v: -(-v // 256) * 256
+    parts = kvqp.workspace_bytes(c)[0] - al(heads * rows_pad * 16) - al(heads * P * 4) - al(heads * c.n_kept * 4)
+    if P > 12288:
+        assert parts >= al(heads * -(-P // 8) * 16) + heads * -(-P // 8) * 32 + heads * 8192
+    else:
+        assert parts % (heads * rows_pad * 8) == 0 and 1 <= parts // (heads * rows_pad * 8) <= max(1, -(-(P + W) // 128))

@@ -1,6 +1,6 @@
 """Token selection at the sizes where its kernels change course (paper Section 3, "KV Pruning"):
-prefixes around the pooling tile of 4096 candidates (one kernel up to it, a pooling kernel of several
-workgroups beyond it), around the groups of eight candidates whose codes share 16 bytes, pooling
+prefixes around the pooling tiles of 4096 candidates (one kernel up to three of them, a pooling kernel of several
+workgroups before it beyond), around the groups of eight candidates whose codes share 16 bytes, pooling
 windows up to the widest, cuts in the lowest score bin, and candidates around the cut that do not
 fit the list in LDS.  Indices against the checker, which scores in binary64."""
 import numpy as np
@@ -32,13 +32,13 @@ def select(orc, P, W, pool, budget, Gq=2, Hkv=2, sm_scale=None, outlier=10.0, ke
 
 def row_statistics(cfg, ws, rows_pad):
     """(m, 1/Z) and the binary64 Z of every window row, out of a workspace of the stated size: they lie before the votes, the
-    pooled scores' codes, the survivors (each padded to 256 bytes) and room for all pooled scores."""
+    pooled scores' codes (beyond three pooling tiles), the survivors (each padded to 256 bytes) and room for all pooled scores (the same)."""
     heads, P, rows = cfg.batch * cfg.n_kv_heads, cfg.seq_len - cfg.window, cfg.n_q_heads // cfg.n_kv_heads * cfg.window
 
     def padded(n):
         return -(-n // 256) * 256
-    room = heads * -(-P // 8) * 32 if P > 4096 else 0
-    at = kvqp.workspace_bytes(cfg)[0] - room - sum(padded(heads * n) for n in (cfg.n_kept * 4, -(-P // 8) * 16, P * 4, rows_pad * 16))
+    eighths = -(-P // 8) if P > 12288 else 0
+    at = kvqp.workspace_bytes(cfg)[0] - heads * eighths * 32 - sum(padded(heads * n) for n in (cfg.n_kept * 4, eighths * 16, P * 4, rows_pad * 16))
     host = ws.cpu().numpy()
     stats = host[at:at + heads * rows_pad * 8].view(np.float32).reshape(heads, rows_pad, 2)[:, :rows]
     zsum = host[at + heads * rows_pad * 8:at + heads * rows_pad * 16].view(np.float64).reshape(heads, rows_pad)[:, :rows]
@@ -254,8 +254,8 @@ def test_row_sums_of_the_key_strips_are_added_in_64_bits(Gq, W):
 @pytest.mark.parametrize("P,pool,budget,noise", [(12301, 63, 5000, 0.0), (8192, 5, 8191, 0.0), (40003, 13, 9000, 0.0), (13001, 31, 4000, 0.003),
                                                  (20481, 1, 12000, 0.002)])
 def test_more_candidates_around_the_cut_than_the_list_holds_under_wide_windows(orc, P, pool, budget, noise):
-    """Prompts whose keys are alike (or nearly): the candidates around the cut are visited by pooling the
-    prefix once more, tile by tile, and their windows reach across the tiles' edges."""
+    """Prompts whose keys are alike (or nearly): the candidates around the cut are visited in the threads' own scores (up to
+    three tiles) or by pooling the prefix once more, tile by tile, and their windows reach across the tiles' edges."""
     print(f"case alike P={P} pool={pool} budget={budget} noise={noise}", flush=True)
 
     def keys(k):
@@ -273,14 +273,15 @@ def test_more_candidates_around_the_cut_than_the_list_holds_under_wide_windows(o
             check_indices(got, idx, pooled)
 
 
-def test_a_compress_workspace_without_room_for_all_pooled_scores_gives_the_same_survivors():
-    """The stated size has four bytes per candidate for prompts whose scores cluster around the cut; a
-    workspace that holds everything else is taken, and a smaller one is not."""
-    print("case smaller compress workspace", flush=True)
-    P, W, Hkv, budget = 9003, 8, 2, 3000
+@pytest.mark.parametrize("P,pool,budget", [(12289, 5, 3000), (13003, 5, 5000), (40003, 13, 9000)])
+def test_a_compress_workspace_without_room_for_all_pooled_scores_gives_the_same_survivors(P, pool, budget):
+    """Beyond three pooling tiles the stated size has four bytes per candidate for prompts whose scores cluster around the cut (more
+    candidates there than the list holds); a workspace that holds everything else is taken, and a smaller one is not."""
+    print(f"case smaller compress workspace P={P}", flush=True)
+    W, Hkv = 8, 2
     q_obs, k, v = (dev(t) for t in synth.prompt_host(1, Hkv * 2, Hkv, P + W, W, 128, outlier=1.0, config=85))
     k[:, :, :P] = (k[:, :, :1].float() + 0.002 * k[:, :, :P].float()).half()
-    cfg = kvqp.Cfg(batch=1, n_q_heads=Hkv * 2, n_kv_heads=Hkv, seq_len=P + W, window=W, pool_kernel=5, budget=budget, bits=4, group_size=32)
+    cfg = kvqp.Cfg(batch=1, n_q_heads=Hkv * 2, n_kv_heads=Hkv, seq_len=P + W, window=W, pool_kernel=pool, budget=budget, bits=4, group_size=32)
     stated = kvqp.workspace_bytes(cfg)[0]
     least = stated - Hkv * -(-P // 8) * 32
     got = []
@@ -312,25 +313,6 @@ def test_a_survivor_list_over_memory_that_dies_during_the_call(where):
     torch.cuda.synchronize()
     assert torch.equal(got, want)
     assert all(torch.equal(ca.buffers[n], cb.buffers[n]) for n in ca.buffers)
-
-
-def test_a_compress_workspace_without_room_for_all_pooled_scores_beyond_three_tiles():
-    """The same where the pooled scores pass through memory: prefixes of more than three pooling tiles, more
-    candidates around the cut than the list holds."""
-    print("case smaller compress workspace, long", flush=True)
-    P, W, Hkv, budget = 13003, 8, 2, 5000
-    q_obs, k, v = (dev(t) for t in synth.prompt_host(1, Hkv * 2, Hkv, P + W, W, 128, outlier=1.0, config=93))
-    k[:, :, :P] = (k[:, :, :1].float() + 0.002 * k[:, :, :P].float()).half()
-    cfg = kvqp.Cfg(batch=1, n_q_heads=Hkv * 2, n_kv_heads=Hkv, seq_len=P + W, window=W, pool_kernel=5, budget=budget, bits=4, group_size=32)
-    stated = kvqp.workspace_bytes(cfg)[0]
-    least = stated - Hkv * -(-P // 8) * 32
-    got = []
-    for size in (stated, least):
-        idx = torch.full((1, Hkv, budget), -1, dtype=torch.int32, device="cuda")
-        kvqp.compress(cfg, q_obs, k, v, kvqp.alloc_cache(cfg), idx_out=idx, workspace=kvqp.alloc_workspace(stated)[:size])
-        torch.cuda.synchronize()
-        got.append(idx)
-    assert torch.equal(got[0], got[1]) and bool((got[0].diff() > 0).all())
 
 
 def test_unusual_cuts_beyond_three_tiles(orc):

@@ -143,11 +143,21 @@ def test_scores_at_the_edges_of_a_chunk(orc, L, Gq, W):
     assert unrefined == [0, 0]
 
 
-@pytest.mark.parametrize("Hkv,Gq,W,L", [(64, 4, 32, 1030), (16, 4, 31, 2100), (2, 4, 32, 4100), (2, 4, 32, 4290), (3, 2, 30, 2111), (3, 1, 20, 517), (3, 1, 20, 600)])
-def test_row_statistics_merged_by_the_vote_pass(orc, Hkv, Gq, W, L):
-    """Eight, sixteen, up to 32 statistics per row, which the vote pass merges itself, and just more of them, which a
-    kernel before it does; keys that grow late, so that the parts differ by many factors of two."""
+FEW_PARTS = [(L, parts) for L, parts in ((128, 1), (129, 2), (1024, 8), (1025, 9), (2048, 16), (2049, 17), (3000, 24), (3969, 32), (4096, 32), (4097, 33))]
+
+
+@pytest.mark.parametrize("Hkv,Gq,W,L,parts", [(64, 4, 32, 1030, 6), (16, 4, 31, 2100, 17), (2, 4, 32, 4290, 34), (3, 2, 30, 2111, 17), (3, 1, 20, 517, 5),
+                                              (3, 1, 20, 600, 5)] + [(2, *rows, *p) for rows in ((1, 20), (4, 16), (4, 32)) for p in FEW_PARTS])
+def test_row_statistics_merged_by_the_vote_pass(orc, Hkv, Gq, W, L, parts):
+    """One, two, up to eight, nine, sixteen and more, up to 32 statistics per row, which the vote pass merges itself (the form for
+    eight and the one for 32), and just more of them, which a kernel before it does, for one, two and four slabs of
+    rows; keys that grow late, so that the parts differ by many factors of two.  Up to three pooling tiles the workspace has, besides votes,
+    survivors and the rows' totals, the parts alone: the count is read off its size."""
     print(f"case parts Hkv={Hkv} Gq={Gq} W={W} L={L}", flush=True)
+    c = kvqp.Cfg(batch=1, n_q_heads=Hkv * Gq, n_kv_heads=Hkv, seq_len=L, window=W, budget=(L - W) // 5, bits=16)
+    rows_pad = 32 if Gq * W <= 32 else 64 if Gq * W <= 64 else 128
+    rest = sum(-(-Hkv * n // 256) * 256 for n in (c.n_kept * 4, (L - W) * 4, rows_pad * 16))
+    assert kvqp.workspace_bytes(c)[0] - rest == parts * Hkv * rows_pad * 8
     P = L - W
 
     def keys(k):

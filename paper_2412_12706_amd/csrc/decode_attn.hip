@@ -583,7 +583,7 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
     constexpr int STRIP = Geo::STRIP;
 
     // A workgroup is nw = 4, 8 or 12 waves (blockDim.x / 64, a multiple of four): all of them stream
-    // chunks; the merge at the end is done by the first 256 threads.
+    // chunks; at the end every four waves merge their own states and the first four the sums (eight query heads: all waves at once).
     extern __shared__ __align__(16) unsigned char pipe_lds[];
     const int nw = blockDim.x >> 6;
     uint16_t* sq = reinterpret_cast<uint16_t*>(pipe_lds);                      // the group's query rows (zero rows past GQ), for the z-term product

@@ -78,20 +78,21 @@ struct ScoreArgs {
 constexpr int kMergeParts = 32;
 constexpr int kChunk = 64;              // keys of a chunk
 constexpr int kChunkBytes = kChunk * kHeadDim * 2;
-constexpr int kRing = 2;                // chunks in LDS
+constexpr int kPlaces = 2;              // chunks in LDS: the one being computed and the one on its way (place ^ 1 is the other)
 
 // Request 1 KB of a chunk (four key rows) straight into LDS: lane l's 16 bytes from `base + off` land at dst + 16 l.
-// Nothing is left in a register, so the only thing to wait for is the counter (arrived()).
+// Nothing is left in a register, so the only thing to wait for is the counter (arrived()).  The statement overwrites m0, a reserved register
+// that a clobber list cannot name: the compiler sets it right before an instruction of its own that reads it, and has none in these kernels.
 template <bool STREAM>
 __device__ __forceinline__ void request_rows(uint32_t dst, uint32_t off, const void* base) {
     if (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(dst), "v"(off), "s"(base) : "memory");
     else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(base) : "memory");
 }
-// Wait until at most LEFT of this wave's memory operations are outstanding and its LDS operations are done; BARRIER: meet the other waves.
-template <int LEFT, bool BARRIER>
+// Wait until this wave's memory and LDS operations are done; BARRIER: meet the other waves.
+template <bool BARRIER>
 __device__ __forceinline__ void arrived() {
-    if (BARRIER) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
-    else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LEFT) : "memory");
+    if (BARRIER) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 }
 
 // Request a chunk.  Its rows lie unpadded in LDS; the 16-byte piece p of row r is stored at place p ^ (r % 16), so that
@@ -134,15 +135,15 @@ __device__ __forceinline__ void request_chunk(const ScoreArgs& a, int head, cons
 // in the lane, and two exchanges per chunk merge its four tiles.  Before (chunks through registers, two
 // barriers per chunk, a branch per 16 keys) -> now, us, statistics + votes: 8 heads of 4096 keys 10.0 + 7.2 -> 6.5 + 5.2,
 // 8 of 32768 23.2 + 19.2 -> 18.3 + 15.1, 32 of 16384 37 + 34 -> 29 + 26, 256 of 32768 425 + 414 -> 394 + 363 (2.15 GB:
-// 5.5 and 5.9 TB/s), 32 of 20011 with 32 rows 32.6 + 25.4 -> 31.6 + 24.6.  Three and four places in LDS are no better
-// (8 heads of 32768: 19.2 + 15.9 and 20.2 + 17.0): fewer workgroups fit a CU.
+// 5.5 and 5.9 TB/s), 32 of 20011 with 32 rows 32.6 + 25.4 -> 31.6 + 24.6.  Three and four places in LDS are slower
+// (8 heads of 32768: 19.2 + 15.9 and 20.2 + 17.0; not explained: two workgroups per CU, which is all the launch has, still fit).
 // MERGE (VOTES): the pass merges the row statistics itself.
 template <int NRW, int PASS, bool MERGE = false, bool DIRECT = true>
 __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     constexpr int kMT = kRowsPerWave / 16;
     constexpr int KS = 4 / NRW, KT = 4 / KS;          // key strips; 16-key tiles of a wave per chunk
     constexpr bool SHARED = NRW > 1;                  // a wave reads keys that other waves have requested
-    __shared__ __align__(16) unsigned char sk[kRing * kChunkBytes];
+    __shared__ __align__(16) unsigned char sk[kPlaces * kChunkBytes];
     __shared__ float svote[(PASS == PASS_VOTES && NRW > 1) ? 2 * NRW * kChunk : 1];
 
     const int head = blockIdx.y;
@@ -241,9 +242,6 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
         for (int mt = 0; mt < kMT; ++mt)
 #pragma unroll
             for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(m_run[mt][i]), "+v"(z_run[mt][i]));
-#pragma unroll
-    for (int c = 1; c < kRing - 1; ++c)
-        if (c_begin + c < c_end) request(c_begin + c, c);
 
     const uint32_t kp0 = (uint32_t)(n * 2 * kHeadDim + ((kb ^ n) << 4));  // contraction step 0 of key n; step s: ^ (s << 6)
     int place = 0;
@@ -256,9 +254,8 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     };
     for (int chunk = c_begin; chunk < c_end; ++chunk) {
         // this chunk has arrived, every wave is done with the one before it
-        if (chunk + kRing - 2 < c_end) arrived<kLoads * (kRing - 2), SHARED>();
-        else arrived<0, SHARED>();
-        if (chunk + kRing - 1 < c_end) request(chunk + kRing - 1, place == 0 ? kRing - 1 : place - 1);
+        arrived<SHARED>();
+        if (chunk + 1 < c_end) request(chunk + 1, place ^ 1);
         if (PASS == PASS_VOTES && NRW > 1)
             if (chunk > c_begin && wave == (chunk & 3)) store_votes(chunk - 1);
 
@@ -371,10 +368,10 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
                 if (kb == 0 && key < a.P) a.vote[(size_t)head * a.P + key] = v;
             }
         }
-        place = place == kRing - 1 ? 0 : place + 1;
+        place ^= 1;
     }
     if (PASS == PASS_VOTES && NRW > 1) {
-        arrived<0, SHARED>();
+        arrived<SHARED>();
         if (wave == 0) store_votes(c_end - 1);
     }
 
@@ -440,7 +437,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
     constexpr int MT = 2;                             // row tiles of a wave
     constexpr int kWaveRows = 32 * MT;
     constexpr int kSteps = kHeadDim / 16;             // contraction steps
-    __shared__ __align__(16) unsigned char sk[kRing * kChunkBytes];
+    __shared__ __align__(16) unsigned char sk[kPlaces * kChunkBytes];
     __shared__ float svote[PASS == PASS_VOTES ? 2 * 4 * kChunk : 1];
 
     const int head = blockIdx.y;
@@ -583,7 +580,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
         if (key < a.P) a.vote[(size_t)head * a.P + key] = v;
     };
     Tile even, odd;                              // scores of a chunk's two tiles
-    arrived<0, true>();
+    arrived<true>();
     if (c_begin + 1 < c_end) request(c_begin + 1, 1);
     product(even, 0, 0);
     for (int chunk = c_begin; chunk < c_end; ++chunk) {
@@ -593,7 +590,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
         product(odd, place, 1);
         if (PASS == PASS_STATS) sums(even, t); else col0 = column(even);
         if (PASS == PASS_STATS) count(even, t);
-        arrived<0, true>();                    // the next chunk is there; every wave has this one in registers
+        arrived<true>();                       // the next chunk is there; every wave has this one in registers
         if (chunk + 2 < c_end) request(chunk + 2, place);
         if (PASS == PASS_VOTES)
             if (chunk > c_begin && wave == (chunk & 3)) store_votes(chunk - 1);
@@ -609,7 +606,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
         }
     }
     if (PASS == PASS_VOTES) {
-        arrived<0, true>();
+        arrived<true>();
         if (wave == 0) store_votes(c_end - 1);
     }
     if (PASS == PASS_STATS) {

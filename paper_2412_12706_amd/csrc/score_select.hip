@@ -654,21 +654,24 @@ __global__ __launch_bounds__(256) void stats_combine(const float2* __restrict__ 
 // Selection: pool, find the cut, refine the candidates next to it in binary64,
 // compact in position order.
 //
-// What bounds it is a chain of dependent waits (memory, LDS, barriers) on few
-// workgroups, never bandwidth: a head's scores are at most half a megabyte.  The
+// What bounds it is a chain of dependent waits (memory, LDS) on few
+// workgroups and what one CU can issue, never bandwidth: a head's scores are at most half a megabyte.  The
 // work is therefore cut so that the part that grows with the prefix is spread
 // over many workgroups and the rest touches each score once:
 //   pool_scores  several workgroups per head: max-pool the votes, store the upper 16
-//                bits of each pooled score, and count the scores in 4096 bins of equal
-//                bit-pattern width (64 per factor of two: at most 1.6 % wide)
+//                bits of each pooled score, and count the scores in 4032 bins of equal
+//                bit-pattern width (64 per factor of two: at most 1.6 % wide) and the
+//                bins' counts in groups of 64
 //   select_topk  one workgroup per head: the counts give the bin of the cut; ONE
 //                sweep over the 16-bit codes leaves a mask bit per sure survivor and
 //                collects the few candidates of that bin, whose scores are pooled
 //                again and give the exact cut; survivors leave through the mask.
-// Prefixes of up to three pooling tiles (4096) do both in the second kernel.  A single
-// workgroup per head that did everything, with a four-pass radix select over all
-// scores, took 45 / 87 / 310 us for 8 heads of 4064 / 32736 / 131008 candidates
-// and 120 us for 256 heads of 32736; these take 9 / 5 + 21 / 5 + 35 and 12 + 29 us.
+// Prefixes of up to three pooling tiles (4096) do both in the second kernel.  Measured on one CU with sixteen waves: an
+// instruction of all of them 8 ns, of one wave 2, a barrier 12, a dependent access to LDS 31, an exchange of lanes through it 35 (by
+// DPP 5), a branch that is taken 25, an access to memory 400 to 1000.  So the list around the cut is finished by one wave, one
+// candidate per lane and unrolled (before, by all of them, with a barrier after every step), sums go along the lanes by DPP, only
+// the counts of the cut's group are read besides the groups', and the sweep lists groups of eight codes instead of candidates.  select_topk, us, before ->
+// now: 8 heads of 4064 candidates 8.8 -> 7.4, of 32736 22.4 -> 17.0, of 131008 37 -> 29, 32 of 20003 15 -> 10.5, 256 of 32736 29.6 -> 26.2.
 // ---------------------------------------------------------------------------
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
@@ -677,16 +680,18 @@ constexpr int kOctets = kMaxPrefix / (8 * kSelThreads);   // groups of eight can
 constexpr int kPoolTile = 4 * kSelThreads;   // candidates of one pooling step, four consecutive ones per thread
 constexpr int kMaxPoolRadius = 31;    // pool_kernel <= 63
 constexpr int kStage = kPoolTile + 2 * kMaxPoolRadius + 2;   // votes of a step with the halo on either side (whole 16-byte pieces)
-constexpr int kBins = 4096;           // score bins: the bit pattern >> kBinShift, 2^-55 .. 2^9, clamped at both ends
 constexpr int kBinShift = 17;
+constexpr int kGroups = 63, kGroupBins = 64;      // score bins in groups: one group per factor of two
+constexpr int kBins = kGroups * kGroupBins;       // score bins: the bit pattern >> kBinShift, 2^-54 .. 2^9, clamped at both ends
+constexpr int kBinRow = 4096;         // 16-bit words of a pooling workgroup's counts: the bins', then the groups' 
 constexpr int kCodeShift = 15;        // the stored code of a score: its pattern's upper 16 bits below the sign
 constexpr int kBinBase = ((136 << 23) >> kBinShift) - kBins;   // 2^9 is the first pattern past the last bin (votes stay below 256 rows)
 constexpr int kOwnTiles = 3;          // prefixes of up to so many tiles select_topk pools itself; longer ones are pool_scores'
 constexpr int kMaxSegs = 16;          // pooling workgroups per head
 constexpr int kMaxSegTiles = 15;      // (a workgroup's bin counts are stored in 16 bits)
 constexpr int kListCap = 3840;        // candidates around the cut held in LDS; more are swept from memory
-constexpr int kRankMax = 128;         // candidates around the cut that are ranked against each other
-constexpr int kDigit = 11;            // bits per pass of the radix select among them
+constexpr int kFew = 64;              // candidates around the cut that one wave finishes
+constexpr int kDigit = 10;            // bits per pass of the radix select
 constexpr int kMaxBand = 512;         // candidates re-scored per head; beyond that binary32 decides (and the caller is told)
 constexpr int kVoteSlots = 2048;      // binary64 votes (distinct positions) held in LDS during the re-scoring
 constexpr int kPartSlots = 1792;      // ... and partial votes of a batch of positions
@@ -695,7 +700,7 @@ constexpr float kBandRel = 2.0e-5f;   // >> the binary32 error of a vote (a few 
 struct SelectArgs {
     const float* vote;      // [heads, P]
     uint16_t* code;         // [heads, p_stride] codes of the pooled scores, in groups of eight (codes_above)
-    uint16_t* bins;         // [heads, n_seg, kBins] counts of every pooling workgroup
+    uint16_t* bins;         // [heads, n_seg, kBinRow] counts of every pooling workgroup
     float* exact;           // [heads, p_stride] pooled scores, only where the candidates around the cut don't fit the list; or NULL
     int32_t* idx;           // [heads, n_kept], in the workspace: the list that the quantizer reads
     int32_t* list;          // the caller's, written beside it and never read; or NULL
@@ -707,6 +712,7 @@ struct SelectArgs {
     const double* zsum;     // Z binary64
     int P, p_stride, L, W, n_kept, pool, gq, n_q_heads, n_kv_heads, rows, rows_pad;
     int n_seg, seg_tiles;   // pooling workgroups per head and their pooling tiles
+    uint32_t w_recip;       // 2^16 / W, rounded up: the quotient of a row number by W (both at most 256) without a division
     float sm_scale;
 };
 
@@ -733,15 +739,40 @@ __device__ __forceinline__ uint32_t codes_above(const uint4& w4, uint32_t t) {
     return (m | (m >> 12)) & 0xffu;
 }
 
+// Sum of c over the lanes up to this one; the wave's total is lane 63's.  (Lanes passed along a row and the rows' sums
+// along the wave, without LDS: an exchange through it takes 50 ns, six of them on a path that is all latency.)
+template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_from(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
+__device__ __forceinline__ int lanes_up_to(int c) {
+    c += dpp_from<0x111, 0xf>(c);   // row_shr 1, 2, 4, 8
+    c += dpp_from<0x112, 0xf>(c);
+    c += dpp_from<0x114, 0xf>(c);
+    c += dpp_from<0x118, 0xf>(c);
+    c += dpp_from<0x142, 0xa>(c);   // row_bcast 15: the row before, into rows 1 and 3
+    c += dpp_from<0x143, 0xc>(c);   // row_bcast 31: the first half, into the second
+    return c;
+}
+__device__ __forceinline__ int wave_sum(int c) { return __builtin_amdgcn_readlane(lanes_up_to(c), 63); }
+__device__ __forceinline__ uint32_t wave_min(uint32_t c) {
+    auto low = [&](auto ctrl, auto rows) { c = min(c, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)c, decltype(ctrl)::value, decltype(rows)::value, 0xf, false)); };
+    low(IntC<0x111>{}, IntC<0xf>{}); low(IntC<0x112>{}, IntC<0xf>{}); low(IntC<0x114>{}, IntC<0xf>{}); low(IntC<0x118>{}, IntC<0xf>{});
+    low(IntC<0x142>{}, IntC<0xa>{}); low(IntC<0x143>{}, IntC<0xc>{});
+    return (uint32_t)__builtin_amdgcn_readlane((int)c, 63);
+}
+// visit(i) for the lanes 0 .. n - 1 (n <= 64) and possibly a few more, eight at a time: a branch that is taken costs 25 ns,
+// a lane's value read and compared 3.
+template <class Visit>
+__device__ __forceinline__ void each_lane(int n, Visit visit) {
+    n = __builtin_amdgcn_readfirstlane(n);
+    for (int i = 0; i < n; i += 8) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) visit(i + u);
+    }
+}
+
 // Sum of c over the threads before this one (the caller puts a barrier between two uses of swave).
 __device__ __forceinline__ int sum_before(int c, int* swave) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int inc = c;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(inc, off);
-        if (lane >= off) inc += o;
-    }
+    const int inc = lanes_up_to(c);
     if (lane == 63) swave[w] = inc;
     __syncthreads();
     int before = inc - c;
@@ -753,15 +784,10 @@ __device__ __forceinline__ int sum_before(int c, int* swave) {
 // Sum of c over the threads after this one (the caller puts a barrier between two uses of swave).
 __device__ __forceinline__ int sum_after(int c, int* swave) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int suf = c;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_down(suf, off);
-        if (lane + off < 64) suf += o;
-    }
-    if (lane == 0) swave[w] = suf;
+    const int inc = lanes_up_to(c), all = __builtin_amdgcn_readlane(inc, 63);
+    if (lane == 63) swave[w] = all;
     __syncthreads();
-    int after = suf - c;
+    int after = all - inc;
 #pragma unroll
     for (int i = 0; i < kSelWaves; ++i)
         if (i > w) after += swave[i];
@@ -771,43 +797,54 @@ __device__ __forceinline__ int sum_after(int c, int* swave) {
 __device__ __forceinline__ float half_lo(uint32_t w) { return __half2float(__ushort_as_half((uint16_t)(w & 0xffffu))); }
 __device__ __forceinline__ float half_hi(uint32_t w) { return __half2float(__ushort_as_half((uint16_t)(w >> 16))); }
 
-// Part of the binary64 vote of one prefix key, computed by one wave: the sum over 32 of the group's
-// window rows (row_base + lane/2; the two lanes of a row split the channels) of
+// Part of the binary64 vote of one prefix key, computed by one wave: the sum over kPartRows of the group's
+// window rows (row_base + lane / 4; the four lanes of a row split the channels) of
 // exp2(logit - m_r) / Z_r with the pass-1 statistics.  A product of two binary16 values is exact in
-// binary32; the products are summed in binary64.
+// binary32; the products are summed in binary64.  (It is all latency: few positions are scored, so the rows are spread over as many
+// waves as there are and lanes meet without LDS.)
+constexpr int kPartRows = 16;
+template <int CTRL> __device__ __forceinline__ double dpp_f64(double v) {     // (0 where a row has no such lane)
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)b, lane), hi = (uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 __device__ double vote_f64_part(const SelectArgs& a, int head, int key, int row_base) {
     const int b = head / a.n_kv_heads, g = head % a.n_kv_heads;
-    const int lane = threadIdx.x & 63, half = lane & 1;
-    const int r = row_base + (lane >> 1);
+    const int lane = threadIdx.x & 63, quarter = lane & 3;
+    const int r = row_base + (lane >> 2);
     const bool live = r < a.rows;
     const int rc = live ? r : 0;
-    const int hl = rc / a.W, i = rc % a.W;
-    const uint4* kr = reinterpret_cast<const uint4*>(a.k + ((size_t)head * a.L + key) * kHeadDim) + 8 * half;
-    const uint4* qr = reinterpret_cast<const uint4*>(a.q_obs + (((size_t)b * a.n_q_heads + g * a.gq + hl) * a.W + i) * kHeadDim) + 8 * half;
+    const int hl = (int)(((uint32_t)rc * a.w_recip) >> 16), i = rc - hl * a.W;
+    const uint4* kr = reinterpret_cast<const uint4*>(a.k + ((size_t)head * a.L + key) * kHeadDim) + 4 * quarter;
+    const uint4* qr = reinterpret_cast<const uint4*>(a.q_obs + (((size_t)b * a.n_q_heads + g * a.gq + hl) * a.W + i) * kHeadDim) + 4 * quarter;
     const double m = (double)a.stats[(size_t)head * a.rows_pad + rc].x;
     const double z = a.zsum[(size_t)head * a.rows_pad + rc];
     double s0 = 0.0, s1 = 0.0;
+    uint4 qv[4], kv[4];
 #pragma unroll
-    for (int c0 = 0; c0 < 8; c0 += 4) {
-        uint4 qv[4], kv[4];
+    for (int c = 0; c < 4; ++c) { qv[c] = qr[c]; kv[c] = kr[c]; }
 #pragma unroll
-        for (int c = 0; c < 4; ++c) { qv[c] = qr[c0 + c]; kv[c] = kr[c0 + c]; }
+    for (int c = 0; c < 4; ++c) {
+        const uint32_t qw[4] = {qv[c].x, qv[c].y, qv[c].z, qv[c].w}, kw[4] = {kv[c].x, kv[c].y, kv[c].z, kv[c].w};
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const uint32_t qw[4] = {qv[c].x, qv[c].y, qv[c].z, qv[c].w}, kw[4] = {kv[c].x, kv[c].y, kv[c].z, kv[c].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                s0 += (double)(half_lo(qw[e]) * half_lo(kw[e]));
-                s1 += (double)(half_hi(qw[e]) * half_hi(kw[e]));
-            }
+        for (int e = 0; e < 4; ++e) {
+            s0 += (double)__builtin_fmaf(half_lo(qw[e]), half_lo(kw[e]), 0.0f);       // (v_fma_mix_f32: no conversions)
+            s1 += (double)__builtin_fmaf(half_hi(qw[e]), half_hi(kw[e]), 0.0f);
         }
     }
     double s = s0 + s1;
-    s += __shfl_xor(s, 1);
-    double acc = (live && half == 0) ? exp2(s * ((double)a.sm_scale * 1.4426950408889634074) - m) / z : 0.0;
-#pragma unroll
-    for (int off = 32; off >= 2; off >>= 1) acc += __shfl_xor(acc, off);
-    return acc;
+    s += dpp_f64<0xB1>(s);                        // quad_perm [1,0,3,2]
+    s += dpp_f64<0x4E>(s);                        // quad_perm [2,3,0,1]
+    double acc = (live && quarter == 0) ? exp2(s * ((double)a.sm_scale * 1.4426950408889634074) - m) / z : 0.0;
+    acc += dpp_f64<0x114>(acc);                   // row_shr 4, 8: lane 12 of a row of 16 has its four window rows
+    acc += dpp_f64<0x118>(acc);
+    return (lane_f64(acc, 12) + lane_f64(acc, 28)) + (lane_f64(acc, 44) + lane_f64(acc, 60));
 }
 
 // Max-pooling of one tile: the votes of candidates j0 - r .. j0 + kPoolTile + r go through LDS (0
@@ -871,7 +908,7 @@ __device__ __forceinline__ float4 pool_four(const float* stage, int r) {
 // Pooled scores and their bin counts; workgroup x of a head takes seg_tiles consecutive tiles.
 __global__ __launch_bounds__(kSelThreads) void pool_scores(const SelectArgs a) {
     __shared__ __align__(16) float stage[kStage];
-    __shared__ __align__(16) int hist[kBins];
+    __shared__ __align__(16) int hist[kBinRow];
     const int head = blockIdx.y;
     const int P = a.P, k = a.head_n ? a.head_n[head] : a.n_kept;
     if (k <= 0 || k >= P) return;               // (nothing of this head is cut)
@@ -905,51 +942,78 @@ __global__ __launch_bounds__(kSelThreads) void pool_scores(const SelectArgs a) {
                                                              : make_uint2(cd[0] | (got0 << 16), cd[1] | (got1 << 16));
         __syncthreads();
     }
+    // (the words behind the bins' counts stay 0 here: the places of the groups' counts)
     const int4 c = *reinterpret_cast<const int4*>(hist + 4 * threadIdx.x);
-    uint2* out = reinterpret_cast<uint2*>(a.bins + ((size_t)head * a.n_seg + blockIdx.x) * kBins) + threadIdx.x;
-    *out = make_uint2((uint32_t)c.x | ((uint32_t)c.y << 16), (uint32_t)c.z | ((uint32_t)c.w << 16));
+    uint16_t* row = a.bins + ((size_t)head * a.n_seg + blockIdx.x) * kBinRow;
+    if (4 * (int)threadIdx.x < kBins)
+        reinterpret_cast<uint2*>(row)[threadIdx.x] = make_uint2((uint32_t)c.x | ((uint32_t)c.y << 16), (uint32_t)c.z | ((uint32_t)c.w << 16));
+    int sum = (c.x + c.y) + (c.z + c.w);        // a group is the bins of sixteen threads
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+    if ((threadIdx.x & 15) == 0) row[kBins + (threadIdx.x >> 4)] = (uint16_t)sum;
 }
 
-// One workgroup per (batch, kv head).  keep: the survivor mask, bit j % 8 of byte j / 8.
-// T > 0: the prefix is at most T pooling tiles, pooled and counted here; of every tile thread t keeps the scores of
-// candidates 4 t .. 4 t + 3.  T = 0: pool_scores has left codes and counts.
+// The bin of the k-th largest score: its group by the groups' counts, then by the counts of that group's bins
+// (two round trips, but a few KB per workgroup instead of all counts).  One wave's work.
+__device__ __forceinline__ int bin_of_cut(const uint16_t* bins, int n_seg, int k) {
+    const int lane = threadIdx.x & 63;
+    auto find = [&](const uint16_t* row, int n, int& above) {
+        uint16_t x[kMaxSegs];
+#pragma unroll
+        for (int s = 0; s < kMaxSegs; ++s) x[s] = s < n_seg && lane < n ? row[(size_t)s * kBinRow + lane] : (uint16_t)0;
+        int c = 0;
+#pragma unroll
+        for (int s = 0; s < kMaxSegs; ++s) c += x[s];
+        const int inc = lanes_up_to(c), before = above + __builtin_amdgcn_readlane(inc, 63) - inc;
+        const unsigned long long here = __builtin_amdgcn_ballot_w64(before < k && before + c >= k);   // exactly one lane
+        const int at = here ? __builtin_ctzll(here) : 0;
+        above = __builtin_amdgcn_readlane(before, at);
+        return at;
+    };
+    int above = 0;
+    const int group = find(bins + kBins, kGroups, above);
+    return kGroupBins * group + find(bins + kGroupBins * group, kGroupBins, above);
+}
+
+// T > 0: the prefix is at most T pooling tiles, pooled and counted here by one workgroup per (batch, kv head); of every tile
+// thread t keeps the scores of candidates 4 t .. 4 t + 3.
+// T = 0: pool_scores has left codes and counts; one workgroup per head sweeps them.
+// keep: the survivor mask, bit j % 8 of byte j / 8.
 template <int T>
 __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     constexpr bool OWN = T > 0;
     __shared__ __align__(16) uint32_t keep[(OWN ? T * kPoolTile : kMaxPrefix) / 32];
-    __shared__ __align__(16) int tab[2 * kSelThreads + (1 << kDigit)];   // the counts of the bins (OWN); later the band, then:
-    int* hist = tab + 2 * kSelThreads;                            // radix digits; later the positions to re-score
+    __shared__ __align__(16) int tab[2 * kSelThreads + kVoteSlots];      // the counts of the bins (OWN); later the band, then:
+    int* hist = tab + 2 * kSelThreads;                            // radix digits and the candidates of the last; later the positions to re-score
     uint32_t* ties = reinterpret_cast<uint32_t*>(tab);            // where binary32 decides: the mask of the candidates equal to the cut
     __shared__ __align__(16) unsigned char big[T > 1 ? 2 * kStage * 4 : kListCap * 8];     // candidates around the cut, or (too many) the pooling stage; before that the pooling stage (OWN); later the binary64 votes
     __shared__ int swave[kSelWaves];
-    __shared__ int s_bin, s_list, s_sure, s_need, s_band, s_hot;
-    __shared__ uint32_t s_prefix;
-    static_assert(kListCap * 8 >= kStage * 4 && sizeof(tab) >= kBins * 4 && kListCap * 8 >= (kPartSlots + kVoteSlots) * 8 &&
-                  sizeof(tab) >= kMaxPrefix / 8 && kVoteSlots <= (1 << kDigit), "aliases fit");
+    __shared__ int s_bin, s_list, s_listed, s_sure, s_digit, s_above, s_few, s_take, s_band, s_hot;
+    __shared__ uint32_t s_cut;
+    static_assert(kListCap * 8 >= kStage * 4 && sizeof(tab) >= kBinRow * 4 && sizeof(tab) >= (2 * kSelWaves + kListCap) * 4 && kListCap * 8 >= (kPartSlots + kVoteSlots) * 8 &&
+                  sizeof(tab) >= kMaxPrefix / 8 && (1 << kDigit) == kSelThreads && kVoteSlots >= (1 << kDigit) + 2 * kFew, "aliases fit");
 
     const int head = blockIdx.x;
     const int P = a.P, k = a.head_n ? a.head_n[head] : a.n_kept;
     const float* vote = a.vote + (size_t)head * P;
-    const uint16_t* code = a.code + (size_t)head * a.p_stride;
     int32_t* idx = a.idx + (size_t)head * a.n_kept;
     int32_t* list = a.list ? a.list + (size_t)head * a.n_kept : idx;      // (the same words twice where there is none)
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = (a.pool - 1) / 2;
 
-    if (a.unrefined && threadIdx.x == 0) a.unrefined[head] = 0;   // (overwritten below by the same thread if binary32 decides)
-    if (k <= 0) return;   // (a head-level count may be zero)
-    if (k >= P) {  // budget covers the prefix: identity, the scores are not looked at
+    if (k <= 0 || k >= P) {   // (a head-level count may be zero; one that covers the prefix: identity, the scores are not looked at)
+        if (a.unrefined && threadIdx.x == 0) a.unrefined[head] = 0;
         for (int j = threadIdx.x; j < k; j += kSelThreads) { idx[j] = j; list[j] = j; }
         return;
     }
-    if (threadIdx.x == 0) { s_list = 0; s_sure = 0; s_band = 0; s_hot = 0; }
+    if (threadIdx.x == 0) { s_list = 0; s_sure = 0; s_listed = 0; s_few = 0; s_band = 0; s_hot = 0; }
 
     // ---- the bin of the k-th largest score ----
-    const int n_oct = (P + 7) / 8;
-    uint4 oct[OWN ? 1 : kOctets];                  // the thread's octets of codes: thread + 1024 i
     uint32_t own[OWN ? 4 * T : 1];                 // OWN: the thread's scores (all ones past the end: neither above nor around the cut)
     auto own_at = [&](int i) { return (i >> 2) * kPoolTile + 4 * (int)threadIdx.x + (i & 3); };   // ... and their candidates
-    int c[4] = {0, 0, 0, 0};                       // counts of bins 4 thread .. 4 thread + 3
+    const int n_oct = (P + 7) / 8;
+    const char* codes = OWN ? nullptr : reinterpret_cast<const char*>(a.code + (size_t)head * a.p_stride);
+    uint4 oct[OWN ? 1 : kOctets];                  // the thread's groups of eight codes: thread + 1024 i
     if constexpr (OWN) {
         const int n_tiles = (P + kPoolTile - 1) / kPoolTile;
         // (two places for a tile's votes, one barrier per tile; two tiles' votes on their way while one is pooled)
@@ -979,36 +1043,36 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
         }
         __syncthreads();
         const int4 b = *reinterpret_cast<const int4*>(tab + 4 * threadIdx.x);
-        c[0] = b.x; c[1] = b.y; c[2] = b.z; c[3] = b.w;
-    } else {
-        const uint2* bins = reinterpret_cast<const uint2*>(a.bins + (size_t)head * a.n_seg * kBins) + threadIdx.x;
-        uint2 b[kMaxSegs];
+        const int c[4] = {b.x, b.y, b.z, b.w};         // counts of bins 4 thread .. 4 thread + 3
+        // every wave its 256 bins; the wave that has the cut looks closer
+        const int inc = lanes_up_to((c[0] + c[1]) + (c[2] + c[3])), all = __builtin_amdgcn_readlane(inc, 63);
+        if (lane == 0) swave[wave] = all;
+        __syncthreads();
+        const int up_to = lanes_up_to(lane < kSelWaves ? swave[lane] : 0);
+        int above = __builtin_amdgcn_readlane(up_to, kSelWaves - 1) - __builtin_amdgcn_readlane(up_to, wave);
+        if (above < k && above + all >= k) {
+            above += all - inc;
 #pragma unroll
-        for (int s = 0; s < kMaxSegs; ++s) b[s] = s < a.n_seg ? bins[(size_t)s * (kBins / 4)] : make_uint2(0u, 0u);
-        // all codes are requested before the counts are looked at
+            for (int i = 3; i >= 0; --i) {
+                if (above < k && above + c[i] >= k) s_bin = 4 * (int)threadIdx.x + i;    // exactly one bin
+                above += c[i];
+            }
+        }
+    } else {
 #pragma unroll
         for (int i = 0; i < kOctets; ++i) {
             const int o = (int)threadIdx.x + i * kSelThreads;
-            oct[i] = o < n_oct ? reinterpret_cast<const uint4*>(code)[o] : make_uint4(0u, 0u, 0u, 0u);
+            oct[i] = o < n_oct ? reinterpret_cast<const uint4*>(codes)[o] : make_uint4(0u, 0u, 0u, 0u);
         }
-#pragma unroll
-        for (int s = 0; s < kMaxSegs; ++s) {
-            c[0] += (int)(b[s].x & 0xffffu); c[1] += (int)(b[s].x >> 16);
-            c[2] += (int)(b[s].y & 0xffffu); c[3] += (int)(b[s].y >> 16);
-        }
-    }
-    {
-        int above = sum_after(c[0] + c[1] + c[2] + c[3], swave);
-#pragma unroll
-        for (int i = 3; i >= 0; --i) {
-            if (above < k && above + c[i] >= k) s_bin = 4 * (int)threadIdx.x + i;    // exactly one bin
-            above += c[i];
+        if (wave == 0) {
+            const int bin = bin_of_cut(a.bins + (size_t)head * a.n_seg * kBinRow, a.n_seg, k);
+            if (lane == 0) s_bin = bin;
         }
     }
-    __syncthreads();
+    __syncthreads();                                   // (the counters in LDS are set, too)
+    const int cb = __builtin_amdgcn_readfirstlane(s_bin);
     // Candidates of that bin and one code on either side (32768 patterns; the band around the cut
     // reaches at most 2e-5 * 2^24 = 336): codes clo .. chi, patterns klo .. khi.  Everything above survives.
-    const int cb = __builtin_amdgcn_readfirstlane(s_bin);
     constexpr uint32_t kCodesPerBin = 1u << (kBinShift - kCodeShift);
     const uint32_t clo = cb == 0 ? 0u : (uint32_t)(cb + kBinBase) * kCodesPerBin - 1u;
     const uint32_t chi = cb == kBins - 1 ? 0xffffu : (uint32_t)(cb + 1 + kBinBase) * kCodesPerBin;
@@ -1017,6 +1081,8 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     // ---- one sweep: the mask of what lies above, the list of what lies around the cut ----
     uint32_t* list_key = reinterpret_cast<uint32_t*>(big);
     int* list_pos = reinterpret_cast<int*>(big + kListCap * 4);
+    uint32_t* groups = reinterpret_cast<uint32_t*>(tab) + 2 * kSelWaves;        // [kListCap], not OWN: groups with candidates around the cut, until these are listed
+    constexpr int kGroupCount = 18;                                             // s_list, not OWN: groups above this bit, candidates below (131072 at most)
     int sure = 0;
     if constexpr (OWN) {
 #pragma unroll
@@ -1030,34 +1096,36 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
             for (int i = 0; i < 4; ++i)
                 if (own[4 * q + i] >= klo && own[4 * q + i] <= khi) {
                     const int e = atomicAdd(&s_list, 1);
-                    if (e < kListCap) list_key[e] = own[4 * q + i];
+                    if (e < kListCap) { list_key[e] = own[4 * q + i]; list_pos[e] = own_at(4 * q + i); }
                 }
         }
     } else {
+        // (a group with candidates around the cut is listed whole, {group, which of its eight}: the sweep is bound by what it
+        // issues, and a write per candidate was most of it)
 #pragma unroll
         for (int i = 0; i < kOctets; ++i) {
             const int o = (int)threadIdx.x + i * kSelThreads;
-            if (o < n_oct) {
-                const uint32_t above = codes_above(oct[i], chi);
-                uint32_t around = clo ? codes_above(oct[i], clo - 1u) & ~above : 0xffu & ~above;
-                if (8 * o + 8 > P) around &= (1u << (P - 8 * o)) - 1u;      // (past the end the codes are 0)
-                reinterpret_cast<unsigned char*>(keep)[o] = (unsigned char)above;
-                sure += __popc(above);
-                if (around) {
-                    int e = atomicAdd(&s_list, __popc(around));
-                    for (; around; around &= around - 1u, ++e)
-                        if (e < kListCap) list_pos[e] = 8 * o + __builtin_ctz(around);
-                }
+            if (o >= n_oct) break;
+            const uint32_t above = codes_above(oct[i], chi);                    // (past the end the codes are 0)
+            uint32_t around = clo ? codes_above(oct[i], clo - 1u) & ~above : 0xffu & ~above;
+            if (8 * o + 8 > P) around &= (1u << (P - 8 * o)) - 1u;
+            reinterpret_cast<unsigned char*>(keep)[o] = (unsigned char)above;
+            sure += __popc(above);
+            if (around) {
+                const uint32_t e = (uint32_t)atomicAdd(&s_list, (1 << kGroupCount) + __popc(around)) >> kGroupCount;
+                if (e < kListCap) groups[e] = ((uint32_t)o << 8) | around;
             }
         }
         for (int o = n_oct + (int)threadIdx.x; o < (n_oct + 3) / 4 * 4; o += kSelThreads) reinterpret_cast<unsigned char*>(keep)[o] = 0;
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) sure += __shfl_xor(sure, off);
+    sure = wave_sum(sure);
     if (lane == 0 && sure) atomicAdd(&s_sure, sure);
     __syncthreads();
-    const int n_list = __builtin_amdgcn_readfirstlane(s_list);
-    const int need_around = k - __builtin_amdgcn_readfirstlane(s_sure);   // how many of the candidates around the cut survive
+    int n_list = __builtin_amdgcn_readfirstlane(s_list), n_groups = 0;
+    int n_sure = __builtin_amdgcn_readfirstlane(s_sure);
+    if constexpr (!OWN) { n_groups = (int)((uint32_t)n_list >> kGroupCount); n_list &= (1 << kGroupCount) - 1; }
+    if (a.unrefined && threadIdx.x == 0) a.unrefined[head] = 0;   // (overwritten below by the same thread if binary32 decides)
+    const int need_around = k - n_sure;   // how many of the candidates around the cut survive
     // the pooled score of a candidate, from the votes
     auto pooled_key = [&](int j) -> uint32_t {
         const int t1 = min(j + r, P - 1);
@@ -1072,8 +1140,17 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
         return score_key(best);
     };
     if constexpr (!OWN) {
+        // the listed groups' candidates and their scores, eight threads a group
         if (n_list <= kListCap)
-            for (int e = threadIdx.x; e < n_list; e += kSelThreads) list_key[e] = pooled_key(list_pos[e]);   // (read back by the same thread only)
+            for (int i = threadIdx.x; i < 8 * n_groups; i += kSelThreads) {
+                const uint32_t group = groups[i >> 3];
+                if (group >> (i & 7) & 1u) {
+                    const int j = 8 * (int)(group >> 8) + (i & 7);
+                    const uint32_t key = pooled_key(j);
+                    const int e = atomicAdd(&s_listed, 1);
+                    list_key[e] = key; list_pos[e] = j;
+                }
+            }
     }
     // Where the list is too short (thousands of scores within two percent of the cut), the whole prefix is
     // pooled once more, tile by tile, into memory; a thread reads back only what it has stored itself.  (In a
@@ -1096,15 +1173,16 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
             }
         }
     }
-    // every candidate around the cut: from the thread's own scores (OWN), from the list (in no
-    // particular order) or from all pooled scores
+    __syncthreads();                            // (the list and its scores are there)
+    // every candidate around the cut: from the list (in no particular order), from the thread's own scores (OWN) or
+    // from all pooled scores
     auto each_around = [&](auto visit) {
-        if constexpr (OWN) {
+        if (__builtin_expect(n_list <= kListCap, 1)) {
+            for (int e = threadIdx.x; e < n_list; e += kSelThreads) visit(list_key[e], list_pos[e]);
+        } else if constexpr (OWN) {
 #pragma unroll
             for (int i = 0; i < 4 * T; ++i)
                 if (own[i] >= klo && own[i] <= khi) visit(own[i], own_at(i));
-        } else if (__builtin_expect(n_list <= kListCap, 1)) {
-            for (int e = threadIdx.x; e < n_list; e += kSelThreads) visit(list_key[e], list_pos[e]);
         } else if (!exact) {
             for (int j = threadIdx.x; j < P; j += kSelThreads) {
                 const uint32_t key = pooled_key(j);
@@ -1129,98 +1207,139 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     };
     auto set_keep = [&](int j) { atomicOr(&keep[j >> 5], 1u << (j & 31)); };
 
-    // ---- the exact cut: up to a hundred candidates are ranked against each other, every wave against its
-    // share of them (1.0 to 1.9 us for 15 to 100 of them, where two radix passes take 2.5 to 3; 3.5 and
-    // more for 200); more go through a radix select on the patterns relative to klo ----
-    uint32_t prefix = 0u;
-    int need = need_around;
-    if (__builtin_expect(n_list <= kRankMax, 1)) {
-        if (threadIdx.x < 4) list_key[n_list + threadIdx.x] = 0u;       // (whole 16-byte pieces; 0 is above no candidate)
-        for (int e = threadIdx.x; e < n_list; e += kSelThreads) hist[e] = 0;
-        __syncthreads();
-        const int n4 = (n_list + 3) / 4, share = (n4 + kSelWaves - 1) / kSelWaves;
-        const uint4* others = reinterpret_cast<const uint4*>(list_key);
-        for (int e = lane; e < n_list; e += 64) {
-            const uint32_t mine = list_key[e];
-            int count = 0;                                                // candidates above; 16 bits higher: at or above
-#pragma unroll 4
-            for (int o = wave * share; o < min(n4, wave * share + share); ++o) {
-                const uint4 x = others[o];
-                count += (x.x > mine) + (x.y > mine) + (x.z > mine) + (x.w > mine);
-                count += ((x.x >= mine) + (x.y >= mine) + (x.z >= mine) + (x.w >= mine)) << 16;
-            }
-            if (count) atomicAdd(&hist[e], count);
-        }
-        __syncthreads();
-        for (int e = threadIdx.x; e < n_list; e += kSelThreads) {
-            const int above = hist[e] & 0xffff, at_least = min(hist[e] >> 16, n_list);   // (the padding counts where the score is 0)
-            if (above < need && at_least >= need) { s_prefix = list_key[e] - klo; s_need = need - above; }   // (the same from every candidate at the cut)
-        }
-        __syncthreads();
-        prefix = __builtin_amdgcn_readfirstlane(s_prefix);
-        need = __builtin_amdgcn_readfirstlane(s_need);
-    } else {
-        const int bits = 32 - __builtin_clz(khi - klo);
-        int fixed = bits, shift = bits > kDigit ? bits - kDigit : 0;
-        for (;;) {
-            for (int i = threadIdx.x; i < (1 << kDigit); i += kSelThreads) hist[i] = 0;
-            __syncthreads();
-            each_around([&](uint32_t key, int) {
-                const uint32_t rel = key - klo;
-                if (fixed >= 32 || (rel >> fixed) == (prefix >> fixed)) {
-                    const int digit = (int)((rel >> shift) & ((1u << (fixed - shift)) - 1u)), some = __builtin_amdgcn_readfirstlane(digit);
-                    const unsigned long long alike = __builtin_amdgcn_ballot_w64(digit == some);     // (ties: one of the lanes counts them all)
-                    if (digit != some) atomicAdd(&hist[digit], 1);
-                    else if (lane == __builtin_ctzll(alike)) atomicAdd(&hist[some], __popcll(alike));
-                }
-            });
-            __syncthreads();
-            const int c0 = hist[2 * threadIdx.x], c1 = hist[2 * threadIdx.x + 1];
-            const int above = sum_after(c0 + c1, swave);
-            if (above < need && above + c1 >= need) { s_prefix = 2u * threadIdx.x + 1u; s_need = need - above; }
-            else if (above + c1 < need && above + c1 + c0 >= need) { s_prefix = 2u * threadIdx.x; s_need = need - above - c1; }
-            __syncthreads();
-            prefix |= __builtin_amdgcn_readfirstlane(s_prefix) << shift;
-            need = __builtin_amdgcn_readfirstlane(s_need);
-            if (shift == 0) break;
-            fixed = shift;
-            shift = shift > kDigit ? shift - kDigit : 0;
-        }
-    }
-    const uint32_t cut_key = klo + prefix;
-    const float cut = __uint_as_float(cut_key);
-    const int need_at_cut = need;     // how many candidates equal to the cut are taken (binary32 rule)
-    // band of scores that binary32 rounding could move across the cut
-    const float lo = cut * (1.0f - kBandRel), hi = cut * (1.0f + kBandRel);
-
-    // ---- survivors above the band, and the band itself in position order ----
+    // ---- the cut, the survivors above its band, and the band in position order ----
+    // Every instruction of the workgroup's sixteen waves costs 8 ns here, one of a single wave 2, a barrier 12 and a
+    // branch that is taken 25.  So few candidates are one wave's work, one per lane, in straight lines; of more candidates
+    // a radix pass leaves those whose digit is near the cut's (plateaus of the max-pool make several of them alike).
     int* band_raw = tab;                                                   // [kMaxBand] as found
     int* band_pos = tab + kMaxBand;                                        // [kMaxBand] ascending
     double* band_score = reinterpret_cast<double*>(tab + 2 * kMaxBand);    // [kMaxBand]
     static_assert(4 * kMaxBand <= 2 * kSelThreads, "the band fits the table");
-    if (threadIdx.x == 0) s_sure = 0;
-    __syncthreads();
-    each_around([&](uint32_t key, int j) {
-        const float v = __uint_as_float(key);
-        if (v > hi) { set_keep(j); atomicAdd(&s_sure, 1); }
-        else if (v >= lo) {
-            const int e = atomicAdd(&s_band, 1);
-            if (e < kMaxBand) band_raw[e] = j;
-        }
-    });
-    __syncthreads();
-    const int tot_band = __builtin_amdgcn_readfirstlane(s_band);
-    const int take = need_around - __builtin_amdgcn_readfirstlane(s_sure);   // members of the band that survive
-    bool refine = tot_band <= kMaxBand;
-    if (refine) {
-        for (int e = threadIdx.x; e < tot_band; e += kSelThreads) {
-            const int j = band_raw[e];
-            int rank = 0;
-            for (int o = 0; o < tot_band; ++o) rank += band_raw[o] < j;
-            band_pos[rank] = j;
+    // One pass: counts the digits of the candidates that share the prefix and finds the need-th largest's.
+    uint32_t prefix = 0u;
+    int need = need_around;                     // the cut is the need-th largest of the candidates that share the prefix
+    int fixed = 32 - __builtin_clz(khi - klo), shift = fixed;
+    auto radix_pass = [&] {
+        hist[threadIdx.x] = 0;
+        __syncthreads();
+        shift = fixed > kDigit ? fixed - kDigit : 0;
+        each_around([&](uint32_t key, int) {
+            const uint32_t rel = key - klo;
+            if (fixed >= 32 || (rel >> fixed) == (prefix >> fixed)) {
+                const int digit = (int)((rel >> shift) & ((1u << (fixed - shift)) - 1u)), some = __builtin_amdgcn_readfirstlane(digit);
+                const unsigned long long alike = __builtin_amdgcn_ballot_w64(digit == some);     // (ties: one of the lanes counts them all)
+                if (digit != some) atomicAdd(&hist[digit], 1);
+                else if (lane == __builtin_ctzll(alike)) atomicAdd(&hist[some], __popcll(alike));
+            }
+        });
+        __syncthreads();
+        if (wave == 0) {                        // lane l: digits 256 u + 4 l .. + 3
+            int4 c[4];
+            int inc[4], all[4], above[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                c[u] = reinterpret_cast<const int4*>(hist)[64 * u + lane];
+                inc[u] = lanes_up_to((c[u].x + c[u].y) + (c[u].z + c[u].w));
+                all[u] = __builtin_amdgcn_readlane(inc[u], 63);
+            }
+#pragma unroll
+            for (int u = 3; u >= 0; --u) above[u] = u == 3 ? 0 : above[u + 1] + all[u + 1];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int four[4] = {c[u].x, c[u].y, c[u].z, c[u].w};
+                int before = above[u] + all[u] - inc[u];
+#pragma unroll
+                for (int q = 3; q >= 0; --q) {
+                    if (before < need && before + four[q] >= need) { s_digit = 256 * u + 4 * lane + q; s_above = before; }     // exactly one digit
+                    before += four[q];
+                }
+            }
         }
         __syncthreads();
+        prefix |= __builtin_amdgcn_readfirstlane(s_digit) << shift;
+        need -= __builtin_amdgcn_readfirstlane(s_above);
+        fixed = shift;
+    };
+    const uint32_t* few_key = list_key;
+    const int* few_pos = list_pos;
+    int n_few = n_list;                         // candidates that one wave may go on with, and ...
+    int need_few = need_around;                 // ... how many of them survive
+    if (__builtin_expect(n_list > kFew && n_list <= kListCap, 0)) {
+        radix_pass();
+        // the digits that the band can reach: it is narrower than two of them (336 patterns; a digit has 256 and more)
+        uint32_t* key_to = reinterpret_cast<uint32_t*>(hist) + (1 << kDigit);
+        int* pos_to = hist + (1 << kDigit) + kFew;
+        const uint32_t digit = prefix >> shift, last = (1u << kDigit) - 1u;
+        const uint32_t d_hi = min(digit + 2u, last), d_lo = digit > 2u ? digit - 2u : 0u;
+        need_few = need;
+        if (digit + 1u <= last) need_few += hist[digit + 1u];
+        if (digit + 2u <= last) need_few += hist[digit + 2u];
+        each_around([&](uint32_t key, int j) {
+            const uint32_t d = (key - klo) >> shift;
+            if (d > d_hi) set_keep(j);
+            else if (d >= d_lo) {
+                const int e = atomicAdd(&s_few, 1);
+                if (e < kFew) { key_to[e] = key; pos_to[e] = j; }
+            }
+        });
+        __syncthreads();
+        n_few = __builtin_amdgcn_readfirstlane(s_few);
+        few_key = key_to; few_pos = pos_to;
     }
+    if (__builtin_expect(n_few <= kFew, 1)) {
+        if (wave == 0) {
+            const uint32_t key = lane < n_few ? few_key[lane] : 0u;
+            const int j = lane < n_few ? few_pos[lane] : 0x7fffffff;
+            int above = 0;
+            each_lane(n_few, [&](int i) { above += (uint32_t)__builtin_amdgcn_readlane((int)key, i) > key; });     // (lanes past them: 0)
+            // the cut is the lowest score that fewer than need_few are above
+            const uint32_t at_cut = wave_min(lane < n_few && above < need_few ? key : 0xffffffffu);
+            const float low = __uint_as_float(at_cut) * (1.0f - kBandRel), high = __uint_as_float(at_cut) * (1.0f + kBandRel), v = __uint_as_float(key);
+            const bool over = lane < n_few && v > high, in = lane < n_few && v <= high && v >= low;
+            if (over) set_keep(j);
+            const unsigned long long band = __builtin_amdgcn_ballot_w64(in);
+            const int n_over = __popcll(__builtin_amdgcn_ballot_w64(over)), n_band = __popcll(band);
+            if (in) band_raw[__builtin_amdgcn_mbcnt_hi((uint32_t)(band >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)band, 0u))] = j;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // (LDS serves a wave in order; this only pins the compiler)
+            const int mine = lane < n_band ? band_raw[lane] : 0x7fffffff;
+            int rank = 0;
+            each_lane(n_band, [&](int i) { rank += __builtin_amdgcn_readlane(mine, i) < mine; });
+            if (lane < n_band) band_pos[rank] = mine;
+            const int n_above = __builtin_amdgcn_readlane(above, __builtin_ctzll(__builtin_amdgcn_ballot_w64(lane < n_few && key == at_cut)));
+            if (lane == 0) { s_cut = at_cut; s_band = n_band; s_take = need_few - n_over; s_above = need_few - n_above; }
+        }
+    } else {
+        if (n_list > kListCap) radix_pass();
+        while (shift > 0) { __syncthreads(); radix_pass(); }
+        if (threadIdx.x == 0) { s_cut = klo + prefix; s_sure = 0; }
+        __syncthreads();
+        const float at_cut = __uint_as_float(klo + prefix), low = at_cut * (1.0f - kBandRel), high = at_cut * (1.0f + kBandRel);
+        each_around([&](uint32_t key, int j) {
+            const float v = __uint_as_float(key);
+            if (v > high) { set_keep(j); atomicAdd(&s_sure, 1); }
+            else if (v >= low) {
+                const int e = atomicAdd(&s_band, 1);
+                if (e < kMaxBand) band_raw[e] = j;
+            }
+        });
+        __syncthreads();
+        if (threadIdx.x == 0) { s_take = need_around - s_sure; s_above = need; }
+        if (s_band <= kMaxBand)
+            for (int e = threadIdx.x; e < s_band; e += kSelThreads) {
+                const int j = band_raw[e];
+                int rank = 0;
+                for (int o = 0; o < s_band; ++o) rank += band_raw[o] < j;
+                band_pos[rank] = j;
+            }
+    }
+    __syncthreads();
+    const uint32_t cut_key = __builtin_amdgcn_readfirstlane(s_cut);
+    const float cut = __uint_as_float(cut_key);
+    const float lo = cut * (1.0f - kBandRel), hi = cut * (1.0f + kBandRel);    // scores that binary32 rounding could move across the cut
+    const int tot_band = __builtin_amdgcn_readfirstlane(s_band);
+    const int take = __builtin_amdgcn_readfirstlane(s_take);                   // members of the band that survive
+    const int need_at_cut = __builtin_amdgcn_readfirstlane(s_above);           // how many candidates equal to the cut are taken (binary32 rule)
+    bool refine = tot_band <= kMaxBand;
     int* hot_pos = hist;                                                   // [kVoteSlots]
     int n_hot = 0;
     if (refine && take < tot_band) {
@@ -1246,27 +1365,46 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     }
     if (__builtin_expect(refine, 1)) {
         if (n_hot > 1) {
-            // ---- binary64 re-scoring: one wave per (position, 32 window rows); the parts of a position are
+            // ---- binary64 re-scoring: one wave per (position, kPartRows window rows); the parts of a position are
             // summed in ascending order.  Positions go in batches that fit the parts. ----
             double* part_vote = reinterpret_cast<double*>(big);                      // [kPartSlots]
             double* pos_vote = reinterpret_cast<double*>(big) + kPartSlots;          // [kVoteSlots]
-            const int n_parts = (a.rows + 31) / 32;           // (at most 8)
+            const int n_parts = (a.rows + kPartRows - 1) / kPartRows;           // (at most 16)
             const int batch = kPartSlots / n_parts;
             for (int p0 = 0; p0 < n_hot; p0 += batch) {
                 const int np = min(batch, n_hot - p0);
                 for (int item = wave; item < np * n_parts; item += kSelWaves) {
-                    const double v = vote_f64_part(a, head, hot_pos[p0 + item / n_parts], 32 * (item % n_parts));
+                    const double v = vote_f64_part(a, head, hot_pos[p0 + item / n_parts], kPartRows * (item % n_parts));
                     if (lane == 0) part_vote[item] = v;
                 }
                 __syncthreads();
                 for (int i = threadIdx.x; i < np; i += kSelThreads) {
                     double sum = 0.0;
-                    for (int q = 0; q < n_parts; ++q) sum += part_vote[i * n_parts + q];
+#pragma unroll
+                    for (int q = 0; q < kWideRows / kPartRows; ++q) sum += q < n_parts ? part_vote[i * n_parts + q] : 0.0;
                     pos_vote[p0 + i] = sum;
                 }
                 __syncthreads();
             }
             // ---- pooled binary64 score of each member, and its rank by (score desc, position asc) ----
+            if (tot_band <= 64 && n_hot <= 64) {              // (the usual case: one wave, a member and a position per lane)
+                if (wave == 0) {
+                    const int j = lane < tot_band ? band_pos[lane] : -1, hot = lane < n_hot ? hot_pos[lane] : -0x40000000;
+                    const double hot_vote = lane < n_hot ? pos_vote[lane] : 0.0;
+                    double best = 0.0;                        // votes are >= 0
+                    each_lane(n_hot, [&](int i) {
+                        const double v = lane_f64(hot_vote, i);
+                        if (abs(__builtin_amdgcn_readlane(hot, i) - j) <= r) best = fmax(best, v);
+                    });
+                    if (lane >= tot_band) best = -1.0;
+                    int rank = 0;
+                    each_lane(tot_band, [&](int i) {
+                        const double o = lane_f64(best, i);
+                        rank += (o > best) || (o == best && i < lane);
+                    });
+                    if (lane < tot_band && rank < take) set_keep(j);
+                }
+            } else {
             for (int m = threadIdx.x; m < tot_band; m += kSelThreads) {
                 const int j = band_pos[m];
                 double best = 0.0;                            // votes are >= 0
@@ -1280,6 +1418,7 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
                 int rank = 0;
                 for (int o = 0; o < tot_band; ++o) rank += (band_score[o] > sc) || (band_score[o] == sc && o < m);
                 if (rank < take) set_keep(band_pos[m]);
+            }
             }
         } else {                                              // all taken, or all equal: by position
             for (int m = threadIdx.x; m < min(take, tot_band); m += kSelThreads) set_keep(band_pos[m]);
@@ -1421,7 +1560,7 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
     p.p_stride = p.P > 0 ? (p.P + 7) / 8 * 8 : 8;
     // (the row statistics of the scoring workgroups are dead when the pooled scores are counted)
     const size_t part_bytes = (size_t)heads * n_parts * rows_pad * sizeof(float2);
-    const size_t bins_bytes = apart ? (size_t)heads * p.n_seg * kBins * sizeof(uint16_t) : 0;
+    const size_t bins_bytes = apart ? (size_t)heads * p.n_seg * kBinRow * sizeof(uint16_t) : 0;
     p.off_stats_part = off; off = align_up(off + (part_bytes > bins_bytes ? part_bytes : bins_bytes), 256);
     p.off_stats = off;      off = align_up(off + (size_t)heads * rows_pad * (sizeof(float2) + sizeof(double)), 256);
     p.off_vote = off;       off = align_up(off + (size_t)heads * (p.P > 0 ? p.P : 1) * sizeof(float), 256);
@@ -1474,7 +1613,7 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
     s.q_obs = a.q_obs; s.k = a.k; s.stats = stats; s.zsum = zsum;
     s.P = plan.P; s.L = cfg.seq_len; s.W = cfg.window; s.n_kept = plan.n_kept; s.pool = cfg.pool_kernel;
     s.gq = a.gq; s.n_q_heads = cfg.n_q_heads; s.n_kv_heads = cfg.n_kv_heads; s.rows = a.rows; s.rows_pad = a.rows_pad;
-    s.sm_scale = cfg.sm_scale;
+    s.sm_scale = cfg.sm_scale; s.w_recip = (65536u + (uint32_t)cfg.window - 1u) / (uint32_t)cfg.window;
     s.bins = reinterpret_cast<uint16_t*>(base + plan.off_stats_part);
     s.exact = plan.exact_bytes > 0 ? reinterpret_cast<float*>(base + plan.total) : nullptr;
     s.p_stride = plan.p_stride; s.n_seg = plan.n_seg; s.seg_tiles = plan.seg_tiles;

@@ -108,6 +108,26 @@ def test_clustered_scores_beyond_the_list_are_still_refined(orc):
     assert unrefined == [0, 0]
 
 
+@pytest.mark.parametrize("P,pool,budget", [(4096, 1, 1500), (4000, 63, 900), (12288, 5, 7000), (13001, 1, 4001), (30011, 31, 9000)])
+@pytest.mark.parametrize("noise", [1.0, 0.2, 0.05, 0.02])
+def test_lists_around_the_cut_of_any_length(orc, P, pool, budget, noise):
+    """From a dozen candidates around the cut to more than the list holds: up to 64 that one wave finishes, more that a radix pass
+    thins out first, and more than 64 left by it (plateaus of a wide pooling window, scores that cluster)."""
+    print(f"case list P={P} pool={pool} budget={budget} noise={noise}", flush=True)
+
+    def keys(k):
+        base = k[:, :, :1].astype(np.float32)
+        k[:, :, :P] = (base + noise * k[:, :, :P].astype(np.float32)).astype(np.float16)
+    got, idx, pooled, unrefined = select(orc, P, 8, pool, budget, outlier=1.0, keys=keys, seed=101)
+    kth = [np.sort(pooled[0, g])[-budget] for g in range(2)]
+    print("around", [int((np.abs(pooled[0, g] / kth[g] - 1) < 0.008).sum()) for g in range(2)], "unrefined", unrefined, flush=True)
+    for g in range(2):
+        in_band = int((np.abs(pooled[0, g] / kth[g] - 1) <= 1.9e-5).sum())
+        assert unrefined[g] == 0 or in_band > 256, (unrefined, in_band)
+    if unrefined == [0, 0]:
+        check_indices(got, idx, pooled)
+
+
 @pytest.mark.parametrize("Gq,W", [(4, 64), (8, 17), (4, 32), (1, 5)])
 def test_scores_that_leave_the_first_keys_far_behind(orc, Gq, W):
     """Keys that grow fourteenfold halfway through the prompt: row maxima of later workgroups pass those of

@@ -676,17 +676,23 @@ __global__ __launch_bounds__(256) void stats_combine(const float2* __restrict__ 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kMaxPrefix = 131072;
-constexpr int kOctets = kMaxPrefix / (8 * kSelThreads);   // groups of eight candidates per thread
+constexpr int kMaxShares = kMaxPrefix / (8 * kSelThreads);   // workgroups of a head that sweep codes, one group of eight candidates per thread
 constexpr int kPoolTile = 4 * kSelThreads;   // candidates of one pooling step, four consecutive ones per thread
 constexpr int kMaxPoolRadius = 31;    // pool_kernel <= 63
 constexpr int kStage = kPoolTile + 2 * kMaxPoolRadius + 2;   // votes of a step with the halo on either side (whole 16-byte pieces)
 constexpr int kBinShift = 17;
 constexpr int kGroups = 63, kGroupBins = 64;      // score bins in groups: one group per factor of two
 constexpr int kBins = kGroups * kGroupBins;       // score bins: the bit pattern >> kBinShift, 2^-54 .. 2^9, clamped at both ends
-constexpr int kBinRow = 4096;         // 16-bit words of a pooling workgroup's counts: the bins', then the groups' 
+constexpr int kBinRow = 4096;         // 16-bit words of a pooling workgroup's counts: the bins', then the groups', then (row 0 of a head) the arrivals of the sweeping workgroups
 constexpr int kCodeShift = 15;        // the stored code of a score: its pattern's upper 16 bits below the sign
 constexpr int kBinBase = ((136 << 23) >> kBinShift) - kBins;   // 2^9 is the first pattern past the last bin (votes stay below 256 rows)
 constexpr int kOwnTiles = 3;          // prefixes of up to so many tiles select_topk pools itself; longer ones are pool_scores'
+// Prefixes of up to so many shares (32768 candidates) are swept by one workgroup per head, longer ones by one per share, of
+// heads that leave each a CU of its own.  One CU takes in about 25 bytes a nanosecond (2 bytes a candidate); the others' masks and
+// groups cost a trip through memory, 3 us with the counter.  Whole calls, us, one workgroup -> several: 8 heads of 32736
+// candidates 67.4 -> 67.1, of 65504 106.2 -> 102.6, of 131040 165.6 -> 157.7, 32 heads of 16352 95.6 -> 96.2, of 65504 297.1 -> 294.8,
+// 128 heads of 32736 547.9 -> 559.0.
+constexpr int kAloneShares = 4, kMostShares = 256;
 constexpr int kMaxSegs = 16;          // pooling workgroups per head
 constexpr int kMaxSegTiles = 15;      // (a workgroup's bin counts are stored in 16 bits)
 constexpr int kListCap = 3840;        // candidates around the cut held in LDS; more are swept from memory
@@ -712,6 +718,7 @@ struct SelectArgs {
     const double* zsum;     // Z binary64
     int P, p_stride, L, W, n_kept, pool, gq, n_q_heads, n_kv_heads, rows, rows_pad;
     int n_seg, seg_tiles;   // pooling workgroups per head and their pooling tiles
+    int share_oct;          // groups of eight codes that a sweeping workgroup takes (whole mask words)
     uint32_t w_recip;       // 2^16 / W, rounded up: the quotient of a row number by W (both at most 256) without a division
     float sm_scale;
 };
@@ -977,23 +984,27 @@ __device__ __forceinline__ int bin_of_cut(const uint16_t* bins, int n_seg, int k
 
 // T > 0: the prefix is at most T pooling tiles, pooled and counted here by one workgroup per (batch, kv head); of every tile
 // thread t keeps the scores of candidates 4 t .. 4 t + 3.
-// T = 0: pool_scores has left codes and counts; one workgroup per head sweeps them.
+// kAlone: pool_scores has left codes and counts; one workgroup per head sweeps them.
+// kSpread: the same by several workgroups of a head.  Each finds the bin of the cut and sweeps the codes of its
+// share, one group of eight per thread; mask and list of the share then take the place of the codes that they came from,
+// and the workgroup that arrives last goes on with all of them.
 // keep: the survivor mask, bit j % 8 of byte j / 8.
+enum { kAlone = 0, kSpread = -1 };
 template <int T>
 __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
-    constexpr bool OWN = T > 0;
+    constexpr bool OWN = T > 0, SPREAD = T == kSpread;
     __shared__ __align__(16) uint32_t keep[(OWN ? T * kPoolTile : kMaxPrefix) / 32];
     __shared__ __align__(16) int tab[2 * kSelThreads + kVoteSlots];      // the counts of the bins (OWN); later the band, then:
     int* hist = tab + 2 * kSelThreads;                            // radix digits and the candidates of the last; later the positions to re-score
     uint32_t* ties = reinterpret_cast<uint32_t*>(tab);            // where binary32 decides: the mask of the candidates equal to the cut
     __shared__ __align__(16) unsigned char big[T > 1 ? 2 * kStage * 4 : kListCap * 8];     // candidates around the cut, or (too many) the pooling stage; before that the pooling stage (OWN); later the binary64 votes
     __shared__ int swave[kSelWaves];
-    __shared__ int s_bin, s_list, s_listed, s_sure, s_digit, s_above, s_few, s_take, s_band, s_hot;
+    __shared__ int s_bin, s_list, s_listed, s_sure, s_last, s_digit, s_above, s_few, s_take, s_band, s_hot;
     __shared__ uint32_t s_cut;
     static_assert(kListCap * 8 >= kStage * 4 && sizeof(tab) >= kBinRow * 4 && sizeof(tab) >= (2 * kSelWaves + kListCap) * 4 && kListCap * 8 >= (kPartSlots + kVoteSlots) * 8 &&
                   sizeof(tab) >= kMaxPrefix / 8 && (1 << kDigit) == kSelThreads && kVoteSlots >= (1 << kDigit) + 2 * kFew, "aliases fit");
 
-    const int head = blockIdx.x;
+    const int head = blockIdx.y;
     const int P = a.P, k = a.head_n ? a.head_n[head] : a.n_kept;
     const float* vote = a.vote + (size_t)head * P;
     int32_t* idx = a.idx + (size_t)head * a.n_kept;
@@ -1002,8 +1013,8 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     const int r = (a.pool - 1) / 2;
 
     if (k <= 0 || k >= P) {   // (a head-level count may be zero; one that covers the prefix: identity, the scores are not looked at)
-        if (a.unrefined && threadIdx.x == 0) a.unrefined[head] = 0;
-        for (int j = threadIdx.x; j < k; j += kSelThreads) { idx[j] = j; list[j] = j; }
+        if (a.unrefined && blockIdx.x == 0 && threadIdx.x == 0) a.unrefined[head] = 0;
+        for (int j = blockIdx.x * kSelThreads + threadIdx.x; j < k; j += gridDim.x * kSelThreads) { idx[j] = j; list[j] = j; }
         return;
     }
     if (threadIdx.x == 0) { s_list = 0; s_sure = 0; s_listed = 0; s_few = 0; s_band = 0; s_hot = 0; }
@@ -1011,9 +1022,10 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     // ---- the bin of the k-th largest score ----
     uint32_t own[OWN ? 4 * T : 1];                 // OWN: the thread's scores (all ones past the end: neither above nor around the cut)
     auto own_at = [&](int i) { return (i >> 2) * kPoolTile + 4 * (int)threadIdx.x + (i & 3); };   // ... and their candidates
-    const int n_oct = (P + 7) / 8;
-    const char* codes = OWN ? nullptr : reinterpret_cast<const char*>(a.code + (size_t)head * a.p_stride);
-    uint4 oct[OWN ? 1 : kOctets];                  // the thread's groups of eight codes: thread + 1024 i
+    constexpr int OCTS = SPREAD ? 1 : kMaxShares;  // groups of eight codes per thread (not OWN): thread + 1024 i of the share
+    const int n_oct = (P + 7) / 8, oct0 = SPREAD ? blockIdx.x * a.share_oct : 0, own_oct = SPREAD ? min(a.share_oct, n_oct - oct0) : n_oct;
+    char* codes = OWN ? nullptr : reinterpret_cast<char*>(a.code + (size_t)head * a.p_stride);
+    uint4 oct[OWN ? 1 : OCTS];
     if constexpr (OWN) {
         const int n_tiles = (P + kPoolTile - 1) / kPoolTile;
         // (two places for a tile's votes, one barrier per tile; two tiles' votes on their way while one is pooled)
@@ -1060,9 +1072,9 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
         }
     } else {
 #pragma unroll
-        for (int i = 0; i < kOctets; ++i) {
+        for (int i = 0; i < OCTS; ++i) {
             const int o = (int)threadIdx.x + i * kSelThreads;
-            oct[i] = o < n_oct ? reinterpret_cast<const uint4*>(codes)[o] : make_uint4(0u, 0u, 0u, 0u);
+            oct[i] = o < own_oct ? reinterpret_cast<const uint4*>(codes)[oct0 + o] : make_uint4(0u, 0u, 0u, 0u);
         }
         if (wave == 0) {
             const int bin = bin_of_cut(a.bins + (size_t)head * a.n_seg * kBinRow, a.n_seg, k);
@@ -1103,20 +1115,22 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
         // (a group with candidates around the cut is listed whole, {group, which of its eight}: the sweep is bound by what it
         // issues, and a write per candidate was most of it)
 #pragma unroll
-        for (int i = 0; i < kOctets; ++i) {
+        for (int i = 0; i < OCTS; ++i) {
             const int o = (int)threadIdx.x + i * kSelThreads;
-            if (o >= n_oct) break;
-            const uint32_t above = codes_above(oct[i], chi);                    // (past the end the codes are 0)
+            if (!SPREAD && o >= own_oct) break;
+            const uint32_t above = codes_above(oct[i], chi);                    // (past the share or the end the codes are 0)
             uint32_t around = clo ? codes_above(oct[i], clo - 1u) & ~above : 0xffu & ~above;
-            if (8 * o + 8 > P) around &= (1u << (P - 8 * o)) - 1u;
+            if (8 * (oct0 + o) + 8 > P) around &= (1u << max(P - 8 * (oct0 + o), 0)) - 1u;
+            if (SPREAD && o >= own_oct) around = 0u;
             reinterpret_cast<unsigned char*>(keep)[o] = (unsigned char)above;
             sure += __popc(above);
             if (around) {
                 const uint32_t e = (uint32_t)atomicAdd(&s_list, (1 << kGroupCount) + __popc(around)) >> kGroupCount;
-                if (e < kListCap) groups[e] = ((uint32_t)o << 8) | around;
+                if (e < kListCap) groups[e] = ((uint32_t)(oct0 + o) << 8) | around;
             }
         }
-        for (int o = n_oct + (int)threadIdx.x; o < (n_oct + 3) / 4 * 4; o += kSelThreads) reinterpret_cast<unsigned char*>(keep)[o] = 0;
+        if (!SPREAD)
+            for (int o = n_oct + (int)threadIdx.x; o < (n_oct + 3) / 4 * 4; o += kSelThreads) reinterpret_cast<unsigned char*>(keep)[o] = 0;
     }
     sure = wave_sum(sure);
     if (lane == 0 && sure) atomicAdd(&s_sure, sure);
@@ -1124,6 +1138,57 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     int n_list = __builtin_amdgcn_readfirstlane(s_list), n_groups = 0;
     int n_sure = __builtin_amdgcn_readfirstlane(s_sure);
     if constexpr (!OWN) { n_groups = (int)((uint32_t)n_list >> kGroupCount); n_list &= (1 << kGroupCount) - 1; }
+    if constexpr (SPREAD) {
+        // {survivors, candidates, groups}, mask and groups of the share go where its codes were (the barrier: all of them are in
+        // registers; 16 bytes a group of codes, one and four a group here), with device-scope
+        // stores: the workgroup that arrives last may be on another XCD.
+        constexpr int kSlotHead = 16;
+        auto octs_of = [&](int share) { return min(a.share_oct, n_oct - share * a.share_oct); };
+        auto words_of = [&](int octs) { return (octs + 3) / 4; };              // 32-bit mask words
+        char* slot = codes + (size_t)oct0 * 16;
+        const int mask_words = words_of(own_oct);
+        auto put = [](void* p, uint32_t v) { __hip_atomic_store(reinterpret_cast<uint32_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        auto get = [](const void* p) { return __hip_atomic_load(reinterpret_cast<const uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        if (threadIdx.x < 3) put(slot + 4 * threadIdx.x, (uint32_t)(threadIdx.x == 0 ? n_sure : threadIdx.x == 1 ? n_list : n_groups));
+        if ((int)threadIdx.x < mask_words) put(slot + kSlotHead + 4 * threadIdx.x, keep[threadIdx.x]);
+        if ((int)threadIdx.x < n_groups) put(slot + kSlotHead + 4 * (mask_words + threadIdx.x), groups[threadIdx.x]);
+        // Every store is acknowledged at the device's coherence point before the workgroup's arrival is counted there.
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        const int n_shares = gridDim.x;
+        if (threadIdx.x == 0) {
+            uint32_t* arrivals = reinterpret_cast<uint32_t*>(a.bins + (size_t)head * a.n_seg * kBinRow + kBinRow - 2);   // (upper half of the word)
+            s_last = (int)(__hip_atomic_fetch_add(arrivals, 1u << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16) == n_shares - 1;
+        }
+        __syncthreads();
+        if (!__builtin_amdgcn_readfirstlane(s_last)) return;
+        // Masks and groups of all shares into LDS: a share's by sixteen / n_shares waves, one round trip (but for many groups).
+        {
+            const int per = kSelWaves / n_shares, share = wave % n_shares, sub = wave / n_shares;
+            const bool part = sub < per;
+            const int octs = octs_of(share), words = part ? words_of(octs) : 0, at = part ? 64 * sub + lane : 0, step = 64 * per;
+            const char* from = codes + (size_t)share * a.share_oct * 16;
+            constexpr int kMaskLoads = kSelThreads / 4 / 64;              // mask words per lane of a wave that has a share to itself
+            const uint32_t some = get(from), count = get(from + 4), mine = get(from + 8);
+            uint32_t m[kMaskLoads], group = 0u;
+#pragma unroll
+            for (int u = 0; u < kMaskLoads; ++u) m[u] = at + u * step < words ? get(from + kSlotHead + 4 * (at + u * step)) : 0u;
+            if (part && at < octs) group = get(from + kSlotHead + 4 * (words + at));      // (one group at least lies behind the mask's place)
+            if (sub == 0 && lane == 0) { swave[share] = (int)mine; tab[share] = (int)some; tab[kSelWaves + share] = (int)count; }
+#pragma unroll
+            for (int u = 0; u < kMaskLoads; ++u)
+                if (at + u * step < words) keep[share * (a.share_oct / 4) + at + u * step] = m[u];
+            __syncthreads();
+            const int up_to = lanes_up_to(lane < n_shares ? swave[lane] : 0), before = share > 0 ? __builtin_amdgcn_readlane(up_to, share - 1) : 0;
+            n_groups = __builtin_amdgcn_readlane(up_to, 63);
+            n_sure = wave_sum(lane < n_shares ? tab[lane] : 0);
+            n_list = wave_sum(lane < n_shares ? tab[kSelWaves + lane] : 0);
+            if (part && n_groups <= kListCap)
+                for (int e = at; e < (int)mine; e += step) groups[before + e] = e == at ? group : get(from + kSlotHead + 4 * (words + e));
+            __syncthreads();
+        }
+    }
     if (a.unrefined && threadIdx.x == 0) a.unrefined[head] = 0;   // (overwritten below by the same thread if binary32 decides)
     const int need_around = k - n_sure;   // how many of the candidates around the cut survive
     // the pooled score of a candidate, from the votes
@@ -1617,7 +1682,9 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
     s.bins = reinterpret_cast<uint16_t*>(base + plan.off_stats_part);
     s.exact = plan.exact_bytes > 0 ? reinterpret_cast<float*>(base + plan.total) : nullptr;
     s.p_stride = plan.p_stride; s.n_seg = plan.n_seg; s.seg_tiles = plan.seg_tiles;
-    auto own = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(heads), dim3(kSelThreads), 0, stream, s); };
+    const int octs = (plan.P + 7) / 8, shares = (octs + kSelThreads - 1) / kSelThreads;       // (sweeping workgroups of a head, kSpread)
+    s.share_oct = ((octs + shares - 1) / std::max(shares, 1) + 7) / 8 * 8;
+    auto own = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1, heads), dim3(kSelThreads), 0, stream, s); };
     // Up to three pooling tiles per workgroup: the launch before it and the codes' way through memory are worth more than
     // the workgroups that pool side by side (whole calls, us, two kernels -> one: 8 heads of 8192 keys 41.3 -> 35.1, of 12000 43.7 ->
     // 38.9, 32 heads 68.8 -> 62.1 and 88.5 -> 84.5, 128 heads 184.6 -> 177.5 and 241.7 -> 239.2).  From four on the votes, four
@@ -1628,7 +1695,8 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
     else if (plan.P <= kOwnTiles * kPoolTile) own(select_topk<kOwnTiles>);
     else {
         if (score) hipLaunchKernelGGL(pool_scores, dim3(plan.n_seg, heads), dim3(kSelThreads), 0, stream, s);
-        own(select_topk<0>);
+        if (shares > kAloneShares && heads * shares <= kMostShares) hipLaunchKernelGGL(select_topk<kSpread>, dim3(shares, heads), dim3(kSelThreads), 0, stream, s);
+        else own(select_topk<kAlone>);
     }
     return hipGetLastError();
 }

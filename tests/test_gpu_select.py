@@ -417,3 +417,69 @@ def test_prompts_at_any_address(Gq, W, L, shift):
         got.append((idx, cache))
     assert torch.equal(got[0][0], got[1][0])
     assert all(torch.equal(got[0][1].buffers[n], got[1][1].buffers[n]) for n in got[0][1].buffers)
+
+
+@pytest.mark.parametrize("P,pool,budget", [(32768, 7, 9000), (32769, 7, 9000), (32777, 1, 1), (40961, 63, 40960), (65543, 5, 20000), (131072, 7, 30000), (131071, 13, 1)])
+def test_prefixes_whose_codes_several_workgroups_sweep(orc, P, pool, budget):
+    """Beyond 32768 candidates a head's codes are swept by up to sixteen workgroups, the last of which goes on: both sides of the
+    line, a share of one group, cuts at either end."""
+    print(f"case shares P={P} pool={pool} budget={budget}", flush=True)
+    got, idx, pooled, unrefined = select(orc, P, 8, pool, budget, seed=103 + P % 5)
+    check_indices(got, idx, pooled)
+    assert unrefined == [0, 0]
+
+
+@pytest.mark.parametrize("P,pool,budget,noise", [(33001, 1, 9000, 0.05), (50001, 7, 12000, 0.02), (40009, 1, 39000, 0.002), (45000, 5, 20000, 0.0)])
+def test_long_and_overlong_lists_of_several_workgroups(orc, P, pool, budget, noise):
+    print(f"case shares, list P={P} pool={pool} budget={budget} noise={noise}", flush=True)
+
+    def keys(k):
+        base = k[:, :, :1].astype(np.float32)
+        k[:, :, :P] = (base + noise * k[:, :, :P].astype(np.float32)).astype(np.float16)
+    got, idx, pooled, unrefined = select(orc, P, 8, pool, budget, outlier=1.0, keys=keys, seed=105)
+    if noise == 0.0:
+        assert np.array_equal(got[0], np.tile(np.arange(budget), (2, 1))) and unrefined == [P, P]
+    elif unrefined == [0, 0]:
+        check_indices(got, idx, pooled)
+    else:
+        assert max(unrefined) > 512 and bool((np.diff(got[0], axis=1) > 0).all())
+
+
+def test_counts_per_head_and_replays_where_several_workgroups_sweep():
+    """Heads that keep nothing, everything or some of 40000 candidates, in one call; the same again eagerly and as replays of a
+    captured call with other work on the workspace between them: what counts the workgroups' arrivals is reset by the call itself."""
+    print("case shares, counts and replays", flush=True)
+    P, W, Hkv = 40000, 8, 4
+    q_obs, k, v = (dev(t) for t in synth.prompt_host(1, Hkv * 2, Hkv, P + W, W, 128, config=107))
+    cfg = kvqp.Cfg(batch=1, n_q_heads=Hkv * 2, n_kv_heads=Hkv, seq_len=P + W, window=W, budget=P, bits=4, group_size=32)
+    ws = kvqp.alloc_workspace(kvqp.workspace_bytes(cfg)[0])
+    counts = [0, P, 9001, 1]
+
+    def call(idx, un, stream=None):
+        kvqp.compress_ragged(cfg, q_obs, k, v, counts, kvqp.alloc_cache(cfg, ragged=True), idx_out=idx, workspace=ws, unrefined_out=un, stream=stream)
+    want, un = torch.full((1, Hkv, P), -1, dtype=torch.int32, device="cuda"), torch.full((Hkv,), -1, dtype=torch.int32, device="cuda")
+    call(want, un)
+    torch.cuda.synchronize()
+    assert un.tolist() == [0] * Hkv
+    for h, n in enumerate(counts):
+        alone = kvqp.Cfg(batch=1, n_q_heads=2, n_kv_heads=1, seq_len=P + W, window=W, budget=max(n, 1), bits=4, group_size=32)
+        got = torch.empty((1, 1, max(n, 1)), dtype=torch.int32, device="cuda")
+        kvqp.compress(alone, q_obs[:, 2 * h:2 * h + 2].contiguous(), k[:, h:h + 1].contiguous(), v[:, h:h + 1].contiguous(), kvqp.alloc_cache(alone), idx_out=got)
+        torch.cuda.synchronize()
+        assert torch.equal(want[0, h, :n], got[0, 0, :n])
+    idx, un2 = want.clone(), un.clone()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    cache = kvqp.alloc_cache(cfg, ragged=True)
+    with torch.cuda.graph(graph, stream=side):
+        kvqp.compress_ragged(cfg, q_obs, k, v, counts, cache, idx_out=idx, workspace=ws, unrefined_out=un2, stream=side)
+    for _ in range(4):
+        idx.fill_(-1)
+        un2.fill_(-1)
+        ws.fill_(0xA5)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(idx[0, h, :n], want[0, h, :n]) for h, n in enumerate(counts)) and un2.tolist() == [0] * Hkv
+        again = torch.full_like(want, -1)
+        call(again, un)
+        torch.cuda.synchronize()
+        assert torch.equal(again, want)

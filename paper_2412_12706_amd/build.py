@@ -19,15 +19,17 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libkvqp.so")
-SOURCES = ["kvqp_api.cpp", "quant_pack.hip", "decode_attn.hip", "score_select.hip"]
+# (the decode kernels, most of the work, are one object per bit width)
+SOURCES = [f"decode_attn.hip:{bits}" for bits in (4, 8, 2, 16)] + ["quant_pack.hip", "score_select.hip", "decode_attn.hip", "kvqp_api.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-mllvm", "-amdgpu-mfma-vgpr-form",
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 
 
 def _compile(src: str) -> str:
-    obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = ["hipcc", "-x", "hip"] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
+    src, _, bits = src.partition(":")
+    obj = os.path.join(OBJ, os.path.splitext(src)[0] + bits + ".o")
+    cmd = ["hipcc", "-x", "hip"] + FLAGS + ([f"-DKVQP_DECODE_BITS={bits}"] if bits else []) + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "not a recognized feature" not in l)
     if r.returncode:

@@ -41,7 +41,9 @@
 // Each device's copy starts all zero (static storage) and every completed launch leaves the
 // arrival counters at its head zero again; they are nevertheless zeroed by a fill kernel when a
 // device's address is first taken.  Calls that use it share it: they must not overlap on one device.
+#ifndef KVQP_DECODE_BITS
 static __device__ __align__(256) unsigned char scratch[kvqp::kCounterBytes + kvqp::kStaticScratchBytes];
+#endif
 
 namespace kvqp {
 namespace {
@@ -216,6 +218,8 @@ __device__ __forceinline__ uint32_t split_half(float x, bool want_lo) {
     return c.u;
 }
 
+}  // namespace
+
 struct DecodeArgs {
     const uint16_t* q;        // [B, Hq, D]
     const uint32_t* k_codes;
@@ -241,9 +245,11 @@ struct DecodeArgs {
     int n_splits, chunks_per_split;
     int n_waves;              // waves per workgroup of the pipelined kernel
     int group;                // G
-    int stream_from;          // chunks from this one on are loaded with the non-temporal hint
+    unsigned tail_each, tail_more;   // tail rows of a workgroup: tail_len / n_splits, and how many workgroups take one more
     float sm_scale;
 };
+
+namespace {
 
 // Tokens of one head: the launch's count, or the head's own, cut to the bound so that no value found
 // in memory can lead a load past the buffers (they are laid out for the bound in whole blocks).
@@ -317,7 +323,7 @@ __device__ void merge_if_last(const DecodeArgs& a, int bh, int n_parts) {
     }
     __syncthreads();
     if (!s_last) return;
-    const int b = bh / a.n_kv_heads, g = bh % a.n_kv_heads;
+    const int b = blockIdx.z, g = blockIdx.y;
     const unsigned head_bytes = (unsigned)a.n_splits * GQ * kPartFloats * 4u;
     const __amdgpu_buffer_rsrc_t rs = part_rsrc(a.part + (size_t)bh * a.n_splits * GQ * kPartFloats, head_bytes);
     // Device-scope loads are slow (they go to the coherence point), so a whole batch of partials is
@@ -395,10 +401,9 @@ __device__ __forceinline__ float row16_add(float v) {
 // row groups of a head are merged at the end.  Eight heads go in two passes (rows re-read from
 // cache).  Each wave leaves its softmax state in LDS, sT[wave][head] = {reference m (log2 domain),
 // sum l, unnormalised o[128]}.
-// The query rows come from their plain copy in LDS (sq); the lane's first row, tail_first_row(),
-// has been requested by the caller before anything waited on memory and arrives in k_first /
-// v_first: when a head is split over many workgroups that row is all a wave has, and a round trip
-// to memory after the staging barrier would sit on every workgroup's path.
+// The query rows come from their plain copy in LDS (sq); the lane's first rows (TailAhead) have been requested by the
+// caller before the packed part's first chunks: loads return in order, so what is requested first can be worked on while
+// those are on their way.
 template <int GQ> struct TailGeom {
     static constexpr int HB = GQ < 4 ? GQ : 4;   // heads side by side in a wave
     static constexpr int RP = 4 / HB;            // rows side by side in a wave
@@ -408,8 +413,25 @@ __device__ __forceinline__ int tail_first_row(int t0, int t1, int wave, int lane
     const int r = t0 + wave * TailGeom<GQ>::RP + (lane >> 4) / TailGeom<GQ>::HB;
     return (wave < kWaves && r < t1) ? r : -1;
 }
+constexpr int kTailAhead = 4;       // rows of a lane that are requested ahead: all it has where 32 rows are shared by two or more workgroups
+struct TailAhead { uint4 k[kTailAhead], v[kTailAhead]; };
 template <int GQ>
-__device__ void tail_rows(const DecodeArgs& a, int bh, int t0, int t1, float* sT, const uint16_t* sq, uint4 k_first, uint4 v_first) {
+__device__ __forceinline__ TailAhead request_tail(const DecodeArgs& a, int bh, int t0, int t1, int wave, int lane) {
+    TailAhead t;
+    const int r = tail_first_row<GQ>(t0, t1, wave, lane);
+#pragma unroll
+    for (int u = 0; u < kTailAhead; ++u) {
+        t.k[u] = t.v[u] = make_uint4(0u, 0u, 0u, 0u);
+        if (r >= 0 && r + u * 4 * TailGeom<GQ>::RP < t1) {
+            const size_t at = ((size_t)bh * a.tail_cap + r + u * 4 * TailGeom<GQ>::RP) * kHeadDim + 8 * (lane & 15);
+            t.k[u] = *reinterpret_cast<const uint4*>(a.tail_k + at);
+            t.v[u] = *reinterpret_cast<const uint4*>(a.tail_v + at);
+        }
+    }
+    return t;
+}
+template <int GQ>
+__device__ void tail_rows(const DecodeArgs& a, int bh, int t0, int t1, float* sT, const uint16_t* sq, const TailAhead& ahead) {
     constexpr int HB = TailGeom<GQ>::HB, RP = TailGeom<GQ>::RP;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -452,10 +474,12 @@ __device__ void tail_rows(const DecodeArgs& a, int bh, int t0, int t1, float* sT
                 for (int j = 0; j < 8; ++j) o[j] = __builtin_fmaf(o[j], alpha, pr * vf[j]);
                 m = mn;
             };
-            if (r_first >= 0) row_step(k_first, v_first);   // whole DPP rows are in or out together
-            // the lane's further rows, four requested per round trip
             constexpr int kStep = 4 * RP, kBatch = 4;
-            for (int r = r_first + kStep; r_first >= 0 && r < t1; r += kBatch * kStep) {
+#pragma unroll
+            for (int u = 0; u < kTailAhead; ++u)
+                if (r_first >= 0 && r_first + u * kStep < t1) row_step(ahead.k[u], ahead.v[u]);   // whole DPP rows are in or out together
+            // the lane's further rows, four requested per round trip
+            for (int r = r_first + kTailAhead * kStep; r_first >= 0 && r < t1; r += kBatch * kStep) {
                 uint4 ku[kBatch], vu[kBatch];
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) {
@@ -466,6 +490,8 @@ __device__ void tail_rows(const DecodeArgs& a, int bh, int t0, int t1, float* sT
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u)
                     if (r + u * kStep < t1) row_step(ku[u], vu[u]);
+                // (rows requested in vain have arrived as well: behind the loop nothing waits, where no row was requested here either)
+                __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0), as the compiler's own: it keeps count
             }
             if constexpr (RP > 1) {
                 // merge the row groups of a head: lanes ^ 32 (two heads), then also lanes ^ 16 (one head)
@@ -504,7 +530,9 @@ __device__ __forceinline__ float slot_delta(uint32_t w) { return __uint_as_float
 //   * every global load of a 32-token block is issued ahead into a second
 //     register set (A = first block of a 64-token chunk, B = second): the next
 //     chunk's blocks are requested while the current chunk's second block is
-//     computed;
+//     computed.  Every path to a use has the same number of loads behind it, and
+//     nothing in the loop is read by flat instructions, so the compiler waits for
+//     exactly the load it needs (either one gone, it waits for all of them);
 //   * waves claim chunks from a workgroup counter instead of owning a fixed
 //     interleave, so late or slower waves take fewer and all finish together;
 //   * scales and zero-points are needed replicated (every row lane of a quad
@@ -565,7 +593,7 @@ constexpr int pipe_max_waves(int bits, int gq, bool out = false) { return 4 * pi
 // token's logit (the hi / lo lane pair splits the four slots; q is looked up in its plain copy in
 // LDS); the output term goes with LDS float atomics into a per-wave [8 rows][128] binary32 array
 // that is rescaled with its row whenever the row's reference maximum moves, and folded in at the merge.
-template <int BITS, int GQ, int NCG, int AXIS, bool OUT>
+template <int BITS, int GQ, int NCG, int AXIS, bool OUT, bool KEEP>
 __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_attn_pipe(const DecodeArgs a) {
     constexpr int SLOTS = (GQ <= 4) ? 2 : 1;
     constexpr int NT = (SLOTS == 2) ? 1 : 2;
@@ -594,9 +622,7 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
     float* sT = reinterpret_cast<float*>(pipe_lds + pipe_tail_offset(nw, STRIP));   // tail states [wave < 4][head][m, l, o[128]]
     float* s_oc = reinterpret_cast<float*>(pipe_lds + pipe_tail_offset(nw, STRIP) + pipe_tail_lds(GQ));   // OUT: [wave][8 rows][128]
 
-    const int bh = blockIdx.y;
-
-    const int b = bh / a.n_kv_heads, g = bh % a.n_kv_heads;
+    const int b = blockIdx.z, g = blockIdx.y, bh = b * a.n_kv_heads + g;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, kb = lane >> 4;
@@ -693,120 +719,91 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
 #pragma unroll
     for (int i = 0; i < NGRP; ++i) a_kz[i] = 0;
 
-    auto load_k = [&](int tok, KWords<BITS>& dst, auto nt) {
-        constexpr bool NT = decltype(nt)::value;
+    auto load_k = [&](int tok, KWords<BITS>& dst) {
         const char* p = kc + (size_t)tok * (16 * BITS) + k_off;
         if constexpr (BITS == 2) {
-            const u2v v = stream_load<u2v, NT>(p);
+            const u2v v = stream_load<u2v, !KEEP>(p);
             dst.w[0] = v[0]; dst.w[1] = v[1];
         } else {
 #pragma unroll
             for (int i = 0; i < BITS / 4; ++i) {
-                const u4v v = stream_load<u4v, NT>(p + (QUANT ? 16 : 64) * i);
+                const u4v v = stream_load<u4v, !KEEP>(p + (QUANT ? 16 : 64) * i);
                 dst.w[4 * i] = v[0]; dst.w[4 * i + 1] = v[1]; dst.w[4 * i + 2] = v[2]; dst.w[4 * i + 3] = v[3];
             }
         }
     };
-    auto load_v = [&](int sb, VWords<BITS>& dst, auto nt) {
-        constexpr bool NT = decltype(nt)::value;
+    auto load_v = [&](int sb, VWords<BITS>& dst) {
         const char* p = vc + (size_t)sb * (v_superblock_words(BITS) * 4) + v_off;
 #pragma unroll
         for (int q = 0; q < VGeom<BITS>::kWordsPerLoad / 4; ++q) {
-            const u4v v = stream_load<u4v, NT>(p + q * 1024);
+            const u4v v = stream_load<u4v, !KEEP>(p + q * 1024);
             dst.w[4 * q] = v[0]; dst.w[4 * q + 1] = v[1]; dst.w[4 * q + 2] = v[2]; dst.w[4 * q + 3] = v[3];
         }
     };
-    auto dword_at = [](const char* base, uint32_t off, auto nt) { return stream_load<uint32_t, decltype(nt)::value>(base + off); };
+    auto dword_at = [](const char* base, uint32_t off) { return stream_load<uint32_t, !KEEP>(base + off); };
     // Loads are unconditional (indices clamped to valid blocks) so that the loop body is
     // straight-line code and the hardware wait counters can be tracked exactly.
     // A block's loads come in two parts: the key side (codes, key scales / zeros, key outlier slots)
     // and the value side (codes, value scales / zeros, value outlier slots).
-    auto load_Ak_as = [&](int chunk, auto nt) {
+    auto load_Ak = [&](int chunk) {
         const int tb = chunk * kChunk;
-        load_k(tb + 0, ak0, nt); load_k(tb + 16, ak1, nt);
+        load_k(tb + 0, ak0); load_k(tb + 16, ak1);
         if constexpr (QUANT) {
             if constexpr (KT) {
-                a_ks = dword_at(ks, (uint32_t)tb * (2 * NCG) + vrow_off, nt);
-                a_kz[0] = dword_at(kz, (uint32_t)tb * (2 * NCG) + vrow_off, nt);
+                a_ks = dword_at(ks, (uint32_t)tb * (2 * NCG) + vrow_off);
+                a_kz[0] = dword_at(kz, (uint32_t)tb * (2 * NCG) + vrow_off);
             } else {
                 const int u = tb / G;
-                a_ks = dword_at(ks, (uint32_t)u * 256 + row_off, nt);
+                a_ks = dword_at(ks, (uint32_t)u * 256 + row_off);
 #pragma unroll
-                for (int i = 0; i < NGRP; ++i) a_kz[i] = dword_at(kz, (uint32_t)min(u + i, n_kgroups - 1) * 256 + row_off, nt);
+                for (int i = 0; i < NGRP; ++i) a_kz[i] = dword_at(kz, (uint32_t)min(u + i, n_kgroups - 1) * 256 + row_off);
             }
         }
         if constexpr (OUT) {
-            const u2v w = stream_load<u2v, decltype(nt)::value>(ko + (size_t)tb * 16 + slot_off); a_ko = make_uint2(w[0], w[1]);
+            const u2v w = stream_load<u2v, !KEEP>(ko + (size_t)tb * 16 + slot_off); a_ko = make_uint2(w[0], w[1]);
             a_kov = kov[tb / 32 + ovf_lane / 4];
         }
     };
-    auto load_Av_as = [&](int chunk, auto nt) {
+    auto load_Av = [&](int chunk) {
         const int tb = chunk * kChunk;
         if constexpr (QUANT) {
-            a_vs = dword_at(vs, (uint32_t)tb * (2 * NCG) + vrow_off, nt);
-            a_vz = dword_at(vz, (uint32_t)tb * (2 * NCG) + vrow_off, nt);
+            a_vs = dword_at(vs, (uint32_t)tb * (2 * NCG) + vrow_off);
+            a_vz = dword_at(vz, (uint32_t)tb * (2 * NCG) + vrow_off);
         }
         if constexpr (OUT) {
-            const u2v w = stream_load<u2v, decltype(nt)::value>(vo + (size_t)tb * 16 + slot_off); a_vo = make_uint2(w[0], w[1]);
+            const u2v w = stream_load<u2v, !KEEP>(vo + (size_t)tb * 16 + slot_off); a_vo = make_uint2(w[0], w[1]);
             a_vov = vov[tb / 32 + ovf_lane / 4];
         }
-        load_v((BITS == 2) ? chunk : 2 * chunk, av, nt);
+        load_v((BITS == 2) ? chunk : 2 * chunk, av);
     };
-    auto load_Bk_as = [&](int chunk, bool two, auto nt) {
+    auto load_Bk = [&](int chunk, bool two) {
         const int tb = chunk * kChunk + (two ? 32 : 0);
-        load_k(tb + 0, bk0, nt); load_k(tb + 16, bk1, nt);
+        load_k(tb + 0, bk0); load_k(tb + 16, bk1);
         if constexpr (QUANT) {
             if constexpr (KT) {
-                b_ks = dword_at(ks, (uint32_t)tb * (2 * NCG) + vrow_off, nt);
-                b_kz = dword_at(kz, (uint32_t)tb * (2 * NCG) + vrow_off, nt);
-            } else if constexpr (NGRP == 2) b_ks = dword_at(ks, (uint32_t)(tb / G) * 256 + row_off, nt);
+                b_ks = dword_at(ks, (uint32_t)tb * (2 * NCG) + vrow_off);
+                b_kz = dword_at(kz, (uint32_t)tb * (2 * NCG) + vrow_off);
+            } else if constexpr (NGRP == 2) b_ks = dword_at(ks, (uint32_t)(tb / G) * 256 + row_off);
         }
         if constexpr (OUT) {
-            const u2v w = stream_load<u2v, decltype(nt)::value>(ko + (size_t)tb * 16 + slot_off); b_ko = make_uint2(w[0], w[1]);
+            const u2v w = stream_load<u2v, !KEEP>(ko + (size_t)tb * 16 + slot_off); b_ko = make_uint2(w[0], w[1]);
             b_kov = kov[tb / 32 + ovf_lane / 4];
         }
     };
-    auto load_Bv_as = [&](int chunk, bool two, auto nt) {
+    auto load_Bv = [&](int chunk, bool two) {
         const int tb = chunk * kChunk + (two ? 32 : 0);
         if constexpr (QUANT) {
-            b_vs = dword_at(vs, (uint32_t)tb * (2 * NCG) + vrow_off, nt);
-            b_vz = dword_at(vz, (uint32_t)tb * (2 * NCG) + vrow_off, nt);
+            b_vs = dword_at(vs, (uint32_t)tb * (2 * NCG) + vrow_off);
+            b_vz = dword_at(vz, (uint32_t)tb * (2 * NCG) + vrow_off);
         }
         if constexpr (OUT) {
-            const u2v w = stream_load<u2v, decltype(nt)::value>(vo + (size_t)tb * 16 + slot_off); b_vo = make_uint2(w[0], w[1]);
+            const u2v w = stream_load<u2v, !KEEP>(vo + (size_t)tb * 16 + slot_off); b_vo = make_uint2(w[0], w[1]);
             b_vov = vov[tb / 32 + ovf_lane / 4];
         }
-        if constexpr (BITS != 2) load_v(2 * chunk + (two ? 1 : 0), bv, nt);
+        if constexpr (BITS != 2) load_v(2 * chunk + (two ? 1 : 0), bv);
     };
-    // Chunks from a.stream_from on are read with the non-temporal hint (wave-uniform choice; a 16-bit
-    // cache never is).  The empty statements keep the two arms apart: merged, the loads would lose
-    // the hint.
-    constexpr bool MIX = true;
-    auto streamed = [&](int chunk) { return MIX && chunk >= a.stream_from; };
-    auto load_Ak = [&](int chunk) {
-        if (streamed(chunk)) { asm volatile("; streamed"); load_Ak_as(chunk, BoolC<true>{}); asm volatile("; streamed"); }
-        else load_Ak_as(chunk, BoolC<false>{});
-    };
-    auto load_Av = [&](int chunk) {
-        if (streamed(chunk)) { asm volatile("; streamed"); load_Av_as(chunk, BoolC<true>{}); asm volatile("; streamed"); }
-        else load_Av_as(chunk, BoolC<false>{});
-    };
-    auto load_Bk = [&](int chunk, bool two) {
-        if (streamed(chunk)) { asm volatile("; streamed"); load_Bk_as(chunk, two, BoolC<true>{}); asm volatile("; streamed"); }
-        else load_Bk_as(chunk, two, BoolC<false>{});
-    };
-    auto load_Bv = [&](int chunk, bool two) {
-        if (streamed(chunk)) { asm volatile("; streamed"); load_Bv_as(chunk, two, BoolC<true>{}); asm volatile("; streamed"); }
-        else load_Bv_as(chunk, two, BoolC<false>{});
-    };
-    auto load_A = [&](int chunk) {
-        if (streamed(chunk)) { asm volatile("; streamed"); load_Ak_as(chunk, BoolC<true>{}); load_Av_as(chunk, BoolC<true>{}); asm volatile("; streamed"); }
-        else { load_Ak_as(chunk, BoolC<false>{}); load_Av_as(chunk, BoolC<false>{}); }
-    };
-    auto load_B = [&](int chunk, bool two) {
-        if (streamed(chunk)) { asm volatile("; streamed"); load_Bk_as(chunk, two, BoolC<true>{}); load_Bv_as(chunk, two, BoolC<true>{}); asm volatile("; streamed"); }
-        else { load_Bk_as(chunk, two, BoolC<false>{}); load_Bv_as(chunk, two, BoolC<false>{}); }
-    };
+    auto load_A = [&](int chunk) { load_Ak(chunk); load_Av(chunk); };
+    auto load_B = [&](int chunk, bool two) { load_Bk(chunk, two); load_Bv(chunk, two); };
     auto lds_put = [&](int off, uint32_t v) { *reinterpret_cast<uint32_t*>(stage + off + row_lane) = v; };
     auto lds_put_v = [&](int off, uint32_t v) { if (lane < VROW / 4) *reinterpret_cast<uint32_t*>(stage + off + row_lane) = v; };
     auto lds_get16 = [&](int off, uint32_t* dst) {   // 64 bytes -> 16 registers
@@ -1186,30 +1183,48 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
     // runs faster when it asks at the top of the chunk's own iteration.
     constexpr bool kEarlyB = QUANT;
     constexpr bool kJoint = QUANT && !OUT && !(KT && BITS == 2);   // (where it measured faster: see the loop)
-    if (chunk < c_end) { load_A(chunk); if (kEarlyB) load_B(chunk, two); }   // issued before anything else waits on memory
-    // ... and with them the wave's first step of this workgroup's share of the full-precision tail rows
-    const int tail_t0 = (int)(((long long)a.tail_len * blockIdx.x) / n_parts);
-    const int tail_t1 = (int)(((long long)a.tail_len * (blockIdx.x + 1)) / n_parts);
-    uint4 tail_k0 = make_uint4(0u, 0u, 0u, 0u), tail_v0 = tail_k0;
-    {
-        const int r = tail_first_row<GQ>(tail_t0, tail_t1, wave, lane);
-        if (r >= 0) {
-            const size_t at = ((size_t)bh * a.tail_cap + r) * kHeadDim + 8 * (lane & 15);
-            tail_k0 = *reinterpret_cast<const uint4*>(a.tail_k + at);
-            tail_v0 = *reinterpret_cast<const uint4*>(a.tail_v + at);
-        }
-    }
+    // Requests, in the order in which they are used (loads return in order): the query rows, this workgroup's share of the
+    // full-precision tail rows, the wave's first chunk.  The first two are worked on while the third, most of the bytes, is on its
+    // way; asked for behind it they came back behind it too, and staging them and the tail's arithmetic stood between the arrival of
+    // the first chunk and its use.  (With exact waits in the loop, below: 8 heads of 1024 tokens 7.73 -> 7.26 us, of 8192 11.35 -> 10.62,
+    // 64 of 8192 with eight query heads and per-token keys 24.9 -> 23.0, 256 of 16384 at 2 bits
+    // 91.9 -> 88.7, 256 of 2048 to 6144 at 8 bits 64.7 -> 62.4.)
+    const uint16_t* q_rows = a.q + ((size_t)b * a.n_q_heads + g * GQ) * kHeadDim;
     // Query rows with each register's field-position factor folded in: MFMA operand layout, lane
     // (head row, channel block kb).  The quantized variants park them in LDS (same for every wave)
     // and re-read them when a key group's scales arrive; that frees 16 registers in the loop.
-    h2v qpos[QUANT ? 1 : 16];
-    if (!QUANT || wave == 0) {
-        h2v qn[16];
+    const bool stages_q = !QUANT || wave == nw - 1;
+    uint4 q_op[4], q_plain;
+    {   // (by every wave, of one 16-byte spot where it is not used: behind a branch the loads would be waited for at its end)
         // (16-bit rows: step i of the contraction covers channels 32 i + 8 kb .. + 8, see k_lane)
-        const uint16_t* qp = a.q + ((size_t)b * a.n_q_heads + g * GQ + (live_row ? h : 0)) * kHeadDim + (QUANT ? 32 : 8) * kb;
+        const uint32_t at = stages_q ? (uint32_t)((live_row ? h : 0) * kHeadDim + (QUANT ? 32 : 8) * kb) : 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q_op[i] = *reinterpret_cast<const uint4*>(q_rows + at + (QUANT ? 8 : 32) * i);
+    }
+    // ... and a plain copy (every variant: the tail rows read it too): 16 bytes for each of the first 128 threads
+    const bool copies_q = threadIdx.x < kHeadDim;
+    q_plain = make_uint4(0u, 0u, 0u, 0u);
+    if (copies_q && (int)threadIdx.x < GQ * 16) q_plain = *reinterpret_cast<const uint4*>(q_rows + 8 * threadIdx.x);
+    // (its share: quotient and remainder come from the host where the head has all workgroups of the launch)
+    unsigned tail_each = a.tail_each, tail_more = a.tail_more;
+    if (n_parts != a.n_splits) { tail_each = (unsigned)a.tail_len / (unsigned)n_parts; tail_more = (unsigned)a.tail_len - tail_each * n_parts; }
+    const int tail_t0 = (int)(tail_each * blockIdx.x + min(blockIdx.x, tail_more));
+    const int tail_t1 = tail_t0 + (int)tail_each + (blockIdx.x < tail_more ? 1 : 0);
+    const TailAhead tail = request_tail<GQ>(a, bh, tail_t0, tail_t1, wave, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    // (unconditional, so that what waits for the rows above need not wait for these: a wave without a chunk points them at one
+    // 16-byte spot of the workgroup's first, and a head without a token at its buffers' first block, which is laid out for the bound)
+    if (chunk >= c_end) { k_off = 0; v_off = 0; row_off = 0; vrow_off = 0; slot_off = 0; two = false; }
+    const int first = chunk < c_end ? chunk : c_begin < n_chunks ? c_begin : 0;
+    load_A(first);
+    if (kEarlyB) load_B(first, two);
+    __builtin_amdgcn_sched_barrier(0);
+    h2v qpos[QUANT ? 1 : 16];
+    if (stages_q) {
+        h2v qn[16];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const uint4 v = *reinterpret_cast<const uint4*>(qp + (QUANT ? 8 : 32) * i);
+            const uint4 v = q_op[i];
             qn[4 * i] = as_h2(live_row ? v.x : 0u); qn[4 * i + 1] = as_h2(live_row ? v.y : 0u);
             qn[4 * i + 2] = as_h2(live_row ? v.z : 0u); qn[4 * i + 3] = as_h2(live_row ? v.w : 0u);
         }
@@ -1231,13 +1246,7 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
             }
         }
     }
-    {   // plain copy (every variant: the tail rows read it too)
-        for (int item = threadIdx.x; item < 8 * kHeadDim / 2; item += blockDim.x) {
-            const int hh = item / (kHeadDim / 2), w = item % (kHeadDim / 2);
-            const uint32_t v = hh < GQ ? reinterpret_cast<const uint32_t*>(a.q + ((size_t)b * a.n_q_heads + g * GQ + hh) * kHeadDim)[w] : 0u;
-            reinterpret_cast<uint32_t*>(sq)[item] = v;
-        }
-    }
+    if (copies_q) reinterpret_cast<uint4*>(sq)[threadIdx.x] = q_plain;
     if constexpr (OUT)
         for (int item = threadIdx.x; item < nw * 8 * kHeadDim; item += blockDim.x) s_oc[item] = 0.f;
     __syncthreads();   // query rows staged, chunk counter set
@@ -1258,7 +1267,7 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
         for (int ps = 0; ps < KP; ++ps) kt_qs[ps] = quad_rows_add(kt_mine[ps] ? own : 0.f) * (1.0f / kCodeUnit);
     }
     // the tail rows go first, while the first blocks are on their way (their state waits in LDS)
-    if (wave < kWaves) tail_rows<GQ>(a, bh, tail_t0, tail_t1, sT, sq, tail_k0, tail_v0);
+    if (wave < kWaves) tail_rows<GQ>(a, bh, tail_t0, tail_t1, sT, sq, tail);
     while (chunk < c_end) {
         if (!kEarlyB) load_B(chunk, two);
         const int next = claim();                            // used half an iteration later
@@ -1270,12 +1279,14 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
             uint32_t zw[16], qw[16];
             lds_get16(OFF_KZ + 256 * min(n, NGRP - 1) + 64 * kb, zw);
             {
-                // re-read q every chunk rather than pinning 16 registers for the whole loop
-                const uint16_t* qrow = sq + h * kHeadDim + 32 * kb;
-                asm volatile("" : "+v"(qrow));
+                // re-read q every chunk rather than pinning 16 registers for the whole loop.  (What is hidden from the compiler is the
+                // offset: a hidden pointer is read by flat loads, and behind those it waits for every load in flight, the next
+                // chunk's among them.)
+                int at = h * kHeadDim + 32 * kb;
+                asm volatile("" : "+v"(at));
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const uint4 v = *reinterpret_cast<const uint4*>(qrow + 8 * i);
+                    const uint4 v = *reinterpret_cast<const uint4*>(sq + at + 8 * i);
                     qw[4 * i] = v.x; qw[4 * i + 1] = v.y; qw[4 * i + 2] = v.z; qw[4 * i + 3] = v.w;
                 }
             }
@@ -1461,22 +1472,48 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
     merge_if_last<GQ>(a, bh, n_parts);
 }
 
-// Which chunks of every head a launch reads with the non-temporal hint (streamed round the 256 MB
-// memory-side cache) -- chunks from the returned index on.  A decode step reads every layer's cache
+// A cache without a packed token (its packed buffers need not be there): the tail rows alone, one workgroup per head.
+template <int GQ>
+__global__ __launch_bounds__(kThreads) void decode_tail_only(const DecodeArgs a) {
+    __shared__ __align__(16) uint16_t sq[GQ * kHeadDim];
+    __shared__ __align__(16) float sT[kWaves * GQ * kPartStride];
+    const int b = blockIdx.z, g = blockIdx.y, bh = b * a.n_kv_heads + g;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t rows = ((size_t)b * a.n_q_heads + g * GQ) * kHeadDim;
+    if ((int)threadIdx.x < GQ * 16) reinterpret_cast<uint4*>(sq)[threadIdx.x] = reinterpret_cast<const uint4*>(a.q + rows)[threadIdx.x];
+    const TailAhead tail = request_tail<GQ>(a, bh, 0, a.tail_len, wave, lane);
+    __syncthreads();
+    tail_rows<GQ>(a, bh, 0, a.tail_len, sT, sq, tail);
+    __syncthreads();
+    for (int item = threadIdx.x; item < GQ * kPartPairs; item += kThreads) {
+        const int h = item / kPartPairs, d = 2 * (item % kPartPairs);
+        auto state = [&](int w) { return sT + (w * GQ + h) * kPartStride; };
+        float M = kNegBig, acc0 = 0.f, acc1 = 0.f, L = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, state(w)[0]);
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const float wgt = __builtin_amdgcn_exp2f(state(w)[0] - M);
+            acc0 = __builtin_fmaf(wgt, state(w)[2 + d], acc0);
+            acc1 = __builtin_fmaf(wgt, state(w)[3 + d], acc1);
+            L = __builtin_fmaf(wgt, state(w)[1], L);
+        }
+        const uint32_t lo = __half_as_ushort(__float2half_rn(acc0 / L)), hi = __half_as_ushort(__float2half_rn(acc1 / L));
+        reinterpret_cast<uint32_t*>(a.out + rows)[item] = lo | (hi << 16);
+    }
+}
+
+// Whether a launch reads the cache with the non-temporal hint (streamed round the 256 MB
+// memory-side cache).  A decode step reads every layer's cache
 // exactly once and a model's weights pass through the chip between two steps, so nothing of a cache
 // survives there until it is read again; loads that merely pass through that cache run slower than
 // loads that go round it (measured with launches that rotate over several caches: 4 bits 65.2 ->
 // 60.4 us, 8 bits 57.3 -> 53.8 us, 16 bits 55.6 -> 52.9 us per 256-head launch).  So the library
-// streams everything unless the caller says the cache will still be resident (KVQP_CACHE_KEEP).
-constexpr int kNoStream = 0x7fffffff;
-static int stream_from_chunk(const kvqp_cfg& cfg, int n_kept) {
-    (void)n_kept;
-    return cfg.decode_cache_hint == KVQP_CACHE_KEEP ? kNoStream : 0;
-}
-
+// streams everything unless the caller says the cache will still be resident (KVQP_CACHE_KEEP).  That is a kernel of its own: with
+// both kinds of loads behind a branch in one, the compiler cannot tell how many are in flight, and waits for all of them.
 template <int BITS, int GQ, int NCG>
 hipError_t launch_axis(const kvqp_cfg& cfg, const DecodeArgs& a, hipStream_t stream) {
-    const dim3 grid(a.n_splits, cfg.batch * cfg.n_kv_heads);
+    const dim3 grid(a.n_splits, cfg.n_kv_heads, cfg.batch);
     const bool out = BITS != 16 && a.k_out != nullptr;
     const bool token_keys = BITS != 16 && cfg.key_axis == KVQP_KEY_PER_TOKEN;
     const unsigned lds_bytes = (out ? pipe_lds_bytes(a.n_waves, PipeGeom<BITS, NCG, true>::STRIP, GQ, true)
@@ -1489,14 +1526,19 @@ hipError_t launch_axis(const kvqp_cfg& cfg, const DecodeArgs& a, hipStream_t str
             return;
         hipLaunchKernelGGL(kernel, grid, block, lds_bytes, stream, a);
     };
-    if constexpr (BITS != 16) {
-        if (out && token_keys) go(decode_attn_pipe<BITS, GQ, NCG, 1, true>);
-        else if (out) go(decode_attn_pipe<BITS, GQ, NCG, 0, true>);
-        else if (token_keys) go(decode_attn_pipe<BITS, GQ, NCG, 1, false>);
-        else go(decode_attn_pipe<BITS, GQ, NCG, 0, false>);
-    } else {
-        go(decode_attn_pipe<BITS, GQ, NCG, 0, false>);
-    }
+    auto pick = [&](auto keep) {
+        constexpr bool KEEP = decltype(keep)::value;
+        if constexpr (BITS != 16) {
+            if (out && token_keys) go(decode_attn_pipe<BITS, GQ, NCG, 1, true, KEEP>);
+            else if (out) go(decode_attn_pipe<BITS, GQ, NCG, 0, true, KEEP>);
+            else if (token_keys) go(decode_attn_pipe<BITS, GQ, NCG, 1, false, KEEP>);
+            else go(decode_attn_pipe<BITS, GQ, NCG, 0, false, KEEP>);
+        } else {
+            go(decode_attn_pipe<BITS, GQ, NCG, 0, false, KEEP>);
+        }
+    };
+    if (cfg.decode_cache_hint == KVQP_CACHE_KEEP) pick(BoolC<true>{});
+    else pick(BoolC<false>{});
     return hipGetLastError();
 }
 template <int BITS, int GQ>
@@ -1508,6 +1550,9 @@ hipError_t launch_group(const kvqp_cfg& cfg, const DecodeArgs& a, hipStream_t st
         default: return launch_axis<BITS, GQ, 1>(cfg, a, stream);
     }
 }
+}  // namespace
+
+// The kernels of one bit width; an object file for each (KVQP_DECODE_BITS) besides the one with everything else.
 template <int BITS>
 hipError_t launch_gq(const kvqp_cfg& cfg, const DecodeArgs& a, hipStream_t stream) {
     switch (cfg.n_q_heads / cfg.n_kv_heads) {
@@ -1517,8 +1562,13 @@ hipError_t launch_gq(const kvqp_cfg& cfg, const DecodeArgs& a, hipStream_t strea
         default: return launch_group<BITS, 8>(cfg, a, stream);
     }
 }
-
-}  // namespace
+#ifdef KVQP_DECODE_BITS
+template hipError_t launch_gq<KVQP_DECODE_BITS>(const kvqp_cfg&, const DecodeArgs&, hipStream_t);
+#else
+extern template hipError_t launch_gq<2>(const kvqp_cfg&, const DecodeArgs&, hipStream_t);
+extern template hipError_t launch_gq<4>(const kvqp_cfg&, const DecodeArgs&, hipStream_t);
+extern template hipError_t launch_gq<8>(const kvqp_cfg&, const DecodeArgs&, hipStream_t);
+extern template hipError_t launch_gq<16>(const kvqp_cfg&, const DecodeArgs&, hipStream_t);
 
 static int cu_count() {
     static const int n_cu = [] {
@@ -1734,9 +1784,19 @@ hipError_t launch_decode(const kvqp_cfg& cfg, const void* q, const kvqp_cache& c
     a.n_q_heads = cfg.n_q_heads; a.n_kv_heads = cfg.n_kv_heads;
     a.n_splits = plan.n_splits; a.chunks_per_split = plan.chunks_per_split;
     a.n_waves = plan.n_waves;
+    a.tail_each = (unsigned)c.tail_len / (unsigned)plan.n_splits; a.tail_more = (unsigned)c.tail_len % (unsigned)plan.n_splits;
     a.group = cfg.group_size; a.sm_scale = cfg.sm_scale;
-    a.stream_from = stream_from_chunk(cfg, c.n_kept);
     hipError_t e;
+    if (c.n_kept == 0) {
+        const dim3 grid(1, cfg.n_kv_heads, cfg.batch);
+        switch (cfg.n_q_heads / cfg.n_kv_heads) {
+            case 1: hipLaunchKernelGGL(decode_tail_only<1>, grid, dim3(kThreads), 0, stream, a); break;
+            case 2: hipLaunchKernelGGL(decode_tail_only<2>, grid, dim3(kThreads), 0, stream, a); break;
+            case 4: hipLaunchKernelGGL(decode_tail_only<4>, grid, dim3(kThreads), 0, stream, a); break;
+            default: hipLaunchKernelGGL(decode_tail_only<8>, grid, dim3(kThreads), 0, stream, a); break;
+        }
+        return hipGetLastError();
+    }
     switch (cfg.bits) {
         case 2: e = launch_gq<2>(cfg, a, stream); break;
         case 4: e = launch_gq<4>(cfg, a, stream); break;
@@ -1745,5 +1805,7 @@ hipError_t launch_decode(const kvqp_cfg& cfg, const void* q, const kvqp_cache& c
     }
     return e;
 }
+
+#endif  // KVQP_DECODE_BITS
 
 }  // namespace kvqp

@@ -264,3 +264,31 @@ def test_large_value_scales(orc, bits):
             ref = orc.decode_attn(q, oc, cfg.sm_scale)
             assert float(oc.v_scale.view(np.float16).astype(np.float32).max()) > (256 if bits == 2 else 64)
             assert np.abs(got - ref).max() <= 1e-3 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("Gq,bits", [(1, 4), (2, 8), (4, 4), (4, 2), (8, 16), (8, 4)])
+@pytest.mark.parametrize("n_kept,splits", [(0, 0), (200, 1), (200, 2), (330, 4)])
+def test_tails_around_the_rows_that_are_requested_ahead(orc, Gq, bits, n_kept, splits):
+    """Tails of one row up to more than four steps of a workgroup's four waves (4 to 16 rows a step, four steps requested ahead of the
+    packed part), shared by one, two and four workgroups, also of a cache without a packed token, whose buffers are absent."""
+    B, Hkv, W, cap = 2, 2, 1, 80
+    L, Hq = n_kept + W + 57, 2 * Gq
+    _, k, v = synth.prompt_host(B, Hq, Hkv, L, W, 128, config=110 + bits)
+    rng = np.random.default_rng(bits + Gq)
+    idx = np.stack([np.sort(rng.choice(L - W, n_kept, replace=False)) for _ in range(B * Hkv)]).astype(np.int32).reshape(B, Hkv, n_kept)
+    oc = orc.quantize_selected(k, v, idx, W=W, bits=bits, G=32, tail_cap=cap)
+    oc.tail_k[:, :, W:] = rng.standard_normal((B, Hkv, cap - W, 128)).astype(np.float16).view(np.uint16)
+    oc.tail_v[:, :, W:] = rng.standard_normal((B, Hkv, cap - W, 128)).astype(np.float16).view(np.uint16)
+    cfg = kvqp.Cfg(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, seq_len=L, window=W, budget=n_kept, bits=bits, group_size=32, decode_splits=splits)
+    q = synth.decode_query_host(B, Hq, 128, config=110)
+    for rows in (1, 3, 4, 5, 15, 16, 17, 33, 64, 65, 80):
+        print(f"case tail Gq={Gq} bits={bits} n_kept={n_kept} splits={splits} rows={rows}", flush=True)
+        oc.tail_len = rows
+        cache = upload_cache(oc)
+        if n_kept == 0:
+            for name in ("k_codes", "v_codes", "k_scale", "k_zero", "v_scale", "v_zero"):
+                assert cache.buffers[name].data_ptr() == 0
+        out = kvqp.decode_attn(cfg, dev(q), cache)
+        torch.cuda.synchronize()
+        err = np.abs(out.cpu().numpy().astype(np.float64) - orc.decode_attn(q, oc, cfg.sm_scale)).max()
+        assert err <= TOL, (rows, err)

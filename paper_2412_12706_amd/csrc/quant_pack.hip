@@ -312,15 +312,19 @@ __global__ __launch_bounds__(kThreads, quant_waves(BITS, G, OUT)) void gather_qu
         kb += (size_t)t0 * kHeadDim;
         vb += (size_t)t0 * kHeadDim;
     }
+    // (Keys first, all of them: they are worked on while the values are on their way; whole calls, us, keys and values in turn -> this:
+    // 8 heads of 4096 tokens 23.6 -> 23.25, of 32768 65.1 -> 64.7, 131072 213.0 -> 212.3.  Prompt rows are read once: non-temporal.)
+    auto gather = [&](const uint16_t* base, uint32_t (&w)[R][4]) {
 #pragma unroll
-    for (int j = 0; j < R; ++j) {
-        // (prompt rows are read once: non-temporal)
-        typedef uint32_t u4v __attribute__((ext_vector_type(4)));
-        const u4v a = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(kb + (pos[j] * kHeadDim + 8u * c8)));
-        const u4v b = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(vb + (pos[j] * kHeadDim + 8u * c8)));
-        kw[j][0] = a[0]; kw[j][1] = a[1]; kw[j][2] = a[2]; kw[j][3] = a[3];
-        vw[j][0] = b[0]; vw[j][1] = b[1]; vw[j][2] = b[2]; vw[j][3] = b[3];
-    }
+        for (int j = 0; j < R; ++j) {
+            typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+            const u4v a = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(base + (pos[j] * kHeadDim + 8u * c8)));
+            w[j][0] = a[0]; w[j][1] = a[1]; w[j][2] = a[2]; w[j][3] = a[3];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    gather(kb, kw);
+    gather(vb, vw);
     if (ntok < TB) {                      // (uniform) the head's last block: rows past the count are zeros
         // (but a copy of the last row leaves the minima and maxima of per-channel groups alone)
         const bool clear_k = !QUANT || OUT || key_axis != KVQP_KEY_PER_CHANNEL;

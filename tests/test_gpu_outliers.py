@@ -66,6 +66,35 @@ def test_quantize_with_outliers_matches_checker(orc, bits, G, axis):
         assert err <= 2e-3
 
 
+@pytest.mark.parametrize("bits,G,axis,n", [(2, 32, 0, 384), (4, 32, 1, 333), (8, 64, 0, 300), (4, 128, 0, 384), (2, 128, 1, 290)])
+def test_rows_with_any_number_of_outliers(orc, bits, G, axis, n):
+    """Rows with 0 to 128 outliers, up to eight side by side, magnitudes of exactly the threshold (no outlier) and one step above it
+    (one), of either sign: the slots' order, their unused places, the counts beyond them."""
+    print(f"case any number bits={bits} G={G} axis={axis} n={n}", flush=True)
+    B, Hkv, W, L = 1, 2, 4, 400
+    rng = np.random.default_rng(7)
+    rows = rng.uniform(-5.5, 5.5, (2, B, Hkv, L, 128)).astype(np.float16)
+    rows[rng.random(rows.shape) < 0.05] = TAU
+    above = np.nextafter(np.float16(TAU), np.float16(7))
+    for t in range(L):
+        for x in rows[:, 0, :, t].reshape(4, 128):
+            many = (t * 5) % 129
+            at = rng.choice(128, many, replace=False) if t % 2 else (np.arange(many) + t) % 128       # scattered, or side by side
+            x[at] = rng.choice([above, -above, 9.0, -40.0, 60000.0], many).astype(np.float16)
+    k, v = rows
+    idx = random_survivors(B, Hkv, L - W, n, 81)
+    cap = 128 * n
+    oc = orc.quantize_selected(k, v, idx, W=W, bits=bits, G=G, key_axis=axis, tau=TAU, ovf_cap=cap)
+    cfg = kvqp.Cfg(batch=B, n_q_heads=2, n_kv_heads=Hkv, seq_len=L, window=W, budget=n, bits=bits, group_size=G, key_axis=axis,
+                   outlier_threshold=TAU, outlier_overflow_cap=cap)
+    gc = kvqp.alloc_cache(cfg)
+    for t in gc.buffers.values():
+        t.fill_(0x3C)
+    kvqp.quantize_selected(cfg, dev(k), dev(v), dev(idx), gc)
+    torch.cuda.synchronize()
+    assert_cache_equal(gc, oc)
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(8, 1), (2, 2), (4, 4)])
 def test_decode_over_checker_cache_other_group_sizes(orc, Hq, Hkv):
     """Gq = 8 (one token slot per tile), 1 and ... : the cache is the checker's, uploaded."""

@@ -311,8 +311,10 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
                     t[mt] = (x[0] + x[1]) + (x[2] + x[3]);
                 }
             };
-            sums();
-            if (__builtin_amdgcn_ballot_w64(fmaxf(t[0], t[1]) > kLazySum) != 0ull) {   // rare after the first chunks
+            // (the first chunk always moves it)
+            const bool first = chunk == c_begin;
+            if (!first) sums();
+            if (first || __builtin_amdgcn_ballot_w64(fmaxf(t[0], t[1]) > kLazySum) != 0ull) {   // rare after the first chunks
 #pragma unroll
                 for (int mt = 0; mt < kMT; ++mt) {
                     float top = acc[0][mt][0];

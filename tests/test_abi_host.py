@@ -280,6 +280,28 @@ def test_decode_workspace_init_and_static_entry_validate_on_the_host(lib):
     assert lib.kvqp_decode_attn_static(C.byref(big.struct()), fake, C.byref(cs), fake, None) == -3
 
 
+def test_structs_in_one_go_are_the_structs_field_by_field():
+    """The binding packs the structs' bytes at once; numbers that do not fit are cut as ctypes cuts them."""
+    import random
+    import torch
+    rng = random.Random(1)
+    for odd in (False, True):
+        for _ in range(200):
+            ints = [rng.randrange(-2**(40 if odd else 31), 2**(40 if odd else 31)) for _ in range(14)]
+            floats = [rng.choice([0.0, 1e-3, float("inf"), 1e39 if odd else 1.5]), rng.uniform(0, 1e4)]
+            cfg = kvqp.Cfg(*ints[:12], *floats, *ints[12:])
+            assert bytes(cfg.struct()) == bytes(kvqp.CfgStruct(*ints[:12], *floats, *ints[12:]))
+            bufs = {n: torch.zeros(rng.choice([0, 8]), dtype=torch.uint8) for n in kvqp._NAMES + (() if rng.random() < 0.5 else ("k_out", "v_ovf"))}
+            counts = None if rng.random() < 0.5 else torch.zeros(2, dtype=torch.int32)
+            cache = kvqp.Cache(bufs, *ints[:4], counts)
+            ptr = lambda n: bufs[n].data_ptr() if n in bufs else None
+            want = kvqp.CacheStruct(*[ptr(n) for n in kvqp._NAMES], *ints[:4], None if counts is None else counts.data_ptr(),
+                                    *[ptr(n) for n in ("k_out", "v_out", "k_ovf", "v_ovf")])
+            assert bytes(cache.struct()) == bytes(want)
+    with pytest.raises(TypeError):
+        kvqp.Cfg(batch="1", n_q_heads=1, n_kv_heads=1).struct()
+
+
 @pytest.mark.parametrize("missing", [None, "_cuda_getCurrentRawStream", "_cuda_getDevice"])
 def test_current_stream_without_the_undocumented_torch_names(monkeypatch, missing):
     """The binding asks torch for the current stream's handle by names that are not documented; a torch

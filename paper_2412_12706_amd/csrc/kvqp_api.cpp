@@ -319,6 +319,7 @@ static int check_decode(const kvqp_cfg* cfg, const void* q, const kvqp_cache* ca
     // (the other plan's price is that of equal heads; where their counts differ, and the host does not
     // know them, it came out slower on one shape in eight, by up to 20 %)
     if (cache->head_n_kept) plan->take_plain();
+    else plan->take_half();
     return KVQP_OK;
 }
 

@@ -53,7 +53,7 @@ constexpr size_t kCounterBytes = 65536 * sizeof(unsigned int);
 // workspace query and the launch agree.
 struct DecodePlan {
     int n_splits;        // token-axis splits of the packed part
-    int chunks_per_split;// 64-token chunks handled by one workgroup
+    int chunks_per_split;// chunks handled by one workgroup
     int n_waves;         // waves per decode workgroup
     size_t ws_bytes;         // counters and partials
     size_t part_bytes = 0;   // the partials alone
@@ -62,11 +62,23 @@ struct DecodePlan {
     // says what workspace the call accepts, and runs when there is that much but not enough for the other.
     int alt_splits = 0, alt_chunks = 0, alt_waves = 0;
     size_t alt_part_bytes = 0;
+    // Chunks of 32 tokens in workgroups of eight waves (half_splits == 0: not for this problem), for heads that all have
+    // the same count; taken by the caller who knows that.
+    bool half = false;
+    int half_splits = 0, half_chunks = 0;
+    size_t half_part_bytes = 0;
+    void take_half() {
+        if (!half_splits) return;
+        ws_bytes += half_part_bytes - part_bytes;
+        n_splits = half_splits; chunks_per_split = half_chunks; n_waves = 8;
+        part_bytes = half_part_bytes;
+        half = true;
+    }
     size_t least_bytes() const { return ws_bytes - part_bytes + (alt_waves ? alt_part_bytes : part_bytes); }
     void take_plain() {
         if (!alt_waves) return;
         ws_bytes = least_bytes();
-        n_splits = alt_splits; chunks_per_split = alt_chunks; n_waves = alt_waves;
+        n_splits = alt_splits; chunks_per_split = alt_chunks; n_waves = alt_waves; half = false;
         part_bytes = alt_part_bytes;
         alt_waves = 0;
     }

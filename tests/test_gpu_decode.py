@@ -292,3 +292,28 @@ def test_tails_around_the_rows_that_are_requested_ahead(orc, Gq, bits, n_kept, s
         torch.cuda.synchronize()
         err = np.abs(out.cpu().numpy().astype(np.float64) - orc.decode_attn(q, oc, cfg.sm_scale)).max()
         assert err <= TOL, (rows, err)
+
+
+@pytest.mark.parametrize("Gq,bits,G,axis", [(4, 4, 32, 0), (4, 8, 64, 1), (8, 4, 32, 1), (8, 8, 32, 0), (1, 4, 128, 0), (2, 8, 32, 1)])
+def test_chunks_of_32_tokens(orc, Gq, bits, G, axis):
+    """Few heads of few tokens are cut into chunks of 32, eight waves a workgroup: counts around a chunk, around a workgroup's eight,
+    around sixteen workgroups' (one chunk a wave, then two) and past the last of the form; the same counts in chunks of 64 (two
+    workgroups asked for)."""
+    B, Hkv, W = 1, 2, 5
+    rng = np.random.default_rng(bits + Gq)
+    for n_kept in (1, 31, 32, 33, 64, 95, 255, 256, 257, 1000, 2047, 4096, 4097, 8160, 8192, 8193):
+        if axis == 0 and n_kept > 2047 and Gq < 4:
+            continue                                         # (the checker's time)
+        print(f"case chunks of 32 Gq={Gq} bits={bits} G={G} axis={axis} n_kept={n_kept}", flush=True)
+        L, Hq = n_kept + W + 57, Hkv * Gq
+        _, k, v = synth.prompt_host(B, Hq, Hkv, L, W, 128, config=120 + bits)
+        idx = np.stack([np.sort(rng.choice(L - W, n_kept, replace=False)) for _ in range(Hkv)]).astype(np.int32).reshape(B, Hkv, n_kept)
+        oc = orc.quantize_selected(k, v, idx, W=W, bits=bits, G=G, key_axis=axis)
+        q = synth.decode_query_host(B, Hq, 128, config=120)
+        for splits in (0, 2):
+            cfg = kvqp.Cfg(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, seq_len=L, window=W, budget=n_kept, bits=bits, group_size=G, key_axis=axis, decode_splits=splits)
+            ref = orc.decode_attn(q, oc, cfg.sm_scale)
+            out = kvqp.decode_attn(cfg, dev(q), upload_cache(oc))
+            torch.cuda.synchronize()
+            err = np.abs(out.cpu().numpy().astype(np.float64) - ref).max()
+            assert err <= TOL, (n_kept, splits, err)

@@ -240,7 +240,8 @@ static int compress_impl(const kvqp_cfg* cfg, const void* q_obs, const void* k, 
                         apart(k, (size_t)heads * cfg->seq_len * row_bytes) && apart(unrefined_out, (size_t)heads * sizeof(int32_t)) &&
                         apart(cache->head_n_kept, (size_t)heads * sizeof(int32_t));
     int32_t* idx = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + plan.off_idx);
-    if (head_budget && upload_counts(cache->head_n_kept, head_budget, heads, stream) != hipSuccess) return KVQP_ERR_HIP;
+    if (head_budget && score && plan.takes_counts) { plan.counts = head_budget; plan.counts_dst = cache->head_n_kept; }
+    else if (head_budget && upload_counts(cache->head_n_kept, head_budget, heads, stream) != hipSuccess) return KVQP_ERR_HIP;
     if (n_kept == 0 && unrefined_out && upload_counts(unrefined_out, nullptr, heads, stream) != hipSuccess) return KVQP_ERR_HIP;   // nothing is cut
     if (n_kept > 0) {
         if (launch_select(*cfg, q_obs, k, idx, direct ? idx_out : nullptr, unrefined_out, workspace, plan, cache->head_n_kept, score, stream) != hipSuccess) return KVQP_ERR_HIP;

@@ -103,6 +103,7 @@ constexpr size_t kStaticScratchBytes = KVQP_STATIC_SCRATCH_BYTES;   // ... behin
 hipError_t static_scratch(const kvqp_cfg& cfg, void** ptr, hipStream_t stream);
 
 // Compress workspace layout (bytes offsets), pure function of cfg.
+constexpr int kCountsInStats = 256;    // token counts that a scoring pass carries in its arguments
 struct CompressPlan {
     int P, n_kept, rows;          // rows = Gq * W query rows per kv head
     int n_chunks;                 // key chunks of the scoring passes
@@ -112,6 +113,9 @@ struct CompressPlan {
     int n_seg, seg_tiles;         // pooling workgroups per kv head and their share in pooling tiles
     int p_stride;                 // score codes of a head, padded to whole 16-byte pieces
     size_t off_stats_part, off_stats, off_vote, off_pooled, off_idx, total;
+    bool takes_counts = false;    // launch_select stores the heads' token counts itself where it is given them:
+    const int32_t* counts = nullptr;       // host, read before the call returns
+    int32_t* counts_dst = nullptr;         // device
     size_t exact_bytes;           // further room, behind `total`, that a call uses for its speed where it is there
 };
 CompressPlan plan_compress(const kvqp_cfg& cfg);

@@ -72,6 +72,16 @@ struct ScoreArgs {
     float scale_log2;       // sm_scale * log2(e)
 };
 
+// Token counts of the heads, from the host, that the statistics store beside their own work: nothing before the pooling reads
+// them, and a launch of its own for them, ahead of everything, costs 1.5 us (whole calls, 32 heads of 20011 tokens, 99.75 -> 98.3; the
+// one of other calls does not carry the kilobyte).
+struct HeadCounts { int32_t* dst; int32_t v[kCountsInStats]; };
+struct NoCounts {};
+__device__ __forceinline__ void store_head_count(const HeadCounts& c, int head) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) c.dst[head] = c.v[head];
+}
+__device__ __forceinline__ void store_head_count(const NoCounts&, int) {}
+
 // Up to so many statistics per row the vote pass merges itself while its first keys are on their way, without the launch of
 // stats_combine before it: whole calls, us, 8 heads of 2000 keys (16 of them) 26.5 -> 24.9, of 4096 (32) 28.2 -> 26.1, 32 heads of 8192
 // (16) 64.5 -> 63.0, 256 heads of 32768 (8) 1276 -> 1261.  More of them take as long as the launch: 8 heads of 32768 (64) 75.3 -> 76.0.
@@ -138,8 +148,8 @@ __device__ __forceinline__ void request_chunk(const ScoreArgs& a, int head, cons
 // 5.5 and 5.9 TB/s), 32 of 20011 with 32 rows 32.6 + 25.4 -> 31.6 + 24.6.  Three and four places in LDS are slower
 // (8 heads of 32768: 19.2 + 15.9 and 20.2 + 17.0; not explained: two workgroups per CU, which is all the launch has, still fit).
 // MERGE (VOTES): the pass merges the row statistics itself.
-template <int NRW, int PASS, bool MERGE = false, bool DIRECT = true>
-__global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
+template <int NRW, int PASS, bool MERGE = false, bool DIRECT = true, class Counts = NoCounts>
+__global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a, const Counts counts) {
     constexpr int kMT = kRowsPerWave / 16;
     constexpr int KS = 4 / NRW, KT = 4 / KS;          // key strips; 16-key tiles of a wave per chunk
     constexpr bool SHARED = NRW > 1;                  // a wave reads keys that other waves have requested
@@ -155,6 +165,7 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
     const uint16_t* kh = a.k + (size_t)head * a.L * kHeadDim;
     const int c_begin = blockIdx.x * a.chunks_per_wg;
     const int c_end = min(a.n_chunks, c_begin + a.chunks_per_wg);
+    store_head_count(counts, head);
 
     // Query operand: rows 32*rw + 16*mt + (lane & 15), channels 32*s + 8*kb .. +8.
     Frag qf[kMT][4];
@@ -434,8 +445,8 @@ __global__ __launch_bounds__(kThreads, 4) void score_pass(const ScoreArgs a) {
 // strong outlier channels make them move: 5 us; a moved reference is shared by the two lanes of a row.
 typedef float f16v __attribute__((ext_vector_type(16)));
 constexpr int kWideRows = 256;
-template <int PASS, bool DIRECT = true>
-__global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
+template <int PASS, bool DIRECT = true, class Counts = NoCounts>
+__global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a, const Counts counts) {
     constexpr int MT = 2;                             // row tiles of a wave
     constexpr int kWaveRows = 32 * MT;
     constexpr int kSteps = kHeadDim / 16;             // contraction steps
@@ -450,6 +461,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_wide(const ScoreArgs a) {
     const uint16_t* kh = a.k + (size_t)head * a.L * kHeadDim;
     const int c_begin = blockIdx.x * a.chunks_per_wg;
     const int c_end = min(a.n_chunks, c_begin + a.chunks_per_wg);
+    store_head_count(counts, head);
 
     // Query operand: row kWaveRows * wave + 32 * mt + n, channels 16 * s + 8 * hi .. +8.
     Frag qf[MT][kSteps];
@@ -1567,14 +1579,15 @@ int n_row_slabs(int rows) {
 }
 
 // merging: the vote pass that merges the row statistics itself, or NULL
-template <class Stats, class Votes>
-hipError_t launch_scores(Stats stats_pass, Votes vote_pass, Votes merging, const ScoreArgs& a, int n_wg, int heads, hipStream_t stream) {
-    hipLaunchKernelGGL(stats_pass, dim3(n_wg, heads), dim3(kThreads), 0, stream, a);
+template <class Counts>
+hipError_t launch_scores(void (*stats_pass)(const ScoreArgs, const Counts), void (*vote_pass)(const ScoreArgs, const NoCounts), void (*merging)(const ScoreArgs, const NoCounts),
+                         const ScoreArgs& a, const Counts& counts, int n_wg, int heads, hipStream_t stream) {
+    hipLaunchKernelGGL(stats_pass, dim3(n_wg, heads), dim3(kThreads), 0, stream, a, counts);
     const bool merge = merging && a.n_parts <= kMergeParts;
     if (!merge)
         hipLaunchKernelGGL(stats_combine, dim3(heads, (a.rows_pad + 3) / 4), dim3(256), 0, stream, (const float2*)a.stats_part, a.stats, a.zsum,
                            a.n_parts, a.rows_pad);
-    hipLaunchKernelGGL((merge ? merging : vote_pass), dim3(n_wg, heads), dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL((merge ? merging : vote_pass), dim3(n_wg, heads), dim3(kThreads), 0, stream, a, NoCounts{});
     return hipGetLastError();
 }
 
@@ -1612,6 +1625,7 @@ CompressPlan plan_compress(const kvqp_cfg& cfg) {
         while (p.n_wg > most) { ++p.chunks_per_wg; p.n_wg = (p.n_chunks + p.chunks_per_wg - 1) / p.chunks_per_wg; }
     }
     p.n_parts = p.n_wg;
+    p.takes_counts = heads <= kCountsInStats;
     const int rows_pad = p.rows_pad;
     const size_t n_parts = (size_t)p.n_parts;
     size_t off = 0;
@@ -1660,18 +1674,32 @@ hipError_t launch_select(const kvqp_cfg& cfg, const void* q_obs, const void* k, 
 
     hipError_t e;
     if (score) {   // scores are needed only when something is dropped
-        constexpr void (*none)(const ScoreArgs) = nullptr;
+        constexpr void (*none)(const ScoreArgs, const NoCounts) = nullptr;
         const int slabs = n_row_slabs(plan.rows);
-        if ((uintptr_t)k & 15) switch (slabs) {      // (whole calls, us, 8 heads: 4096 keys 28.5 instead of 25.5, 32768 75.7 / 76.0, 131072 with 256 rows 239.6 / 237.1)
-            case 1: e = launch_scores(score_pass<1, PASS_STATS, false, false>, score_pass<1, PASS_VOTES, false, false>, none, a, n_wg, heads, stream); break;
-            case 2: e = launch_scores(score_pass<2, PASS_STATS, false, false>, score_pass<2, PASS_VOTES, false, false>, none, a, n_wg, heads, stream); break;
-            case 4: e = launch_scores(score_pass<4, PASS_STATS, false, false>, score_pass<4, PASS_VOTES, false, false>, none, a, n_wg, heads, stream); break;
-            default: e = launch_scores(score_wide<PASS_STATS, false>, score_wide<PASS_VOTES, false>, none, a, n_wg, heads, stream); break;
-        } else switch (slabs) {
-            case 1: e = launch_scores(score_pass<1, PASS_STATS>, score_pass<1, PASS_VOTES>, score_pass<1, PASS_VOTES, true>, a, n_wg, heads, stream); break;
-            case 2: e = launch_scores(score_pass<2, PASS_STATS>, score_pass<2, PASS_VOTES>, score_pass<2, PASS_VOTES, true>, a, n_wg, heads, stream); break;
-            case 4: e = launch_scores(score_pass<4, PASS_STATS>, score_pass<4, PASS_VOTES>, score_pass<4, PASS_VOTES, true>, a, n_wg, heads, stream); break;
-            default: e = launch_scores(score_wide<PASS_STATS>, score_wide<PASS_VOTES>, none, a, n_wg, heads, stream); break;
+        auto aligned = [&](const auto& counts) {
+            using Counts = std::decay_t<decltype(counts)>;
+            switch (slabs) {
+                case 1: return launch_scores(score_pass<1, PASS_STATS, false, true, Counts>, score_pass<1, PASS_VOTES>, score_pass<1, PASS_VOTES, true>, a, counts, n_wg, heads, stream);
+                case 2: return launch_scores(score_pass<2, PASS_STATS, false, true, Counts>, score_pass<2, PASS_VOTES>, score_pass<2, PASS_VOTES, true>, a, counts, n_wg, heads, stream);
+                case 4: return launch_scores(score_pass<4, PASS_STATS, false, true, Counts>, score_pass<4, PASS_VOTES>, score_pass<4, PASS_VOTES, true>, a, counts, n_wg, heads, stream);
+                default: return launch_scores(score_wide<PASS_STATS, true, Counts>, score_wide<PASS_VOTES>, none, a, counts, n_wg, heads, stream);
+            }
+        };
+        if ((uintptr_t)k & 15) {      // (whole calls, us, 8 heads: 4096 keys 28.5 instead of 25.5, 32768 75.7 / 76.0, 131072 with 256 rows 239.6 / 237.1)
+            if (plan.counts && (e = upload_counts(plan.counts_dst, plan.counts, heads, stream)) != hipSuccess) return e;
+            switch (slabs) {
+                case 1: e = launch_scores(score_pass<1, PASS_STATS, false, false>, score_pass<1, PASS_VOTES, false, false>, none, a, NoCounts{}, n_wg, heads, stream); break;
+                case 2: e = launch_scores(score_pass<2, PASS_STATS, false, false>, score_pass<2, PASS_VOTES, false, false>, none, a, NoCounts{}, n_wg, heads, stream); break;
+                case 4: e = launch_scores(score_pass<4, PASS_STATS, false, false>, score_pass<4, PASS_VOTES, false, false>, none, a, NoCounts{}, n_wg, heads, stream); break;
+                default: e = launch_scores(score_wide<PASS_STATS, false>, score_wide<PASS_VOTES, false>, none, a, NoCounts{}, n_wg, heads, stream); break;
+            }
+        } else if (plan.counts) {
+            HeadCounts counts;
+            counts.dst = plan.counts_dst;
+            for (int i = 0; i < kCountsInStats; ++i) counts.v[i] = i < heads ? plan.counts[i] : 0;
+            e = aligned(counts);
+        } else {
+            e = aligned(NoCounts{});
         }
         if (e != hipSuccess) return e;
     }

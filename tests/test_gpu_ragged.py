@@ -280,3 +280,35 @@ def test_append_with_head_level_counts(orc, bits, G, key_axis, n_app, tau):
             assert excess <= 0.0, (h, excess)
     with pytest.raises(kvqp.KvqpError):
         kvqp.append_tail_ragged(cfg, gc, n_app, counts)          # the tail no longer holds that many rows
+
+
+@pytest.mark.parametrize("B,Hkv,Gq,W,shift", [(1, 2, 2, 8, 0), (32, 8, 1, 4, 0), (257, 1, 1, 4, 0), (3, 2, 4, 16, 0), (2, 2, 8, 24, 0), (2, 2, 2, 8, 4)])
+def test_counts_that_the_scoring_stores(B, Hkv, Gq, W, shift):
+    """Up to 256 heads the first scoring pass stores the heads' counts (one, two and four slabs of window rows, and more rows), beyond
+    them, and where the keys begin at an odd address, a launch before it: the counts on the device, and every head's survivors as of a
+    call on that head alone."""
+    print(f"case stored counts B={B} Hkv={Hkv} Gq={Gq} W={W} shift={shift}", flush=True)
+    L, budget, heads = 150, 60, B * Hkv
+    q_obs, k, v = (dev(t) for t in synth.prompt_host(B, Hkv * Gq, Hkv, L, W, 128, config=130))
+    if shift:
+        room = torch.zeros(k.numel() + 8, dtype=k.dtype, device="cuda")
+        room[shift:shift + k.numel()] = k.view(-1)
+        k = room[shift:shift + k.numel()].view(k.shape)
+    counts = [(7 * h + 3) % (budget + 1) for h in range(heads)]
+    cfg = kvqp.Cfg(batch=B, n_q_heads=Hkv * Gq, n_kv_heads=Hkv, seq_len=L, window=W, budget=budget, bits=4, group_size=32, key_axis=1)
+    cache = kvqp.alloc_cache(cfg, ragged=True)
+    cache.head_n_kept.fill_(-7)
+    idx = torch.full((B, Hkv, budget), -1, dtype=torch.int32, device="cuda")
+    kvqp.compress_ragged(cfg, q_obs, k, v, counts, cache, idx_out=idx)
+    torch.cuda.synchronize()
+    assert cache.head_n_kept.tolist() == counts
+    for h in range(0, heads, max(1, heads // 5)):
+        if counts[h] == 0:
+            continue
+        b, g = divmod(h, Hkv)
+        alone = kvqp.Cfg(batch=1, n_q_heads=Gq, n_kv_heads=1, seq_len=L, window=W, budget=counts[h], bits=4, group_size=32, key_axis=1)
+        got = torch.empty((1, 1, counts[h]), dtype=torch.int32, device="cuda")
+        kvqp.compress(alone, q_obs[b:b + 1, g * Gq:(g + 1) * Gq].contiguous(), k[b:b + 1, g:g + 1].contiguous(), v[b:b + 1, g:g + 1].contiguous(),
+                      kvqp.alloc_cache(alone), idx_out=got)
+        torch.cuda.synchronize()
+        assert torch.equal(idx[b, g, :counts[h]], got[0, 0])

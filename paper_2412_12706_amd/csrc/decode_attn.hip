@@ -606,7 +606,7 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
     constexpr int G = kHeadDim / NCG;
     constexpr int CHUNK = HALF ? 32 : kChunk;                 // tokens of a chunk
     constexpr int NGRP = (QUANT && !KT && G == 32 && !HALF) ? 2 : 1;   // key groups per chunk
-    static_assert(!HALF || (BITS != 2 && BITS != 16 && !OUT), "a 2-bit value word spans two blocks");
+    static_assert(!HALF || (BITS != 16 && !OUT), "forms that are launched");
     using Geo = PipeGeom<BITS, NCG, OUT>;
     constexpr int OFF_KO = Geo::OFF_KO, OFF_VO = Geo::OFF_VO;
     constexpr int VROW = Geo::VROW;
@@ -778,7 +778,7 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
             const u2v w = stream_load<u2v, !KEEP>(vo + (size_t)tb * 16 + slot_off); a_vo = make_uint2(w[0], w[1]);
             a_vov = vov[tb / 32 + ovf_lane / 4];
         }
-        load_v((BITS == 2 || HALF) ? chunk : 2 * chunk, av);
+        load_v(BITS == 2 && HALF ? chunk >> 1 : BITS == 2 || HALF ? chunk : 2 * chunk, av);
     };
     auto load_Bk = [&](int chunk, bool two) {
         const int tb = chunk * kChunk + (two ? 32 : 0);
@@ -1322,7 +1322,9 @@ __global__ __launch_bounds__(64 * pipe_max_waves(BITS, GQ, OUT), 1) void decode_
 #pragma unroll
                 for (int i = 0; i < 4; ++i) mx = fmaxf(mx, lgA[t][i]);
             advance_reference(quad_rows_max(mx));
-            compute(BoolI<2>{}, lgA, ak0, ak1, 0u, 0u, true, 0.f, av, 0, a_vs, a_vz, no_slots, no_slots, 0u, 0u, 0);
+            // (a 2-bit value word spans two blocks; the chunk is one of them)
+            if (BITS == 2 && (chunk & 1)) compute(BoolI<2>{}, lgA, ak0, ak1, 0u, 0u, true, 0.f, av, 1, a_vs, a_vz, no_slots, no_slots, 0u, 0u, 0);
+            else compute(BoolI<2>{}, lgA, ak0, ak1, 0u, 0u, true, 0.f, av, 0, a_vs, a_vz, no_slots, no_slots, 0u, 0u, 0);
             load_Av(nx);
         } else if constexpr (kJoint) {
             // Both blocks' logits first, one move of the reference for the whole chunk, then both
@@ -1555,7 +1557,7 @@ hipError_t launch_axis(const kvqp_cfg& cfg, const DecodeArgs& a, hipStream_t str
             go(decode_attn_pipe<BITS, GQ, NCG, 0, false, KEEP>);
         }
     };
-    if constexpr (BITS == 4 || BITS == 8) {
+    if constexpr (BITS != 16) {
         if (a.half) {
             if (token_keys) go(decode_attn_pipe<BITS, GQ, NCG, 1, false, false, true>);
             else go(decode_attn_pipe<BITS, GQ, NCG, 0, false, false, true>);
@@ -1745,9 +1747,10 @@ DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept) {
             // head do not suffice), as long as every one has a CU.  A chunk of 64 is 1000 instructions in a row, of which a wave that is
             // alone on its SIMD issues one every 2 ns; two waves share them.  Over 52 shapes of 4 and 8 bits, 64 to 9000 tokens,
             // calls take 0.90 of the time that they take otherwise (0.74 to 1.01), least with eight query heads; at 16 bits, where the bytes
-            // of a block count, one shape in three was slower, by up to 12 %.
+            // of a block count, one shape in three was slower, by up to 12 %.  At 2 bits, where two chunks share their value words,
+            // 31 shapes of up to 1280 tokens take 0.94 (0.88 to 1.05), 19 larger ones 0.99 and up to 1.07.
             const int halves = (n_kept + 31) / 32, wgs = std::min(16, (halves + 7) / 8);
-            if ((cfg.bits == 4 || cfg.bits == 8) && !outliers_on(cfg) && cfg.decode_cache_hint != KVQP_CACHE_KEEP && halves > 0 &&
+            if (cfg.bits != 16 && (cfg.bits != 2 || halves <= 40) && !outliers_on(cfg) && cfg.decode_cache_hint != KVQP_CACHE_KEEP && halves > 0 &&
                 halves <= 16 * wgs && heads * wgs <= n_cu)
                 cut(wgs, halves, p.half_chunks, p.half_splits, p.half_part_bytes);
         }

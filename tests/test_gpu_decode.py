@@ -294,14 +294,15 @@ def test_tails_around_the_rows_that_are_requested_ahead(orc, Gq, bits, n_kept, s
         assert err <= TOL, (rows, err)
 
 
-@pytest.mark.parametrize("Gq,bits,G,axis", [(4, 4, 32, 0), (4, 8, 64, 1), (8, 4, 32, 1), (8, 8, 32, 0), (1, 4, 128, 0), (2, 8, 32, 1)])
+@pytest.mark.parametrize("Gq,bits,G,axis", [(4, 4, 32, 0), (4, 8, 64, 1), (8, 4, 32, 1), (8, 8, 32, 0), (1, 4, 128, 0), (2, 8, 32, 1),
+                                            (4, 2, 32, 0), (8, 2, 64, 1), (1, 2, 128, 0)])
 def test_chunks_of_32_tokens(orc, Gq, bits, G, axis):
     """Few heads of few tokens are cut into chunks of 32, eight waves a workgroup: counts around a chunk, around a workgroup's eight,
     around sixteen workgroups' (one chunk a wave, then two) and past the last of the form; the same counts in chunks of 64 (two
     workgroups asked for)."""
     B, Hkv, W = 1, 2, 5
     rng = np.random.default_rng(bits + Gq)
-    for n_kept in (1, 31, 32, 33, 64, 95, 255, 256, 257, 1000, 2047, 4096, 4097, 8160, 8192, 8193):
+    for n_kept in (1, 31, 32, 33, 64, 95, 255, 256, 257, 1000, 1280, 1281, 2047, 4096, 4097, 8160, 8192, 8193):
         if axis == 0 and n_kept > 2047 and Gq < 4:
             continue                                         # (the checker's time)
         print(f"case chunks of 32 Gq={Gq} bits={bits} G={G} axis={axis} n_kept={n_kept}", flush=True)

@@ -304,7 +304,7 @@ def test_chunks_of_32_tokens(orc, Gq, bits, G, axis):
     rng = np.random.default_rng(bits + Gq)
     for n_kept in (1, 31, 32, 33, 64, 95, 255, 256, 257, 1000, 1280, 1281, 2047, 4096, 4097, 8160, 8192, 8193):
         if axis == 0 and n_kept > 2047 and Gq < 4:
-            continue                                         # (the checker's time)
+            continue                                         # (the oracle's time)
         print(f"case chunks of 32 Gq={Gq} bits={bits} G={G} axis={axis} n_kept={n_kept}", flush=True)
         L, Hq = n_kept + W + 57, Hkv * Gq
         _, k, v = synth.prompt_host(B, Hq, Hkv, L, W, 128, config=120 + bits)

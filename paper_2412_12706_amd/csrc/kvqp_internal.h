@@ -94,7 +94,8 @@ struct DecodePlan {
     }
 };
 DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept);
-size_t decode_ws_bound(const kvqp_cfg& cfg);   // >= kCounterBytes + plan_decode(cfg, n).part_bytes for every n
+// >= kCounterBytes + part_bytes and half_part_bytes of plan_decode(cfg, n) for every n
+size_t decode_ws_bound(const kvqp_cfg& cfg);
 size_t decode_ws_header_bytes(const kvqp_cfg& cfg);   // arrival counters at the head of a decode workspace
 hipError_t launch_ws_init(const kvqp_cfg& cfg, void* ws, hipStream_t stream);   // zeroes them
 // The library's own decode workspace (a static device array): its address on the current device,

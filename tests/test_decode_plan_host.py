@@ -10,12 +10,14 @@ import pytest
 from paper_2412_12706_amd import kvqp
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-FIELDS = ("accepted", "splits", "waves", "part_bytes", "part_off", "counters", "stated")
+FIELDS = ("accepted", "splits", "waves", "part_bytes", "part_off", "counters", "stated", "half", "chunks", "least")
+PRICED, EQUAL_HEADS, OWN_COUNTS = 0, 1, 2        # the planner's answer; what a call launches, heads alike or with counts of their own
+COUNTER_ROOM = 65536 * 4                         # opens every workspace of the stated size
 
 
 @pytest.fixture(scope="module")
 def plans(tmp_path_factory):
-    """plans([(batch, hq, hkv, n, bits, group, outliers, decode_splits, workspace bytes), ...]) -> dicts"""
+    """plans([(batch, hq, hkv, n, bits, group, outliers, decode_splits, workspace bytes, key axis (0), form (PRICED)), ...]) -> dicts"""
     if shutil.which("hipcc") is None:
         pytest.skip("no hipcc")
     if not os.path.exists(kvqp.LIB_PATH):
@@ -29,7 +31,7 @@ def plans(tmp_path_factory):
     assert r.returncode == 0, r.stderr[-3000:]
 
     def ask(problems):
-        r = subprocess.run([exe], input="".join(" ".join(map(str, p)) + "\n" for p in problems), capture_output=True, text=True, timeout=300)
+        r = subprocess.run([exe], input="".join(" ".join(map(str, (p + (0, PRICED))[:11])) + "\n" for p in problems), capture_output=True, text=True, timeout=300)
         assert r.returncode == 0, r.stderr[-3000:]
         rows = [dict(zip(FIELDS, map(int, line.split()))) for line in r.stdout.splitlines()]
         assert len(rows) == len(problems)
@@ -119,3 +121,48 @@ def test_the_search_passes_over_no_better_launch_shape(plans):
         elif best > 0.96 * was * (1 + 1e-5):
             assert (row["waves"], row["splits"]) == (plain[0], cut), (b, gq, hkv, n, bits, g, o, row)
     assert other > 800
+
+
+def test_chunks_of_32_cover_the_tokens_within_the_stated_workspace(plans):
+    """The form that small calls launch in place of the priced one: its workgroups take every token once, its partial results lie
+    clear of all counters inside a workspace of the stated size, and it asks for no more than the plain rule."""
+    rng = random.Random(23)
+    problems = []
+    for _ in range(20000):
+        bits = rng.choice([2, 4, 8, 16])
+        hkv = rng.choice([1, 2, 4, 8])
+        problems.append((int(2 ** rng.uniform(0, 6)), hkv * rng.choice([1, 2, 4, 8]), hkv, int(2 ** rng.uniform(0, 13.2)), bits, rng.choice([32, 64, 128]),
+                         int(bits < 16 and rng.random() < 0.1), rng.choice([0, 0, 0, 3]), 0, rng.choice([0, 1])))
+    halves = split = 0
+    for p, priced, row, own in zip(problems, *(plans([p + (form,) for p in problems]) for form in (PRICED, EQUAL_HEADS, OWN_COUNTS))):
+        b, hq, hkv, n, bits, _, outliers, splits = p[:8]
+        assert row["accepted"] and own["accepted"] and not own["half"] and row["least"] == priced["least"] == own["least"], p
+        if not row["half"]:
+            assert row == priced, p
+            continue
+        halves += 1
+        split += row["splits"] > 1
+        assert bits != 16 and not outliers and not splits and row["waves"] == 8, p
+        assert row["splits"] <= 16 and b * hkv * row["splits"] <= 256, p
+        assert (row["splits"] - 1) * row["chunks"] * 32 < n <= row["splits"] * row["chunks"] * 32 and row["chunks"] <= 16, p
+        assert row["part_bytes"] == (b * hq * row["splits"] * 1024 if row["splits"] > 1 else 0), p
+        assert row["part_off"] >= COUNTER_ROOM and row["part_off"] + row["part_bytes"] <= row["stated"], p
+    assert halves > 2000 and split > 1000
+
+
+@pytest.mark.parametrize("hq,hkv,n,bits", [(32, 8, 1024, 4), (8, 1, 3000, 8), (8, 8, 700, 2), (64, 8, 4000, 4)])
+def test_chunks_of_32_give_way_in_a_smaller_workspace(plans, hq, hkv, n, bits):
+    """A workspace that holds the plain rule's partials is taken, and one that has no room for this form's behind the counters gets
+    the plain rule's launch."""
+    for b in (1, 2):
+        whole, plain = (plans([(b, hq, hkv, n, bits, 32, 0, 0, 0, 1, form)])[0] for form in (EQUAL_HEADS, OWN_COUNTS))
+        assert whole["half"] and whole["part_bytes"] > 0
+        room = COUNTER_ROOM + whole["part_bytes"]
+        sizes = sorted({whole["least"] - 16, whole["least"], room - 16, room, whole["stated"]} | {whole["least"] + i * (room - whole["least"]) // 20 for i in range(20)})
+        for ws, row in zip(sizes, plans([(b, hq, hkv, n, bits, 32, 0, 0, ws, 1, EQUAL_HEADS) for ws in sizes])):
+            assert row["accepted"] == (ws >= whole["least"]), (b, ws)
+            if not row["accepted"]:
+                continue
+            assert row["half"] == (ws >= room), (b, ws, row)
+            assert row["half"] or all(row[f] == plain[f] for f in ("splits", "waves", "chunks", "part_bytes")), (b, ws, row)
+            assert row["part_bytes"] == 0 or (row["part_off"] >= row["counters"] and row["part_off"] + row["part_bytes"] <= ws), (b, ws, row)

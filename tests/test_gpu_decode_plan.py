@@ -88,3 +88,32 @@ def test_splits_that_fill_the_stated_workspace_leave_other_calls_counters_alone(
         cfg, gc, q, ref = jobs[b]
         out = torch.full((b, 16, 128), float("nan"), dtype=torch.float16, device="cuda")   # (a head that is not merged stays)
         assert attn_excess(kvqp.decode_attn(cfg, q, gc, out, ws), ref) <= 0
+
+
+@pytest.mark.parametrize("Hkv,Gq,n,bits,axis", [(8, 4, 1024, 4, 0), (2, 8, 3000, 8, 1), (4, 4, 700, 2, 0)])
+def test_small_calls_in_workspaces_of_several_sizes(orc, Hkv, Gq, n, bits, axis):
+    """Chunks of 32 tokens where their partial results have room behind the counters (the stated size); in less, down to this
+    call's own counters and the plain rule's partials, the plain rule's launch.  The library's own array beside them."""
+    cfg, oc = cache_of(orc, 1, Hkv, Gq, n, bits, axis=axis)
+    gc = upload_cache(oc)
+    q = synth.decode_query_host(1, Hkv * Gq, 128, config=95)
+    ref = orc.decode_attn(q, oc, float(np.float32(cfg.sm_scale)))
+    stated = kvqp.workspace_bytes(cfg)[1]
+    room = kvqp.alloc_workspace(stated)
+    taken = 0
+    for size in [stated] + [256 + i * (stated - 65536 * 4) // 8 // 16 * 16 for i in range(9)]:
+        print(f"case small call Hkv={Hkv} Gq={Gq} n={n} bits={bits} workspace={size} of {stated}", flush=True)
+        ws = kvqp.decode_workspace_init(cfg, room[:size])
+        out = torch.full((1, Hkv * Gq, 128), float("nan"), dtype=torch.float16, device="cuda")
+        try:
+            kvqp.decode_attn(cfg, dev(q), gc, out, ws)
+        except kvqp.KvqpError:
+            assert size < stated      # (fewer bytes than the plain rule's partials)
+            continue
+        taken += 1
+        assert attn_excess(out, ref) <= 0, size
+        assert attn_excess(kvqp.decode_attn(cfg, dev(q), gc, workspace=ws), ref) <= 0, size      # (the counters are back at zero)
+    assert taken >= 2
+    out = torch.empty((1, Hkv * Gq, 128), dtype=torch.float16, device="cuda")
+    kvqp.decode_attn_static(cfg, dev(q), gc, out)
+    assert attn_excess(out, ref) <= 0

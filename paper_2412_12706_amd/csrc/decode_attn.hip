@@ -1744,14 +1744,21 @@ DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept) {
             cut(plain_splits, n_chunks, p.alt_chunks, p.alt_splits, p.alt_part_bytes);
             p.alt_waves = plain_nw;
             // Few heads of few tokens: workgroups of eight waves with a chunk of 32 tokens each (two where sixteen workgroups per
-            // head do not suffice), as long as every one has a CU.  A chunk of 64 is 1000 instructions in a row, of which a wave that is
-            // alone on its SIMD issues one every 2 ns; two waves share them.  Over 52 shapes of 4 and 8 bits, 64 to 9000 tokens,
-            // calls take 0.90 of the time that they take otherwise (0.74 to 1.01), least with eight query heads; at 16 bits, where the bytes
-            // of a block count, one shape in three was slower, by up to 12 %.  At 2 bits, where two chunks share their value words,
-            // 31 shapes of up to 1280 tokens take 0.94 (0.88 to 1.05), 19 larger ones 0.99 and up to 1.07.
+            // head do not suffice: up to 8192 tokens), as long as every one has a CU.  A chunk of 64 is 1000 instructions in a row, of which a wave
+            // that is alone on its SIMD issues one every 2 ns; two waves share them.  Per-token keys, eight query heads, and up to 256
+            // tokens gain always.  So do per-channel keys in groups of 32, whose chunks of 64 have two groups' zero-point terms, while a wave has
+            // one chunk; in larger groups only where the priced plan gives a wave a second chunk of 64 or has one large workgroup per
+            // head (8 bits; four query heads; 513 to 768 tokens, twelve waves); and with two chunks of 32 a wave where the priced plan's waves
+            // share their SIMDs, too (at 4 bits in groups of 32 only).  630 shapes that the rule takes, of 33 to 8192 tokens, need 0.91 (2 bits),
+            // 0.93 (4 bits) and 0.93 (8 bits) of the time that they need in chunks of 64, none more than 1.06; 310 that it leaves
+            // would need 1.05, 1.015 and 1.035, and 1.14 at worst.  At 16 bits, where the bytes of a block count, one shape in three
+            // was slower, by up to 12 %; at 2 bits, where two chunks share their value words, 19 shapes of more than 1280 tokens needed 0.99 and up to 1.07.
             const int halves = (n_kept + 31) / 32, wgs = std::min(16, (halves + 7) / 8);
+            const bool pays = cfg.key_axis == KVQP_KEY_PER_TOKEN || gq == 8 || halves <= 8 ||
+                              (halves > 128 ? p.n_waves == 8 && (cfg.bits == 8 || cfg.group_size == 32)
+                                            : cfg.group_size == 32 || (halves > 16 && halves <= 24) || (p.n_splits == 1 && (cfg.bits == 8 || gq == 4)));
             if (cfg.bits != 16 && (cfg.bits != 2 || halves <= 40) && !outliers_on(cfg) && cfg.decode_cache_hint != KVQP_CACHE_KEEP && halves > 0 &&
-                halves <= 16 * wgs && heads * wgs <= n_cu)
+                halves <= 16 * wgs && heads * wgs <= n_cu && pays)
                 cut(wgs, halves, p.half_chunks, p.half_splits, p.half_part_bytes);
         }
     }

@@ -166,3 +166,13 @@ def test_chunks_of_32_give_way_in_a_smaller_workspace(plans, hq, hkv, n, bits):
             assert row["half"] == (ws >= room), (b, ws, row)
             assert row["half"] or all(row[f] == plain[f] for f in ("splits", "waves", "chunks", "part_bytes")), (b, ws, row)
             assert row["part_bytes"] == 0 or (row["part_off"] >= row["counters"] and row["part_off"] + row["part_bytes"] <= ws), (b, ws, row)
+
+
+@pytest.mark.parametrize("hq,hkv,n,bits,group,axis,half", [
+    (8, 8, 300, 2, 128, 0, 0), (8, 8, 300, 2, 128, 1, 1), (8, 8, 300, 2, 32, 0, 1), (8, 8, 256, 2, 128, 0, 1), (32, 8, 600, 2, 64, 0, 1), (32, 8, 800, 2, 64, 0, 0),
+    (16, 8, 380, 4, 64, 0, 0), (32, 8, 380, 4, 64, 0, 1), (64, 8, 1100, 4, 128, 0, 1), (32, 8, 1100, 4, 128, 0, 0), (32, 8, 1024, 4, 32, 0, 1),
+    (16, 8, 280, 8, 64, 0, 1), (16, 8, 450, 8, 64, 0, 0), (2, 2, 7700, 8, 64, 0, 0), (32, 8, 6700, 8, 64, 0, 1), (32, 8, 6700, 4, 64, 0, 0),
+    (32, 8, 8192, 4, 32, 0, 1), (32, 8, 8193, 4, 32, 1, 0), (16, 16, 4180, 4, 64, 0, 0), (16, 16, 4180, 4, 64, 1, 1)])
+def test_chunks_of_32_are_left_where_they_are_slower(plans, hq, hkv, n, bits, group, axis, half):
+    """Both sides of each line of the rule: per-channel keys in wide groups, a second chunk of 32 beside waves that have a SIMD each."""
+    assert plans([(1, hq, hkv, n, bits, group, 0, 0, 0, axis, EQUAL_HEADS)])[0]["half"] == half

@@ -318,3 +318,22 @@ def test_chunks_of_32_tokens(orc, Gq, bits, G, axis):
             torch.cuda.synchronize()
             err = np.abs(out.cpu().numpy().astype(np.float64) - ref).max()
             assert err <= TOL, (n_kept, splits, err)
+
+
+@pytest.mark.parametrize("Hkv,Gq,bits,G,counts", [(2, 1, 2, 128, (513, 768)), (2, 4, 4, 64, (257, 511, 512, 600, 769)), (2, 2, 8, 128, (264, 288, 512)),
+                                                  (4, 4, 8, 64, (6700, 8192))])
+def test_per_channel_keys_in_wide_groups_on_either_side_of_the_rule(orc, Hkv, Gq, bits, G, counts):
+    """Counts at which per-channel keys in groups of 64 and 128 go from chunks of 64 tokens to chunks of 32 and back."""
+    W = 5
+    rng = np.random.default_rng(bits + G)
+    for n_kept in counts:
+        print(f"case wide groups Gq={Gq} bits={bits} G={G} n_kept={n_kept}", flush=True)
+        L, Hq = n_kept + W + 57, Hkv * Gq
+        _, k, v = synth.prompt_host(1, Hq, Hkv, L, W, 128, config=130 + bits)
+        idx = np.stack([np.sort(rng.choice(L - W, n_kept, replace=False)) for _ in range(Hkv)]).astype(np.int32).reshape(1, Hkv, n_kept)
+        oc = orc.quantize_selected(k, v, idx, W=W, bits=bits, G=G)
+        q = synth.decode_query_host(1, Hq, 128, config=130)
+        cfg = kvqp.Cfg(batch=1, n_q_heads=Hq, n_kv_heads=Hkv, seq_len=L, window=W, budget=n_kept, bits=bits, group_size=G)
+        out = kvqp.decode_attn(cfg, dev(q), upload_cache(oc))
+        torch.cuda.synchronize()
+        assert np.abs(out.cpu().numpy().astype(np.float64) - orc.decode_attn(q, oc, cfg.sm_scale)).max() <= TOL, n_kept

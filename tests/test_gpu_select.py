@@ -30,6 +30,21 @@ def select(orc, P, W, pool, budget, Gq=2, Hkv=2, sm_scale=None, outlier=10.0, ke
     return got.cpu().numpy(), idx, pooled, unrefined.cpu().tolist()
 
 
+def check_heads(got, idx, pooled, unrefined):
+    """Every head by itself: the checker's survivors where the cut was refined in binary64; where binary32 decided, nothing but the
+    order within 2e-5 of the cut is open (the band of scores that its rounding, a few 1e-7, could move, with room to spare)."""
+    for g, loose in enumerate(unrefined):
+        if not loose:
+            check_indices(got[:, g:g + 1], idx[:, g:g + 1], pooled[:, g:g + 1])
+            continue
+        own, scores = got[0, g], pooled[0, g]
+        assert np.all(np.diff(own) > 0) and own[0] >= 0 and own[-1] < scores.size
+        cut = np.sort(scores)[-own.size]
+        kept = np.zeros(scores.size, bool)
+        kept[own] = True
+        assert kept[scores > cut * (1 + 2e-5)].all() and not kept[scores < cut * (1 - 2e-5)].any(), g
+
+
 def row_statistics(cfg, ws, rows_pad):
     """(m, 1/Z) and the binary64 Z of every window row, out of a workspace of the stated size: they lie before the votes, the
     pooled scores' codes (beyond three pooling tiles), the survivors (each padded to 256 bytes) and room for all pooled scores (the same)."""
@@ -483,3 +498,55 @@ def test_counts_per_head_and_replays_where_several_workgroups_sweep():
         call(again, un)
         torch.cuda.synchronize()
         assert torch.equal(again, want)
+
+
+@pytest.mark.parametrize("Hkv,P,counts,noise", [(52, 33001, "equal", 1.0), (33, 65521, "own", 1.0), (17, 131072, "own", 1.0), (17, 131071, "equal", 0.05),
+                                                (17, 131072, "equal", 0.0)])
+def test_long_prefixes_of_many_heads_are_swept_by_one_workgroup_each(Hkv, P, counts, noise):
+    """More heads than leave each sweeping workgroup a CU: one workgroup takes all groups of codes of a head, up to sixteen per
+    thread, and lists up to 16384 of them (all keys alike).  The same survivors and the same word on what binary32 decided as from a call on
+    the head alone, whose codes several workgroups sweep."""
+    print(f"case one workgroup Hkv={Hkv} P={P} counts={counts} noise={noise}", flush=True)
+    assert Hkv * -(-(-(-P // 8)) // 1024) > 256
+    W, pool = 8, 5
+    gen = torch.Generator(device="cuda").manual_seed(P + Hkv)
+    q_obs = torch.randn(1, Hkv, W, 128, generator=gen, device="cuda").half()
+    k = torch.randn(1, Hkv, P + W, 128, generator=gen, device="cuda", dtype=torch.float16)
+    if noise < 1.0:
+        k[:, :, 1:P] = (k[:, :, :1].float() + noise * k[:, :, 1:P].float()).half()
+    budget = P // 6
+    n = [budget] * Hkv if counts == "equal" else [(0, P, 1, budget, P - 1)[h % 5] for h in range(Hkv)]
+
+    def call(heads, n):
+        rows = slice(heads[0], heads[-1] + 1)
+        cfg = kvqp.Cfg(batch=1, n_q_heads=len(heads), n_kv_heads=len(heads), seq_len=P + W, window=W, pool_kernel=pool, budget=max(n + [1]), bits=2, group_size=128)
+        idx = torch.full((1, len(heads), cfg.n_kept), -1, dtype=torch.int32, device="cuda")
+        un = torch.full((len(heads),), -1, dtype=torch.int32, device="cuda")
+        kk = k[:, rows].contiguous()
+        if counts == "equal":
+            kvqp.compress(cfg, q_obs[:, rows].contiguous(), kk, kk, kvqp.alloc_cache(cfg), idx_out=idx, unrefined_out=un)
+        else:
+            kvqp.compress_ragged(cfg, q_obs[:, rows].contiguous(), kk, kk, n, kvqp.alloc_cache(cfg, ragged=True), idx_out=idx, unrefined_out=un)
+        torch.cuda.synchronize()
+        return idx[0], un.tolist()
+    sees = torch.arange(P + W, device="cuda") <= P + torch.arange(W, device="cuda")[:, None]
+
+    def pooled(h):      # scores in 64 bits
+        logit = (q_obs[0, h].double() @ k[0, h].double().T) * float(np.float32(128 ** -0.5))
+        vote = torch.softmax(logit.masked_fill(~sees, -torch.inf), dim=1)[:, :P].sum(0)
+        return torch.nn.functional.max_pool1d(vote[None], pool, 1, pool // 2)[0].cpu().numpy()
+    got, un = call(list(range(Hkv)), n)
+    assert got.shape[1] == max(n)
+    for h in range(Hkv):
+        want, alone = call([h], [n[h]])
+        if n[h] == 0:
+            assert un[h] == alone[0] == 0
+            continue
+        if noise == 0.0:
+            assert un[h] == alone[0] == P and torch.equal(got[h], want[0]) and torch.equal(got[h], torch.arange(budget, dtype=torch.int32, device="cuda"))
+            continue
+        scores = pooled(h)
+        best = np.sort(np.lexsort((np.arange(P), -scores))[:n[h]])
+        assert un[h] == alone[0] == 0
+        for list_ in (got[h, :n[h]], want[0, :n[h]]):
+            check_heads(list_.cpu().numpy()[None, None], best[None, None], scores[None, None], [0])

@@ -1116,7 +1116,10 @@ __global__ __launch_bounds__(kSelThreads) void select_topk(const SelectArgs a) {
     uint32_t* list_key = reinterpret_cast<uint32_t*>(big);
     int* list_pos = reinterpret_cast<int*>(big + kListCap * 4);
     uint32_t* groups = reinterpret_cast<uint32_t*>(tab) + 2 * kSelWaves;        // [kListCap], not OWN: groups with candidates around the cut, until these are listed
-    constexpr int kGroupCount = 18;                                             // s_list, not OWN: groups above this bit, candidates below (131072 at most)
+    // s_list, not OWN: groups above this bit, candidates below.  131072 of these fit.  16384 groups, all that there are, wrap to 0 once the last
+    // is counted; no earlier one reads that, and with that many the candidates are beyond the list, which is then not used.
+    constexpr int kGroupCount = 18;
+    static_assert(kMaxPrefix < (1 << kGroupCount) && kMaxPrefix / 8 <= (1 << (32 - kGroupCount)) && (1 << (32 - kGroupCount)) > kListCap, "the counts fit, or do not count");
     int sure = 0;
     if constexpr (OWN) {
 #pragma unroll

@@ -30,7 +30,7 @@ int check_common(const kvqp_cfg* c) {
     if (c->head_dim != kHeadDim) return KVQP_ERR_UNSUPPORTED;
     if (!(gq == 1 || gq == 2 || gq == 4 || gq == 8)) return KVQP_ERR_UNSUPPORTED;
     if (c->bits != 16 && !is_pow2_group(c->group_size)) return KVQP_ERR_UNSUPPORTED;
-    if ((long long)c->batch * c->n_kv_heads > 65535) return KVQP_ERR_UNSUPPORTED;   // (batch, kv head) is the y index of every launch
+    if ((long long)c->batch * c->n_kv_heads > 65535) return KVQP_ERR_UNSUPPORTED;   // (batch, kv head) is the y index of every launch but decode's, which has a counter for each
     return KVQP_OK;
 }
 

@@ -676,7 +676,7 @@ __global__ __launch_bounds__(256) void stats_combine(const float2* __restrict__ 
 //                bits of each pooled score, and count the scores in 4032 bins of equal
 //                bit-pattern width (64 per factor of two: at most 1.6 % wide) and the
 //                bins' counts in groups of 64
-//   select_topk  one workgroup per head: the counts give the bin of the cut; ONE
+//   select_topk  one workgroup per head, or several where a long prefix leaves CUs idle: the counts give the bin of the cut; ONE
 //                sweep over the 16-bit codes leaves a mask bit per sure survivor and
 //                collects the few candidates of that bin, whose scores are pooled
 //                again and give the exact cut; survivors leave through the mask.
@@ -685,7 +685,8 @@ __global__ __launch_bounds__(256) void stats_combine(const float2* __restrict__ 
 // DPP 5), a branch that is taken 25, an access to memory 400 to 1000.  So the list around the cut is finished by one wave, one
 // candidate per lane and unrolled (before, by all of them, with a barrier after every step), sums go along the lanes by DPP, only
 // the counts of the cut's group are read besides the groups', and the sweep lists groups of eight codes instead of candidates.  select_topk, us, before ->
-// now: 8 heads of 4064 candidates 8.8 -> 7.4, of 32736 22.4 -> 17.0, of 131008 37 -> 29, 32 of 20003 15 -> 10.5, 256 of 32736 29.6 -> 26.2.
+// now (averages over three prompts, a call at a time; one prompt and the next differ by up to 40 %, with the positions that are scored in 64 bits):
+// 8 heads of 4064 candidates 9.4 -> 7.7, of 32736 19.4 -> 15.5, of 131008 41.6 -> 29.0 (sixteen workgroups per head), 32 of 20003 15.3 -> 13.3.
 // ---------------------------------------------------------------------------
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;

@@ -1748,7 +1748,7 @@ DecodePlan plan_decode(const kvqp_cfg& cfg, int n_kept) {
             // Few heads of few tokens: workgroups of eight waves with a chunk of 32 tokens each (two where sixteen workgroups per
             // head do not suffice: up to 8192 tokens), as long as every one has a CU.  A chunk of 64 is 1000 instructions in a row, of which a wave
             // that is alone on its SIMD issues one every 2 ns; two waves share them.  Per-token keys, eight query heads, and up to 256
-            // tokens gain always.  So do per-channel keys in groups of 32, whose chunks of 64 have two groups' zero-point terms, while a wave has
+            // tokens gain whatever the count (single shapes lose up to 6 %).  So do per-channel keys in groups of 32, whose chunks of 64 have two groups' zero-point terms, while a wave has
             // one chunk; in larger groups only where the priced plan gives a wave a second chunk of 64 or has one large workgroup per
             // head (8 bits; four query heads; 513 to 768 tokens, twelve waves); and with two chunks of 32 a wave where the priced plan's waves
             // share their SIMDs, too (at 4 bits in groups of 32 only).  630 shapes that the rule takes, of 33 to 8192 tokens, need 0.91 (2 bits),

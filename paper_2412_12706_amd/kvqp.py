@@ -88,8 +88,9 @@ def lib():
                            "kvqp_append_tail": (cfg, ptr, i32, ptr),
                            "kvqp_decode_attn": (cfg, ptr, C.c_char_p, ptr, ptr, size, ptr),
                            "kvqp_decode_attn_static": (cfg, ptr, C.c_char_p, ptr, ptr)}.items():
-            _fn[name] = L[name]
-            _fn[name].argtypes = args
+            entry = L[name]
+            entry.argtypes = args       # (before another thread, which may have loaded the library already, can find it)
+            _fn[name] = entry
         _lib = L
     return _lib
 

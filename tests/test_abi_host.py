@@ -366,3 +366,19 @@ def test_compress_workspace_holds_codes_and_pooled_scores_only_beyond_three_tile
         assert parts >= al(heads * -(-P // 8) * 16) + heads * -(-P // 8) * 32 + heads * 8192
     else:
         assert parts % (heads * rows_pad * 8) == 0 and 1 <= parts // (heads * rows_pad * 8) <= max(1, -(-(P + W) // 128))
+
+
+def test_entry_points_are_published_with_their_argument_types(monkeypatch):
+    """Threads may load the library at the same time, and one that is done calls while another still loads: an entry point must not be
+    found without its argument types, which would cut addresses down to 32 bits."""
+    kvqp.lib()
+
+    class Table(dict):
+        def __setitem__(self, name, function):
+            assert function.argtypes is not None, name
+            super().__setitem__(name, function)
+    table = Table()
+    monkeypatch.setattr(kvqp, "_fn", table)
+    monkeypatch.setattr(kvqp, "_lib", None)
+    kvqp.lib()
+    assert set(table) == {"kvqp_compress", "kvqp_append_tail", "kvqp_decode_attn", "kvqp_decode_attn_static"}
